@@ -12,7 +12,7 @@ constexpr int kWave = 64;
 constexpr int kTraceBlock = 256;
 constexpr int kFinalBlock = 256;
 constexpr int kFinalCellsPerThread = 4;
-constexpr unsigned long long kReserveMax = 256;   // next-level queue slots a wave reserves per atomic
+constexpr unsigned long long kReserveMax = 64;    // next-level queue slots (of 4 rays) a wave reserves per atomic
 // Time-dependent rays: a wave reserves the halt list's records in blocks of
 // kHaltBlock; the records of its last block that it does not fill are empty,
 // with the level kHaltHole (above every HEALPix level, so they sort last).
@@ -23,21 +23,12 @@ constexpr unsigned long long kReserveMax = 256;   // next-level queue slots a wa
 constexpr int kHaltBlock = 256;
 constexpr int kHaltHole = 31;
 static_assert(kLevels <= kHaltHole, "empty halt records need a level above every real one");
-constexpr uint32_t kNoTree = 0xffffffffu;      // tree index of an empty queue slot
+constexpr uint32_t kNoTree = 0xffffffffu;      // tree of an empty queue slot
 constexpr int kDropRanges = 16;                // tree ranges one queue filter pass removes (serving)
-constexpr int kSkip = 0, kStarted = 1, kEscaped = 2;
-constexpr int kCacheLog2 = 9;                  // per-wave LDS deposit cache: 512 entries
-constexpr int kCacheEntries = 1 << kCacheLog2;
 constexpr uint32_t kNoSlot = 0xffffffffu;      // empty cache entry
+constexpr int kPack = 4;                       // most energy groups of a source one ray carries
 constexpr double kHydrogenMassG = 1.6735575e-24;   // mass of a hydrogen atom, g
 constexpr double kLightCms = 2.99792458e10;        // speed of light, cm/s
-constexpr int kEvictCap = 128;                 // per-wave buffer of evicted sums (drained at > 64)
-constexpr int kTallyLog2 = 7;                  // per-block LDS table of per-tree statistics: 128 entries
-constexpr int kTallySlots = 1 << kTallyLog2;
-constexpr int kTallyProbes = 16;               // entries a tree tries before it adds to global counters
-constexpr int kStageFlush = 16;                // split parents staged before their children are written
-constexpr int kStageCap = kStageFlush + kWave; // one iteration adds at most 64 parents
-
 // One uniform grid patch of one problem, in the batch-wide cell numbering.
 struct GridDev {
   int nx, ny, nz;
@@ -54,37 +45,48 @@ struct GridDev {
                            // out_acc[k * (problem's cells) + i]; NULL when not asked for
 };
 
+// kAccSums: the absorbed rate, one plane per group.
+// kAccMoments (rays carry several groups): the absorbed rate summed over the
+//   groups, then the absorbed rate times (E - E_ion) summed over them; one plane.
+// kAccThin (optically-thin approximation): the absorbed rate, then the deposits
+//   of thin rays in cells that hold their source (nothing removed); one plane per group.
+// kAccRadp (radiation pressure asked for): the absorbed rate, then the three
+//   components of the absorbed momentum rate; one plane per group.
+constexpr int kAccSums = 0, kAccMoments = 1, kAccThin = 2, kAccRadp = 3;
+
 struct ProblemDev {
   int root_grid;           // index of the root grid in the grid table
   int n_groups;
   long long cell_off;      // first cell of the problem
   long long n_cells;       // cells of all its grids
-  long long acc_off;       // first accumulator slot: group g of cell c is acc_off + g*n_cells + (c - cell_off)
+  long long acc_off;       // its first accumulator
   int eexc_off;            // first of its n_groups (E - E_ion) values in erg
-  int pad;
-  int acc_stride = 1;      // 1: one float64 sum per (group, cell), group g of cell c at
-                           //   acc_off + g*n_cells + (c - cell_off);
-                           // 2 (optically-thin approximation): a 16-byte record per (group, cell) at
-                           //   acc_off + 2*(g*n_cells + (c - cell_off)): absorbed rate, then the
-                           //   deposits of thin rays in cells that hold their source (nothing removed);
-                           // 4 (radiation pressure asked for): a 32-byte record per (group, cell) at
-                           //   acc_off + 4*(g*n_cells + (c - cell_off)): absorbed rate, then the three
-                           //   components of the absorbed momentum rate
+  // Accumulators: acc_planes records of acc_stride float64 sums per cell, record p of cell c at
+  // acc_off + acc_stride * (p*n_cells + (c - cell_off)). acc_mode says what a record holds:
+  int acc_mode = kAccSums;
+  int acc_stride = 1;
+  int acc_planes = 1;
   // optically-thin approximation: the mark of the problem's (source, group) tree t (tree table
-  // index sg_first + t) on cell c is the byte mark[mark_off + t*n_cells + (c - cell_off)], t < mark_trees
+  // index tree_first + t) on cell c is the byte mark[mark_off + t*n_cells + (c - cell_off)], t < mark_trees
   int mark_trees = 0;      // 0: the problem does not use the approximation
-  int sg_first = 0;        // its first tree in the tree table (its trees are consecutive)
+  int tree_first = 0;      // its first tree in the tree table (its trees are consecutive)
   long long mark_off = 0;
 };
 
-// One (source, group) ray tree, with the shape of its problem's root grid so
-// a ray can start without another table lookup.
-struct SgDev {
+// One ray tree: the rays of one source that carry a pack of n_grp consecutive
+// energy groups (1 to kPack of them), with the shape of its problem's root
+// grid so a ray can start without another table lookup. All groups of a pack
+// share the rays' geometry, which depends on the source alone; each keeps its
+// own photon rate and ends by itself. Entries of absent groups (n_grp and
+// beyond) hold P0 = -1, the mark of a group that has ended.
+struct TreeDev {
   double sx, sy, sz;       // source position, root cells
-  double P0;               // photon rate of one seed ray
-  double pmin0;            // p_min_frac * P0 (quartered per level below the seeds)
-  long long acc_slot;      // accumulator of cell c (batch numbering) is acc[acc_slot + c]
-  float sigma32;
+  double P0[kPack];        // photon rate of one seed ray, per group
+  double pmin0[kPack];     // p_min_frac * P0 (quartered per level below the seeds)
+  double sigma64[kPack];   // cross-section, cm^2
+  double eexc[kPack];      // E - E_ion, erg (0 where the problem's records have no second moment)
+  float sigma32[kPack];
+  long long acc_slot;      // accumulator of cell c (batch numbering) is acc[acc_slot + acc_stride * c]
   float split_t2_base;     // 12 / (4 pi phi_c), float; FLT_MAX when the problem never splits
   int level_init;
   int level_max;
@@ -93,16 +95,16 @@ struct SgDev {
   int root_grid;           // grid-table index of the problem's root grid
   int rnx, rny, rnz;       // its shape
   long long rcell_off;     // its first cell
-  double sigma64;          // cross-section, cm^2
   double four_pi_phi_c;    // 4 pi phi_c of its problem
   int problem;
   int covering;            // scale deposits into the accumulators by the covering factor
-  uint32_t acc_stride = 1; // its problem's acc_stride: the deposit into cell c (batch numbering) goes to
-                           //   acc[acc_slot + acc_stride * c], the momentum (stride 4) to the next three
-  double mom_scale;        // E_ph / c of the group (erg s/cm), 0 without radiation pressure
+  int n_grp;               // groups of the pack
+  uint32_t stat0;          // statistics of its first group (those of the others follow)
+  uint32_t acc_stride = 1; // its problem's acc_stride
+  double mom_scale;        // E_ph / c of the (one) group (erg s/cm), 0 without radiation pressure
   double r_halt = __builtin_huge_val();   // time-dependent rays: radius (root cells) where the
                                           // tree's rays halt in this step
-  // optically-thin approximation (tau_thin > 0)
+  // optically-thin approximation (tau_thin > 0; one group per tree)
   double tau_thin = 0.0;   // a ray is thin in a cell while its optical depth on leaving it is below this
   double four_pi_phi_thin; // 4 pi min(1, phi_c): the split threshold of thin rays
   float split_t2_thin;     // 12 / (4 pi min(1, phi_c)), float; FLT_MAX when the problem never splits
@@ -110,6 +112,7 @@ struct SgDev {
   double thin_coef;        // sigma Ndot_g / (4 pi dx_root^2): the thin rate at r root cells is thin_coef / r^2
 };
 
+// Statistics of one (source, group).
 struct SgStats {
   double esc_P;            // escaped photon rate
   double trunc_P;          // photon rate left in truncated rays
@@ -127,7 +130,6 @@ struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
   unsigned long long head[kLevels][kSegMax];    // slots claimed from each segment
   unsigned long long lost_rays;                 // children dropped on overflow
-  double lost_P;
   unsigned int err;                             // bit flags, see kErr*
   unsigned int pad;
   unsigned long long halt_count;                // time-dependent rays halted in this step
@@ -138,22 +140,28 @@ constexpr unsigned kErrOverflow = 1u;
 constexpr unsigned kErrBadInput = 2u;
 constexpr unsigned kErrInternal = 8u;
 
-// Level queue, structure of arrays. The radius is float64 in both precision
-// modes so a child starts exactly where its parent's exit distance put it.
+// Level queue, structure of arrays. A slot holds a ray of the level above that
+// split; its four children (pixels 4p .. 4p+3, a quarter of the photon rates
+// each) are formed when they are claimed: ray index i of a segment is child
+// i & 3 of slot i >> 2. The photon rates are one plane per group of the pack,
+// pstride apart; a group that has ended holds a negative rate. The radius is
+// float64 in both precision modes so a child starts exactly where its
+// parent's exit distance put it. The halt lists of time-dependent rays use
+// the same arrays for single rays.
 struct RayQueue {
   uint64_t* pix;
-  uint32_t* sg;
+  uint32_t* tree;
   double* r;
   double* P;
+  unsigned long long pstride;
 };
 
 template <typename R>
 struct TraceArgs {
   const GridDev* grids;
-  const ProblemDev* probs;
-  const SgDev* sgs;
+  const TreeDev* trees;
   const R* kappa;          // n_H x_HI dx_root per leaf cell; -(child+1) on covered root cells
-  double* acc;             // absorbed photons/s per (problem, group, leaf cell)
+  double* acc;             // accumulators (see ProblemDev)
   uint32_t rec_base;       // deposit keys >= rec_base start 4-sum radiation-pressure records (32-byte aligned)
   RayQueue in, out;                    // nseg segments of seg_cap slots each
   unsigned long long seg_cap;
@@ -163,17 +171,20 @@ struct TraceArgs {
   int gen;                             // launch generation (the HEALPix level in a one-shot solve)
   int cin, cout;                       // counter rows of the input and output queues
   int seed_level;                      // HEALPix level of the seed rays of this launch
-  int seed_sg_begin, seed_sg_end;      // trees seeded in this launch
+  int seed_begin, seed_end;            // trees seeded in this launch
   int chunk;                           // rays claimed per atomic
   int refill;                          // idle lanes that trigger a refill
   unsigned max_steps;                  // hard cap on cells per ray (never reached)
-  unsigned long long reserve;          // next-level slots a wave reserves at once (multiple of 4)
-  // time-dependent rays: where rays halted in this step go (halt_cap records; level in halt_lev)
+  unsigned long long reserve;          // next-level slots a wave reserves at once
+  // time-dependent rays: where rays halted in this step go (halt_cap records; level in halt_lev),
+  // and the ones halted in the previous step that are of this launch's level: records
+  // held[held_order[held_first + i]], i < n_held
   RayQueue halt;
   int* halt_lev;
   unsigned long long halt_cap;
-  uint32_t tree_fold;                  // statistics of tree k are kept under k % tree_fold (the trees
-                                       // of one batch), so the block tables hold one batch's trees
+  RayQueue held;
+  const uint32_t* held_order;
+  unsigned long long held_first, n_held;
   uint8_t* mark;                       // optically-thin marks (see ProblemDev), or NULL
   const double* kappa64;               // float kernels with the optically-thin approximation: the
                                        // columns in float64 (same layout as kappa), else NULL

@@ -22,29 +22,24 @@ template <typename R>
 hipError_t launch_prep(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long, long long, R*, double*,
                        Counters*, uint8_t* mark = nullptr, double* kappa64 = nullptr);
 template <typename R>
-hipError_t launch_trace_level(hipStream_t, int, const TraceArgs<R>&, bool cache, bool cover, bool radp,
+hipError_t launch_trace_level(hipStream_t, int, const TraceArgs<R>&, bool cache, int width, bool cover, bool radp,
                               bool thin = false);
 template <typename R>
-hipError_t launch_trace_level_halt(hipStream_t, int, const TraceArgs<R>&, bool cache);
-hipError_t launch_prefill_level(hipStream_t, int num_cu, const RayQueue& pool, const int* pool_lev,
-                                unsigned long long n_pool, int level, const RayQueue& q, unsigned long long seg_cap,
-                                int nseg, Counters* ctr, int row);
+hipError_t launch_trace_level_halt(hipStream_t, int, const TraceArgs<R>&, bool cache, int width);
 // Serving: empty the queued rays (counter row `row`, nseg segments) whose
 // tree index lies in one of the n ranges [lo[i], hi[i]) (n <= kDropRanges).
-hipError_t launch_drop_trees(hipStream_t, uint32_t* sg, const Counters* ctr, int row, unsigned long long seg_cap,
+hipError_t launch_drop_trees(hipStream_t, uint32_t* tree, const Counters* ctr, int row, unsigned long long seg_cap,
                              int nseg, const int* lo, const int* hi, int n);
-hipError_t launch_sum_blocks(hipStream_t, int blocks, const double* v, unsigned long long n, double* part);
-// moray_td_kernels.hip: the halt list sorted by (level, tree, pixel), and its per-level runs as queue input
+hipError_t launch_sum_blocks(hipStream_t, int blocks, const double* v, unsigned long long n, int planes,
+                             unsigned long long pstride, double* part);
+// moray_td_kernels.hip: the halt list sorted by (level, tree, pixel)
 hipError_t td_sort_temp_bytes(unsigned long long cap, size_t* bytes);
 hipError_t launch_td_sort(hipStream_t, int num_cu, const RayQueue& pool, const int* lev, unsigned long long n,
-                          int tree_bits, int pix_bits, unsigned long long* keys_in, unsigned long long* keys_out,
+                          int tree_bits, int pix_bits, int pix_drop, unsigned long long* keys_in, unsigned long long* keys_out,
                           uint32_t* idx_in, uint32_t* idx_out, void* temp, size_t temp_bytes);
-hipError_t launch_prefill_sorted(hipStream_t, int num_cu, const RayQueue& pool, const uint32_t* order,
-                                 unsigned long long first, unsigned long long count, const RayQueue& q,
-                                 unsigned long long seg_cap, int nseg, Counters* ctr, int row);
-// sgs, mark: the tree table and the optically-thin marks (NULL when no problem uses them)
+// trees, mark: the tree table and the optically-thin marks (NULL when no problem uses them)
 hipError_t launch_finalize(hipStream_t, int, const GridDev*, const ProblemDev*, const FinalBlock*, const double*,
-                           const double*, double*, const Counters*, const SgDev* sgs = nullptr,
+                           const double*, double*, const Counters*, const TreeDev* trees = nullptr,
                            const uint8_t* mark = nullptr);
 hipError_t trace_occupancy(int precision, bool cache, int* blocks_per_cu);
 // photo-ionisation equilibrium (moray_equilibrium.hip)
@@ -99,8 +94,8 @@ struct moray_ctx {
   bool overflow_serve_once = false;  // test hook (MORAY_INJECT_SERVE_OVERFLOW=1 at moray_init): the serving
                                      // engine's first launch with two or more problems reports a queue overflow
   size_t allocated = 0;
-  moray::DevBuf grids, probs, sgs, stats, ctr, kappa, kappa64, acc, mark, eexc, fblocks, partial, fields, outs;
-  moray::DevBuf q_pix[2], q_sg[2], q_r[2], q_P[2];
+  moray::DevBuf grids, probs, trees, stats, ctr, kappa, kappa64, acc, mark, eexc, fblocks, partial, fields, outs;
+  moray::DevBuf q_pix[2], q_tree[2], q_r[2], q_P[2];
   size_t q_cap = 0;
   void* h_stage = nullptr;
   size_t h_stage_bytes = 0;
@@ -125,7 +120,25 @@ moray_status validate(moray_ctx* c, const moray_problem& P, int pi);
 int reach_level(const moray_problem& P);
 double level_rays_bound(const moray_problem& P);
 
-// Segments of a level queue of `cap` slots: a power of two up to kSegMax, so
+// Energy groups a ray of a problem with n groups carries: n split evenly over
+// the fewest packs of at most kPack; pack k holds groups [first, first + count).
+inline int pack_count(int n) { return (n + kPack - 1) / kPack; }
+inline int pack_first(int n, int k) { return (int)((long long)n * k / pack_count(n)); }
+inline int pack_width(int n) { return (n + pack_count(n) - 1) / pack_count(n); }
+
+// Planes of photon rates a queue slot holds for rays of up to `width` groups
+// (the widths the trace kernel is built for).
+inline int rate_planes(int width) { return width <= 1 ? 1 : (width == 2 ? 2 : kPack); }
+
+// Bytes of one queue slot.
+inline size_t slot_bytes(int planes) { return sizeof(uint64_t) + sizeof(uint32_t) + sizeof(double) * (1 + planes); }
+
+// The parts of a tree's record that follow from its problem: the rays of
+// source `src` carrying groups [g0, g0 + n) (one group per ray in the modes
+// that keep a plane of accumulators per group).
+void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const ProblemDev& pd, const GridDev& root);
+
+// Segments of a level queue for `cap` rays: a power of two up to kSegMax, so
 // the trace kernel splits a launch's seeds among them with shifts.
 inline int queue_segments(size_t cap) {
   int n = 1;

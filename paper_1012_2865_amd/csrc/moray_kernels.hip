@@ -12,14 +12,14 @@
 //
 // Inside trace_level the grid is persistent: every wave keeps 64 rays in
 // flight, one per lane, marches them cell by cell (Eq. trace), tests the split
-// criterion at each cell exit (Eq. split), and deposits P (1 - e^-tau) into
-// the (problem, group) accumulator of the cell (Eqs. dtau, flux, kph; heating
-// is the group-weighted sum formed in finalize, Eq. gamma). Deposits combine
-// in a per-wave LDS table and reach the float64 accumulators in HBM as
-// atomics only when evicted; per-tree ray statistics combine in a per-block
-// LDS table. Idle lanes refill from a private chunk of the level queue
-// claimed with one atomic. Children of splitting lanes are compacted with a
-// wave ballot and written as four consecutive structure-of-arrays records.
+// criterion at each cell exit (Eq. split), and deposits P (1 - e^-tau) of every
+// energy group the ray carries into the cell's accumulators (Eqs. dtau, flux,
+// kph): with one group the absorbed rate, with more the absorbed rate and its
+// energy moment, summed over the groups (Eq. gamma). Deposits combine in a
+// per-wave LDS table and reach the float64 accumulators in HBM as atomics only
+// when evicted; per-tree ray statistics combine per wave. Idle lanes refill
+// from a private chunk of the level queue claimed with one atomic. Splitting
+// lanes are compacted with a wave ballot into one queue slot each.
 #include "moray_device.h"
 
 #include <hip/hip_runtime.h>
@@ -353,29 +353,35 @@ __device__ __forceinline__ double absorb(double& P, float tau) {
   return thin ? a : Pin - a;
 }
 
-// Per-lane ray state. The tree fields (source, photon rates, absorber
-// accumulator, cross-section, root grid) belong to the lane's current tree
-// and are reloaded only when the lane starts a ray of another tree.
-template <typename R>
+// Per-lane ray state. A ray carries NG energy groups of its source: they share
+// its geometry, and each has its own photon rate, cross-section and end. The
+// tree fields (source, cross-sections, accumulator, root grid) belong to the
+// lane's current tree and are reloaded only when the lane starts a ray of
+// another tree.
+template <typename R, int NG>
 struct Ray {
   typename GeomOf<R>::type g;
   uint64_t pix;
-  uint32_t sg;
+  uint32_t tree;          // of the ray
   int q;                  // grid index
   int c0, c1, c2;         // local cell
   int n0, n1, n2;         // grid dims
   int lin;                // batch-wide cell index
-  double P, pmin;
-  uint32_t slot0;         // the ray's (problem, group) accumulator of cell lin is acc[slot0 + lin]
-  R sigma;
+  double P[NG], pmin[NG];
+  bool alive[NG];         // groups the ray still carries (an ended group's P is 0)
+  uint32_t slot0;         // the ray's accumulator of cell lin is acc[slot0 + astride * lin]
+  R sigma[NG];
+  double eexc[NG];        // E - E_ion (moments only)
   R kap;                  // absorber column per root-cell length of the current cell
   R split_t;              // float path: split when u^2 > split_t; float64 path: 12*4^l (inf: never)
   double fpp;             // 4 pi phi_c (float64 path)
   unsigned segs;
   // the lane's tree
-  uint32_t tree;
+  uint32_t ltree;
+  uint32_t stat0;
+  int n_grp;
   int level;              // HEALPix level of the tree's rays in this launch
-  double sx, sy, sz, P0;
+  double sx, sy, sz;
   int root, rn0, rn1, rn2, rcell;
   bool cover;             // its deposits are scaled by the covering factor
   uint32_t astride;       // deposit key of cell lin: slot0 + astride * lin (4: a radiation-pressure record)
@@ -392,14 +398,21 @@ struct Ray {
   double fpp_thin;
   long long mark_base;
   unsigned tsegs;         // the ray's thin segments
+
+  __device__ bool any_alive() const {
+    bool m = alive[0];
+#pragma unroll
+    for (int g = 1; g < NG; ++g) m = m || alive[g];
+    return m;
+  }
 };
 
-template <typename R>
+template <typename R, int NG>
 struct Tracer {
   const TraceArgs<R>& a;
   __device__ explicit Tracer(const TraceArgs<R>& args) : a(args) {}
 
-  __device__ void root_frame(Ray<R>& L) const {
+  __device__ void root_frame(Ray<R, NG>& L) const {
     L.q = L.root;
     L.n0 = L.rn0; L.n1 = L.rn1; L.n2 = L.rn2;
     const double sl[3] = {L.sx, L.sy, L.sz};
@@ -407,7 +420,7 @@ struct Tracer {
     L.lin = L.rcell + L.c0 + L.n0 * (L.c1 + L.n1 * L.c2);
   }
 
-  __device__ void child_frame(Ray<R>& L, int q) const {
+  __device__ void child_frame(Ray<R, NG>& L, int q) const {
     const GridDev& G = a.grids[q];
     L.q = q;
     L.n0 = G.nx; L.n1 = G.ny; L.n2 = G.nz;
@@ -420,7 +433,7 @@ struct Tracer {
   // moving in direction `dir`, at the current radius: along the crossing axis
   // the fine cell follows from the face, along the others from the position,
   // kept among the two fine cells under the root cell.
-  __device__ void enter_child(Ray<R>& L, int ch, int rc0, int rc1, int rc2, int ax, int dir) const {
+  __device__ void enter_child(Ray<R, NG>& L, int ch, int rc0, int rc1, int rc2, int ax, int dir) const {
     const GridDev& G = a.grids[ch];
     const int rc[3] = {rc0, rc1, rc2};
     const int o[3] = {G.ox, G.oy, G.oz};
@@ -446,12 +459,12 @@ struct Tracer {
   // After a step along `ax` by `dir` out of the current grid, or into a root
   // cell covered by a child: find the new leaf cell. Returns false when the
   // ray left the root grid.
-  __device__ bool settle(Ray<R>& L, int ax, int dir) const {
+  __device__ bool settle(Ray<R, NG>& L, int ax, int dir) const {
     const bool inside = find_cell(L, ax, dir);
     finish_vector_loads();
     return inside;
   }
-  __device__ bool find_cell(Ray<R>& L, int ax, int dir) const {
+  __device__ bool find_cell(Ray<R, NG>& L, int ax, int dir) const {
     if (L.q == L.root) {
       if ((unsigned)L.c0 >= (unsigned)L.n0 || (unsigned)L.c1 >= (unsigned)L.n1 || (unsigned)L.c2 >= (unsigned)L.n2)
         return false;
@@ -486,33 +499,44 @@ struct Tracer {
   }
 
   // A ray starts in three steps:
-  //   fetch  - its queue record (a child) or its tree and pixel (a seed);
+  //   fetch  - its queue record (a child of a split ray), its halted record,
+  //            or its tree and pixel (a seed, whose rates load_tree gives);
   //   tree   - the tree's constants, unless the lane already holds them;
   //   locate - direction, start cell and frame, and that cell's absorber column.
-  __device__ void fetch(Ray<R>& L, bool child, unsigned long long idx, double& r64) const {
-    if (child) {
-      L.sg = a.in.sg[idx];
-      L.pix = a.in.pix[idx];
-      r64 = a.in.r[idx];
-      L.P = a.in.P[idx];
-    } else {
-      const unsigned long long npix = 12ull << (2 * a.seed_level);
-      L.sg = (uint32_t)(a.seed_sg_begin + idx / npix);
-      L.pix = idx % npix;
-      r64 = 0.0;
-      L.P = -__builtin_huge_val();         // the tree's seed rate, set in locate
-    }
+  __device__ void fetch_child(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+    const unsigned long long slot = i >> 2;
+    L.tree = a.in.tree[slot];
+    L.pix = 4ull * a.in.pix[slot] + (i & 3ull);
+    r64 = a.in.r[slot];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) L.P[g] = 0.25 * a.in.P[g * a.in.pstride + slot];
+  }
+  __device__ void fetch_held(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+    const unsigned long long slot = a.held_order[a.held_first + i];
+    L.tree = a.held.tree[slot];
+    L.pix = a.held.pix[slot];
+    r64 = a.held.r[slot];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) L.P[g] = a.held.P[g * a.held.pstride + slot];
+  }
+  __device__ void fetch_seed(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+    const unsigned long long npix = 12ull << (2 * a.seed_level);
+    L.tree = (uint32_t)(a.seed_begin + i / npix);
+    L.pix = i % npix;
+    r64 = 0.0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) L.P[g] = a.trees[L.tree].P0[g];
   }
 
-  __device__ void load_tree(Ray<R>& L) const {
-    const SgDev& S = a.sgs[L.sg];
+  __device__ void load_tree(Ray<R, NG>& L) const {
+    const TreeDev& S = a.trees[L.tree];
     const int level = S.level_init + (a.gen - S.gen0);
-    L.tree = L.sg;
+    L.ltree = L.tree;
     L.level = level;
     L.sx = S.sx; L.sy = S.sy; L.sz = S.sz;
-    L.P0 = S.P0;
-    L.pmin = ldexp(S.pmin0, -2 * (level - S.level_init));
     L.slot0 = (uint32_t)S.acc_slot;
+    L.stat0 = S.stat0;
+    L.n_grp = S.n_grp;
     L.root = S.root_grid;
     L.rn0 = S.rnx; L.rn1 = S.rny; L.rn2 = S.rnz;
     L.rcell = (int)S.rcell_off;
@@ -520,21 +544,25 @@ struct Tracer {
     L.astride = S.acc_stride;
     L.mscale = S.mom_scale;
     L.rhalt = S.r_halt;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      L.pmin[g] = ldexp(S.pmin0[g], -2 * (level - S.level_init));
+      L.sigma[g] = sizeof(R) == 4 ? (R)S.sigma32[g] : (R)S.sigma64[g];
+      L.eexc[g] = S.eexc[g];
+    }
     const bool can_split = level < S.level_max;
     if constexpr (sizeof(R) == 4) {
-      L.sigma = S.sigma32;
       L.split_t = can_split ? ldexpf(S.split_t2_base, 2 * level) : FLT_MAX;
       L.fpp = 0.0;
     } else {
-      L.sigma = S.sigma64;
       L.split_t = can_split ? ldexp(12.0, 2 * level) : __builtin_huge_val();
       L.fpp = S.four_pi_phi_c;
     }
   }
 
   // The optically-thin constants of the lane's tree (after load_tree).
-  __device__ void load_thin(Ray<R>& L) const {
-    const SgDev& S = a.sgs[L.sg];
+  __device__ void load_thin(Ray<R, NG>& L) const {
+    const TreeDev& S = a.trees[L.tree];
     L.mark_base = S.mark_base;
     const bool can_split = L.level < S.level_max;
     if constexpr (sizeof(R) == 4) {
@@ -548,22 +576,22 @@ struct Tracer {
 
   // Thin state of a fetched ray (before locate). A thin ray has removed no
   // photons, so its rate is its seed's, quartered per level; its queue
-  // record holds -(1 + rem) in place of the rate (its parent staged
-  // -4 (1 + rem), which the child writer quarters like any rate). A seed is
-  // thin when its tree uses the approximation. rem is capped at kRemMax (a
-  // zero cross-section), which keeps every record finite.
+  // record holds -4 (1 + rem) in place of the rate, which reading a child
+  // quarters like any rate. A seed is thin when its tree uses the
+  // approximation. rem is capped at kRemMax (a zero cross-section), which
+  // keeps every record finite.
   static constexpr double kRemMax = 1e300;
-  __device__ void thin_start(Ray<R>& L) const {
+  __device__ void thin_start(Ray<R, NG>& L, bool seed) const {
     L.tsegs = 0;
-    const SgDev& S = a.sgs[L.sg];
-    if (L.P == -__builtin_huge_val()) {
+    const TreeDev& S = a.trees[L.tree];
+    if (seed) {
       L.thin = S.tau_thin > 0.0;
-      const double r = S.tau_thin / S.sigma64;
+      const double r = S.tau_thin / S.sigma64[0];
       L.rem = r < kRemMax ? r : kRemMax;
-    } else if (L.P < 0.0) {
+    } else if (L.P[0] < 0.0) {
       L.thin = true;
-      L.rem = -L.P - 1.0;
-      L.P = ldexp(S.P0, -2 * (L.level - S.level_init));
+      L.rem = -L.P[0] - 1.0;
+      L.P[0] = ldexp(S.P0[0], -2 * (L.level - S.level_init));
     } else {
       L.thin = false;
     }
@@ -572,7 +600,7 @@ struct Tracer {
   // Does the ray's current cell hold its source (inside or on its boundary)?
   // Only a cell within sqrt(3) local cells of the source can: nearer than 2
   // the test is taken exactly, on the source's float64 local coordinates.
-  __device__ bool holds_source(const Ray<R>& L) const {
+  __device__ bool holds_source(const Ray<R, NG>& L) const {
     const bool child = L.q != L.root;
     if (L.g.radius64() * (child ? 2.0 : 1.0) >= 2.0) return false;
     double sl[3] = {L.sx, L.sy, L.sz};
@@ -592,9 +620,13 @@ struct Tracer {
   // Start cell of a fetched ray whose tree constants are loaded. Returns false
   // when the ray starts outside the root grid; otherwise the ray is framed in
   // the root cell holding s + r d and `k` receives that cell's column.
-  __device__ bool locate(Ray<R>& L, double r64, R& k) const {
-    if (L.P < 0.0) L.P = L.P0;
+  __device__ bool locate(Ray<R, NG>& L, double r64, R& k) const {
     L.segs = 0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      L.alive[g] = NG == 1 || (g < L.n_grp && L.P[g] >= 0.0);   // a record may hold fewer rates than NG
+      if (NG > 1) L.P[g] = L.alive[g] ? L.P[g] : 0.0;
+    }
     double v[3];
     healpix_dir(L.level, L.pix, v[0], v[1], v[2]);
     L.g.set_dir(v);
@@ -613,7 +645,7 @@ struct Tracer {
   // The located ray becomes active: in the root cell, or when that cell is
   // covered by a child grid, in the fine cell under it that holds s + r d
   // (exact in floating point; kept in range regardless).
-  __device__ void begin(Ray<R>& L, R k) const {
+  __device__ void begin(Ray<R, NG>& L, R k) const {
     if (k >= (R)0) {
       L.kap = k;
       return;
@@ -635,13 +667,13 @@ struct Tracer {
 
   // Float64 re-evaluation of the split test for the current cell, in the
   // canonical form 12 * 4^l < (4 pi phi_c) * u^2, u = t_exit in local cells.
-  __device__ bool split_exact(const Ray<R>& L, bool thin) const {
+  __device__ bool split_exact(const Ray<R, NG>& L, bool thin) const {
     const bool sp = split_exact64(L, thin);
     finish_vector_loads();
     return sp;
   }
-  __device__ bool split_exact64(const Ray<R>& L, bool thin) const {
-    const SgDev& S = a.sgs[L.sg];
+  __device__ bool split_exact64(const Ray<R, NG>& L, bool thin) const {
+    const TreeDev& S = a.trees[L.tree];
     const bool child = L.q != L.root;
     int o[3] = {0, 0, 0};
     if (child) {
@@ -667,7 +699,7 @@ struct Tracer {
 
   // thin: the ray is optically thin in this cell and is split against
   // min(1, phi_c) rays per cell face (section 2.4)
-  __device__ bool split_test(const Ray<R>& L, int ax, bool thin = false) const {
+  __device__ bool split_test(const Ray<R, NG>& L, int ax, bool thin = false) const {
     if constexpr (sizeof(R) == 4) {
       const float u = L.g.local_u(ax);
       const float t = thin ? L.split_t_thin : L.split_t;
@@ -689,7 +721,7 @@ struct Tracer {
   // sqrt(4 pi / N_pix) = sqrt(pi/3) 2^-l), both in local cells, and
   // f_c = (1/2 + D_edge / L_pix)^2, at most 1 (1 also for R_0 = 0). Float64
   // throughout, from the float64 direction and source.
-  __device__ double covering_factor(const Ray<R>& L, double dr) const {
+  __device__ double covering_factor(const Ray<R, NG>& L, double dr) const {
     const double h = (double)L.g.hloc;
     const double r0 = L.g.radius64();
     const double rmid = (r0 + 0.5 * dr) * h;
@@ -707,107 +739,6 @@ struct Tracer {
   }
 };
 
-// Per-tree statistics of finished rays (segments, splits, escaped and
-// truncated rays with their photon rates), combined per block in LDS: a lane
-// whose ray ends adds to its tree's entry with LDS atomics, and the block adds
-// each entry to the tree's global counters once, when all its waves are done.
-// Consecutive rays of a lane seldom share a tree, and a global atomic per ray
-// end would sit in the same in-order memory counter as the next absorber
-// gather. A tree that finds no free entry among its kTallyProbes probes adds
-// to the global counters directly: those are atomics on its tree's counters,
-// one address that every ray end of the tree on the device then shares (two
-// probes left enough trees of the 64-grid batch without an entry to take its
-// step from 37.1 to 42.5 ms; 16 and 32 probes measured alike, a probe of
-// the whole table slower). THIN adds a fifth count, the ray's optically thin
-// segments (the rays of one tree tend to end together, and one global atomic
-// per ray end on the tree's counter serialised at the memory side).
-template <bool THIN>
-struct TallyTable {
-  static constexpr int kRows = THIN ? 5 : 4;
-  uint32_t* key;                 // kTallySlots tree indices (kNoTree: free)
-  unsigned long long* cnt;       // [kRows][kTallySlots]: segs, splits, n_esc, n_trunc(, thin_segs)
-  double* sum;                   // [2][kTallySlots]: esc_P, trunc_P
-
-  // all threads of the block; followed by a block barrier
-  __device__ void init() {
-    __shared__ uint32_t skey[kTallySlots];
-    __shared__ unsigned long long scnt[kRows * kTallySlots];
-    __shared__ double ssum[2 * kTallySlots];
-    key = skey; cnt = scnt; sum = ssum;
-    for (int i = threadIdx.x; i < kTallySlots; i += blockDim.x) {
-      key[i] = kNoTree;
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) cnt[r * kTallySlots + i] = 0ull;
-      sum[i] = sum[kTallySlots + i] = 0.0;
-    }
-  }
-  // kind: 0 escaped, 1 truncated, 2 split, 3 halted (its segments only: the
-  // photons it holds are summed from the halt list)
-  __device__ void add(SgStats* stats, uint32_t sg, unsigned segs, double P, int kind, unsigned tsegs = 0u) {
-    const uint32_t h0 = (sg * 0x9E3779B1u) >> (32 - kTallyLog2);
-    int slot = -1;
-#pragma unroll
-    for (int probe = 0; probe < kTallyProbes; ++probe) {
-      const uint32_t h = (h0 + probe) & (kTallySlots - 1);
-      uint32_t k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (k == kNoTree) {
-        uint32_t seen = kNoTree;
-        __hip_atomic_compare_exchange_strong(&key[h], &seen, sg, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_WORKGROUP);
-        k = seen == kNoTree ? sg : seen;
-      }
-      if (k == sg) {
-        slot = (int)h;
-        break;
-      }
-    }
-    const int c = kind == 2 ? 1 : kind + 2;
-    if (slot >= 0) {
-      __hip_atomic_fetch_add(&cnt[slot], (unsigned long long)segs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (kind < 3)
-        __hip_atomic_fetch_add(&cnt[c * kTallySlots + slot], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (kind < 2)
-        __hip_atomic_fetch_add(&sum[kind * kTallySlots + slot], P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (THIN && tsegs)
-        __hip_atomic_fetch_add(&cnt[4 * kTallySlots + slot], (unsigned long long)tsegs, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-      SgStats& st = stats[sg];
-      if (segs) atomicAdd(&st.segs, (unsigned long long)segs);
-      if (THIN && tsegs) atomicAdd(&st.thin_segs, (unsigned long long)tsegs);
-      if (kind == 2) {
-        atomicAdd(&st.splits, 1ull);
-      } else if (kind == 3) {
-      } else if (kind == 0) {
-        atomicAdd(&st.n_esc, 1ull);
-        unsafeAtomicAdd(&st.esc_P, P);
-      } else {
-        atomicAdd(&st.n_trunc, 1ull);
-        unsafeAtomicAdd(&st.trunc_P, P);
-      }
-    }
-  }
-  // all threads of the block, after a block barrier that follows every add
-  __device__ void flush(SgStats* stats) const {
-    for (int i = threadIdx.x; i < kTallySlots; i += blockDim.x) {
-      const uint32_t k = key[i];
-      if (k == kNoTree) continue;
-      SgStats& st = stats[k];
-      if (cnt[i]) atomicAdd(&st.segs, cnt[i]);
-      if (cnt[kTallySlots + i]) atomicAdd(&st.splits, cnt[kTallySlots + i]);
-      if (cnt[2 * kTallySlots + i]) {
-        atomicAdd(&st.n_esc, cnt[2 * kTallySlots + i]);
-        unsafeAtomicAdd(&st.esc_P, sum[i]);
-      }
-      if (cnt[3 * kTallySlots + i]) {
-        atomicAdd(&st.n_trunc, cnt[3 * kTallySlots + i]);
-        unsafeAtomicAdd(&st.trunc_P, sum[kTallySlots + i]);
-      }
-      if (THIN && cnt[4 * kTallySlots + i]) atomicAdd(&st.thin_segs, cnt[4 * kTallySlots + i]);
-    }
-  }
-};
-
 __device__ __forceinline__ unsigned long long bcast64(unsigned long long v, int src) {
   const unsigned lo = __shfl((unsigned)v, src), hi = __shfl((unsigned)(v >> 32), src);
   return ((unsigned long long)hi << 32) | lo;
@@ -821,218 +752,259 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint32_t cache_index(uint32_t key) {
-  return (key * 0x9E3779B1u) >> (32 - kCacheLog2);
+// Sums over the 64 lanes of a wave in which every lane is active (data-parallel
+// primitives: row shifts inside 16 lanes, then the two row broadcasts; the last
+// lane holds the total).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_zero(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
 }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_zero(double x) {
+  const unsigned long long u = __double_as_longlong(x);
+  const unsigned lo = dpp_zero<CTRL, ROWS>((unsigned)u), hi = dpp_zero<CTRL, ROWS>((unsigned)(u >> 32));
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+template <typename T>
+__device__ __forceinline__ T wave_total(T x) {     // valid in the last lane
+  x += dpp_zero<0x111, 0xf>(x);                    // row_shr:1
+  x += dpp_zero<0x112, 0xf>(x);
+  x += dpp_zero<0x114, 0xf>(x);
+  x += dpp_zero<0x118, 0xf>(x);
+  x += dpp_zero<0x142, 0xa>(x);                    // row_bcast:15 into rows 1 and 3
+  x += dpp_zero<0x143, 0xc>(x);                    // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Per-(tree, group) statistics of finished rays (segments, splits, escaped and
+// truncated rays with their photon rates). The rays of a claim nearly always
+// belong to one tree, so a wave keeps one tree's sums in LDS and adds them to
+// the tree's global counters when it changes trees and at its end; a ray of
+// another tree adds to the global counters directly. Ended rays are tallied
+// when their lanes refill, all at once: the counts come from ballots and the
+// rates from one reduction, so a ray end puts no atomic into the memory
+// counter the next column gather waits on (a global atomic per ray end took
+// the 128^3 workload, 16 sources and 4 groups, from 11.7 to 21 ms).
+// kind: 0 escaped, 1 truncated, 2 split, 3 halted (its segments only: the
+// photons it holds are summed from the halt list).
+template <int NG, bool THIN>
+struct WaveTally {
+  static constexpr int kRows = 5;                  // segs, splits, n_esc, n_trunc, thin_segs
+  unsigned long long* cnt;                         // [kRows][NG]
+  double* sum;                                     // [2][NG]: esc_P, trunc_P
+  uint32_t stat0;                                  // wave-uniform; kNoTree: none yet
+
+  __device__ void init(int lane) {
+    __shared__ unsigned long long scnt[kTraceBlock / kWave][kRows * NG];
+    __shared__ double ssum[kTraceBlock / kWave][2 * NG];
+    cnt = scnt[threadIdx.x / kWave];
+    sum = ssum[threadIdx.x / kWave];
+    stat0 = kNoTree;
+    clear(lane);
+  }
+  __device__ void clear(int lane) {
+    if (lane < kRows * NG) cnt[lane] = 0ull;
+    if (lane < 2 * NG) sum[lane] = 0.0;
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ void flush(SgStats* stats, int lane) {
+    __builtin_amdgcn_wave_barrier();
+    if (stat0 != kNoTree && lane < NG) {
+      SgStats& st = stats[stat0 + lane];
+      if (cnt[lane]) atomicAdd(&st.segs, cnt[lane]);
+      if (cnt[NG + lane]) atomicAdd(&st.splits, cnt[NG + lane]);
+      if (cnt[2 * NG + lane]) {
+        atomicAdd(&st.n_esc, cnt[2 * NG + lane]);
+        unsafeAtomicAdd(&st.esc_P, sum[lane]);
+      }
+      if (cnt[3 * NG + lane]) {
+        atomicAdd(&st.n_trunc, cnt[3 * NG + lane]);
+        unsafeAtomicAdd(&st.trunc_P, sum[NG + lane]);
+      }
+      if (THIN && cnt[4 * NG + lane]) atomicAdd(&st.thin_segs, cnt[4 * NG + lane]);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // the tree whose sums the wave keeps from now on (all lanes)
+  __device__ void follow(SgStats* stats, uint32_t s0, int lane) {
+    if (s0 == stat0) return;
+    flush(stats, lane);
+    clear(lane);
+    stat0 = s0;
+  }
+  static __device__ void direct(SgStats& st, unsigned segs, unsigned tsegs, int kind, double P) {
+    if (segs) atomicAdd(&st.segs, (unsigned long long)segs);
+    if (THIN && tsegs) atomicAdd(&st.thin_segs, (unsigned long long)tsegs);
+    if (kind == 2) {
+      atomicAdd(&st.splits, 1ull);
+    } else if (kind == 0) {
+      atomicAdd(&st.n_esc, 1ull);
+      unsafeAtomicAdd(&st.esc_P, P);
+    } else if (kind == 1) {
+      atomicAdd(&st.n_trunc, 1ull);
+      unsafeAtomicAdd(&st.trunc_P, P);
+    }
+  }
+  // group g of the calling lane's ray is truncated (any subset of lanes)
+  template <typename RAY>
+  __device__ void truncated(SgStats* stats, const RAY& L, int g) {
+    if (L.stat0 == stat0) {
+      __hip_atomic_fetch_add(&cnt[g], (unsigned long long)L.segs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&cnt[3 * NG + g], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&sum[NG + g], L.P[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      direct(stats[L.stat0 + g], L.segs, 0u, 1, L.P[g]);
+    }
+  }
+  // the groups still alive of every lane whose ray ended with `kind` >= 0 (all lanes)
+  template <typename RAY>
+  __device__ void ended(SgStats* stats, const RAY& L, int kind, int lane) {
+    const bool here = kind >= 0 && L.stat0 == stat0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const bool mine = kind >= 0 && L.alive[g];
+      const bool in = here && L.alive[g];
+      if (!__ballot(mine)) continue;
+      const unsigned segs = wave_total(in ? L.segs : 0u);
+      const unsigned tsegs = THIN ? wave_total(in ? L.tsegs : 0u) : 0u;
+      const int n_esc = __popcll(__ballot(in && kind == 0)), n_trunc = __popcll(__ballot(in && kind == 1));
+      const int n_split = __popcll(__ballot(in && kind == 2));
+      const double esc = n_esc ? wave_total(in && kind == 0 ? L.P[g] : 0.0) : 0.0;
+      const double trunc = n_trunc ? wave_total(in && kind == 1 ? L.P[g] : 0.0) : 0.0;
+      if (lane == kWave - 1) {
+        // the wave's only writer here; truncated() adds atomically, at other times
+        cnt[g] += segs;
+        if (n_split) cnt[NG + g] += (unsigned)n_split;
+        if (n_esc) {
+          cnt[2 * NG + g] += (unsigned)n_esc;
+          sum[g] += esc;
+        }
+        if (n_trunc) {
+          cnt[3 * NG + g] += (unsigned)n_trunc;
+          sum[NG + g] += trunc;
+        }
+        if (THIN) cnt[4 * NG + g] += tsegs;
+      }
+      if (mine && !in) direct(stats[L.stat0 + g], L.segs, THIN ? L.tsegs : 0u, kind, L.P[g]);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+};
 
 // Every global store or atomic a wave issues stays outstanding in the same
 // in-order counter as its loads, so the next gather of an absorber column
 // may wait for it, and float64 atomics are performed at the memory side. The
 // trace therefore stages its writes in LDS and issues them in bulk: deposits
 // combine in a per-wave cache, evicted sums collect in a per-wave buffer
-// drained 64 atomics per instruction, and split parents collect in a per-wave
-// stage whose children are written together.
+// drained 64 atomics per instruction, and rays that split collect in a per-wave
+// stage written together.
 
 // Deposit combining: each wave keeps a direct-mapped table of (accumulator
-// slot, float64 sum) in LDS. The rays of a wave come from one small patch of
-// HEALPix pixels, so each cell of their cone receives several of their
+// record, NS float64 sums) in LDS. The rays of a wave come from one small patch
+// of HEALPix pixels, so each cell of their cone receives several of their
 // deposits a few steps apart; those add up in LDS and reach the float64
-// accumulator in HBM only when the entry is evicted or the launch ends.
+// accumulators in HBM only when the entry is evicted or the launch ends.
 // Within an iteration every lane first compares its key, matching lanes add,
 // and only then may a lane claim the entry for a new key (one winner per
-// entry via compare-and-swap), so every deposit lands in its own cell's sum.
-template <bool CACHE>
-struct DepositCache;
+// entry via compare-and-swap), so every deposit lands in its own cell's sums.
+//
+// NS: 1 for the absorbed rate alone; 2 for the moments of rays with several
+// groups (absorbed rate, energy); 4 for the radiation-pressure record. A
+// record's sums are neighbours in memory and leave with (entry, sum) spread over
+// consecutive lanes, so they go out in one instruction to one piece of a
+// cache line: the memory side takes one request for them. Which sums beyond the
+// first a record has: with NS = 2 those that are not zero (a one-group
+// problem's record in a batch of others is one sum, and its second sum stays 0);
+// with NS = 4 all four from rec_base on, one below it.
+//
+// Entries: what three blocks (two with NS = 4) leave of a CU's 160 KB of LDS.
+template <int NS> struct CacheShape;
+template <> struct CacheShape<1> { static constexpr int entries = 512, evict = 64; };
+template <> struct CacheShape<2> { static constexpr int entries = 416, evict = 64; };
+template <> struct CacheShape<4> { static constexpr int entries = 256, evict = 128; };
 
-template <>
-struct DepositCache<false> {
-  __device__ void init(int) {}
-  __device__ void add(double* acc, uint32_t key, double v, bool has, int) { if (has) unsafeAtomicAdd(&acc[key], v); }
-  __device__ bool want_drain() const { return false; }
-  __device__ void drain(double*, int) {}
-  __device__ void flush(double*, int) {}
-};
+template <int N>
+__device__ __forceinline__ uint32_t cache_index(uint32_t key) {
+  const uint32_t h = key * 0x9E3779B1u;
+  if constexpr ((N & (N - 1)) == 0) return h / (0x100000000ull / N);
+  return (uint32_t)(((uint64_t)(h >> 8) * (uint64_t)(N << 8)) >> 32);   // 24-bit factors
+}
 
-template <>
-struct DepositCache<true> {
+template <bool CACHE, int NS>
+struct DepositCache {
+  static constexpr int N = CacheShape<NS>::entries, E = CacheShape<NS>::evict;
   uint32_t* key;
-  double* val;
-  uint32_t* ekey;         // evicted sums waiting for their global atomic
-  double* eval;
+  double* val;            // [NS][N]
+  uint32_t* ekey;         // evicted sums waiting for their global atomics
+  double* eval;           // [NS][E]
   int ecount;             // wave-uniform
+  uint32_t rec_base;
 
-  __device__ void init(int lane) {
-    __shared__ uint32_t skey[kTraceBlock / kWave][kCacheEntries];
-    __shared__ double sval[kTraceBlock / kWave][kCacheEntries];
-    __shared__ uint32_t sekey[kTraceBlock / kWave][kEvictCap];
-    __shared__ double seval[kTraceBlock / kWave][kEvictCap];
-    const int wv = threadIdx.x / kWave;
-    key = skey[wv];
-    val = sval[wv];
-    ekey = sekey[wv];
-    eval = seval[wv];
-    ecount = 0;
-    for (int e = lane; e < kCacheEntries; e += kWave) key[e] = kNoSlot;
-    __builtin_amdgcn_wave_barrier();
+  static __device__ __forceinline__ void out(double* acc, uint32_t kk, int c, double v, uint32_t rec_base) {
+    if (c == 0 || (NS == 2 ? v != 0.0 : kk >= rec_base)) unsafeAtomicAdd(&acc[kk + c], v);
   }
-  __device__ bool want_drain() const { return ecount >= kEvictCap - kWave; }
-  // one global atomic instruction per 64 buffered sums
+
+  __device__ void init(int lane, uint32_t rb) {
+    rec_base = rb;
+    if constexpr (CACHE) {
+      __shared__ uint32_t skey[kTraceBlock / kWave][N];
+      __shared__ double sval[kTraceBlock / kWave][NS * N];
+      __shared__ uint32_t sekey[kTraceBlock / kWave][E];
+      __shared__ double seval[kTraceBlock / kWave][NS * E];
+      const int wv = threadIdx.x / kWave;
+      key = skey[wv];
+      val = sval[wv];
+      ekey = sekey[wv];
+      eval = seval[wv];
+      ecount = 0;
+      for (int e = lane; e < N; e += kWave) key[e] = kNoSlot;
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  // 64 buffered sums per global atomic instruction
   __device__ void drain(double* acc, int lane) {
-    __builtin_amdgcn_wave_barrier();
-    for (int i = lane; i < ecount; i += kWave) unsafeAtomicAdd(&acc[ekey[i]], eval[i]);
-    ecount = 0;
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (CACHE) {
+      __builtin_amdgcn_wave_barrier();
+      for (int j = lane; j < NS * ecount; j += kWave) {
+        const int i = j / NS, c = j % NS;
+        out(acc, ekey[i], c, eval[c * E + i], rec_base);
+      }
+      ecount = 0;
+      __builtin_amdgcn_wave_barrier();
+    }
   }
   // Every lane of the wave calls this (uniform control flow); one pass per
-  // call. Lanes whose key is in the table add to its sum; the others claim
+  // call. Lanes whose key is in the table add to its sums; the others claim
   // their entry by compare-and-swap. A winner swaps its deposit in and passes
-  // the entry's old sum to the eviction buffer. A lane that loses the claim
+  // the entry's old sums to the eviction buffer. A lane that loses the claim
   // sees the winner's key in the failed swap: if it is its own key (two rays
-  // of one tree entering the same cell) it adds to the new sum once the
+  // of one tree entering the same cell) it adds to the new sums once the
   // winner has swapped, otherwise it passes its deposit to the eviction
   // buffer. The phases are separated by wave barriers: per thread the
   // branches are exclusive, and without a convergent barrier between them
   // the compiler may merge them into one if/else and reorder the LDS ops.
-  __device__ void add(double* acc, uint32_t k_new, double v, bool has, int lane) {
+  __device__ void add(double* acc, uint32_t k_new, const double (&v)[NS], bool has, int lane) {
+    if constexpr (!CACHE) {
+      if (has) {
+#pragma unroll
+        for (int c = 0; c < NS; ++c) out(acc, k_new, c, v[c], rec_base);
+      }
+      return;
+    }
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (!__ballot(has)) return;
-    if (ecount > kEvictCap - kWave) drain(acc, lane);     // room for this call's evictions
     uint32_t h = 0, k = kNoSlot;
     bool match = false;
     if (has) {
-      h = cache_index(k_new);
-      k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      match = k == k_new;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (match) __hip_atomic_fetch_add(&val[h], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __builtin_amdgcn_wave_barrier();
-    const bool claim = has && !match;
-    bool won = false, join = false;
-    if (claim) {
-      uint32_t seen = k;
-      won = __hip_atomic_compare_exchange_strong(&key[h], &seen, k_new, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-      join = !won && seen == k_new;
-    }
-    __builtin_amdgcn_wave_barrier();
-    const bool out = claim && !join && (!won || k != kNoSlot);
-    const unsigned long long omask = __ballot(out);
-    uint32_t ok = k_new;
-    double ov = v;
-    if (won) {
-      // the adds of this call precede the exchange, so the old sum is complete
-      ov = __hip_atomic_exchange(&val[h], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      ok = k;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (join) __hip_atomic_fetch_add(&val[h], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (out) {
-      const int e = ecount + __popcll(omask & below);
-      ekey[e] = ok;
-      eval[e] = ov;
-    }
-    ecount += __popcll(omask);
-    __builtin_amdgcn_wave_barrier();
-  }
-  __device__ void flush(double* acc, int lane) {
-    drain(acc, lane);
-    for (int e = lane; e < kCacheEntries; e += kWave) {
-      const uint32_t k = key[e];
-      if (k != kNoSlot) unsafeAtomicAdd(&acc[k], val[e]);
-    }
-  }
-};
-
-// Radiation pressure: a problem that asks for the momentum keeps one 32-byte
-// record per (group, cell), [absorbed rate, momentum x, y, z], so a segment
-// makes one deposit of four sums under one key. Keys at or above rec_base
-// are such records; below it they are the plain one-sum slots of the other
-// problems of the batch. Evicted records are drained with (entry, component)
-// spread over consecutive lanes, so the four float64 atomics of a record go
-// out in one instruction to one 32-byte-aligned piece of a cache line.
-constexpr int kCache4Log2 = 8;                 // entries of the 4-sum table per wave
-constexpr int kCache4Entries = 1 << kCache4Log2;
-
-template <bool CACHE>
-struct DepositCache4;
-
-template <>
-struct DepositCache4<false> {
-  uint32_t rec_base;
-  __device__ void init(int, uint32_t rb) { rec_base = rb; }
-  __device__ void add(double* acc, uint32_t key, const double (&v)[4], bool has, int) {
-    if (!has) return;
-    unsafeAtomicAdd(&acc[key], v[0]);
-    if (key >= rec_base) {
-      unsafeAtomicAdd(&acc[key + 1], v[1]);
-      unsafeAtomicAdd(&acc[key + 2], v[2]);
-      unsafeAtomicAdd(&acc[key + 3], v[3]);
-    }
-  }
-  __device__ bool want_drain() const { return false; }
-  __device__ void drain(double*, int) {}
-  __device__ void flush(double*, int) {}
-};
-
-__device__ __forceinline__ uint32_t cache4_index(uint32_t key) {
-  return (key * 0x9E3779B1u) >> (32 - kCache4Log2);
-}
-
-template <>
-struct DepositCache4<true> {
-  uint32_t* key;
-  double* val;            // [4][kCache4Entries]
-  uint32_t* ekey;
-  double* eval;           // [4][kEvictCap]
-  int ecount;
-  uint32_t rec_base;
-
-  __device__ void init(int lane, uint32_t rb) {
-    __shared__ uint32_t skey[kTraceBlock / kWave][kCache4Entries];
-    __shared__ double sval[kTraceBlock / kWave][4 * kCache4Entries];
-    __shared__ uint32_t sekey[kTraceBlock / kWave][kEvictCap];
-    __shared__ double seval[kTraceBlock / kWave][4 * kEvictCap];
-    const int wv = threadIdx.x / kWave;
-    key = skey[wv];
-    val = sval[wv];
-    ekey = sekey[wv];
-    eval = seval[wv];
-    ecount = 0;
-    rec_base = rb;
-    for (int e = lane; e < kCache4Entries; e += kWave) key[e] = kNoSlot;
-    __builtin_amdgcn_wave_barrier();
-  }
-  __device__ bool want_drain() const { return ecount >= kEvictCap - kWave; }
-  // (entry, component) pairs over consecutive lanes: a record's four sums in one instruction
-  __device__ void drain(double* acc, int lane) {
-    __builtin_amdgcn_wave_barrier();
-    for (int j = lane; j < 4 * ecount; j += kWave) {
-      const int i = j >> 2, k = j & 3;
-      const uint32_t kk = ekey[i];
-      if (k == 0 || kk >= rec_base) unsafeAtomicAdd(&acc[kk + k], eval[k * kEvictCap + i]);
-    }
-    ecount = 0;
-    __builtin_amdgcn_wave_barrier();
-  }
-  // The protocol of the one-sum table (DepositCache<true>::add) with four
-  // sums per entry.
-  __device__ void add(double* acc, uint32_t k_new, const double (&v)[4], bool has, int lane) {
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (!__ballot(has)) return;
-    if (ecount > kEvictCap - kWave) drain(acc, lane);
-    uint32_t h = 0, k = kNoSlot;
-    bool match = false;
-    if (has) {
-      h = cache4_index(k_new);
+      h = cache_index<N>(k_new);
       k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       match = k == k_new;
     }
     __builtin_amdgcn_wave_barrier();
     if (match) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        __hip_atomic_fetch_add(&val[c * kCache4Entries + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      for (int c = 0; c < NS; ++c)
+        __hip_atomic_fetch_add(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
     const bool claim = has && !match;
@@ -1044,66 +1016,78 @@ struct DepositCache4<true> {
       join = !won && seen == k_new;
     }
     __builtin_amdgcn_wave_barrier();
-    const bool out = claim && !join && (!won || k != kNoSlot);
-    const unsigned long long omask = __ballot(out);
+    const bool leave = claim && !join && (!won || k != kNoSlot);
+    const unsigned long long omask = __ballot(leave);
+    const int n_out = __popcll(omask);
+    if (ecount + n_out > E) drain(acc, lane);             // room for this call's evictions (at most 64)
     uint32_t ok = k_new;
-    double ov[4] = {v[0], v[1], v[2], v[3]};
-    if (won) {
+    double ov[NS];
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        ov[c] = __hip_atomic_exchange(&val[c * kCache4Entries + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int c = 0; c < NS; ++c) ov[c] = v[c];
+    if (won) {
+      // the adds of this call precede the exchange, so the old sums are complete
+#pragma unroll
+      for (int c = 0; c < NS; ++c)
+        ov[c] = __hip_atomic_exchange(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       ok = k;
     }
     __builtin_amdgcn_wave_barrier();
     if (join) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        __hip_atomic_fetch_add(&val[c * kCache4Entries + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      for (int c = 0; c < NS; ++c)
+        __hip_atomic_fetch_add(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (out) {
+    if (leave) {
       const int e = ecount + __popcll(omask & below);
       ekey[e] = ok;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) eval[c * kEvictCap + e] = ov[c];
+      for (int c = 0; c < NS; ++c) eval[c * E + e] = ov[c];
     }
-    ecount += __popcll(omask);
+    ecount += n_out;
     __builtin_amdgcn_wave_barrier();
   }
   __device__ void flush(double* acc, int lane) {
-    drain(acc, lane);
-    for (int j = lane; j < 4 * kCache4Entries; j += kWave) {
-      const int e = j >> 2, c = j & 3;
-      const uint32_t kk = key[e];
-      if (kk != kNoSlot && (c == 0 || kk >= rec_base)) unsafeAtomicAdd(&acc[kk + c], val[c * kCache4Entries + e]);
+    if constexpr (CACHE) {
+      drain(acc, lane);
+      for (int j = lane; j < NS * N; j += kWave) {
+        const int e = j / NS, c = j % NS;
+        const uint32_t kk = key[e];
+        if (kk != kNoSlot) out(acc, kk, c, val[c * N + e], rec_base);
+      }
     }
   }
 };
 
-// Split parents waiting for their children to be written: the children of a
-// stage go to the wave's current segment of the next level's queue (its home
-// segment at first) through blocks of slots it reserves with one atomic, in
-// coalesced stores (lane c writes child c), four consecutive records per
-// parent. A segment that is full sends the wave on to the next one, so the
-// splits of a few neighbouring pixel ranges (the rays towards a grid's
-// corners, say) can fill one segment without losing children while the
-// queue has room elsewhere; only when every segment is full are children
-// lost (an overflow, which the host answers by tracing in smaller chunks).
+// Rays that split, waiting for their queue slots: a stage goes to the wave's
+// current segment of the next level's queue (its home segment at first)
+// through blocks of slots it reserves with one atomic, in coalesced stores. A
+// slot holds the split ray; its four children are formed when they are
+// claimed, so a split writes a quarter of the bytes its children would take
+// and the stage needs a quarter of the LDS. A segment that is full sends the
+// wave on to the next one, so the splits of a few neighbouring pixel ranges
+// (the rays towards a grid's corners, say) can fill one segment without losing
+// children while the queue has room elsewhere; only when every segment is full
+// are children lost (an overflow, which the host answers by tracing in smaller
+// chunks).
+constexpr int kStageCap = 32;
+
+template <int NG>
 struct SplitStage {
   uint64_t* pix;
-  uint32_t* sg;
+  uint32_t* tree;
   double* r;
-  double* P;
+  double* P;                                    // [NG][kStageCap]
   int count;                                    // wave-uniform
   int wseg;                                     // segment of the wave's current reservation
   unsigned long long o_next, o_end;             // the wave's reserved slots of segment wseg
 
   __device__ void init(int home) {
     __shared__ uint64_t spix[kTraceBlock / kWave][kStageCap];
-    __shared__ uint32_t ssg[kTraceBlock / kWave][kStageCap];
+    __shared__ uint32_t stree[kTraceBlock / kWave][kStageCap];
     __shared__ double sr[kTraceBlock / kWave][kStageCap];
-    __shared__ double sP[kTraceBlock / kWave][kStageCap];
+    __shared__ double sP[kTraceBlock / kWave][NG * kStageCap];
     const int wv = threadIdx.x / kWave;
-    pix = spix[wv]; sg = ssg[wv]; r = sr[wv]; P = sP[wv];
+    pix = spix[wv]; tree = stree[wv]; r = sr[wv]; P = sP[wv];
     count = 0;
     wseg = home;
     o_next = o_end = 0;
@@ -1111,7 +1095,7 @@ struct SplitStage {
   template <typename R>
   __device__ void write(const TraceArgs<R>& a, int lane) {
     __builtin_amdgcn_wave_barrier();
-    const unsigned long long need = 4ull * (unsigned long long)count;
+    const unsigned long long need = (unsigned long long)count;
     unsigned long long done = 0;
     int full = 0;                                           // segments found full in this call
     while (done < need) {
@@ -1130,24 +1114,21 @@ struct SplitStage {
         o_end = fresh + grab < a.seg_cap ? fresh + grab : a.seg_cap;
       }
       const unsigned long long n = need - done < o_end - o_next ? need - done : o_end - o_next;
-      const unsigned long long base = (unsigned long long)wseg * a.seg_cap + o_next;
-      for (unsigned long long c = lane; c < n; c += kWave) {
-        const unsigned long long k = done + c;
-        const int p = (int)(k >> 2);
-        a.out.pix[base + c] = 4ull * pix[p] + (k & 3);
-        a.out.sg[base + c] = sg[p];
-        a.out.r[base + c] = r[p];
-        a.out.P[base + c] = 0.25 * P[p];
+      if ((unsigned long long)lane < n) {                   // n <= kStageCap <= 64
+        const unsigned long long slot = (unsigned long long)wseg * a.seg_cap + o_next + lane;
+        const int p = (int)done + lane;
+        a.out.pix[slot] = pix[p];
+        a.out.tree[slot] = tree[p];
+        a.out.r[slot] = r[p];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a.out.P[g * a.out.pstride + slot] = P[g * kStageCap + p];
       }
       o_next += n;
       done += n;
     }
-    if (done < need) {
-      for (unsigned long long k = done + lane; k < need; k += kWave) {
-        if (k == done) atomicOr(&a.ctr->err, kErrOverflow);
-        atomicAdd(&a.ctr->lost_rays, 1ull);
-        unsafeAtomicAdd(&a.ctr->lost_P, 0.25 * P[k >> 2]);
-      }
+    if (done < need && done + lane < need) {
+      if (lane == 0) atomicOr(&a.ctr->err, kErrOverflow);
+      atomicAdd(&a.ctr->lost_rays, 4ull);
     }
     count = 0;
     __builtin_amdgcn_wave_barrier();
@@ -1157,7 +1138,7 @@ struct SplitStage {
   template <typename R>
   __device__ void close(const TraceArgs<R>& a, int lane) const {
     for (unsigned long long i = o_next + lane; i < o_end; i += kWave)
-      a.out.sg[(unsigned long long)wseg * a.seg_cap + i] = kNoTree;
+      a.out.tree[(unsigned long long)wseg * a.seg_cap + i] = kNoTree;
   }
 };
 
@@ -1182,24 +1163,35 @@ constexpr int kPhysCover = 1, kPhysRadp = 2, kPhysHalt = 4, kPhysThin = 8;
 // which the LDS of a block (four waves) also allows; two for the
 // radiation-pressure variant with its four-sum deposit table, whose LDS
 // leaves room for two blocks per CU.
-template <typename R, bool CACHE, int PHYS>
+//
+// NG: energy groups a ray carries (its tree's pack is at most that; the
+// radiation-pressure and optically-thin variants carry one). With NG > 1 a
+// deposit has two sums, the absorbed rate and its energy moment over the
+// groups. Groups share all of the geometry, the split test and the deposit's
+// LDS combining, so a step's cost per group is its optical depth, exponential
+// and photon rate alone; a group no lane of the wave still carries is skipped.
+// Traced one group per ray, the 128^3 workload (16 sources, 4 groups) made 895
+// million steps in neutral gas and 2.3 billion in ionised gas; carrying the
+// four groups together makes 580 million of either.
+template <typename R, bool CACHE, int PHYS, int NG>
 __global__ __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(CACHE && (PHYS & kPhysRadp) ? 2 : 3)))
 void trace_level_kernel(TraceArgs<R> a) {
   constexpr bool COVER = (PHYS & kPhysCover) != 0, RADP = (PHYS & kPhysRadp) != 0, HALT = (PHYS & kPhysHalt) != 0;
   constexpr bool THIN = (PHYS & kPhysThin) != 0;
   static_assert(!(THIN && (RADP || HALT)), "the optically-thin approximation is a single-pass option");
+  static_assert(NG == 1 || !(THIN || RADP), "these variants carry one group per ray");
+  constexpr int NS = RADP ? 4 : (NG > 1 ? 2 : 1);
   const int lane = threadIdx.x & (kWave - 1);
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  __shared__ int s_bad;
-  TallyTable<THIN> tally;
-  tally.init();
-  if (threadIdx.x == 0) s_bad = (a.ctr->err & kErrBadInput) != 0;
-  __syncthreads();
-  if (s_bad) return;      // the whole block
+  if (__hip_atomic_load(&a.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrBadInput) return;   // set before this launch: the whole grid
+  WaveTally<NG, THIN> tally;
+  tally.init(lane);
   const int K = a.nseg;                      // a power of two
   const int kshift = __ffs(K) - 1;
   const unsigned long long npix = 12ull << (2 * a.seed_level);
-  const unsigned long long n_seeds = (unsigned long long)(a.seed_sg_end - a.seed_sg_begin) * npix;
+  // rays of the launch that are not children: resumed ones (time-dependent rays), then seeds
+  const unsigned long long n_held = HALT ? a.n_held : 0ull;
+  const unsigned long long n_extra = n_held + (unsigned long long)(a.seed_end - a.seed_begin) * npix;
   const unsigned long long* cnt_in = a.ctr->count[a.cin];
   unsigned long long* head_in = a.ctr->head[a.cin];
   // rays claimed per atomic: the launch's setting, halved while the level
@@ -1210,34 +1202,39 @@ void trace_level_kernel(TraceArgs<R> a) {
   // through the step loop would push the loop's own values out of theirs)
   __shared__ unsigned s_chunk[kTraceBlock / kWave];
   {
-    unsigned long long n = lane < K ? min(cnt_in[lane], a.seg_cap) : 0ull;
+    unsigned long long n = lane < K ? 4ull * min(cnt_in[lane], a.seg_cap) : 0ull;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
       const unsigned lo = __shfl_xor((unsigned)n, o), hi = __shfl_xor((unsigned)(n >> 32), o);
       n += ((unsigned long long)hi << 32) | lo;
     }
-    n += n_seeds;
+    n += n_extra;
     const unsigned long long waves = (unsigned long long)gridDim.x * (kTraceBlock / kWave);
     unsigned chunk = (unsigned)a.chunk;
     while (chunk >= 2u * kWave && (unsigned long long)chunk * waves > n) chunk >>= 1;
     s_chunk[threadIdx.x / kWave] = chunk;   // every lane holds the same sum and stores the same value
   }
-  // the wave's home segment: it claims there first and writes children there
+  // the wave's home segment: it claims there first and writes its splits there
   const int home = (int)((blockIdx.x * (kTraceBlock / kWave) + threadIdx.x / kWave) % (unsigned)K);
-  const Tracer<R> T(a);
-  Ray<R> L;
+  const Tracer<R, NG> T(a);
+  Ray<R, NG> L;
   int ended = -1;          // kind of the lane's ray that ended and is not yet tallied
-  // with radiation pressure one deposit carries four sums (one table entry each)
-  std::conditional_t<RADP, DepositCache4<CACHE>, DepositCache<CACHE>> cache;
-  if constexpr (RADP) cache.init(lane, a.rec_base);
-  else cache.init(lane);
-  SplitStage stage;
+  DepositCache<CACHE, NS> cache;
+  cache.init(lane, a.rec_base);
+  SplitStage<NG> stage;
   stage.init(home);
   bool active = false;
   unsigned steps = 0;
-  L.tree = kNoTree;
+  L.ltree = kNoTree;
+  L.stat0 = kNoTree;
+  L.segs = 0;
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    L.alive[g] = false;
+    L.P[g] = 0.0;
+  }
   // the wave's current claim: [w_next, w_end) of segment w_seg, whose first
-  // w_nch indices are queue slots and the rest seed numbers from w_slo on
+  // w_nch indices are children and the rest resumed rays and seeds from w_slo on
   unsigned long long w_next = 0, w_end = 0, w_nch = 0, w_slo = 0;
   int w_seg = home;
   bool drained = false;
@@ -1262,16 +1259,16 @@ void trace_level_kernel(TraceArgs<R> a) {
       (const __attribute__((address_space(1))) double*)kappa64_v;
 
   for (;;) {
-    if (ended >= 0) {
-      tally.add(a.stats, HALT ? L.sg % a.tree_fold : L.sg, L.segs, L.P, ended, THIN ? L.tsegs : 0u);
-      ended = -1;
-    }
     // ---- refill idle lanes from the wave's claim on the level queue ----
     // Every idle lane first gets its queue slot or seed number (claiming as
     // many chunks as that takes), then all of them start in one pass; lanes
     // whose slot turns out empty wait for the next refill.
     const unsigned long long idle = __ballot(!active);
     if (!drained && idle && (__popcll(idle) >= a.refill || idle == ~0ull)) {
+      if (__ballot(ended >= 0)) {
+        tally.ended(a.stats, L, ended, lane);
+        ended = -1;
+      }
       unsigned long long left = idle;
       bool take = false, child = false;
       unsigned long long q = 0;
@@ -1287,9 +1284,9 @@ void trace_level_kernel(TraceArgs<R> a) {
           for (;;) {
             // the current segment first: one load while it lasts
             {
-              const unsigned long long c_nch = min(cnt_in[w_seg], a.seg_cap);
-              const unsigned long long c_slo = ((unsigned long long)w_seg * n_seeds) >> kshift;
-              const unsigned long long c_size = c_nch + ((((unsigned long long)w_seg + 1) * n_seeds) >> kshift) - c_slo;
+              const unsigned long long c_nch = 4ull * min(cnt_in[w_seg], a.seg_cap);
+              const unsigned long long c_slo = ((unsigned long long)w_seg * n_extra) >> kshift;
+              const unsigned long long c_size = c_nch + ((((unsigned long long)w_seg + 1) * n_extra) >> kshift) - c_slo;
               const unsigned long long seen =
                   uniform64(__hip_atomic_load(&head_in[w_seg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
               if (seen < c_size) {
@@ -1309,19 +1306,19 @@ void trace_level_kernel(TraceArgs<R> a) {
             }
             bool has = false;
             if (lane < K) {
-              const unsigned long long size = min(cnt_in[lane], a.seg_cap) +
-                                              ((((unsigned long long)lane + 1) * n_seeds) >> kshift) -
-                                              (((unsigned long long)lane * n_seeds) >> kshift);
+              const unsigned long long size = 4ull * min(cnt_in[lane], a.seg_cap) +
+                                              ((((unsigned long long)lane + 1) * n_extra) >> kshift) -
+                                              (((unsigned long long)lane * n_extra) >> kshift);
               has = __hip_atomic_load(&head_in[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < size;
             }
             const unsigned long long live = __ballot(has);
             if (!live) break;
             const unsigned long long ahead = live & (~0ull << w_seg);
             const int sg = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
-            // the chosen segment's slots and seeds, once more for the whole wave
-            const unsigned long long s_nch = min(cnt_in[sg], a.seg_cap);
-            const unsigned long long s_slo = ((unsigned long long)sg * n_seeds) >> kshift;
-            const unsigned long long s_size = s_nch + ((((unsigned long long)sg + 1) * n_seeds) >> kshift) - s_slo;
+            // the chosen segment's rays, once more for the whole wave
+            const unsigned long long s_nch = 4ull * min(cnt_in[sg], a.seg_cap);
+            const unsigned long long s_slo = ((unsigned long long)sg * n_extra) >> kshift;
+            const unsigned long long s_size = s_nch + ((((unsigned long long)sg + 1) * n_extra) >> kshift) - s_slo;
             unsigned long long b = 0;
             const unsigned long long chunk = uniform32((int)s_chunk[threadIdx.x / kWave]);
             if (lane == 0) b = atomicAdd(&head_in[sg], chunk);
@@ -1343,7 +1340,7 @@ void trace_level_kernel(TraceArgs<R> a) {
         if (mine) {
           take = true;
           child = idx < w_nch;
-          q = child ? (unsigned long long)w_seg * a.seg_cap + idx : w_slo + (idx - w_nch);
+          q = child ? 4ull * (unsigned long long)w_seg * a.seg_cap + idx : w_slo + (idx - w_nch);
         }
         const unsigned long long got_mask = __ballot(mine);
         w_next += __popcll(got_mask);
@@ -1351,13 +1348,15 @@ void trace_level_kernel(TraceArgs<R> a) {
       }
       if (take) {
         double r64;
-        T.fetch(L, child, q, r64);
-        if (L.sg != kNoTree) {
-          if (L.sg != L.tree) {
+        if (child) T.fetch_child(L, q, r64);
+        else if (HALT && q < n_held) T.fetch_held(L, q, r64);
+        else T.fetch_seed(L, q - n_held, r64);
+        if (L.tree != kNoTree) {
+          if (L.tree != L.ltree) {
             T.load_tree(L);
             if constexpr (THIN) T.load_thin(L);
           }
-          if constexpr (THIN) T.thin_start(L);
+          if constexpr (THIN) T.thin_start(L, !child);
           R k;
           if (T.locate(L, r64, k)) {
             T.begin(L, k);
@@ -1370,6 +1369,9 @@ void trace_level_kernel(TraceArgs<R> a) {
           }
         }
       }
+      // the tree of the first ray started is the one the wave's tally follows
+      const unsigned long long started = __ballot(take && L.tree != kNoTree);
+      if (started) tally.follow(a.stats, (uint32_t)__builtin_amdgcn_readlane((int)L.stat0, __ffsll((long long)started) - 1), lane);
       finish_vector_loads();
     }
     if (!__ballot(active)) {
@@ -1412,23 +1414,32 @@ void trace_level_kernel(TraceArgs<R> a) {
         split = T.split_test(L, ax);
       }
     }
-    const unsigned long long smask = __ballot(split);
-    if (smask) {
-      if (split) {
-        const int e = stage.count + __popcll(smask & below);
+    for (unsigned long long smask = __ballot(split); smask;) {
+      // as many of the splitting lanes as the stage has room for; a full stage is written out
+      if (stage.count == kStageCap) stage.write(a, lane);
+      const int e = stage.count + __popcll(smask & below);
+      const bool put = ((smask >> lane) & 1ull) && e < kStageCap;
+      if (put) {
         stage.pix[e] = L.pix;
-        stage.sg[e] = L.sg;
+        stage.tree[e] = L.tree;
         stage.r[e] = L.g.radius64();
-        // a thin ray's children carry its remaining column as -(1 + rem)
-        stage.P[e] = (THIN && L.thin) ? -4.0 * (1.0 + L.rem) : L.P;
+        // a thin ray's record carries its remaining column as -4 (1 + rem), an ended group a negative rate
+        if constexpr (THIN) {
+          stage.P[e] = L.thin ? -4.0 * (1.0 + L.rem) : L.P[0];
+        } else {
+#pragma unroll
+          for (int g = 0; g < NG; ++g) stage.P[g * kStageCap + e] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
+        }
         ended = 2;
         active = false;
       }
-      stage.count += __popcll(smask);
+      const unsigned long long done = __ballot(put);
+      stage.count += __popcll(done);
+      smask &= ~done;
     }
     bool dep = false, moved = false;
     uint32_t dkey = 0;
-    double dval = 0.0, mval = 0.0;
+    double dval = 0.0, hval = 0.0, mval = 0.0;   // absorbed rate, its energy moment, momentum rate
     int s_ax = 0, s_dir = 0;
     bool halt = false;
     if (active) {
@@ -1445,8 +1456,8 @@ void trace_level_kernel(TraceArgs<R> a) {
       if (THIN && pos && thin_here) {
         // thin: no photons removed
         if (T.holds_source(L)) {
-          double Pc = L.P;
-          dval = absorb(Pc, L.kap * L.sigma * dr);
+          double Pc = L.P[0];
+          dval = absorb(Pc, L.kap * L.sigma[0] * dr);
           if constexpr (COVER) {
             if (L.cover) dval *= T.covering_factor(L, (double)dr);
           }
@@ -1465,17 +1476,30 @@ void trace_level_kernel(TraceArgs<R> a) {
         L.tsegs++;
         L.g.advance(ax);
       } else if (pos) {
-        const R tau = L.kap * L.sigma * dr;
-        dval = absorb(L.P, tau);
+        if constexpr (NG == 1) {
+          dval = absorb(L.P[0], L.kap * L.sigma[0] * dr);
+        } else {
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            if (!__ballot(L.alive[g])) continue;
+            const double d = absorb(L.P[g], L.kap * L.sigma[g] * dr);   // 0 for an ended group's P = 0
+            dval += d;
+            hval = fma(d, L.eexc[g], hval);
+          }
+        }
         if constexpr (THIN) L.thin = false;
         if constexpr (RADP) {
           // the absorbed radiation itself, before any covering-factor scaling
           mval = dval * L.mscale;
         }
         if constexpr (COVER) {
-          if (L.cover) dval *= T.covering_factor(L, (double)dr);
+          if (L.cover) {
+            const double fc = T.covering_factor(L, (double)dr);
+            dval *= fc;
+            hval *= fc;
+          }
         }
-        dkey = (RADP || THIN) ? L.slot0 + L.astride * (uint32_t)L.lin : L.slot0 + (uint32_t)L.lin;
+        dkey = NS > 1 || THIN ? L.slot0 + L.astride * (uint32_t)L.lin : L.slot0 + (uint32_t)L.lin;
         dep = true;
         L.segs++;
         if (HALT && halt) L.g.set_radius(L.rhalt);
@@ -1491,9 +1515,23 @@ void trace_level_kernel(TraceArgs<R> a) {
       L.c2 = ax == 2 ? cnew : L.c2;
       L.lin = e_lin;
       L.g.step(ax, cnew);
-      if (L.P < L.pmin) {
-        ended = 1;
-        active = false;
+      if constexpr (NG == 1) {
+        if (L.P[0] < L.pmin[0]) {
+          ended = 1;
+          active = false;
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          if (L.alive[g] && L.P[g] < L.pmin[g]) {
+            tally.truncated(a.stats, L, g);
+            L.alive[g] = false;
+            L.P[g] = 0.0;
+          }
+        }
+        if (!L.any_alive()) active = false;
+      }
+      if (!active) {
       } else if (++steps > max_steps_v) {
         // cell indices move monotonically, so this bound is never reached by a correct trace
         atomicOr(&a.ctr->err, kErrInternal);
@@ -1524,9 +1562,10 @@ void trace_level_kernel(TraceArgs<R> a) {
           const unsigned long long i = rank < room ? h_next + rank : nb + (rank - room);
           if (i < a.halt_cap) {
             a.halt.pix[i] = L.pix;
-            a.halt.sg[i] = L.sg;
+            a.halt.tree[i] = L.tree;
             a.halt.r[i] = dep ? L.rhalt : L.g.radius64();
-            a.halt.P[i] = L.P;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
             a.halt_lev[i] = a.gen;
           } else {
             atomicOr(&a.ctr->err, kErrOverflow);
@@ -1546,15 +1585,19 @@ void trace_level_kernel(TraceArgs<R> a) {
     if constexpr (RADP) {
       // the momentum rate along the ray, from the float64 direction (zero
       // for a problem that does not ask for it: its key is a one-sum slot)
-      double v[4] = {dval, 0.0, 0.0, 0.0};
+      double v[NS] = {dval, 0.0, 0.0, 0.0};
       if (dep && mval != 0.0) {
         v[1] = mval * L.g.dir64(0);
         v[2] = mval * L.g.dir64(1);
         v[3] = mval * L.g.dir64(2);
       }
       cache.add(a.acc, dkey, v, dep, lane);
+    } else if constexpr (NS == 2) {
+      const double v[NS] = {dval, hval};
+      cache.add(a.acc, dkey, v, dep, lane);
     } else {
-      cache.add(a.acc, dkey, dval, dep, lane);
+      const double v[NS] = {dval};
+      cache.add(a.acc, dkey, v, dep, lane);
     }
     // the gathered column is taken on every path, so that no load is in
     // flight across the loop's back edge
@@ -1581,32 +1624,27 @@ void trace_level_kernel(TraceArgs<R> a) {
     } else if constexpr (THIN) {
       if (kneg) L.kap64 = (double)L.kap;
     }
-    // bulk writes, only when a buffer is nearly full
-    if (stage.count >= kStageFlush) stage.write(a, lane);
-    if (cache.want_drain()) cache.drain(a.acc, lane);
   }
   if (stage.count) stage.write(a, lane);
   cache.flush(a.acc, lane);
-  if (ended >= 0) {
-    tally.add(a.stats, HALT ? L.sg % a.tree_fold : L.sg, L.segs, L.P, ended, THIN ? L.tsegs : 0u);
-  }
+  if (__ballot(ended >= 0)) tally.ended(a.stats, L, ended, lane);
+  tally.flush(a.stats, lane);
   if constexpr (HALT) {
     // the unfilled rest of the wave's last block: empty records (no photons,
     // a level above every real one); the level's count once per wave
     for (unsigned long long i = h_next + lane; i < h_end; i += kWave)
       if (i < a.halt_cap) {
         a.halt.pix[i] = 0;
-        a.halt.sg[i] = 0;
+        a.halt.tree[i] = 0;
         a.halt.r[i] = 0.0;
-        a.halt.P[i] = 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = 0.0;
         a.halt_lev[i] = kHaltHole;
       }
     if (lane == 0 && h_count) atomicAdd(&a.ctr->halt_levels[a.gen], h_count);
   }
   // unused slots of the wave's last reserved block become empty slots
   stage.close(a, lane);
-  __syncthreads();
-  tally.flush(a.stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -1628,7 +1666,7 @@ __global__ void reset_kernel(Counters* ctr, SgStats* stats, int n_sg) {
     (&ctr->head[0][0])[i] = 0;
   }
   if (i == 0) {
-    ctr->lost_rays = 0; ctr->lost_P = 0.0; ctr->err = 0;
+    ctr->lost_rays = 0; ctr->err = 0;
   }
   if (i < kLevels) ctr->halt_levels[i] = 0;
   if (i == 0) ctr->halt_count = 0;
@@ -1653,7 +1691,6 @@ __global__ void reset_generation_kernel(Counters* ctr, int cin, int cout) {
   if (threadIdx.x == 0) {
     ctr->err &= ~kErrOverflow;
     ctr->lost_rays = 0;
-    ctr->lost_P = 0.0;
   }
 }
 
@@ -1692,7 +1729,7 @@ __global__ void prep_kernel(const GridDev* grids, int n_grids, int grid_base, co
     kappa[c] = (R)k64;
     if (kappa64) kappa64[c] = k64;
     const long long base = P.acc_off + P.acc_stride * (c - P.cell_off), gstride = P.acc_stride * P.n_cells;
-    for (int gr = 0; gr < P.n_groups; ++gr)
+    for (int gr = 0; gr < P.acc_planes; ++gr)
       for (int k = 0; k < P.acc_stride; ++k) acc[base + gr * gstride + k] = 0.0;
     for (int t = 0; t < P.mark_trees; ++t) mark[P.mark_off + t * P.n_cells + (c - P.cell_off)] = 0;
   }
@@ -1708,7 +1745,7 @@ __global__ void prep_kernel(const GridDev* grids, int n_grids, int grid_base, co
 __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* grids, const ProblemDev* probs,
                                                                const FinalBlock* blocks, const double* acc,
                                                                const double* eexc, double* partial,
-                                                               const Counters* ctr, const SgDev* sgs,
+                                                               const Counters* ctr, const TreeDev* trees,
                                                                const uint8_t* mark) {
   __shared__ double red[kFinalBlock / kWave];
   if (ctr->err & kErrBadInput) return;
@@ -1723,17 +1760,22 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* gr
     const long long base = P.acc_off + P.acc_stride * (c - P.cell_off), gstride = P.acc_stride * P.n_cells;
     double ab = 0.0, he = 0.0, tab = 0.0, the = 0.0;
     double mom[3] = {0.0, 0.0, 0.0};
-    for (int gr = 0; gr < P.n_groups; ++gr) {
-      const double v = acc[base + gr * gstride];
-      ab += v;
-      he += v * eexc[P.eexc_off + gr];
-      if (P.acc_stride == 2) {
-        const double w = acc[base + gr * gstride + 1];
-        tab += w;
-        the += w * eexc[P.eexc_off + gr];
+    if (P.acc_mode == kAccMoments) {
+      ab = acc[base];
+      he = acc[base + 1];
+    } else {
+      for (int gr = 0; gr < P.n_groups; ++gr) {
+        const double v = acc[base + gr * gstride];
+        ab += v;
+        he += v * eexc[P.eexc_off + gr];
+        if (P.acc_mode == kAccThin) {
+          const double w = acc[base + gr * gstride + 1];
+          tab += w;
+          the += w * eexc[P.eexc_off + gr];
+        }
+        if (P.acc_mode == kAccRadp)
+          for (int d = 0; d < 3; ++d) mom[d] += acc[base + gr * gstride + 1 + d];
       }
-      if (P.acc_stride == 4)
-        for (int d = 0; d < 3; ++d) mom[d] += acc[base + gr * gstride + 1 + d];
     }
     double kt = 0.0, ht = 0.0;
     if (P.mark_trees > 0) {
@@ -1744,7 +1786,7 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* gr
       const double cz = G.is_child ? (double)G.oz + 0.5 * ((double)kk + 0.5) : (double)kk + 0.5;
       for (int t = 0; t < P.mark_trees; ++t) {
         if (!mark[P.mark_off + t * P.n_cells + (c - P.cell_off)]) continue;
-        const SgDev& S = sgs[P.sg_first + t];
+        const TreeDev& S = trees[P.tree_first + t];
         const double dx0 = cx - S.sx, dx1 = cy - S.sy, dx2 = cz - S.sz;
         const double kv = S.thin_coef / (dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
         kt += kv;
@@ -1759,7 +1801,7 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* gr
     }
     G.out_kph[local] = k;
     G.out_heat[local] = h;
-    if (P.acc_stride == 4 && G.out_acc) {
+    if (P.acc_mode == kAccRadp && G.out_acc) {
       const double rho = kHydrogenMassG * (double)G.n_h[local];
       for (int d = 0; d < 3; ++d) G.out_acc[d * P.n_cells + local] = rho > 0.0 ? mom[d] / (rho * vol) : 0.0;
     }
@@ -1826,73 +1868,46 @@ static int resident_blocks(K kernel, int& memo) {
 // `blocks` is sized for the plain kernel's residency; a variant that keeps
 // fewer blocks per CU resident (the radiation-pressure table takes more LDS)
 // is launched with proportionally fewer, so its grid stays persistent.
-template <typename R, int PHYS>
-static void launch_phys(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
+template <typename R, int PHYS, int NG>
+static void launch_one(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
   if (cache) {
     static int plain = 0, mine = 0;
-    const int p = resident_blocks(trace_level_kernel<R, true, 0>, plain);
-    const int m = resident_blocks(trace_level_kernel<R, true, PHYS>, mine);
+    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1>, plain);
+    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG>, mine);
     if (m < p) blocks = (blocks * m + p - 1) / p;
-    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   } else {
-    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   }
 }
 
+// `width`: the widest pack of the launch's trees; 3 takes the kernel for 4 (the
+// fourth group is never alive, which skips it)
+template <typename R, int PHYS>
+static void launch_phys(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width) {
+  if (width <= 1) launch_one<R, PHYS, 1>(s, blocks, args, cache);
+  else if (width == 2) launch_one<R, PHYS, 2>(s, blocks, args, cache);
+  else launch_one<R, PHYS, 4>(s, blocks, args, cache);
+}
+
 template <typename R>
-hipError_t launch_trace_level(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, bool cover,
+hipError_t launch_trace_level(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width, bool cover,
                               bool radp, bool thin) {
-  if (thin && radp) return hipErrorInvalidValue;
-  if (thin && cover) launch_phys<R, kPhysThin | kPhysCover>(s, blocks, args, cache);
-  else if (thin) launch_phys<R, kPhysThin>(s, blocks, args, cache);
-  else if (cover && radp) launch_phys<R, kPhysCover | kPhysRadp>(s, blocks, args, cache);
-  else if (cover) launch_phys<R, kPhysCover>(s, blocks, args, cache);
-  else if (radp) launch_phys<R, kPhysRadp>(s, blocks, args, cache);
-  else launch_phys<R, 0>(s, blocks, args, cache);
+  if ((thin && radp) || ((thin || radp) && width > 1) || width > kPack) return hipErrorInvalidValue;
+  if (thin && cover) launch_one<R, kPhysThin | kPhysCover, 1>(s, blocks, args, cache);
+  else if (thin) launch_one<R, kPhysThin, 1>(s, blocks, args, cache);
+  else if (cover && radp) launch_one<R, kPhysCover | kPhysRadp, 1>(s, blocks, args, cache);
+  else if (radp) launch_one<R, kPhysRadp, 1>(s, blocks, args, cache);
+  else if (cover) launch_phys<R, kPhysCover>(s, blocks, args, cache, width);
+  else launch_phys<R, 0>(s, blocks, args, cache, width);
   return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_trace_level_halt(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
-  launch_phys<R, kPhysHalt>(s, blocks, args, cache);
+hipError_t launch_trace_level_halt(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width) {
+  if (width > kPack) return hipErrorInvalidValue;
+  launch_phys<R, kPhysHalt>(s, blocks, args, cache, width);
   return hipGetLastError();
-}
-
-// Time-dependent rays: the rays of HEALPix level `level` among the n_pool
-// rays halted in the previous step join level queue q (counter row `row`).
-// Each wave pass takes 64 records and puts its matching ones, with one
-// atomic, at the end of one of the queue's nseg segments (a power of two),
-// chosen by the pass; a segment that is full flags an overflow.
-__global__ __launch_bounds__(256) void prefill_level_kernel(RayQueue pool, const int* __restrict__ pool_lev,
-                                                            unsigned long long n_pool, int level, RayQueue q,
-                                                            unsigned long long seg_cap, int nseg, Counters* ctr,
-                                                            int row) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const unsigned long long waves = (unsigned long long)gridDim.x * (blockDim.x / kWave);
-  const unsigned long long wave = blockIdx.x * (unsigned long long)(blockDim.x / kWave) + threadIdx.x / kWave;
-  for (unsigned long long w = wave; w * kWave < n_pool; w += waves) {
-    const unsigned long long i = w * kWave + lane;
-    const bool mine = i < n_pool && pool_lev[i] == level;
-    const unsigned long long m = __ballot(mine);
-    if (!m) continue;
-    const int seg = (int)(w & (unsigned long long)(nseg - 1));
-    unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(&ctr->count[row][seg], (unsigned long long)__popcll(m));
-    base = bcast64(base, 0);
-    if (mine) {
-      const unsigned long long pos = base + __popcll(m & below);
-      if (pos < seg_cap) {
-        const unsigned long long o = (unsigned long long)seg * seg_cap + pos;
-        q.pix[o] = pool.pix[i];
-        q.sg[o] = pool.sg[i];
-        q.r[o] = pool.r[i];
-        q.P[o] = pool.P[i];
-      } else {
-        atomicOr(&ctr->err, kErrOverflow);
-      }
-    }
-  }
 }
 
 // Serving: rays of removed problems leave the queue between two launches.
@@ -1904,12 +1919,12 @@ struct DropRanges {
   int lo[kDropRanges], hi[kDropRanges];
 };
 
-__global__ __launch_bounds__(256) void drop_trees_kernel(uint32_t* __restrict__ sg, const Counters* __restrict__ ctr,
+__global__ __launch_bounds__(256) void drop_trees_kernel(uint32_t* __restrict__ tree, const Counters* __restrict__ ctr,
                                                          int row, unsigned long long seg_cap, int nseg, DropRanges r) {
   const int seg = (int)(blockIdx.x % (unsigned)nseg);
   const unsigned long long part = blockIdx.x / (unsigned)nseg, parts = gridDim.x / (unsigned)nseg;
   const unsigned long long cnt = ctr->count[row][seg] < seg_cap ? ctr->count[row][seg] : seg_cap;
-  uint32_t* q = sg + (unsigned long long)seg * seg_cap;
+  uint32_t* q = tree + (unsigned long long)seg * seg_cap;
   for (unsigned long long i = part * 256ull + threadIdx.x; i < cnt; i += parts * 256ull) {
     const uint32_t t = q[i];
     bool drop = false;
@@ -1918,13 +1933,18 @@ __global__ __launch_bounds__(256) void drop_trees_kernel(uint32_t* __restrict__ 
   }
 }
 
-// Per-block sums of v[0..n) (the photons the halted rays hold).
+// Per-block sums of the positive values of the first n of each plane of v (the photons the halted
+// rays hold; an ended group's rate is stored negative).
 __global__ __launch_bounds__(256) void sum_blocks_kernel(const double* __restrict__ v, unsigned long long n,
+                                                         int planes, unsigned long long pstride,
                                                          double* __restrict__ part) {
   __shared__ double red[256 / kWave];
   double s = 0.0;
-  for (unsigned long long i = blockIdx.x * 256ull + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * 256ull)
-    s += v[i];
+  for (int g = 0; g < planes; ++g)
+    for (unsigned long long i = blockIdx.x * 256ull + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * 256ull) {
+      const double x = v[g * pstride + i];
+      s += x > 0.0 ? x : 0.0;
+    }
   for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_down(s, off);
   if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
   __syncthreads();
@@ -1935,12 +1955,13 @@ __global__ __launch_bounds__(256) void sum_blocks_kernel(const double* __restric
   }
 }
 
-hipError_t launch_sum_blocks(hipStream_t s, int blocks, const double* v, unsigned long long n, double* part) {
-  hipLaunchKernelGGL(sum_blocks_kernel, dim3(blocks), dim3(256), 0, s, v, n, part);
+hipError_t launch_sum_blocks(hipStream_t s, int blocks, const double* v, unsigned long long n, int planes,
+                             unsigned long long pstride, double* part) {
+  hipLaunchKernelGGL(sum_blocks_kernel, dim3(blocks), dim3(256), 0, s, v, n, planes, pstride, part);
   return hipGetLastError();
 }
 
-hipError_t launch_drop_trees(hipStream_t s, uint32_t* sg, const Counters* ctr, int row, unsigned long long seg_cap,
+hipError_t launch_drop_trees(hipStream_t s, uint32_t* tree, const Counters* ctr, int row, unsigned long long seg_cap,
                              int nseg, const int* lo, const int* hi, int n) {
   if (n <= 0) return hipSuccess;
   if (n > kDropRanges || nseg < 1) return hipErrorInvalidValue;
@@ -1950,27 +1971,16 @@ hipError_t launch_drop_trees(hipStream_t s, uint32_t* sg, const Counters* ctr, i
     r.lo[k] = lo[k];
     r.hi[k] = hi[k];
   }
-  hipLaunchKernelGGL(drop_trees_kernel, dim3((unsigned)nseg * 16u), dim3(256), 0, s, sg, ctr, row, seg_cap, nseg, r);
-  return hipGetLastError();
-}
-
-hipError_t launch_prefill_level(hipStream_t s, int num_cu, const RayQueue& pool, const int* pool_lev,
-                                unsigned long long n_pool, int level, const RayQueue& q, unsigned long long seg_cap,
-                                int nseg, Counters* ctr, int row) {
-  if (n_pool == 0) return hipSuccess;
-  unsigned long long blocks = (n_pool + 255) / 256;
-  if (blocks > 16ull * (unsigned long long)num_cu) blocks = 16ull * (unsigned long long)num_cu;
-  hipLaunchKernelGGL(prefill_level_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pool, pool_lev, n_pool, level, q,
-                     seg_cap, nseg, ctr, row);
+  hipLaunchKernelGGL(drop_trees_kernel, dim3((unsigned)nseg * 16u), dim3(256), 0, s, tree, ctr, row, seg_cap, nseg, r);
   return hipGetLastError();
 }
 
 hipError_t launch_finalize(hipStream_t s, int n_blocks, const GridDev* grids, const ProblemDev* probs,
                            const FinalBlock* blocks, const double* acc, const double* eexc, double* partial,
-                           const Counters* ctr, const SgDev* sgs, const uint8_t* mark) {
+                           const Counters* ctr, const TreeDev* trees, const uint8_t* mark) {
   if (n_blocks < 1) return hipSuccess;
   hipLaunchKernelGGL(finalize_kernel, dim3(n_blocks), dim3(kFinalBlock), 0, s, grids, probs, blocks, acc, eexc,
-                     partial, ctr, sgs, mark);
+                     partial, ctr, trees, mark);
   return hipGetLastError();
 }
 
@@ -1978,17 +1988,18 @@ template hipError_t launch_prep<float>(hipStream_t, int, const GridDev*, int, in
                                        long long, float*, double*, Counters*, uint8_t*, double*);
 template hipError_t launch_prep<double>(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long,
                                         long long, double*, double*, Counters*, uint8_t*, double*);
-template hipError_t launch_trace_level<float>(hipStream_t, int, const TraceArgs<float>&, bool, bool, bool, bool);
-template hipError_t launch_trace_level<double>(hipStream_t, int, const TraceArgs<double>&, bool, bool, bool, bool);
-template hipError_t launch_trace_level_halt<float>(hipStream_t, int, const TraceArgs<float>&, bool);
-template hipError_t launch_trace_level_halt<double>(hipStream_t, int, const TraceArgs<double>&, bool);
+template hipError_t launch_trace_level<float>(hipStream_t, int, const TraceArgs<float>&, bool, int, bool, bool, bool);
+template hipError_t launch_trace_level<double>(hipStream_t, int, const TraceArgs<double>&, bool, int, bool, bool, bool);
+template hipError_t launch_trace_level_halt<float>(hipStream_t, int, const TraceArgs<float>&, bool, int);
+template hipError_t launch_trace_level_halt<double>(hipStream_t, int, const TraceArgs<double>&, bool, int);
 
 hipError_t trace_occupancy(int precision, bool cache, int* blocks_per_cu) {
+  auto ask = [&](auto kernel) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, kernel, kTraceBlock, 0);
+  };
   if (precision == 0)
-    return cache ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, trace_level_kernel<double, true, 0>, kTraceBlock, 0)
-                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, trace_level_kernel<double, false, 0>, kTraceBlock, 0);
-  return cache ? hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, trace_level_kernel<float, true, 0>, kTraceBlock, 0)
-               : hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, trace_level_kernel<float, false, 0>, kTraceBlock, 0);
+    return cache ? ask(trace_level_kernel<double, true, 0, 1>) : ask(trace_level_kernel<double, false, 0, 1>);
+  return cache ? ask(trace_level_kernel<float, true, 0, 1>) : ask(trace_level_kernel<float, false, 0, 1>);
 }
 
 }  // namespace moray

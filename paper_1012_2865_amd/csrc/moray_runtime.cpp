@@ -24,12 +24,17 @@ using namespace moray;
 namespace {
 
 struct ChunkPlan {
-  int sg_begin, sg_end;
+  int begin, end;           // trees
 };
 
-// (source, group) tree of a one-shot solve: its seed level, problem, source and group.
+// Statistics entry of a one-shot solve: its problem, source and group.
 struct SgKey {
-  int l0, prob, src, grp;
+  int prob, src, grp;
+};
+
+// Ray tree of a one-shot solve: its seed level, problem, source and pack of groups.
+struct TreeKey {
+  int l0, prob, src, g0, n;
 };
 
 }  // namespace
@@ -38,7 +43,7 @@ struct SgKey {
 // with the launch sequence captured for the same descriptors.
 struct moray::PlanHost {
   std::string key;                  // descriptors, settings and buffer pointers of the solve
-  std::vector<SgKey> keys;
+  std::vector<SgKey> keys;          // of every statistics entry
   std::vector<int> fblock_first;
   int n_sg = 0;
   size_t nfb = 0;
@@ -101,7 +106,7 @@ void collect(moray_ctx* c, const PlanHost& ph, const moray_problem* probs, int n
   for (int l = 0; l < kLevels; ++l) {
     unsigned long long n = 0;
     for (int s = 0; s < ph.nseg; ++s) n += std::min<unsigned long long>(hctr->count[l][s], ph.seg_cap);
-    peak = std::max(peak, n);
+    peak = std::max(peak, 4 * n);     // a slot holds the parent of four rays
   }
   for (int i = 0; i < n_probs; ++i) {
     moray_result& R = outs[i];
@@ -302,6 +307,41 @@ double level_rays_bound(const moray_problem& P) {
   return std::min(std::ldexp(12.0, 2 * lr), geo);
 }
 
+void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const ProblemDev& pd, const GridDev& root) {
+  const moray_source& S = P.sources[src];
+  const moray_spectrum& Sp = *P.spectrum;
+  const double npix0 = std::ldexp(12.0, 2 * P.params.level_init);
+  d = TreeDev{};
+  d.sx = S.x; d.sy = S.y; d.sz = S.z;
+  for (int k = 0; k < kPack; ++k) {
+    if (k >= n) {
+      d.P0[k] = -1.0;
+      continue;
+    }
+    const int g = g0 + k;
+    d.P0[k] = Sp.photon_frac[g] * S.ndot / npix0;
+    d.pmin0[k] = P.params.p_min_frac * d.P0[k];
+    d.sigma64[k] = Sp.sigma_cm2[g];
+    d.sigma32[k] = (float)Sp.sigma_cm2[g];
+    if (pd.acc_mode == kAccMoments) d.eexc[k] = (Sp.energy_ev[g] - Sp.e_ion_ev) * kEvErgConst;
+  }
+  d.n_grp = n;
+  d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
+  d.split_t2_base = P.params.phi_c > 0.0 ? (float)(12.0 / (4.0 * kPiConst * P.params.phi_c)) : FLT_MAX;
+  d.acc_stride = (uint32_t)pd.acc_stride;
+  const long long plane = pd.acc_planes > 1 ? g0 : 0;
+  d.acc_slot = pd.acc_off + (long long)pd.acc_stride * (plane * pd.n_cells - pd.cell_off);
+  d.problem = root.problem;
+  d.covering = P.params.covering != 0;
+  if (pd.acc_mode == kAccRadp) d.mom_scale = Sp.energy_ev[g0] * kEvErgConst / kLightCms;
+  d.root_grid = pd.root_grid;
+  d.rnx = root.nx; d.rny = root.ny; d.rnz = root.nz;
+  d.rcell_off = root.cell_off;
+  d.level_init = P.params.level_init;
+  d.gen0 = P.params.level_init;     // one-shot solve: the launch generation is the HEALPix level
+  d.level_max = P.params.phi_c > 0.0 ? P.params.level_max : P.params.level_init;
+}
+
 }  // namespace moray
 
 extern "C" {
@@ -386,13 +426,13 @@ void moray_free(moray_ctx* c) {
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   else (void)hipDeviceSynchronize();
-  DevBuf* all[] = {&c->grids,   &c->probs,  &c->sgs,   &c->stats,  &c->ctr,     &c->kappa,  &c->kappa64,
+  DevBuf* all[] = {&c->grids,   &c->probs,  &c->trees,   &c->stats,  &c->ctr,     &c->kappa,  &c->kappa64,
                    &c->acc,     &c->mark,   &c->eexc,   &c->fblocks, &c->partial, &c->fields, &c->outs,
                    &c->eq_x,    &c->eq_kph, &c->eq_heat, &c->eq_dx,  &c->ev_lim, &c->eq_skip};
   for (DevBuf* b : all) release(c, *b);
   for (int i = 0; i < 2; ++i) {
     release(c, c->q_pix[i]);
-    release(c, c->q_sg[i]);
+    release(c, c->q_tree[i]);
     release(c, c->q_r[i]);
     release(c, c->q_P[i]);
   }
@@ -458,7 +498,8 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   std::vector<GridDev> grids;
   std::vector<ProblemDev> pdev(n_probs);
   std::vector<double> eexc;
-  long long n_cells = 0, n_acc = 0;
+  long long n_cells = 0;
+  long long acc_legacy = 0;              // accumulators with one plane per group, the bound the interface states
   int max_reach = 0, min_l0 = kMaxLevel;
   unsigned max_steps = 64;
   for (int i = 0; i < n_probs; ++i) {
@@ -487,38 +528,53 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
       steps += 2LL * (G.nx + G.ny + G.nz);
     }
     pd.n_cells = n_cells - pd.cell_off;
-    pd.acc_off = n_acc;
-    n_acc += pd.n_cells * pd.n_groups;
     max_steps = std::max<unsigned>(max_steps, (unsigned)std::min<long long>(steps * 2, 1u << 30));
     max_reach = std::max(max_reach, reach_level(P));
     min_l0 = std::min(min_l0, P.params.level_init);
   }
   if (n_cells >= (1LL << 31) - 1) return fail(c, MORAY_EINVAL, "batch exceeds 2^31 cells");
-  // Accumulators: one float64 sum per (group, cell) for the problems that do
-  // not ask for the radiation-pressure acceleration; after them, from the
-  // first 64-byte boundary (rec_base), a 32-byte record per (group, cell)
-  // (absorbed rate and momentum x, y, z) for those that do.
-  // Problems with the optically-thin approximation keep a second sum per
-  // (group, cell) among the plain ones (stride 2), for the deposits of thin
-  // rays in cells that hold their source.
-  bool thin = false;
+  // What the rays carry. A ray takes up to kPack energy groups of its source
+  // along, except where the groups of a source do not share their geometry
+  // (the optically-thin approximation: a ray's split threshold depends on its
+  // group's optical depth) or keep a momentum record each (radiation pressure).
+  bool thin = false, radp = false;
+  for (int i = 0; i < n_probs; ++i) {
+    thin = thin || probs[i].params.tau_thin > 0.0;
+    radp = radp || outs[i].accel;
+  }
+  const bool packed = !thin && !radp;
+  int width = 1;
+  for (int i = 0; i < n_probs && packed; ++i) width = std::max(width, pack_width(probs[i].spectrum->n_groups));
+  const int planes = rate_planes(width);
+  // Accumulators: two float64 sums per cell (absorbed rate and its energy
+  // moment) for a problem whose rays carry several groups, else one per (group,
+  // cell) for the problems that do not ask for the radiation-pressure
+  // acceleration; after them, from the first 64-byte boundary (rec_base), a
+  // 32-byte record per (group, cell) (absorbed rate and momentum x, y, z) for
+  // those that do. Problems with the optically-thin approximation keep a second
+  // sum per (group, cell) among the plain ones (stride 2), for the deposits of
+  // thin rays in cells that hold their source.
   long long n_plain = 0, n_rec = 0;
-  for (int i = 0; i < n_probs; ++i)
-    if (!outs[i].accel) {
-      const int stride = probs[i].params.tau_thin > 0.0 ? 2 : 1;
-      thin = thin || stride == 2;
-      pdev[i].acc_stride = stride;
-      pdev[i].acc_off = n_plain;
-      n_plain += stride * pdev[i].n_cells * pdev[i].n_groups;
-    }
+  for (int i = 0; i < n_probs; ++i) {
+    ProblemDev& pd = pdev[i];
+    const bool own = probs[i].params.tau_thin > 0.0;
+    acc_legacy += (outs[i].accel ? 4 : (own ? 2 : 1)) * pd.n_cells * pd.n_groups;
+    if (outs[i].accel) continue;
+    pd.acc_mode = own ? kAccThin : (packed && pd.n_groups > 1 ? kAccMoments : kAccSums);
+    pd.acc_stride = pd.acc_mode == kAccSums ? 1 : 2;
+    pd.acc_planes = pd.acc_mode == kAccMoments ? 1 : pd.n_groups;
+    pd.acc_off = n_plain;
+    n_plain += pd.acc_stride * pd.acc_planes * pd.n_cells;
+  }
   const long long rec_base = (n_plain + 7) & ~7LL;
   for (int i = 0; i < n_probs; ++i)
     if (outs[i].accel) {
+      pdev[i].acc_mode = kAccRadp;
       pdev[i].acc_stride = 4;
+      pdev[i].acc_planes = pdev[i].n_groups;
       pdev[i].acc_off = rec_base + n_rec;
       n_rec += 4 * pdev[i].n_cells * pdev[i].n_groups;
     }
-  const bool radp = n_rec > 0;
   const long long n_sums = radp ? rec_base + n_rec : n_plain;
   for (int i = 0; i < n_probs; ++i)
     if (outs[i].accel && probs[i].params.tau_thin > 0.0)
@@ -536,9 +592,8 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
       pdev[i].mark_off = n_mark;
       n_mark += pdev[i].mark_trees * pdev[i].n_cells;
     }
-  (void)n_acc;
   // the trace kernel addresses accumulators with 32-bit indices
-  if (n_sums >= (long long)kNoSlot)
+  if (std::max(n_sums, acc_legacy) >= (long long)kNoSlot)
     return fail(c, MORAY_EINVAL, "a batch needs fewer than 2^32 - 1 accumulators (cells x groups, 4 times that "
                                  "with radiation pressure)");
   bool cover = false;                                   // some problem scales its deposits by the covering factor
@@ -559,78 +614,74 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     fblock_first[n_probs] = (int)fblocks.size();
   }
 
-  // (source, group) trees ordered by seed level, then problem, source, group
-  std::vector<SgKey> keys;
-  for (int i = 0; i < n_probs; ++i)
+  // trees ordered by seed level, then problem, source, groups
+  std::vector<TreeKey> tkeys;
+  for (int i = 0; i < n_probs; ++i) {
+    const int ng = probs[i].spectrum->n_groups, packs = packed ? pack_count(ng) : ng;
     for (int s = 0; s < probs[i].n_sources; ++s)
-      for (int g = 0; g < probs[i].spectrum->n_groups; ++g) keys.push_back({probs[i].params.level_init, i, s, g});
-  std::stable_sort(keys.begin(), keys.end(), [](const SgKey& a, const SgKey& b) { return a.l0 < b.l0; });
-  const int n_sg = (int)keys.size();
-  std::vector<SgDev> sgs(n_sg);
-  std::vector<double> sg_bound(n_sg);
-  for (int k = 0; k < n_sg; ++k) {
-    const SgKey& K = keys[k];
+      for (int k = 0; k < packs; ++k) {
+        const int g0 = packed ? pack_first(ng, k) : k, g1 = packed ? pack_first(ng, k + 1) : k + 1;
+        tkeys.push_back({probs[i].params.level_init, i, s, g0, g1 - g0});
+      }
+  }
+  std::stable_sort(tkeys.begin(), tkeys.end(), [](const TreeKey& a, const TreeKey& b) { return a.l0 < b.l0; });
+  const int n_trees = (int)tkeys.size();
+  std::vector<SgKey> keys;               // statistics: the groups of every tree in order
+  std::vector<TreeDev> trees(n_trees);
+  std::vector<double> tree_bound(n_trees);
+  for (int k = 0; k < n_trees; ++k) {
+    const TreeKey& K = tkeys[k];
     const moray_problem& P = probs[K.prob];
-    const moray_source& S = P.sources[K.src];
-    const moray_spectrum& Sp = *P.spectrum;
-    const ProblemDev& pd = pdev[K.prob];
-    SgDev& d = sgs[k];
-    d.sx = S.x; d.sy = S.y; d.sz = S.z;
-    const double npix0 = std::ldexp(12.0, 2 * P.params.level_init);
-    d.P0 = Sp.photon_frac[K.grp] * S.ndot / npix0;
-    d.pmin0 = P.params.p_min_frac * d.P0;
-    d.sigma64 = Sp.sigma_cm2[K.grp];
-    d.sigma32 = (float)Sp.sigma_cm2[K.grp];
-    d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
-    d.split_t2_base = P.params.phi_c > 0.0 ? (float)(12.0 / (4.0 * kPiConst * P.params.phi_c)) : FLT_MAX;
-    d.acc_stride = (uint32_t)pd.acc_stride;
-    d.acc_slot = pd.acc_off + (long long)pd.acc_stride * ((long long)K.grp * pd.n_cells - pd.cell_off);
-    d.problem = K.prob;
-    d.covering = P.params.covering != 0;
-    if (pd.acc_stride == 4) d.mom_scale = Sp.energy_ev[K.grp] * kEvErgConst / kLightCms;
-    d.root_grid = pd.root_grid;
-    d.rnx = grids[pd.root_grid].nx; d.rny = grids[pd.root_grid].ny; d.rnz = grids[pd.root_grid].nz;
-    d.rcell_off = grids[pd.root_grid].cell_off;
-    d.level_init = P.params.level_init;
-    d.gen0 = P.params.level_init;     // one-shot solve: the launch generation is the HEALPix level
-    d.level_max = P.params.phi_c > 0.0 ? P.params.level_max : P.params.level_init;
-    if (k == 0 || keys[k - 1].prob != K.prob) pdev[K.prob].sg_first = k;
+    ProblemDev& pd = pdev[K.prob];
+    TreeDev& d = trees[k];
+    fill_tree(d, P, K.src, K.g0, K.n, pd, grids[pd.root_grid]);
+    d.stat0 = (uint32_t)keys.size();
+    for (int g = K.g0; g < K.g0 + K.n; ++g) keys.push_back({K.prob, K.src, g});
+    if (k == 0 || tkeys[k - 1].prob != K.prob) pd.tree_first = k;
     if (P.params.tau_thin > 0.0) {
       const double phi_thin = std::min(1.0, P.params.phi_c);
-      const int t = K.src * Sp.n_groups + K.grp;                  // the tree within its problem
+      const int t = K.src * P.spectrum->n_groups + K.g0;          // the tree within its problem
       const double dx_root = P.grids[0].dx_cm;
       d.tau_thin = P.params.tau_thin;
       d.four_pi_phi_thin = 4.0 * kPiConst * phi_thin;
       d.split_t2_thin = phi_thin > 0.0 ? (float)(12.0 / (4.0 * kPiConst * phi_thin)) : FLT_MAX;
       d.mark_base = pd.mark_off + (long long)t * pd.n_cells - pd.cell_off;
-      d.thin_coef = d.sigma64 * (d.P0 * npix0) / (4.0 * kPiConst * dx_root * dx_root);
+      d.thin_coef = d.sigma64[0] * (d.P0[0] * std::ldexp(12.0, 2 * P.params.level_init)) /
+                    (4.0 * kPiConst * dx_root * dx_root);
     }
-    sg_bound[k] = level_rays_bound(P);
+    tree_bound[k] = level_rays_bound(P);
   }
+  const int n_sg = (int)keys.size();
 
-  // ---- queue capacity ----
+  // ---- queue capacity ---- (in rays; a slot holds the parent of four)
   double need = 0.0;
-  for (double b : sg_bound) need += b;
+  for (double b : tree_bound) need += b;
   size_t cap = c->queue_cap_user;
-  const size_t per_ray = 2 * (sizeof(uint64_t) + sizeof(uint32_t) + 2 * sizeof(double));
+  const double per_ray = 2.0 * (double)slot_bytes(planes) / 4.0;
   const size_t out_stage = odev ? 0 : (size_t)n_cells * (radp ? 40 : 16);
   const size_t fixed = (size_t)n_cells * rsz + (size_t)n_sums * 8 + (size_t)n_mark +
-                       (thin && fp32 ? (size_t)n_cells * 8 : 0) + (fdev ? 0 : (size_t)n_cells * 8) + out_stage + (size_t)n_sg * (sizeof(SgDev) + sizeof(SgStats)) +
+                       (thin && fp32 ? (size_t)n_cells * 8 : 0) + (fdev ? 0 : (size_t)n_cells * 8) + out_stage +
+                       (size_t)n_trees * sizeof(TreeDev) + (size_t)n_sg * sizeof(SgStats) +
                        grids.size() * sizeof(GridDev) + fblocks.size() * (sizeof(FinalBlock) + 8) +
                        (c->arena ? (size_t)(1 << 20) : (size_t)(64 << 20));
   if (!cap) {
     const size_t room = c->budget > c->allocated + fixed ? c->budget - fixed : 0;
-    const double fit = (double)room / (double)per_ray;
-    const double slack = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave) * kReserveMax;
+    const double fit = (double)room / per_ray;
+    const double slack = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave) * 4 * kReserveMax;
     cap = (size_t)std::max(4096.0, std::min({need + slack, fit, 2.0e9}));
   }
   cap = std::max<size_t>(cap, 256);
+  // level queues in nseg segments (one claim and one write counter each); a
+  // segment serves about waves/nseg waves, so the reserve fraction holds per segment
+  const int nseg = queue_segments(cap);
+  const unsigned long long seg_cap = cap / 4 / (size_t)nseg;
+  const size_t qslots = (size_t)seg_cap * (size_t)nseg;
 
   // ---- device memory ----
   moray_status st;
   if ((st = ensure(c, c->grids, grids.size() * sizeof(GridDev), "grid table")) ||
       (st = ensure(c, c->probs, pdev.size() * sizeof(ProblemDev), "problem table")) ||
-      (st = ensure(c, c->sgs, std::max<size_t>(1, n_sg) * sizeof(SgDev), "source table")) ||
+      (st = ensure(c, c->trees, std::max<size_t>(1, n_trees) * sizeof(TreeDev), "source table")) ||
       (st = ensure(c, c->stats, std::max<size_t>(1, n_sg) * sizeof(SgStats), "statistics")) ||
       (st = ensure(c, c->ctr, sizeof(Counters), "counters")) ||
       (st = ensure(c, c->kappa, (size_t)n_cells * rsz, "absorber columns")) ||
@@ -644,8 +695,10 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   if (!fdev && (st = ensure(c, c->fields, (size_t)n_cells * 8, "field upload"))) return st;
   if (!odev && (st = ensure(c, c->outs, out_stage, "result staging"))) return st;
   for (int i = 0; i < 2; ++i) {
-    if ((st = ensure(c, c->q_pix[i], cap * 8, "ray queue")) || (st = ensure(c, c->q_sg[i], cap * 4, "ray queue")) ||
-        (st = ensure(c, c->q_r[i], cap * 8, "ray queue")) || (st = ensure(c, c->q_P[i], cap * 8, "ray queue")))
+    if ((st = ensure(c, c->q_pix[i], qslots * 8, "ray queue")) ||
+        (st = ensure(c, c->q_tree[i], qslots * 4, "ray queue")) ||
+        (st = ensure(c, c->q_r[i], qslots * 8, "ray queue")) ||
+        (st = ensure(c, c->q_P[i], qslots * 8 * planes, "ray queue")))
       return st;
   }
   c->q_cap = cap;
@@ -690,16 +743,16 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   };
   if (!up(c->grids, grids.data(), grids.size() * sizeof(GridDev)) ||
       !up(c->probs, pdev.data(), pdev.size() * sizeof(ProblemDev)) ||
-      !up(c->sgs, sgs.data(), n_sg * sizeof(SgDev)) || !up(c->eexc, eexc.data(), eexc.size() * 8) ||
+      !up(c->trees, trees.data(), n_trees * sizeof(TreeDev)) || !up(c->eexc, eexc.data(), eexc.size() * 8) ||
       !up(c->fblocks, fblocks.data(), fblocks.size() * sizeof(FinalBlock)))
     return MORAY_EDEVICE;
 
   // seed ranges per level
   std::vector<int> seed_lo(kLevels, 0), seed_hi(kLevels, 0);
   for (int l = 0; l <= kMaxLevel; ++l) {
-    int lo = n_sg, hi = n_sg;
-    for (int k = 0; k < n_sg; ++k)
-      if (keys[k].l0 == l) { lo = std::min(lo, k); hi = k + 1; }
+    int lo = n_trees, hi = n_trees;
+    for (int k = 0; k < n_trees; ++k)
+      if (tkeys[k].l0 == l) { lo = std::min(lo, k); hi = k + 1; }
     if (lo >= hi) lo = hi = 0;
     seed_lo[l] = lo;
     seed_hi[l] = hi;
@@ -712,14 +765,11 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   // each wave may leave up to one reserved block unused per level: keep that
   // under an eighth of the queue and plan the trees against the rest
   const double waves = (double)blocks * (kTraceBlock / kWave);
-  // level queues in nseg segments (one claim and one write counter each); a
-  // segment serves about waves/nseg waves, so the reserve fraction holds per segment
-  const int nseg = queue_segments(cap);
-  const unsigned long long seg_cap = cap / (size_t)nseg;
-  unsigned long long reserve = (unsigned long long)std::min<double>((double)kReserveMax, (double)cap / (8.0 * waves));
-  if (c->reserve_user > 0) reserve = std::min<unsigned long long>((unsigned long long)c->reserve_user, kReserveMax);
-  reserve = std::max<unsigned long long>(4, reserve & ~3ull);
-  double chunk_limit = std::max(1.0, (double)cap - waves * (double)reserve);
+  unsigned long long reserve =
+      (unsigned long long)std::min<double>((double)kReserveMax, (double)cap / (32.0 * waves));
+  if (c->reserve_user > 0) reserve = std::min<unsigned long long>((unsigned long long)c->reserve_user / 4, kReserveMax);
+  reserve = std::max<unsigned long long>(1, reserve);
+  double chunk_limit = std::max(1.0, (double)cap - waves * 4.0 * (double)reserve);
   const int max_launches = (max_reach - min_l0 + 1);
 
   // pinned staging for the counters, the tree statistics and the partial sums
@@ -774,15 +824,15 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     {
       int b = 0;
       double acc = 0.0;
-      for (int k = 0; k < n_sg; ++k) {
-        if (k > b && acc + sg_bound[k] > chunk_limit) {
+      for (int k = 0; k < n_trees; ++k) {
+        if (k > b && acc + tree_bound[k] > chunk_limit) {
           chunks.push_back({b, k});
           b = k;
           acc = 0.0;
         }
-        acc += sg_bound[k];
+        acc += tree_bound[k];
       }
-      if (n_sg > b) chunks.push_back({b, n_sg});
+      if (n_trees > b) chunks.push_back({b, n_trees});
     }
     const int n_launch_total = (int)chunks.size() * max_launches;
     if (c->profile && (int)c->evs.size() < 2 * n_launch_total) {
@@ -816,34 +866,26 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
         break;
       }
       for (int l = min_l0; l <= max_reach; ++l) {
-        const int lo = std::max(seed_lo[l], ch.sg_begin), hi = std::min(seed_hi[l], ch.sg_end);
-        const RayQueue qin{(uint64_t*)c->q_pix[l & 1].p, (uint32_t*)c->q_sg[l & 1].p, (double*)c->q_r[l & 1].p,
-                           (double*)c->q_P[l & 1].p};
-        const RayQueue qout{(uint64_t*)c->q_pix[(l + 1) & 1].p, (uint32_t*)c->q_sg[(l + 1) & 1].p,
-                            (double*)c->q_r[(l + 1) & 1].p, (double*)c->q_P[(l + 1) & 1].p};
-        if (c->profile) (void)hipEventRecord(c->evs[2 * launches], strm);
-        if (fp32) {
-          TraceArgs<float> A{};
-          A.grids = (GridDev*)c->grids.p; A.probs = (ProblemDev*)c->probs.p; A.sgs = (SgDev*)c->sgs.p;
-          A.kappa = (float*)c->kappa.p; A.acc = (double*)c->acc.p; A.rec_base = (uint32_t)rec_base; A.in = qin; A.out = qout;
+        const int lo = std::max(seed_lo[l], ch.begin), hi = std::min(seed_hi[l], ch.end);
+        auto queue = [&](int k) {
+          return RayQueue{(uint64_t*)c->q_pix[k].p, (uint32_t*)c->q_tree[k].p, (double*)c->q_r[k].p,
+                          (double*)c->q_P[k].p, qslots};
+        };
+        auto launch = [&](auto zero) {
+          using R = decltype(zero);
+          TraceArgs<R> A{};
+          A.grids = (GridDev*)c->grids.p; A.trees = (TreeDev*)c->trees.p; A.kappa = (R*)c->kappa.p;
+          A.acc = (double*)c->acc.p; A.rec_base = (uint32_t)rec_base; A.in = queue(l & 1); A.out = queue((l + 1) & 1);
           A.seg_cap = seg_cap; A.nseg = nseg; A.ctr = ctr; A.stats = stats; A.gen = l; A.cin = l; A.cout = l + 1;
           A.seed_level = l;
-          A.seed_sg_begin = lo < hi ? lo : 0; A.seed_sg_end = lo < hi ? hi : 0;
+          A.seed_begin = lo < hi ? lo : 0; A.seed_end = lo < hi ? hi : 0;
           A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = reserve;
           A.mark = mark;
           A.kappa64 = kappa64;
-          e = launch_trace_level<float>(strm, blocks, A, c->cache, cover, radp, thin);
-        } else {
-          TraceArgs<double> A{};
-          A.grids = (GridDev*)c->grids.p; A.probs = (ProblemDev*)c->probs.p; A.sgs = (SgDev*)c->sgs.p;
-          A.kappa = (double*)c->kappa.p; A.acc = (double*)c->acc.p; A.rec_base = (uint32_t)rec_base; A.in = qin; A.out = qout;
-          A.seg_cap = seg_cap; A.nseg = nseg; A.ctr = ctr; A.stats = stats; A.gen = l; A.cin = l; A.cout = l + 1;
-          A.seed_level = l;
-          A.seed_sg_begin = lo < hi ? lo : 0; A.seed_sg_end = lo < hi ? hi : 0;
-          A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = reserve;
-          A.mark = mark;
-          e = launch_trace_level<double>(strm, blocks, A, c->cache, cover, radp, thin);
-        }
+          return launch_trace_level<R>(strm, blocks, A, c->cache, width, cover, radp, thin);
+        };
+        if (c->profile) (void)hipEventRecord(c->evs[2 * launches], strm);
+        e = fp32 ? launch(0.0f) : launch(0.0);
         if (!hip_ok(c, e, "trace")) {
           launch_failed = true;
           break;
@@ -859,7 +901,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     }
     if (!hip_ok(c, launch_finalize(strm, (int)fblocks.size(), (GridDev*)c->grids.p, (ProblemDev*)c->probs.p,
                                    (FinalBlock*)c->fblocks.p, (double*)c->acc.p, (double*)c->eexc.p,
-                                   (double*)c->partial.p, ctr, (SgDev*)c->sgs.p, mark),
+                                   (double*)c->partial.p, ctr, (TreeDev*)c->trees.p, mark),
                 "finalize")) {
       if (capturing) { abandon_capture(strm); continue; }
       return MORAY_EDEVICE;
@@ -887,7 +929,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     if (hctr->err & kErrInternal) return fail(c, MORAY_EINTERNAL, "a ray exceeded its step bound");
     if (hctr->err & kErrOverflow) {
       bool single = true;
-      for (const ChunkPlan& ch : chunks) single = single && ch.sg_end - ch.sg_begin <= 1;
+      for (const ChunkPlan& ch : chunks) single = single && ch.end - ch.begin <= 1;
       if (c->plan) {
         drop_graph(c->plan);
         c->plan->no_graph = true;
@@ -949,9 +991,9 @@ moray_status moray_trace_noalloc(moray_ctx* c, const moray_problem* probs, int n
   // The context's own buffers step aside for the call (they stay allocated
   // for later moray_trace calls); every buffer of this call is carved from
   // the scratch array, from its start, and graphs and profiling are off.
-  DevBuf* bufs[] = {&c->grids,    &c->probs,    &c->sgs,      &c->stats,    &c->ctr,      &c->kappa,    &c->kappa64,
+  DevBuf* bufs[] = {&c->grids,    &c->probs,    &c->trees,      &c->stats,    &c->ctr,      &c->kappa,    &c->kappa64,
                     &c->acc,      &c->mark,     &c->eexc,     &c->fblocks,  &c->partial,  &c->fields,   &c->outs,
-                    &c->q_pix[0], &c->q_sg[0],  &c->q_r[0],   &c->q_P[0],   &c->q_pix[1], &c->q_sg[1],
+                    &c->q_pix[0], &c->q_tree[0], &c->q_r[0],  &c->q_P[0],   &c->q_pix[1], &c->q_tree[1],
                     &c->q_r[1],   &c->q_P[1]};
   constexpr int nb = (int)(sizeof(bufs) / sizeof(bufs[0]));
   DevBuf saved[nb];

@@ -105,10 +105,10 @@ struct ServeProblem {
   moray_problem prob{};
   double bound = 0.0;            // ray-queue share: rays one level of all its trees can hold
   long long ncells = 0, nacc = 0;
-  int ngroups = 0, ntrees = 0, l0 = 0;
+  int ngroups = 0, width = 1, ntrees = 0, l0 = 0;   // width: groups a ray carries
   unsigned max_steps = 64;
   // placement while admitted
-  int pslot = -1, gbase = -1, tbase = -1;
+  int pslot = -1, gbase = -1, tbase = -1, sbase = -1;   // problem, grids, trees, statistics
   long long cbase = -1, abase = -1;
   int gen0 = 0, launches = 0;
   DevBuf fields, outs;           // device copies of host fields / host results
@@ -116,6 +116,7 @@ struct ServeProblem {
   unsigned long long peak = 0;
   double t_admit = 0.0;
   int restarts = 0;
+  int nstats() const { return (int)sources.size() * ngroups; }
 };
 
 // Ray-queue share of a problem for admission: the largest level population
@@ -154,15 +155,15 @@ struct Engine {
   size_t rsz = 4;
   long long cells_cap = 0, acc_cap = 0;
   int grid_cap = 4096, prob_cap = 1024, tree_cap = 1 << 16;
-  RangeAlloc cells, accs, gslots, pslots, tslots;
-  DevBuf kappa, acc, grids, probs, sgs, stats, ctr, eexc, fblocks, partial;
-  DevBuf qpix[2], qsg[2], qr[2], qP[2];
-  size_t qcap = 0;
+  RangeAlloc cells, accs, gslots, pslots, tslots, sslots;
+  DevBuf kappa, acc, grids, probs, trees, stats, ctr, eexc, fblocks, partial;
+  DevBuf qpix[2], qtree[2], qr[2], qP[2];
+  size_t qcap = 0;                          // rays a level queue holds (a slot is the parent of four)
   int nseg = 1;
   unsigned long long seg_cap = 0, reserve = 4;
   GridDev* hgrids = nullptr;
   ProblemDev* hprobs = nullptr;
-  SgDev* hsgs = nullptr;
+  TreeDev* htrees = nullptr;
   double* heexc = nullptr;
   SgStats* hstats = nullptr;
   Counters* hctr = nullptr;
@@ -214,18 +215,18 @@ void free_pinned(void*& p) {
 
 void engine_release_device(Engine* E) {
   moray_ctx* c = E->c;
-  DevBuf* all[] = {&E->kappa, &E->acc, &E->grids, &E->probs, &E->sgs, &E->stats, &E->ctr, &E->eexc, &E->fblocks,
+  DevBuf* all[] = {&E->kappa, &E->acc, &E->grids, &E->probs, &E->trees, &E->stats, &E->ctr, &E->eexc, &E->fblocks,
                    &E->partial};
   for (DevBuf* b : all) release(c, *b);
   for (int i = 0; i < 2; ++i) {
     release(c, E->qpix[i]);
-    release(c, E->qsg[i]);
+    release(c, E->qtree[i]);
     release(c, E->qr[i]);
     release(c, E->qP[i]);
   }
-  void* pins[] = {E->hgrids, E->hprobs, E->hsgs, E->heexc, E->hstats, E->hctr, E->hfin};
+  void* pins[] = {E->hgrids, E->hprobs, E->htrees, E->heexc, E->hstats, E->hctr, E->hfin};
   for (void* p : pins) free_pinned(p);
-  E->hgrids = nullptr; E->hprobs = nullptr; E->hsgs = nullptr; E->heexc = nullptr;
+  E->hgrids = nullptr; E->hprobs = nullptr; E->htrees = nullptr; E->heexc = nullptr;
   E->hstats = nullptr; E->hctr = nullptr; E->hfin = nullptr;
 }
 
@@ -234,7 +235,7 @@ moray_status engine_setup(moray_ctx* c, Engine* E) {
   E->fp32 = c->precision == MORAY_FP32_ACC64;
   E->rsz = E->fp32 ? sizeof(float) : sizeof(double);
   const double avail = c->budget > c->allocated ? (double)(c->budget - c->allocated) : 0.0;
-  const double per_ray = 2.0 * (sizeof(uint64_t) + sizeof(uint32_t) + 2 * sizeof(double));
+  const double per_ray = 56.0;               // 26 B of queue slots a ray; the rest is left to the other pools
   E->qcap = c->queue_cap_user ? c->queue_cap_user
                               : (size_t)std::min(std::max(avail * 0.3 / per_ray, 65536.0), (double)(1u << 28));
   E->qcap = std::max<size_t>(E->qcap, 256);
@@ -245,35 +246,37 @@ moray_status engine_setup(moray_ctx* c, Engine* E) {
   E->gslots.reset(E->grid_cap);
   E->pslots.reset(E->prob_cap);
   E->tslots.reset(E->tree_cap);
+  E->sslots.reset(E->tree_cap);
+  E->nseg = queue_segments(E->qcap);
+  E->seg_cap = E->qcap / 4 / (size_t)E->nseg;
+  const size_t qslots = (size_t)E->seg_cap * (size_t)E->nseg;
   moray_status st;
   if ((st = ensure(c, E->kappa, (size_t)E->cells_cap * E->rsz, "serving absorber columns")) ||
       (st = ensure(c, E->acc, (size_t)E->acc_cap * 8, "serving accumulators")) ||
       (st = ensure(c, E->grids, (size_t)E->grid_cap * sizeof(GridDev), "serving grid table")) ||
       (st = ensure(c, E->probs, (size_t)E->prob_cap * sizeof(ProblemDev), "serving problem table")) ||
-      (st = ensure(c, E->sgs, (size_t)E->tree_cap * sizeof(SgDev), "serving tree table")) ||
+      (st = ensure(c, E->trees, (size_t)E->tree_cap * sizeof(TreeDev), "serving tree table")) ||
       (st = ensure(c, E->stats, (size_t)E->tree_cap * sizeof(SgStats), "serving statistics")) ||
       (st = ensure(c, E->ctr, sizeof(Counters), "serving counters")) ||
       (st = ensure(c, E->eexc, (size_t)E->prob_cap * kServeMaxGroups * 8, "serving group energies")))
     return st;
   for (int i = 0; i < 2; ++i) {
-    if ((st = ensure(c, E->qpix[i], E->qcap * 8, "serving ray queue")) ||
-        (st = ensure(c, E->qsg[i], E->qcap * 4, "serving ray queue")) ||
-        (st = ensure(c, E->qr[i], E->qcap * 8, "serving ray queue")) ||
-        (st = ensure(c, E->qP[i], E->qcap * 8, "serving ray queue")))
+    if ((st = ensure(c, E->qpix[i], qslots * 8, "serving ray queue")) ||
+        (st = ensure(c, E->qtree[i], qslots * 4, "serving ray queue")) ||
+        (st = ensure(c, E->qr[i], qslots * 8, "serving ray queue")) ||
+        (st = ensure(c, E->qP[i], qslots * 8 * kPack, "serving ray queue")))
       return st;
   }
   auto pin = [&](void** p, size_t bytes) { return hipHostMalloc(p, bytes, hipHostMallocDefault) == hipSuccess; };
   if (!pin((void**)&E->hgrids, (size_t)E->grid_cap * sizeof(GridDev)) ||
       !pin((void**)&E->hprobs, (size_t)E->prob_cap * sizeof(ProblemDev)) ||
-      !pin((void**)&E->hsgs, (size_t)E->tree_cap * sizeof(SgDev)) ||
+      !pin((void**)&E->htrees, (size_t)E->tree_cap * sizeof(TreeDev)) ||
       !pin((void**)&E->heexc, (size_t)E->prob_cap * kServeMaxGroups * 8) ||
       !pin((void**)&E->hstats, (size_t)E->tree_cap * sizeof(SgStats)) || !pin((void**)&E->hctr, sizeof(Counters)))
     return fail(c, MORAY_ENOMEM, "pinned host allocation failed");
-  E->nseg = queue_segments(E->qcap);
-  E->seg_cap = E->qcap / (size_t)E->nseg;
   const double waves = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave);
-  E->reserve = (unsigned long long)std::min<double>((double)kReserveMax, (double)E->qcap / (8.0 * waves));
-  E->reserve = std::max<unsigned long long>(4, E->reserve & ~3ull);
+  E->reserve = (unsigned long long)std::min<double>((double)kReserveMax, (double)E->qcap / (32.0 * waves));
+  E->reserve = std::max<unsigned long long>(1, E->reserve);
   if (!hip_ok(c, launch_reset(c->stream, (Counters*)E->ctr.p, (SgStats*)E->stats.p, 0), "reset") ||
       !hip_ok(c, hipStreamSynchronize(c->stream), "synchronize"))
     return MORAY_EDEVICE;
@@ -302,8 +305,9 @@ void unplace(Engine* E, ServeProblem* p) {
   if (p->gbase >= 0) E->gslots.release(p->gbase, (long long)p->grids.size());
   if (p->pslot >= 0) E->pslots.release(p->pslot, 1);
   if (p->tbase >= 0) E->tslots.release(p->tbase, p->ntrees);
+  if (p->sbase >= 0) E->sslots.release(p->sbase, p->nstats());
   p->cbase = p->abase = -1;
-  p->gbase = p->pslot = p->tbase = -1;
+  p->gbase = p->pslot = p->tbase = p->sbase = -1;
   release(c, p->fields);
   release(c, p->outs);
 }
@@ -316,7 +320,8 @@ bool place(Engine* E, ServeProblem* p) {
   p->abase = E->accs.alloc(p->nacc);
   p->gbase = (int)E->gslots.alloc((long long)p->grids.size());
   p->pslot = (int)E->pslots.alloc(1);
-  bool ok = p->cbase >= 0 && p->abase >= 0 && p->gbase >= 0 && p->pslot >= 0;
+  p->sbase = (int)E->sslots.alloc(p->nstats());
+  bool ok = p->cbase >= 0 && p->abase >= 0 && p->gbase >= 0 && p->pslot >= 0 && p->sbase >= 0;
   if (ok && !(p->flags & MORAY_FIELDS_ON_DEVICE))
     ok = eensure(E, p->fields, (size_t)p->ncells * 8, "request fields") == MORAY_OK;
   if (ok && !(p->flags & MORAY_OUT_ON_DEVICE))
@@ -337,6 +342,8 @@ moray_status write_tables(Engine* E, ServeProblem* p) {
   pd.cell_off = p->cbase;
   pd.n_cells = p->ncells;
   pd.acc_off = p->abase;
+  pd.acc_mode = p->ngroups > 1 ? kAccMoments : kAccSums;
+  pd.acc_stride = p->ngroups > 1 ? 2 : 1;
   pd.eexc_off = p->pslot * kServeMaxGroups;
   for (int g = 0; g < p->ngroups; ++g)
     E->heexc[pd.eexc_off + g] = (p->energy[g] - p->spec.e_ion_ev) * kEvErgConst;
@@ -377,29 +384,14 @@ moray_status write_tables(Engine* E, ServeProblem* p) {
     off += nc;
     within += nc;
   }
-  const double npix0 = std::ldexp(12.0, 2 * P.params.level_init);
-  const GridDev& rg = E->hgrids[p->gbase];
+  const int packs = pack_count(p->ngroups);
   int k = 0;
   for (int si = 0; si < P.n_sources; ++si) {
-    for (int g = 0; g < p->ngroups; ++g, ++k) {
-      SgDev& d = E->hsgs[p->tbase + k];
-      d = SgDev{};
-      const moray_source& S = P.sources[si];
-      d.sx = S.x; d.sy = S.y; d.sz = S.z;
-      d.P0 = p->frac[g] * S.ndot / npix0;
-      d.pmin0 = P.params.p_min_frac * d.P0;
-      d.sigma64 = p->sigma[g];
-      d.sigma32 = (float)p->sigma[g];
-      d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
-      d.split_t2_base = P.params.phi_c > 0.0 ? (float)(12.0 / (4.0 * kPiConst * P.params.phi_c)) : FLT_MAX;
-      d.acc_slot = pd.acc_off + (long long)g * pd.n_cells - pd.cell_off;
-      d.problem = p->pslot;
-      d.covering = P.params.covering != 0;
-      d.root_grid = p->gbase;
-      d.rnx = rg.nx; d.rny = rg.ny; d.rnz = rg.nz;
-      d.rcell_off = rg.cell_off;
-      d.level_init = P.params.level_init;
-      d.level_max = P.params.phi_c > 0.0 ? P.params.level_max : P.params.level_init;
+    for (int j = 0; j < packs; ++j, ++k) {
+      TreeDev& d = E->htrees[p->tbase + k];
+      const int g0 = pack_first(p->ngroups, j), g1 = pack_first(p->ngroups, j + 1);
+      fill_tree(d, P, si, g0, g1 - g0, pd, E->hgrids[p->gbase]);
+      d.stat0 = (uint32_t)(p->sbase + si * p->ngroups + g0);
       d.gen0 = p->gen0;
     }
   }
@@ -410,7 +402,7 @@ moray_status write_tables(Engine* E, ServeProblem* p) {
   if (!up(E->grids, (size_t)p->gbase * sizeof(GridDev), E->hgrids + p->gbase, p->grids.size() * sizeof(GridDev)) ||
       !up(E->probs, (size_t)p->pslot * sizeof(ProblemDev), E->hprobs + p->pslot, sizeof(ProblemDev)) ||
       !up(E->eexc, (size_t)pd.eexc_off * 8, E->heexc + pd.eexc_off, (size_t)p->ngroups * 8) ||
-      !up(E->sgs, (size_t)p->tbase * sizeof(SgDev), E->hsgs + p->tbase, (size_t)p->ntrees * sizeof(SgDev)))
+      !up(E->trees, (size_t)p->tbase * sizeof(TreeDev), E->htrees + p->tbase, (size_t)p->ntrees * sizeof(TreeDev)))
     return MORAY_EDEVICE;
   hipError_t e =
       E->fp32 ? launch_prep<float>(s, c->num_cu, (GridDev*)E->grids.p + p->gbase, (int)p->grids.size(), p->gbase,
@@ -419,9 +411,9 @@ moray_status write_tables(Engine* E, ServeProblem* p) {
               : launch_prep<double>(s, c->num_cu, (GridDev*)E->grids.p + p->gbase, (int)p->grids.size(), p->gbase,
                                     (ProblemDev*)E->probs.p, p->cbase, p->cbase + p->ncells, (double*)E->kappa.p,
                                     (double*)E->acc.p, (Counters*)E->ctr.p);
-  if (!eok(E, e, "prep") || !eok(E, launch_reset_stats(s, (SgStats*)E->stats.p, p->tbase, p->ntrees), "reset"))
+  if (!eok(E, e, "prep") || !eok(E, launch_reset_stats(s, (SgStats*)E->stats.p, p->sbase, p->nstats()), "reset"))
     return MORAY_EDEVICE;
-  p->splits_seen.assign(p->ntrees, 0);
+  p->splits_seen.assign(p->nstats(), 0);
   p->launches = 0;
   p->peak = 0;
   return MORAY_OK;
@@ -490,7 +482,7 @@ moray_status retire(Engine* E, std::vector<ServeProblem*>& done) {
     int k = 0;
     for (int si = 0; si < P.n_sources; ++si) {
       for (int g = 0; g < p->ngroups; ++g, ++k) {
-        const SgStats& S = E->hstats[p->tbase + k];
+        const SgStats& S = E->hstats[p->sbase + k];
         R.emitted += p->frac[g] * P.sources[si].ndot;
         R.escaped += S.esc_P;
         R.truncated += S.trunc_P;
@@ -599,7 +591,7 @@ bool drop_leavers(Engine* E, int row) {
       lo[n] = stop_running[k].first->tbase;
       hi[n] = stop_running[k].first->tbase + stop_running[k].first->ntrees;
     }
-    if (!eok(E, launch_drop_trees(c->stream, (uint32_t*)E->qsg[row].p, (Counters*)E->ctr.p, row, E->seg_cap,
+    if (!eok(E, launch_drop_trees(c->stream, (uint32_t*)E->qtree[row].p, (Counters*)E->ctr.p, row, E->seg_cap,
                                   E->nseg, lo, hi, n),
              "drop rays"))
       return false;
@@ -748,14 +740,15 @@ bool trip(Engine* E) {
   const int g = E->gen;
   const int cin = g & 1, cout = (g + 1) & 1;
   unsigned max_steps = 64;
-  int tlo = E->tree_cap, thi = 0;
+  int slo = E->tree_cap, shi = 0, width = 1;
   bool cover = false;               // some running problem scales its deposits by the covering factor
   for (ServeProblem* p : E->running) {
     max_steps = std::max(max_steps, p->max_steps);
     cover = cover || p->prob.params.covering != 0;
-    if (p->ntrees) {
-      tlo = std::min(tlo, p->tbase);
-      thi = std::max(thi, p->tbase + p->ntrees);
+    width = std::max(width, p->width);
+    if (p->nstats()) {
+      slo = std::min(slo, p->sbase);
+      shi = std::max(shi, p->sbase + p->nstats());
     }
     ++p->launches;
   }
@@ -764,35 +757,27 @@ bool trip(Engine* E) {
   for (ServeProblem* p : admitted) seed_hi = std::max(seed_hi, p->tbase + p->ntrees);
   const int seed_level = admitted.empty() ? 0 : admitted.front()->l0;
   const int blocks = std::max(1, c->num_cu * c->blocks_per_cu);
-  const RayQueue qin{(uint64_t*)E->qpix[cin].p, (uint32_t*)E->qsg[cin].p, (double*)E->qr[cin].p, (double*)E->qP[cin].p};
-  const RayQueue qout{(uint64_t*)E->qpix[cout].p, (uint32_t*)E->qsg[cout].p, (double*)E->qr[cout].p,
-                      (double*)E->qP[cout].p};
+  auto queue = [&](int k) {
+    return RayQueue{(uint64_t*)E->qpix[k].p, (uint32_t*)E->qtree[k].p, (double*)E->qr[k].p, (double*)E->qP[k].p,
+                    E->seg_cap * (unsigned long long)E->nseg};
+  };
+  auto launch = [&](auto zero) {
+    using R = decltype(zero);
+    TraceArgs<R> A{};
+    A.grids = (GridDev*)E->grids.p; A.trees = (TreeDev*)E->trees.p; A.kappa = (R*)E->kappa.p;
+    A.acc = (double*)E->acc.p; A.in = queue(cin); A.out = queue(cout);
+    A.seg_cap = E->seg_cap; A.nseg = E->nseg; A.ctr = (Counters*)E->ctr.p; A.stats = (SgStats*)E->stats.p;
+    A.gen = g; A.cin = cin; A.cout = cout; A.seed_level = seed_level;
+    A.seed_begin = seed_lo; A.seed_end = seed_hi;
+    A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = E->reserve;
+    return launch_trace_level<R>(s, blocks, A, c->cache, width, cover, false);
+  };
   hipError_t e = launch_reset_generation(s, (Counters*)E->ctr.p, cin, cout);
-  if (e == hipSuccess) {
-    if (E->fp32) {
-      TraceArgs<float> A{};
-      A.grids = (GridDev*)E->grids.p; A.probs = (ProblemDev*)E->probs.p; A.sgs = (SgDev*)E->sgs.p;
-      A.kappa = (float*)E->kappa.p; A.acc = (double*)E->acc.p; A.in = qin; A.out = qout;
-      A.seg_cap = E->seg_cap; A.nseg = E->nseg; A.ctr = (Counters*)E->ctr.p; A.stats = (SgStats*)E->stats.p;
-      A.gen = g; A.cin = cin; A.cout = cout; A.seed_level = seed_level;
-      A.seed_sg_begin = seed_lo; A.seed_sg_end = seed_hi;
-      A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = E->reserve;
-      e = launch_trace_level<float>(s, blocks, A, c->cache, cover, false);
-    } else {
-      TraceArgs<double> A{};
-      A.grids = (GridDev*)E->grids.p; A.probs = (ProblemDev*)E->probs.p; A.sgs = (SgDev*)E->sgs.p;
-      A.kappa = (double*)E->kappa.p; A.acc = (double*)E->acc.p; A.in = qin; A.out = qout;
-      A.seg_cap = E->seg_cap; A.nseg = E->nseg; A.ctr = (Counters*)E->ctr.p; A.stats = (SgStats*)E->stats.p;
-      A.gen = g; A.cin = cin; A.cout = cout; A.seed_level = seed_level;
-      A.seed_sg_begin = seed_lo; A.seed_sg_end = seed_hi;
-      A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = E->reserve;
-      e = launch_trace_level<double>(s, blocks, A, c->cache, cover, false);
-    }
-  }
+  if (e == hipSuccess) e = E->fp32 ? launch(0.0f) : launch(0.0);
   if (!eok(E, e, "trace") ||
       !eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
-      (thi > tlo && !eok(E, hipMemcpyAsync(E->hstats + tlo, (SgStats*)E->stats.p + tlo,
-                                              (size_t)(thi - tlo) * sizeof(SgStats), hipMemcpyDeviceToHost, s),
+      (shi > slo && !eok(E, hipMemcpyAsync(E->hstats + slo, (SgStats*)E->stats.p + slo,
+                                              (size_t)(shi - slo) * sizeof(SgStats), hipMemcpyDeviceToHost, s),
                             "copy")) ||
       !eok(E, hipStreamSynchronize(s), "synchronize")) {
     fail_all(E, MORAY_EDEVICE, E->err);
@@ -832,12 +817,12 @@ bool trip(Engine* E) {
   // a clean generation gives back a quarter of what an overflow took
   E->load_frac = std::min(kLoadFrac, E->load_frac * 1.25);
   unsigned long long pop = 0;
-  for (int k = 0; k < E->nseg; ++k) pop += std::min<unsigned long long>(E->hctr->count[cout][k], E->seg_cap);
+  for (int k = 0; k < E->nseg; ++k) pop += 4 * std::min<unsigned long long>(E->hctr->count[cout][k], E->seg_cap);
   std::vector<ServeProblem*> done, still;
   for (ServeProblem* p : E->running) {
     bool live = false;
-    for (int k = 0; k < p->ntrees; ++k) {
-      const unsigned long long sp = E->hstats[p->tbase + k].splits;
+    for (int k = 0; k < p->nstats(); ++k) {
+      const unsigned long long sp = E->hstats[p->sbase + k].splits;
       if (sp != p->splits_seen[k]) live = true;
       p->splits_seen[k] = sp;
     }
@@ -884,14 +869,15 @@ ServeProblem* make_problem(const moray_problem& P, unsigned flags, moray_result*
   p->prob.sources = p->sources.empty() ? nullptr : p->sources.data();
   p->prob.spectrum = &p->spec;
   p->l0 = P.params.level_init;
-  p->ntrees = P.n_sources * Sp.n_groups;
+  p->width = pack_width(Sp.n_groups);
+  p->ntrees = P.n_sources * pack_count(Sp.n_groups);
   long long steps = 16;
   for (const moray_grid& G : p->grids) {
     p->ncells += (long long)G.nx * G.ny * G.nz;
     steps += 2LL * (G.nx + G.ny + G.nz);
   }
   p->max_steps = (unsigned)std::min<long long>(steps * 2, 1u << 30);
-  p->nacc = p->ncells * p->ngroups;
+  p->nacc = p->ncells * (p->ngroups > 1 ? 2 : 1);
   p->bound = serve_rays_estimate(p->prob);
   return p;
 }

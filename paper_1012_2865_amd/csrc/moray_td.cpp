@@ -4,14 +4,14 @@
 // moray_td_free).
 //
 // Every step's sources emit one batch of seed rays (when asked to); a batch
-// is a set of (source, group) trees whose rays halt, in a step where the
-// batch has completed a steps, at the radius (a + 1) c dt_P. The trees of the
+// is a set of trees (a source and the groups its rays carry) whose rays halt,
+// in a step where the batch has completed a steps, at the radius (a + 1) c dt_P. The trees of the
 // live batches sit in a ring of `slots` batches: once (a + 1) c dt_P exceeds
 // the box diagonal every ray of a batch has left, so a slot is reused after
 // `slots` steps. A step is the one-shot launch sequence with two changes:
-// before each level's launch, the rays of that level halted in the previous
-// step join the level's queue (prefill_level_kernel), and the trace kernel's
-// halting variant writes the rays it halts to the other pool.
+// each level's launch also claims the rays of that level halted in the
+// previous step (read through the sorted order of their pool), and the trace
+// kernel's halting variant writes the rays it halts to the other pool.
 #include "moray_internal.h"
 
 #include <algorithm>
@@ -31,16 +31,17 @@ struct moray_td {
   long long step = 0;
   std::vector<long long> emit_step;     // per slot: the step its batch was emitted, -1 if none
   std::vector<double> P0;               // per slot, source and group: seed photon rate
-  size_t cap = 0;                       // pool records; also slots of each level queue
+  int width = 1, planes = 1, n_pack = 1; // groups a ray carries, photon rates a record holds, rays per source and pixel
+  size_t cap = 0;                       // pool records; each level queue has room for as many rays
   int nseg = 1;
   unsigned long long seg_cap = 0;
   int cur = 0;                          // pool holding the rays in flight
   unsigned long long n_in = 0;
   unsigned long long lev_in[kLevels] = {};
   bool broken = false;                  // a failed step leaves the pool undefined
-  DevBuf pix[2], sg[2], r[2], P[2], lev[2];
-  DevBuf qpix[2], qsg[2], qr[2], qP[2];
-  DevBuf grids, probs, sgs, stats, ctr, kappa, acc, eexc, fblocks, partial;
+  DevBuf pix[2], tree[2], r[2], P[2], lev[2];
+  DevBuf qpix[2], qtree[2], qr[2], qP[2];
+  DevBuf grids, probs, trees, stats, ctr, kappa, acc, eexc, fblocks, partial;
   DevBuf keys[2], order[2], sort_temp;  // the halt list sorted by (level, tree, pixel)
   size_t sort_bytes = 0;
   std::vector<FinalBlock> fb;
@@ -61,16 +62,24 @@ static bool same_shape(const moray_td* t, const moray_problem& P) {
          P.params.level_init == t->level_init;
 }
 
+// The pool's records, and level queues with room for as many rays (a slot of
+// a queue holds a split ray, four of the next level).
+static void set_cap(moray_td* t, size_t cap) {
+  t->cap = cap;
+  t->nseg = queue_segments(cap);
+  t->seg_cap = std::max<size_t>(1, cap / 4 / (size_t)t->nseg);
+}
+
 static void td_release(moray_ctx* c, moray_td* t) {
-  DevBuf* all[] = {&t->grids, &t->probs, &t->sgs, &t->stats, &t->ctr, &t->kappa, &t->acc, &t->eexc, &t->fblocks,
+  DevBuf* all[] = {&t->grids, &t->probs, &t->trees, &t->stats, &t->ctr, &t->kappa, &t->acc, &t->eexc, &t->fblocks,
                    &t->partial};
   for (DevBuf* b : all) release(c, *b);
   release(c, t->sort_temp);
   for (int i = 0; i < 2; ++i) {
     release(c, t->keys[i]);
     release(c, t->order[i]);
-    release(c, t->pix[i]); release(c, t->sg[i]); release(c, t->r[i]); release(c, t->P[i]); release(c, t->lev[i]);
-    release(c, t->qpix[i]); release(c, t->qsg[i]); release(c, t->qr[i]); release(c, t->qP[i]);
+    release(c, t->pix[i]); release(c, t->tree[i]); release(c, t->r[i]); release(c, t->P[i]); release(c, t->lev[i]);
+    release(c, t->qpix[i]); release(c, t->qtree[i]); release(c, t->qr[i]); release(c, t->qP[i]);
   }
   if (t->h_stage) (void)hipHostFree(t->h_stage);
   t->h_stage = nullptr;
@@ -92,7 +101,7 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
   const moray_grid& G = prob->grids[0];
   const double diag = std::sqrt((double)G.nx * G.nx + (double)G.ny * G.ny + (double)G.nz * G.nz);
   const double need_slots = std::ceil(diag / c_dt) + 2.0;
-  const long long per = (long long)prob->n_sources * prob->spectrum->n_groups;
+  const long long per = (long long)prob->n_sources * prob->spectrum->n_groups;   // statistics, and trees at most
   if (need_slots * (double)per >= 2.0e9) return fail(c, MORAY_EINVAL, "c_dt too small for this many trees");
   long long n_cells = 0;
   for (int q = 0; q < prob->n_grids; ++q)
@@ -111,10 +120,13 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
   t->slots = (int)need_slots;
   t->emit_step.assign(t->slots, -1);
   t->P0.assign((size_t)t->slots * per, 0.0);
-  t->cap = pool_rays;
-  t->nseg = queue_segments(pool_rays);
-  t->seg_cap = pool_rays / (size_t)t->nseg;
-  const int n_sg = (int)(t->slots * per);
+  t->n_pack = pack_count(t->n_grp);
+  t->width = pack_width(t->n_grp);
+  t->planes = rate_planes(t->width);
+  // pool_rays counts rays of one group; a record holds `width` of them
+  set_cap(t, std::max<size_t>(1024, pool_rays / (size_t)t->width));
+  const int n_trees = t->slots * t->n_src * t->n_pack;
+  const size_t cap = t->cap, qslots = t->seg_cap * (size_t)t->nseg;
   const size_t rsz = c->precision == MORAY_FP32_ACC64 ? sizeof(float) : sizeof(double);
   {
     const long long per_fb = (long long)kFinalBlock * kFinalCellsPerThread;
@@ -123,34 +135,33 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
       for (long long f = 0; f < nc; f += per_fb) t->fb.push_back({q, (int)std::min(per_fb, nc - f), f});
     }
   }
-  const size_t stage = sizeof(Counters) + (size_t)n_sg * sizeof(SgStats) + t->fb.size() * 8;
+  const size_t stage = sizeof(Counters) + (size_t)per * sizeof(SgStats) + t->fb.size() * 8;
   for (int i = 0; i < 2 && st == MORAY_OK; ++i) {
-    if ((st = ensure(c, t->pix[i], pool_rays * 8, "ray pool")) || (st = ensure(c, t->sg[i], pool_rays * 4, "ray pool")) ||
-        (st = ensure(c, t->r[i], pool_rays * 8, "ray pool")) || (st = ensure(c, t->P[i], pool_rays * 8, "ray pool")) ||
-        (st = ensure(c, t->lev[i], pool_rays * 4, "ray pool")) ||
-        (st = ensure(c, t->qpix[i], pool_rays * 8, "ray queue")) ||
-        (st = ensure(c, t->qsg[i], pool_rays * 4, "ray queue")) || (st = ensure(c, t->qr[i], pool_rays * 8, "ray queue")) ||
-        (st = ensure(c, t->qP[i], pool_rays * 8, "ray queue")))
+    if ((st = ensure(c, t->pix[i], cap * 8, "ray pool")) || (st = ensure(c, t->tree[i], cap * 4, "ray pool")) ||
+        (st = ensure(c, t->r[i], cap * 8, "ray pool")) || (st = ensure(c, t->P[i], cap * 8 * t->planes, "ray pool")) ||
+        (st = ensure(c, t->lev[i], cap * 4, "ray pool")) || (st = ensure(c, t->qpix[i], qslots * 8, "ray queue")) ||
+        (st = ensure(c, t->qtree[i], qslots * 4, "ray queue")) || (st = ensure(c, t->qr[i], qslots * 8, "ray queue")) ||
+        (st = ensure(c, t->qP[i], qslots * 8 * t->planes, "ray queue")))
       break;
   }
   if (st == MORAY_OK) {
     (void)((st = ensure(c, t->grids, (size_t)prob->n_grids * sizeof(GridDev), "grid table")) ||
            (st = ensure(c, t->probs, sizeof(ProblemDev), "problem table")) ||
-           (st = ensure(c, t->sgs, (size_t)n_sg * sizeof(SgDev), "source table")) ||
-           (st = ensure(c, t->stats, (size_t)n_sg * sizeof(SgStats), "statistics")) ||
+           (st = ensure(c, t->trees, (size_t)std::max(1, n_trees) * sizeof(TreeDev), "source table")) ||
+           (st = ensure(c, t->stats, (size_t)std::max<long long>(1, per) * sizeof(SgStats), "statistics")) ||
            (st = ensure(c, t->ctr, sizeof(Counters), "counters")) ||
            (st = ensure(c, t->kappa, (size_t)n_cells * rsz, "absorber columns")) ||
-           (st = ensure(c, t->acc, (size_t)n_cells * t->n_grp * 8, "accumulators")) ||
+           (st = ensure(c, t->acc, (size_t)n_cells * (t->n_grp > 1 ? 2 : 1) * 8, "accumulators")) ||
            (st = ensure(c, t->eexc, (size_t)t->n_grp * 8, "group energies")) ||
            (st = ensure(c, t->fblocks, t->fb.size() * sizeof(FinalBlock), "finalize blocks")) ||
            (st = ensure(c, t->partial, t->fb.size() * 8, "partial sums")));
   }
-  if (st == MORAY_OK && pool_rays < ((size_t)1 << 32)) {
-    // sorting needs 32-bit record indices; larger pools are resumed unsorted
-    if (!hip_ok(c, td_sort_temp_bytes(pool_rays, &t->sort_bytes), "sort")) st = MORAY_EDEVICE;
+  if (st == MORAY_OK && cap >= ((size_t)1 << 32))
+    st = fail(c, MORAY_ENOMEM, "the ray pool exceeds the 2^32 records its sorting indexes");
+  if (st == MORAY_OK) {
+    if (!hip_ok(c, td_sort_temp_bytes(cap, &t->sort_bytes), "sort")) st = MORAY_EDEVICE;
     for (int i = 0; i < 2 && st == MORAY_OK; ++i)
-      if ((st = ensure(c, t->keys[i], pool_rays * 8, "sort keys")) ||
-          (st = ensure(c, t->order[i], pool_rays * 4, "sort order")))
+      if ((st = ensure(c, t->keys[i], cap * 8, "sort keys")) || (st = ensure(c, t->order[i], cap * 4, "sort order")))
         break;
     if (st == MORAY_OK) st = ensure(c, t->sort_temp, std::max<size_t>(t->sort_bytes, 256), "sort scratch");
   }
@@ -182,20 +193,25 @@ void moray_td_free(moray_ctx* c, moray_td* t) {
   delete t;
 }
 
+static RayQueue pool_of(const moray_td* t, int i) {
+  return RayQueue{(uint64_t*)t->pix[i].p, (uint32_t*)t->tree[i].p, (double*)t->r[i].p, (double*)t->P[i].p, t->cap};
+}
+
 template <typename R>
-static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, int seed_hi, unsigned max_steps,
-                               unsigned long long reserve) {
+static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, int seed_hi, unsigned long long held_first,
+                               unsigned long long n_held, unsigned max_steps, unsigned long long reserve) {
   const int b = 1 - t->cur;       // the pool the halted rays go to
+  const unsigned long long qslots = t->seg_cap * (unsigned long long)t->nseg;
+  auto queue = [&](int k) {
+    return RayQueue{(uint64_t*)t->qpix[k].p, (uint32_t*)t->qtree[k].p, (double*)t->qr[k].p, (double*)t->qP[k].p, qslots};
+  };
   TraceArgs<R> A{};
   A.grids = (GridDev*)t->grids.p;
-  A.probs = (ProblemDev*)t->probs.p;
-  A.sgs = (SgDev*)t->sgs.p;
+  A.trees = (TreeDev*)t->trees.p;
   A.kappa = (R*)t->kappa.p;
   A.acc = (double*)t->acc.p;
-  A.in = RayQueue{(uint64_t*)t->qpix[l & 1].p, (uint32_t*)t->qsg[l & 1].p, (double*)t->qr[l & 1].p,
-                  (double*)t->qP[l & 1].p};
-  A.out = RayQueue{(uint64_t*)t->qpix[(l + 1) & 1].p, (uint32_t*)t->qsg[(l + 1) & 1].p,
-                   (double*)t->qr[(l + 1) & 1].p, (double*)t->qP[(l + 1) & 1].p};
+  A.in = queue(l & 1);
+  A.out = queue((l + 1) & 1);
   A.seg_cap = t->seg_cap;
   A.nseg = t->nseg;
   A.ctr = (Counters*)t->ctr.p;
@@ -204,17 +220,20 @@ static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, in
   A.cin = l;
   A.cout = l + 1;
   A.seed_level = l;
-  A.seed_sg_begin = seed_lo;
-  A.seed_sg_end = seed_hi;
+  A.seed_begin = seed_lo;
+  A.seed_end = seed_hi;
   A.chunk = c->chunk;
   A.refill = c->refill;
   A.max_steps = max_steps;
   A.reserve = reserve;
-  A.halt = RayQueue{(uint64_t*)t->pix[b].p, (uint32_t*)t->sg[b].p, (double*)t->r[b].p, (double*)t->P[b].p};
+  A.halt = pool_of(t, b);
   A.halt_lev = (int*)t->lev[b].p;
   A.halt_cap = t->cap;
-  A.tree_fold = (uint32_t)(t->n_src * t->n_grp);
-  return launch_trace_level_halt<R>(c->stream, std::max(1, c->num_cu * c->blocks_per_cu), A, c->cache);
+  A.held = pool_of(t, t->cur);
+  A.held_order = (const uint32_t*)t->order[1].p;
+  A.held_first = held_first;
+  A.n_held = n_held;
+  return launch_trace_level_halt<R>(c->stream, std::max(1, c->num_cu * c->blocks_per_cu), A, c->cache, t->width);
 }
 
 // Doubles the pools, the level queues and the sort buffers of a state whose
@@ -225,17 +244,17 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
   // at least double; enough for what the failed step asked for, with room for segment imbalance
   size_t ncap = t->cap * 2;
   while ((double)ncap < 1.5 * (double)demand && ncap <= ((size_t)1 << 34)) ncap *= 2;
-  if (ncap > ((size_t)1 << 34)) return fail(c, MORAY_EQUEUE, "the ray pool cannot grow beyond 2^34 rays");
-  const size_t pool_b = 8 + 4 + 8 + 8 + 4, queue_b = 8 + 4 + 8 + 8, sort_b = 8 + 4;
+  if (ncap >= ((size_t)1 << 32)) return fail(c, MORAY_EQUEUE, "the ray pool cannot grow beyond 2^32 records");
+  const size_t pool_b = slot_bytes(t->planes) + 4, sort_b = 8 + 4;
   size_t sort_tmp = 0;
-  if (ncap < ((size_t)1 << 32) && !hip_ok(c, td_sort_temp_bytes(ncap, &sort_tmp), "sort")) return MORAY_EDEVICE;
-  const size_t nbytes = ncap * (2 * pool_b + 2 * queue_b + (ncap < ((size_t)1 << 32) ? 2 * sort_b : 0)) +
-                        (ncap < ((size_t)1 << 32) ? std::max<size_t>(sort_tmp, 256) : 0);
+  if (!hip_ok(c, td_sort_temp_bytes(ncap, &sort_tmp), "sort")) return MORAY_EDEVICE;
+  const size_t nbytes = ncap * (2 * pool_b + 2 * sort_b) + ncap / 4 * 2 * slot_bytes(t->planes) +
+                        std::max<size_t>(sort_tmp, 256);
   const int a = t->cur;
-  size_t old = t->sort_temp.bytes + t->pix[1 - a].bytes + t->sg[1 - a].bytes + t->r[1 - a].bytes +
+  size_t old = t->sort_temp.bytes + t->pix[1 - a].bytes + t->tree[1 - a].bytes + t->r[1 - a].bytes +
                t->P[1 - a].bytes + t->lev[1 - a].bytes;
   for (int i = 0; i < 2; ++i)
-    old += t->qpix[i].bytes + t->qsg[i].bytes + t->qr[i].bytes + t->qP[i].bytes + t->keys[i].bytes + t->order[i].bytes;
+    old += t->qpix[i].bytes + t->qtree[i].bytes + t->qr[i].bytes + t->qP[i].bytes + t->keys[i].bytes + t->order[i].bytes;
   if (c->allocated - old + nbytes + 4096 > c->budget)
     return fail(c, MORAY_EQUEUE, "the ray pool or a level queue overflowed and cannot double within the HBM budget");
   // everything but the rays in flight can go first
@@ -243,14 +262,14 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
   for (int i = 0; i < 2; ++i) {
     release(c, t->keys[i]);
     release(c, t->order[i]);
-    release(c, t->qpix[i]); release(c, t->qsg[i]); release(c, t->qr[i]); release(c, t->qP[i]);
+    release(c, t->qpix[i]); release(c, t->qtree[i]); release(c, t->qr[i]); release(c, t->qP[i]);
   }
-  release(c, t->pix[1 - a]); release(c, t->sg[1 - a]); release(c, t->r[1 - a]); release(c, t->P[1 - a]);
+  release(c, t->pix[1 - a]); release(c, t->tree[1 - a]); release(c, t->r[1 - a]); release(c, t->P[1 - a]);
   release(c, t->lev[1 - a]);
   DevBuf np[5];
   moray_status st;
   if ((st = ensure(c, np[0], ncap * 8, "ray pool")) || (st = ensure(c, np[1], ncap * 4, "ray pool")) ||
-      (st = ensure(c, np[2], ncap * 8, "ray pool")) || (st = ensure(c, np[3], ncap * 8, "ray pool")) ||
+      (st = ensure(c, np[2], ncap * 8, "ray pool")) || (st = ensure(c, np[3], ncap * 8 * t->planes, "ray pool")) ||
       (st = ensure(c, np[4], ncap * 4, "ray pool"))) {
     for (DevBuf& b : np) release(c, b);
     t->broken = true;
@@ -259,9 +278,10 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
   hipStream_t s = c->stream;
   const unsigned long long n = t->n_in;
   if (n && (!hip_ok(c, hipMemcpyAsync(np[0].p, t->pix[a].p, n * 8, hipMemcpyDeviceToDevice, s), "copy") ||
-            !hip_ok(c, hipMemcpyAsync(np[1].p, t->sg[a].p, n * 4, hipMemcpyDeviceToDevice, s), "copy") ||
+            !hip_ok(c, hipMemcpyAsync(np[1].p, t->tree[a].p, n * 4, hipMemcpyDeviceToDevice, s), "copy") ||
             !hip_ok(c, hipMemcpyAsync(np[2].p, t->r[a].p, n * 8, hipMemcpyDeviceToDevice, s), "copy") ||
-            !hip_ok(c, hipMemcpyAsync(np[3].p, t->P[a].p, n * 8, hipMemcpyDeviceToDevice, s), "copy") ||
+            !hip_ok(c, hipMemcpy2DAsync(np[3].p, ncap * 8, t->P[a].p, t->cap * 8, n * 8, t->planes,
+                                        hipMemcpyDeviceToDevice, s), "copy") ||
             !hip_ok(c, hipMemcpyAsync(np[4].p, t->lev[a].p, n * 4, hipMemcpyDeviceToDevice, s), "copy"))) {
     t->broken = true;
     return MORAY_EDEVICE;
@@ -270,35 +290,33 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
     t->broken = true;
     return MORAY_EDEVICE;
   }
-  release(c, t->pix[a]); release(c, t->sg[a]); release(c, t->r[a]); release(c, t->P[a]); release(c, t->lev[a]);
-  t->pix[a] = np[0]; t->sg[a] = np[1]; t->r[a] = np[2]; t->P[a] = np[3]; t->lev[a] = np[4];
+  release(c, t->pix[a]); release(c, t->tree[a]); release(c, t->r[a]); release(c, t->P[a]); release(c, t->lev[a]);
+  t->pix[a] = np[0]; t->tree[a] = np[1]; t->r[a] = np[2]; t->P[a] = np[3]; t->lev[a] = np[4];
   const int b = 1 - a;
+  set_cap(t, ncap);
+  const size_t qslots = t->seg_cap * (size_t)t->nseg;
   for (int i = 0; i < 2; ++i) {
-    if ((i == b && ((st = ensure(c, t->pix[b], ncap * 8, "ray pool")) || (st = ensure(c, t->sg[b], ncap * 4, "ray pool")) ||
-                    (st = ensure(c, t->r[b], ncap * 8, "ray pool")) || (st = ensure(c, t->P[b], ncap * 8, "ray pool")) ||
-                    (st = ensure(c, t->lev[b], ncap * 4, "ray pool")))) ||
-        (st = ensure(c, t->qpix[i], ncap * 8, "ray queue")) || (st = ensure(c, t->qsg[i], ncap * 4, "ray queue")) ||
-        (st = ensure(c, t->qr[i], ncap * 8, "ray queue")) || (st = ensure(c, t->qP[i], ncap * 8, "ray queue"))) {
+    if ((i == b &&
+         ((st = ensure(c, t->pix[b], ncap * 8, "ray pool")) || (st = ensure(c, t->tree[b], ncap * 4, "ray pool")) ||
+          (st = ensure(c, t->r[b], ncap * 8, "ray pool")) || (st = ensure(c, t->P[b], ncap * 8 * t->planes, "ray pool")) ||
+          (st = ensure(c, t->lev[b], ncap * 4, "ray pool")))) ||
+        (st = ensure(c, t->qpix[i], qslots * 8, "ray queue")) || (st = ensure(c, t->qtree[i], qslots * 4, "ray queue")) ||
+        (st = ensure(c, t->qr[i], qslots * 8, "ray queue")) ||
+        (st = ensure(c, t->qP[i], qslots * 8 * t->planes, "ray queue"))) {
       t->broken = true;
       return fail(c, MORAY_EQUEUE, "the ray pool overflowed and its doubled buffers could not be allocated");
     }
   }
-  t->sort_bytes = 0;
-  if (ncap < ((size_t)1 << 32)) {
-    t->sort_bytes = sort_tmp;
-    for (int i = 0; i < 2; ++i)
-      if ((st = ensure(c, t->keys[i], ncap * 8, "sort keys")) || (st = ensure(c, t->order[i], ncap * 4, "sort order"))) {
-        t->broken = true;
-        return st;
-      }
-    if ((st = ensure(c, t->sort_temp, std::max<size_t>(sort_tmp, 256), "sort scratch"))) {
+  t->sort_bytes = sort_tmp;
+  for (int i = 0; i < 2; ++i)
+    if ((st = ensure(c, t->keys[i], ncap * 8, "sort keys")) || (st = ensure(c, t->order[i], ncap * 4, "sort order"))) {
       t->broken = true;
       return st;
     }
+  if ((st = ensure(c, t->sort_temp, std::max<size_t>(sort_tmp, 256), "sort scratch"))) {
+    t->broken = true;
+    return st;
   }
-  t->cap = ncap;
-  t->nseg = queue_segments(ncap);
-  t->seg_cap = ncap / (size_t)t->nseg;
   return MORAY_OK;
 }
 
@@ -320,11 +338,11 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   if (engine_busy(c)) return fail(c, MORAY_EBUSY, "the context is serving asynchronous solves");
   if (!hip_ok(c, hipSetDevice(c->device), "hipSetDevice")) return MORAY_EDEVICE;
   const moray_problem& P = *prob;
-  const moray_grid& G = P.grids[0];
   const moray_spectrum& Sp = *P.spectrum;
   const long long n_cells = t->n_cells;
   const int per = t->n_src * t->n_grp;
-  const int n_sg = t->slots * per;
+  const int trees_per = t->n_src * t->n_pack;      // of one batch
+  const int n_trees = t->slots * trees_per;
   const int cur_slot = (int)(t->step % t->slots);
   const double npix0 = std::ldexp(12.0, 2 * P.params.level_init);
   // what this step changes in the state before it has run (restored when it fails)
@@ -376,30 +394,24 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   pd.cell_off = 0;
   pd.n_cells = n_cells;
   pd.acc_off = 0;
+  pd.acc_mode = t->n_grp > 1 ? kAccMoments : kAccSums;
+  pd.acc_stride = t->n_grp > 1 ? 2 : 1;
   pd.eexc_off = 0;
   std::vector<double> eexc(t->n_grp);
   for (int g = 0; g < t->n_grp; ++g) eexc[g] = (Sp.energy_ev[g] - Sp.e_ion_ev) * kEvErgConst;
-  std::vector<SgDev> sgs(n_sg);
+  std::vector<TreeDev> trees(n_trees);
   for (int b = 0; b < t->slots; ++b)
     for (int s = 0; s < t->n_src; ++s)
-      for (int g = 0; g < t->n_grp; ++g) {
-        SgDev& d = sgs[(size_t)b * per + s * t->n_grp + g];
-        const moray_source& S = P.sources[s];
-        d.sx = S.x; d.sy = S.y; d.sz = S.z;
-        d.P0 = t->P0[(size_t)b * per + s * t->n_grp + g];
-        d.pmin0 = P.params.p_min_frac * d.P0;
-        d.sigma64 = Sp.sigma_cm2[g];
-        d.sigma32 = (float)Sp.sigma_cm2[g];
-        d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
-        d.split_t2_base = P.params.phi_c > 0.0 ? (float)(12.0 / (4.0 * kPiConst * P.params.phi_c)) : FLT_MAX;
-        d.acc_slot = (long long)g * n_cells;
-        d.problem = 0;
-        d.root_grid = 0;
-        d.rnx = G.nx; d.rny = G.ny; d.rnz = G.nz;
-        d.rcell_off = 0;
-        d.level_init = P.params.level_init;
-        d.gen0 = P.params.level_init;
-        d.level_max = P.params.phi_c > 0.0 ? P.params.level_max : P.params.level_init;
+      for (int k = 0; k < t->n_pack; ++k) {
+        TreeDev& d = trees[(size_t)b * trees_per + s * t->n_pack + k];
+        const int g0 = pack_first(t->n_grp, k), g1 = pack_first(t->n_grp, k + 1);
+        fill_tree(d, P, s, g0, g1 - g0, pd, gds[0]);
+        for (int g = g0; g < g1; ++g) {
+          // the rates of the batch's own emission
+          d.P0[g - g0] = t->P0[(size_t)b * per + s * t->n_grp + g];
+          d.pmin0[g - g0] = P.params.p_min_frac * d.P0[g - g0];
+        }
+        d.stat0 = (uint32_t)(s * t->n_grp + g0);      // every batch's rays under their source and group
         const long long age = t->emit_step[b] >= 0 ? t->step - t->emit_step[b] : -1;
         d.r_halt = age >= 0 ? (double)(age + 1) * t->c_dt : 0.0;
       }
@@ -407,29 +419,26 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   auto up = [&](DevBuf& b, const void* src, size_t bytes) {
     return hip_ok(c, hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, s), "upload");
   };
-  if (!up(t->grids, gds.data(), gds.size() * sizeof(GridDev)) || !up(t->probs, &pd, sizeof pd) || !up(t->sgs, sgs.data(), sgs.size() * sizeof(SgDev)) ||
+  if (!up(t->grids, gds.data(), gds.size() * sizeof(GridDev)) || !up(t->probs, &pd, sizeof pd) || !up(t->trees, trees.data(), trees.size() * sizeof(TreeDev)) ||
       !up(t->eexc, eexc.data(), eexc.size() * 8))
     return MORAY_EDEVICE;
 
   // levels: the seeds' and those of the rays in flight, up to the deepest a ray can reach
-  const int l_hi = reach_level(P);
+  int l_hi = reach_level(P);
+  for (int l = l_hi + 1; l < kLevels; ++l)
+    if (t->lev_in[l]) l_hi = l;            // rays in flight from a step with a larger phi_c
   int l_lo = emit ? P.params.level_init : kLevels;
   for (int l = 0; l < kLevels; ++l)
     if (t->lev_in[l]) { l_lo = std::min(l_lo, l); break; }
   unsigned max_steps = (unsigned)std::min<long long>(2 * steps_bound, 1LL << 30);
   const double waves = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave);
   unsigned long long reserve =
-      (unsigned long long)std::min<double>((double)kReserveMax, (double)t->cap / (8.0 * waves));
-  reserve = std::max<unsigned long long>(4, reserve & ~3ull);
+      (unsigned long long)std::min<double>((double)kReserveMax, (double)t->cap / (32.0 * waves));
+  reserve = std::max<unsigned long long>(1, reserve);
   Counters* ctr = (Counters*)t->ctr.p;
   const bool fp32 = c->precision == MORAY_FP32_ACC64;
   const int a = t->cur;
-  const RayQueue pool_in{(uint64_t*)t->pix[a].p, (uint32_t*)t->sg[a].p, (double*)t->r[a].p, (double*)t->P[a].p};
-  auto queue = [&](int l) {
-    return RayQueue{(uint64_t*)t->qpix[l & 1].p, (uint32_t*)t->qsg[l & 1].p, (double*)t->qr[l & 1].p,
-                    (double*)t->qP[l & 1].p};
-  };
-  hipError_t e = launch_reset(s, ctr, (SgStats*)t->stats.p, n_sg);
+  hipError_t e = launch_reset(s, ctr, (SgStats*)t->stats.p, per);
   if (e == hipSuccess)
     e = fp32 ? launch_prep<float>(s, c->num_cu, (GridDev*)t->grids.p, P.n_grids, 0, (ProblemDev*)t->probs.p, 0, n_cells,
                                   (float*)t->kappa.p, (double*)t->acc.p, ctr)
@@ -437,40 +446,28 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
                                    (double*)t->kappa.p, (double*)t->acc.p, ctr);
   if (!hip_ok(c, e, "prep")) return MORAY_EDEVICE;
   int launches = 0;
-  // the rays in flight sorted by (level, tree, pixel) when the key fits 64 bits
+  // the rays in flight sorted by (level, tree, pixel), the pixel's low bits dropped where the key would exceed 64 bits
   int tree_bits = 1;
-  while (tree_bits < 31 && ((long long)1 << tree_bits) < n_sg) ++tree_bits;
-  const int pix_bits = 2 * l_hi + 4;
-  const bool sorted = t->n_in > 0 && t->keys[0].p && 5 + tree_bits + pix_bits <= 64;
+  while (tree_bits < 31 && ((long long)1 << tree_bits) < n_trees) ++tree_bits;
+  const int pix_all = 2 * l_hi + 4;
+  const int pix_bits = std::min(pix_all, 64 - 5 - tree_bits), pix_drop = pix_all - pix_bits;
   unsigned long long first[kLevels] = {};
-  if (sorted) {
+  if (t->n_in > 0) {
     unsigned long long o = 0;
     for (int l = 0; l < kLevels; ++l) { first[l] = o; o += t->lev_in[l]; }
-    if (!hip_ok(c, launch_td_sort(s, c->num_cu, pool_in, (const int*)t->lev[a].p, t->n_in, tree_bits, pix_bits,
-                                  (unsigned long long*)t->keys[0].p, (unsigned long long*)t->keys[1].p,
+    if (!hip_ok(c, launch_td_sort(s, c->num_cu, pool_of(t, a), (const int*)t->lev[a].p, t->n_in, tree_bits, pix_bits,
+                                  pix_drop, (unsigned long long*)t->keys[0].p, (unsigned long long*)t->keys[1].p,
                                   (uint32_t*)t->order[0].p, (uint32_t*)t->order[1].p, t->sort_temp.p, t->sort_bytes),
                 "sort"))
       return MORAY_EDEVICE;
   }
-  auto prefill = [&](int l) {
-    if (sorted)
-      return launch_prefill_sorted(s, c->num_cu, pool_in, (const uint32_t*)t->order[1].p, first[l], t->lev_in[l],
-                                   queue(l), t->seg_cap, t->nseg, ctr, l);
-    return launch_prefill_level(s, c->num_cu, pool_in, (const int*)t->lev[a].p, t->n_in, l, queue(l), t->seg_cap,
-                                t->nseg, ctr, l);
-  };
-  if (l_lo <= l_hi) {
-    if (t->lev_in[l_lo] && !hip_ok(c, prefill(l_lo), "prefill")) return MORAY_EDEVICE;
-    for (int l = l_lo; l <= l_hi; ++l) {
-      if (l + 1 <= l_hi && l + 1 < kLevels && t->lev_in[l + 1] && !hip_ok(c, prefill(l + 1), "prefill"))
-        return MORAY_EDEVICE;
-      const bool seeds = emit && l == P.params.level_init;
-      const int lo = seeds ? cur_slot * per : 0, hi = seeds ? (cur_slot + 1) * per : 0;
-      e = fp32 ? launch_level<float>(c, t, l, lo, hi, max_steps, reserve)
-               : launch_level<double>(c, t, l, lo, hi, max_steps, reserve);
-      if (!hip_ok(c, e, "trace")) return MORAY_EDEVICE;
-      ++launches;
-    }
+  for (int l = l_lo; l <= l_hi; ++l) {
+    const bool seeds = emit && l == P.params.level_init;
+    const int lo = seeds ? cur_slot * trees_per : 0, hi = seeds ? (cur_slot + 1) * trees_per : 0;
+    e = fp32 ? launch_level<float>(c, t, l, lo, hi, first[l], t->lev_in[l], max_steps, reserve)
+             : launch_level<double>(c, t, l, lo, hi, first[l], t->lev_in[l], max_steps, reserve);
+    if (!hip_ok(c, e, "trace")) return MORAY_EDEVICE;
+    ++launches;
   }
   if (!hip_ok(c, launch_finalize(s, (int)t->fb.size(), (GridDev*)t->grids.p, (ProblemDev*)t->probs.p,
                                  (FinalBlock*)t->fblocks.p, (double*)t->acc.p, (double*)t->eexc.p,
@@ -479,9 +476,9 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   char* hs = (char*)t->h_stage;
   Counters* hctr = (Counters*)hs;
   SgStats* hst = (SgStats*)(hs + sizeof(Counters));
-  double* hpart = (double*)(hs + sizeof(Counters) + (size_t)n_sg * sizeof(SgStats));
+  double* hpart = (double*)(hs + sizeof(Counters) + (size_t)per * sizeof(SgStats));
   if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
-      !hip_ok(c, hipMemcpyAsync(hst, t->stats.p, (size_t)n_sg * sizeof(SgStats), hipMemcpyDeviceToHost, s), "copy") ||
+      !hip_ok(c, hipMemcpyAsync(hst, t->stats.p, (size_t)per * sizeof(SgStats), hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipMemcpyAsync(hpart, t->partial.p, t->fb.size() * 8, hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipStreamSynchronize(s), "synchronize"))
     return MORAY_EDEVICE;
@@ -494,12 +491,12 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
     return fail(c, MORAY_EINTERNAL, "a ray exceeded its step bound");
   }
   if (hctr->err & kErrOverflow) {
-    // what the step asked for: the halt list's records and the largest level queue's slots
+    // what the step asked for: the halt list's records and the largest level queue's rays
     unsigned long long demand = hctr->halt_count;
     for (int l = 0; l < kLevels; ++l) {
       unsigned long long n = 0;
       for (int sgi = 0; sgi < t->nseg; ++sgi) n += hctr->count[l][sgi];
-      demand = std::max(demand, n);
+      demand = std::max(demand, 4 * n);
     }
     const moray_status gs = attempt < 8 ? td_grow(c, t, demand)
                                         : fail(c, MORAY_EQUEUE, "the ray pool or a level queue overflowed eight times");
@@ -523,18 +520,17 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   const unsigned long long n_held = std::min<unsigned long long>(hctr->halt_count, t->cap);
   if (n_held) {
     const int nb = (int)std::min<size_t>(t->fb.size(), 1024);
-    if (!hip_ok(c, launch_sum_blocks(s, nb, (const double*)t->P[1 - t->cur].p, n_held, (double*)t->partial.p),
+    if (!hip_ok(c, launch_sum_blocks(s, nb, (const double*)t->P[1 - t->cur].p, n_held, t->planes, t->cap,
+                                     (double*)t->partial.p),
                 "sum") ||
         !hip_ok(c, hipMemcpyAsync(hpart, t->partial.p, (size_t)nb * 8, hipMemcpyDeviceToHost, s), "copy") ||
         !hip_ok(c, hipStreamSynchronize(s), "synchronize"))
       return MORAY_EDEVICE;
     for (int b = 0; b < nb; ++b) h += hpart[b];
   }
-  if (Rr.escaped_sg)
-    for (int k = 0; k < per; ++k) Rr.escaped_sg[k] = 0.0;
-  for (int k = 0; k < n_sg; ++k) {
+  for (int k = 0; k < per; ++k) {
     const SgStats& S = hst[k];
-    if (Rr.escaped_sg) Rr.escaped_sg[k % per] += S.esc_P;
+    if (Rr.escaped_sg) Rr.escaped_sg[k] = S.esc_P;
     Rr.escaped += S.esc_P;
     Rr.truncated += S.trunc_P;
     Rr.segments += S.segs;
@@ -547,7 +543,7 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   for (int l = 0; l < kLevels; ++l) {
     unsigned long long n = 0;
     for (int sgi = 0; sgi < t->nseg; ++sgi) n += std::min<unsigned long long>(hctr->count[l][sgi], t->seg_cap);
-    peak = std::max(peak, n);
+    peak = std::max(peak, 4 * n);
   }
   Rr.peak_level_rays = peak;
   Rr.trace_ms = 0.0;

@@ -4,7 +4,8 @@
 // 64 unrelated rays whose deposits seldom fall in the same cells. Sorting the
 // halt list by (level, tree, pixel) before the next step puts every level's
 // rays in one contiguous run, in which neighbouring records are neighbouring
-// pixels of one tree, as in the single pass's queues.
+// pixels of one tree, as in the single pass's queues. Each level's launch
+// reads its run through the sorted order.
 #include "moray_device.h"
 #include "moray_internal.h"
 
@@ -13,56 +14,17 @@
 
 namespace moray {
 
-__device__ __forceinline__ unsigned long long lane0_u64(unsigned long long v) {
-  const unsigned lo = __shfl((unsigned)v, 0), hi = __shfl((unsigned)(v >> 32), 0);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
-// key = level << (tree_bits + pix_bits) | tree << pix_bits | pixel; value = record index
-__global__ __launch_bounds__(256) void td_keys_kernel(const uint32_t* __restrict__ sg,
+// key = level << (tree_bits + pix_bits) | tree << pix_bits | pixel >> pix_drop; value = record index
+__global__ __launch_bounds__(256) void td_keys_kernel(const uint32_t* __restrict__ tree,
                                                       const uint64_t* __restrict__ pix,
                                                       const int* __restrict__ lev, unsigned long long n,
-                                                      int tree_bits, int pix_bits,
+                                                      int tree_bits, int pix_bits, int pix_drop,
                                                       unsigned long long* __restrict__ keys,
                                                       uint32_t* __restrict__ idx) {
   for (unsigned long long i = blockIdx.x * 256ull + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * 256ull) {
-    keys[i] = ((unsigned long long)lev[i] << (tree_bits + pix_bits)) | ((unsigned long long)sg[i] << pix_bits) |
-              pix[i];
+    keys[i] = ((unsigned long long)lev[i] << (tree_bits + pix_bits)) | ((unsigned long long)tree[i] << pix_bits) |
+              (pix[i] >> pix_drop);
     idx[i] = (uint32_t)i;
-  }
-}
-
-// Records [first, first + count) of the sorted order join level queue q
-// (counter row `row`): each 64 consecutive records go, with one atomic, to
-// the end of one of the nseg segments (a power of two).
-__global__ __launch_bounds__(256) void prefill_sorted_kernel(RayQueue pool, const uint32_t* __restrict__ order,
-                                                             unsigned long long first, unsigned long long count,
-                                                             RayQueue q, unsigned long long seg_cap, int nseg,
-                                                             Counters* ctr, int row) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const unsigned long long waves = (unsigned long long)gridDim.x * (blockDim.x / kWave);
-  const unsigned long long wave = blockIdx.x * (unsigned long long)(blockDim.x / kWave) + threadIdx.x / kWave;
-  for (unsigned long long w = wave; w * kWave < count; w += waves) {
-    const unsigned long long j = w * kWave + lane;
-    const unsigned long long live = count - w * kWave;
-    const int take = live < (unsigned long long)kWave ? (int)live : kWave;
-    const int seg = (int)(w & (unsigned long long)(nseg - 1));
-    unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(&ctr->count[row][seg], (unsigned long long)take);
-    base = lane0_u64(base);
-    if (lane < take) {
-      const unsigned long long pos = base + (unsigned long long)lane;
-      if (pos < seg_cap) {
-        const uint32_t i = order[first + j];
-        const unsigned long long o = (unsigned long long)seg * seg_cap + pos;
-        q.pix[o] = pool.pix[i];
-        q.sg[o] = pool.sg[i];
-        q.r[o] = pool.r[i];
-        q.P[o] = pool.P[i];
-      } else {
-        atomicOr(&ctr->err, kErrOverflow);
-      }
-    }
   }
 }
 
@@ -73,7 +35,7 @@ hipError_t td_sort_temp_bytes(unsigned long long cap, size_t* bytes) {
 }
 
 hipError_t launch_td_sort(hipStream_t s, int num_cu, const RayQueue& pool, const int* lev, unsigned long long n,
-                          int tree_bits, int pix_bits, unsigned long long* keys_in, unsigned long long* keys_out,
+                          int tree_bits, int pix_bits, int pix_drop, unsigned long long* keys_in, unsigned long long* keys_out,
                           uint32_t* idx_in, uint32_t* idx_out, void* temp, size_t temp_bytes) {
   if (n == 0) return hipSuccess;
   const int end_bit = 5 + tree_bits + pix_bits;
@@ -85,24 +47,13 @@ hipError_t launch_td_sort(hipStream_t s, int num_cu, const RayQueue& pool, const
   if (need > temp_bytes) return hipErrorInvalidValue;
   unsigned long long blocks = (n + 255) / 256;
   if (blocks > 16ull * (unsigned long long)num_cu) blocks = 16ull * (unsigned long long)num_cu;
-  hipLaunchKernelGGL(td_keys_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pool.sg, pool.pix, lev, n, tree_bits,
-                     pix_bits, keys_in, idx_in);
+  hipLaunchKernelGGL(td_keys_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pool.tree, pool.pix, lev, n, tree_bits,
+                     pix_bits, pix_drop, keys_in, idx_in);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   size_t tb = temp_bytes;
   return rocprim::radix_sort_pairs(temp, tb, (const unsigned long long*)keys_in, keys_out, (const uint32_t*)idx_in,
                                    idx_out, n, 0u, (unsigned)end_bit, s);
-}
-
-hipError_t launch_prefill_sorted(hipStream_t s, int num_cu, const RayQueue& pool, const uint32_t* order,
-                                 unsigned long long first, unsigned long long count, const RayQueue& q,
-                                 unsigned long long seg_cap, int nseg, Counters* ctr, int row) {
-  if (count == 0) return hipSuccess;
-  unsigned long long blocks = (count + 255) / 256;
-  if (blocks > 16ull * (unsigned long long)num_cu) blocks = 16ull * (unsigned long long)num_cu;
-  hipLaunchKernelGGL(prefill_sorted_kernel, dim3((unsigned)blocks), dim3(256), 0, s, pool, order, first, count, q,
-                     seg_cap, nseg, ctr, row);
-  return hipGetLastError();
 }
 
 }  // namespace moray
