@@ -85,9 +85,9 @@ struct TreeDev {
   double pmin0[kPack];     // p_min_frac * P0 (quartered per level below the seeds)
   double sigma64[kPack];   // cross-section, cm^2
   double eexc[kPack];      // E - E_ion, erg (0 where the problem's records have no second moment)
-  float sigma32[kPack];
   long long acc_slot;      // accumulator of cell c (batch numbering) is acc[acc_slot + acc_stride * c]
-  float split_t2_base;     // 12 / (4 pi phi_c), float; FLT_MAX when the problem never splits
+  double split_r;          // sqrt(12 / (4 pi phi_c)): a ray of level l splits beyond 2^l times this many
+                           // local cells; infinite when the problem never splits
   int level_init;
   int level_max;
   int gen0;                // launch generation of the tree's seed rays: a ray of generation g is at
@@ -107,7 +107,7 @@ struct TreeDev {
   // optically-thin approximation (tau_thin > 0; one group per tree)
   double tau_thin = 0.0;   // a ray is thin in a cell while its optical depth on leaving it is below this
   double four_pi_phi_thin; // 4 pi min(1, phi_c): the split threshold of thin rays
-  float split_t2_thin;     // 12 / (4 pi min(1, phi_c)), float; FLT_MAX when the problem never splits
+  double split_r_thin;     // split_r for min(1, phi_c)
   long long mark_base;     // its mark on cell c (batch numbering) is the byte mark[mark_base + c]
   double thin_coef;        // sigma Ndot_g / (4 pi dx_root^2): the thin rate at r root cells is thin_coef / r^2
 };
@@ -162,7 +162,6 @@ struct TraceArgs {
   const TreeDev* trees;
   const R* kappa;          // n_H x_HI dx_root per leaf cell; -(child+1) on covered root cells
   double* acc;             // accumulators (see ProblemDev)
-  uint32_t rec_base;       // deposit keys >= rec_base start 4-sum radiation-pressure records (32-byte aligned)
   RayQueue in, out;                    // nseg segments of seg_cap slots each
   unsigned long long seg_cap;
   int nseg;                            // segments per level queue: a power of two

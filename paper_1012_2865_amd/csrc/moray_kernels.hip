@@ -155,161 +155,172 @@ template <typename T> __device__ __forceinline__ T sel3(int k, T a, T b, T c) { 
 // issued since; those paths therefore finish their own loads before rejoining.
 __device__ __forceinline__ void finish_vector_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) alone
 
-// ---------------------------------------------------------------------------
-// Geometry, float64: the definition's expressions (true division, no
-// contraction), so every decision equals the reference's.
-// ---------------------------------------------------------------------------
-struct Geom64 {
-  double d0, d1, d2;       // direction
-  double s0, s1, s2;       // source in local cells
-  double t0, t1, t2;       // distance to the next plane per axis, root cells
-  double r;                // radius, root cells
-  double hinv, hloc;
+// PHYS selects the optional physics some tree of the launch asks for:
+// kPhysCover scales deposits by the covering factor (section 2.3), kPhysRadp
+// adds the absorbed momentum E_ph dP / c n to three more sums per cell
+// (radiation pressure, section 2.5.4), kPhysHalt halts every ray at its
+// tree's radius r_halt (time-dependent rays, section 2.1 and section 3.1
+// step 3j): the segment in that cell ends there and the ray, with the
+// photons it still carries, goes to the halt list for the next step.
+// kPhysThin applies the optically-thin approximation (section 2.4, Eq.
+// optthin): a ray whose optical depth from its source stays below tau_thin
+// through a cell removes no photons there, is split against min(1, phi_c)
+// rays per cell face, and sets its tree's mark on the cell (a byte; the rate
+// sigma P / (Omega_ray r_cell^2) is the same for every thin ray of a tree,
+// so finalize adds it once per marked tree); in a cell that holds the source
+// it adds its general deposit to the cell's second sum instead.
+// PHYS = 0 is the plain trace.
+constexpr int kPhysCover = 1, kPhysRadp = 2, kPhysHalt = 4, kPhysThin = 8;
 
-  __device__ void set_dir(const double v[3]) { d0 = v[0]; d1 = v[1]; d2 = v[2]; }
-  __device__ double dir64(int k) const { return sel3(k, d0, d1, d2); }
-  __device__ double src64(int k) const { return sel3(k, s0, s1, s2); }
-  __device__ float dirf(int k) const { return (float)sel3(k, d0, d1, d2); }
-  __device__ void set_radius(double r64) { r = r64; }
-  __device__ double radius64() const { return r; }
-  __device__ double plane(double d, double s, int c) const {
-    if (d == 0.0) return __builtin_huge_val();
-    return (((double)(c + (d > 0.0 ? 1 : 0)) - s) / d) * hinv;
-  }
-  __device__ void set_frame(const double sl[3], int c0, int c1, int c2, bool child) {
-    s0 = sl[0]; s1 = sl[1]; s2 = sl[2];
-    hinv = child ? 0.5 : 1.0;
-    hloc = child ? 2.0 : 1.0;
-    t0 = plane(d0, s0, c0); t1 = plane(d1, s1, c1); t2 = plane(d2, s2, c2);
-  }
-  __device__ int exit_axis() const {
-    int ax = 0;
-    double b = t0;
-    if (t1 < b) { ax = 1; b = t1; }
-    if (t2 < b) ax = 2;
-    return ax;
-  }
-  __device__ double te(int ax) const { return sel3(ax, t0, t1, t2); }
-  __device__ double exit64(int ax) const { return te(ax); }
-  __device__ double chord(int ax) const { return te(ax) - r; }
-  __device__ bool positive(double dr, int) const { return dr > 0.0; }
-  __device__ void advance(int ax) { r = te(ax); }
-  __device__ double local_u(int ax) const { return te(ax) * hloc; }
-  __device__ void step(int ax, int cnew) {
-    const double d = sel3(ax, d0, d1, d2), s = sel3(ax, s0, s1, s2);
-    const double t = (((double)(cnew + (d > 0.0 ? 1 : 0)) - s) / d) * hinv;   // d != 0 on the exit axis
-    t0 = ax == 0 ? t : t0;
-    t1 = ax == 1 ? t : t1;
-    t2 = ax == 2 ? t : t2;
-  }
+// ---------------------------------------------------------------------------
+// Geometry. Per axis a ray holds the distance t to the next cell plane (root
+// cells); the nearest is the exit of the current cell, and stepping across it
+// moves that axis to its next plane. The radius and every t are float64 in both
+// precision modes: float64 vector adds, multiplies and fmas issue at the float32
+// rate here, and one 64-bit value takes the place of a float pair and its
+// error terms.
+//
+// An axis without a direction component never sets the exit: its t is kFar.
+// ---------------------------------------------------------------------------
+constexpr double kFar = 1e300;
+
+// v_min_f64 alone (fmin would first quiet its operands, which are never NaN here)
+__device__ __forceinline__ double min_f64(double x, double y) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
+// x where m, else 0, for an x whose low word is 0 (one select)
+__device__ __forceinline__ double masked_hi(bool m, int hi) { return __hiloint2double(m ? hi : 0, 0); }
+
+// The current cell's exit: distance, and which axis (neither flag: x). Ties go
+// to the lowest axis.
+struct Exit {
+  double t;
+  bool y, z;
+  __device__ int axis() const { return z ? 2 : (y ? 1 : 0); }
+  template <typename T> __device__ T pick(T a, T b, T c) const { return z ? c : (y ? b : a); }
 };
 
-// ---------------------------------------------------------------------------
-// Geometry, float32: every plane distance is a pair hi + lo of floats.
-// The source coordinate is split into a 2^-12-lattice part q (so b - q is
-// exact) and a residual e, |e| <= 2^-13; the reciprocal of the float64
-// direction into i + j. Then t = (b - q - e)(i + j) = hi + lo, hi = (b-q) i
-// rounded, lo = its exact fma residual + (b-q) j - e i. A pair is within
-// about 2^-36 / |d| cells of the float64 distance (e rounded to float and the
-// dropped e j), so chords, which are differences of pairs, place every
-// segment where float64 would up to that: a plane tie closer than that is a
-// segment of that length in either of two cells. hi alone is not the
-// distance: near the source e i is comparable to it.
-// ---------------------------------------------------------------------------
-// The float path keeps each lane's float64 direction in LDS rather than in
-// registers: it is read only by the rare exact paths (a split test within
-// rounding of its threshold, entering or starting in a child grid), and
-// recomputing it from the pixel there would set the kernel's register peak.
-__device__ __forceinline__ double* lane_dir() {
-  __shared__ double sdir[3][kTraceBlock];
-  return &sdir[0][threadIdx.x];
-}
-
-struct Geom32 {
-  float d0, d1, d2;
-  float i0, i1, i2, j0, j1, j2;      // 1/d = i + j
-  float q0, q1, q2, e0, e1, e2;      // local source = q + e
-  float h0, h1, h2, l0, l1, l2;      // plane distance = h + l (root cells)
-  float rh, rl;                      // radius = rh + rl
-  float hinv, hloc;
+// Float64 mode: the definition's expressions, t = ((b - s) / d) / h for the
+// plane coordinate b, so every decision equals the reference's. The quotient is
+// rounded correctly without a division: with y = 1/d rounded and q = (b - s) y,
+// q + (b - s - q d) y is the rounded quotient (Markstein 1990).
+struct Geom64 {
+  double d[3], inv[3];     // direction and its reciprocal
+  double s[3];             // source in local cells
+  double b[3];             // coordinate of the next plane
+  double t[3];             // distance to it
+  double r;                // radius
+  double hinv;             // root cells per local cell
+  int sgn[3];              // high word of the float64 +1 or -1 that moves b
 
   __device__ void set_dir(const double v[3]) {
-    d0 = (float)v[0]; d1 = (float)v[1]; d2 = (float)v[2];
-    split_inv(v[0], i0, j0); split_inv(v[1], i1, j1); split_inv(v[2], i2, j2);
-    double* vd = lane_dir();
-    vd[0] = v[0]; vd[kTraceBlock] = v[1]; vd[2 * kTraceBlock] = v[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      d[k] = v[k];
+      inv[k] = v[k] == 0.0 ? kFar : 1.0 / v[k];
+      sgn[k] = v[k] > 0.0 ? 0x3ff00000 : (int)0xbff00000;
+    }
   }
-  static __device__ void split_inv(double d, float& i, float& j) {
-    if (d == 0.0) { i = 0.0f; j = 0.0f; return; }
-    const double inv = 1.0 / d;
-    i = (float)inv;
-    j = (float)(inv - (double)i);
+  __device__ bool up(int k) const { return d[k] > 0.0; }
+  __device__ double quotient(int k, double bk) const {
+    const double a = bk - s[k], q = a * inv[k];
+    const double e = fma(-q, d[k], a);
+    return fma(e, inv[k], q) * hinv;
   }
-  __device__ double dir64(int k) const { return lane_dir()[k * kTraceBlock]; }
-  __device__ double src64(int k) const { return (double)sel3(k, q0, q1, q2) + (double)sel3(k, e0, e1, e2); }
-  __device__ float dirf(int k) const { return sel3(k, d0, d1, d2); }
-  __device__ void set_radius(double r64) { rh = (float)r64; rl = (float)(r64 - (double)rh); }
-  __device__ double radius64() const { return (double)rh + (double)rl; }
-  __device__ void plane(float d, float i, float j, float q, float e, int c, float& h, float& l) const {
-    if (d == 0.0f) { h = __builtin_huge_valf(); l = 0.0f; return; }
-    const float bs = (float)(c + (d > 0.0f ? 1 : 0)) - q;     // exact
-    const float th = bs * i;
-    float tl = fmaf(bs, i, -th);
-    tl = fmaf(bs, j, tl);
-    tl = fmaf(-e, i, tl);
-    h = th * hinv;
-    l = tl * hinv;
+  __device__ void frame(const double sl[3], const int c[3], const int n[3], bool child, double& tbox) {
+    hinv = child ? 0.5 : 1.0;
+    tbox = __builtin_huge_val();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      s[k] = sl[k];
+      const bool none = d[k] == 0.0;
+      if (none) sgn[k] = 0;                        // its plane does not move
+      b[k] = (double)(c[k] + (d[k] > 0.0 || none ? 1 : 0));
+      t[k] = none ? kFar : quotient(k, b[k]);
+      const double face = none ? kFar : quotient(k, d[k] > 0.0 ? (double)n[k] : 0.0);
+      tbox = face < tbox ? face : tbox;
+    }
   }
-  static __device__ void split_src(double s, float& q, float& e) {
-    const double qd = rint(s * 4096.0) * (1.0 / 4096.0);
-    q = (float)qd;
-    e = (float)(s - (double)q);
+  __device__ Exit exit() const {
+    Exit e;
+    const double m = min_f64(t[0], t[1]);
+    e.y = t[1] < t[0];
+    e.t = min_f64(m, t[2]);
+    e.z = t[2] < m;
+    return e;
   }
-  __device__ void set_frame(const double sl[3], int c0, int c1, int c2, bool child) {
-    split_src(sl[0], q0, e0); split_src(sl[1], q1, e1); split_src(sl[2], q2, e2);
-    hinv = child ? 0.5f : 1.0f;
-    hloc = child ? 2.0f : 1.0f;
-    plane(d0, i0, j0, q0, e0, c0, h0, l0);
-    plane(d1, i1, j1, q1, e1, c1, h1, l1);
-    plane(d2, i2, j2, q2, e2, c2, h2, l2);
+  __device__ void step(const Exit& e) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      b[k] += masked_hi(k == 2 ? e.z : (k == 1 ? e.y && !e.z : !e.y && !e.z), sgn[k]);
+      t[k] = quotient(k, b[k]);                    // (b - s) kFar and more without a component: far
+    }
   }
-  // (ah + al) < (bh + bl), exact enough to order distinct planes
-  static __device__ bool lt(float ah, float al, float bh, float bl) { return ((ah - bh) + (al - bl)) < 0.0f; }
-  __device__ int exit_axis() const {
-    int ax = 0;
-    float bh = h0, bl = l0;
-    if (lt(h1, l1, bh, bl)) { ax = 1; bh = h1; bl = l1; }
-    if (lt(h2, l2, bh, bl)) ax = 2;
-    return ax;
+  // a segment counts when it is longer than 0
+  static __device__ bool positive(double dr, double) { return dr > 0.0; }
+  __device__ double hloc() const { return 1.0 / hinv; }
+  // coordinate of the current cell's centre (local cells), and the source's
+  __device__ double centre(int k) const { return d[k] == 0.0 ? b[k] - 0.5 : (d[k] > 0.0 ? b[k] - 0.5 : b[k] + 0.5); }
+};
+
+// Mixed mode: the planes of an axis are equally spaced, so a step adds the
+// spacing e = 1/|d| to that axis' t: one select and one fma per axis, against the
+// plane coordinate, its difference from the source, the product and its error
+// terms. A t that has been stepped N times is off by at most N/2 of its ulps;
+// kResync steps, after which t is formed afresh, keep that below 2^-42 of t.
+// Segments shorter than 2^-40 of their exit radius are plane ties (dr = 0 in
+// exact arithmetic, or a length no float64 coordinate resolves) and are not
+// counted.
+constexpr int kResync = 2048;
+struct Geom32 {
+  double t[3], e[3];       // distance to the next plane, spacing (0: no component along the axis)
+  double r;
+  double hinv;
+  unsigned neg;            // bit k: the direction's component k is negative
+
+  __device__ void set_dir(const double v[3]) {
+    neg = 0u;
+    hinv = 1.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      e[k] = v[k] == 0.0 ? 0.0 : 1.0 / fabs(v[k]);
+      if (v[k] < 0.0) neg |= 1u << k;
+    }
   }
-  __device__ float chord(int ax) const {
-    return (sel3(ax, h0, h1, h2) - rh) + (sel3(ax, l0, l1, l2) - rl);
+  __device__ bool up(int k) const { return e[k] != 0.0 && !((neg >> k) & 1u); }
+  __device__ void frame(const double sl[3], const int c[3], const int n[3], bool child, double& tbox) {
+    hinv = child ? 0.5 : 1.0;
+    tbox = __builtin_huge_val();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      e[k] *= hinv;                                // set_dir precedes every frame
+      const bool up_k = up(k), none = e[k] == 0.0;
+      const double a = up_k ? (double)(c[k] + 1) - sl[k] : sl[k] - (double)c[k];
+      t[k] = none ? kFar : a * e[k];
+      const double face = none ? kFar : (up_k ? (double)n[k] - sl[k] : sl[k]) * e[k];
+      tbox = face < tbox ? face : tbox;
+    }
+    // a step within a plane tie of the box's face is taken as leaving, so the
+    // rounding of a stepped t never carries a ray past the face
+    tbox -= tbox * 0x1p-40;
   }
-  // a pair resolves distances to ~2^-46 t: anything below 2^-40 t is a plane tie (dr = 0 in float64)
-  __device__ bool positive(float dr, int ax) const { return dr > sel3(ax, h0, h1, h2) * 9.094947e-13f; }
-  __device__ void advance(int ax) { rh = sel3(ax, h0, h1, h2); rl = sel3(ax, l0, l1, l2); }
-  // The split test's distance takes both halves of the pair: the low half
-  // holds the source's off-lattice residual e (t = (b - q - e) / d), which
-  // near the source is not small against the high half.
-  __device__ float local_u(int ax) const { return (sel3(ax, h0, h1, h2) + sel3(ax, l0, l1, l2)) * hloc; }
-  __device__ double exit64(int ax) const { return (double)sel3(ax, h0, h1, h2) + (double)sel3(ax, l0, l1, l2); }
-  // The exit axis always has a nonzero direction component (an axis with
-  // none is at infinity), so its next plane needs no special case; selects
-  // instead of a branch per axis keep the wave converged.
-  __device__ void step(int ax, int cnew) {
-    const bool a0 = ax == 0, a1 = ax == 1, a2 = ax == 2;
-    const float d = sel3(ax, d0, d1, d2), i = sel3(ax, i0, i1, i2), j = sel3(ax, j0, j1, j2);
-    const float q = sel3(ax, q0, q1, q2), e = sel3(ax, e0, e1, e2);
-    const float bs = (float)(cnew + (d > 0.0f ? 1 : 0)) - q;  // exact
-    const float th = bs * i;
-    float tl = fmaf(bs, i, -th);
-    tl = fmaf(bs, j, tl);
-    tl = fmaf(-e, i, tl);
-    const float h = th * hinv, l = tl * hinv;
-    h0 = a0 ? h : h0; l0 = a0 ? l : l0;
-    h1 = a1 ? h : h1; l1 = a1 ? l : l1;
-    h2 = a2 ? h : h2; l2 = a2 ? l : l2;
+  __device__ Exit exit() const {
+    Exit x;
+    const double m = min_f64(t[0], t[1]);
+    x.y = t[1] < t[0];
+    x.t = min_f64(m, t[2]);
+    x.z = t[2] < m;
+    return x;
   }
+  __device__ void step(const Exit& x) {
+    t[0] = fma(masked_hi(!x.y && !x.z, 0x3ff00000), e[0], t[0]);
+    t[1] = fma(masked_hi(x.y && !x.z, 0x3ff00000), e[1], t[1]);
+    t[2] = fma(masked_hi(x.z, 0x3ff00000), e[2], t[2]);
+  }
+  static __device__ bool positive(double dr, double t) { return fma(t, -0x1p-40, dr) > 0.0; }
+  __device__ double hloc() const { return 1.0 / hinv; }
 };
 
 template <typename R> struct GeomOf;
@@ -317,85 +328,106 @@ template <> struct GeomOf<double> { using type = Geom64; };
 template <> struct GeomOf<float> { using type = Geom32; };
 
 // Photons removed in a segment of optical depth tau: dP = P (1 - e^-tau)
-// (Eq. flux), P -= dP. Float64 takes the definition literally. Float32 keeps
-// both parts accurate to its own precision: 1 - e^-tau as -expm1f for thin
-// segments, and for thick ones (tau > ln 2) the transmitted part P e^-tau
-// from expf, the absorbed part as the float64 difference, so dP + P_new = P
-// holds to float64 rounding either way.
+// (Eq. flux), P -= dP.
+//
+// Float64: 1 - e^-tau by Cody-Waite reduction x = -tau = k ln2 + r, |r| <= ln2/2,
+// and the Taylor series of expm1(r) to r^13 (the first omitted term is below
+// 1e-17 of r): e^x - 1 = 2^k expm1(r) + (2^k - 1), within 2 ulp.
 __device__ __forceinline__ double absorb(double& P, double tau) {
-  const double dP = P * -expm1(-tau);
+  const double x = -fmin(tau, 745.0);                       // e^-745 is the smallest float64
+  const double k = __builtin_rint(x * 1.4426950408889634);
+  // ln 2 in two parts, the first with 32 bits so k times it is exact
+  double r = fma(-k, 0.69314718036912381649, x);
+  r = fma(-k, 1.9082149292705877e-10, r);
+  double q = 1.0 / 6227020800.0;                            // 1/13!
+  q = fma(q, r, 1.0 / 479001600.0);
+  q = fma(q, r, 1.0 / 39916800.0);
+  q = fma(q, r, 1.0 / 3628800.0);
+  q = fma(q, r, 1.0 / 362880.0);
+  q = fma(q, r, 1.0 / 40320.0);
+  q = fma(q, r, 1.0 / 5040.0);
+  q = fma(q, r, 1.0 / 720.0);
+  q = fma(q, r, 1.0 / 120.0);
+  q = fma(q, r, 1.0 / 24.0);
+  q = fma(q, r, 1.0 / 6.0);
+  q = fma(q, r, 0.5);
+  q = fma(r * r, q, r);
+  const double p2 = ldexp(1.0, (int)k);
+  const double dP = -P * fma(p2, q, p2 - 1.0);
   P -= dP;
   return dP;
 }
-// One exponential core serves both: Cody-Waite reduction x = k ln2 + r with
-// |r| <= ln2/2 (ln 2 split so k ln2 is exact) and the Taylor series of
-// expm1(r) to r^7 (truncation below 2e-8 relative there). Then
-// e^x - 1 = 2^k expm1(r) + (2^k - 1) is accurate for thin segments (k is 0
-// or -1) and e^x = 2^k (1 + expm1(r)) for thick ones, without a branch.
-__device__ __forceinline__ double absorb(double& P, float tau) {
-  const float x = -tau;
-  const float k = rintf(x * 1.44269504f);
-  const float r = fmaf(-k, 1.42860677e-06f, fmaf(-k, 0.693145752f, x));
-  float q = fmaf(r, 1.0f / 5040.0f, 1.0f / 720.0f);
-  q = fmaf(r, q, 1.0f / 120.0f);
-  q = fmaf(r, q, 1.0f / 24.0f);
-  q = fmaf(r, q, 1.0f / 6.0f);
-  q = fmaf(r, q, 0.5f);
-  q = fmaf(r * r, q, r);                                   // expm1(r)
-  const int ki = (int)k;
-  const bool thin = tau < 0.6931472f;
-  const float p2 = ldexpf(1.0f, ki);
-  const float absorbed = -fmaf(p2, q, p2 - 1.0f);          // 1 - e^-tau (thin: k is 0 or -1)
-  const float transmitted = ldexpf(1.0f + q, ki);          // e^-tau
-  const double Pin = P;
-  const double a = Pin * (double)(thin ? absorbed : transmitted);
-  P = thin ? Pin - a : a;
-  return thin ? a : Pin - a;
+// Float32, of y = tau / ln 2 (the factor is folded into the cross-section):
+// 1 - 2^-y = y (c0 - c1 y + ...), c_n = ln2^(n+1) / (n+1)!, to y^7 for thin
+// segments (y <= 1/2; truncation below 2e-8), and for thick ones the transmitted
+// part P 2^-y from the hardware exp2 (1 ulp) and the absorbed part as the float64
+// difference, so that both are accurate to float rounding and dP + P_new = P to
+// float64 rounding. Where no lane is thick, as in ionised gas and for the
+// hardest photons everywhere, the wave takes the series alone.
+__device__ __forceinline__ double absorb(double& P, float y) {
+  float q = fmaf(y, 1.5252733804e-5f, -1.5403530394e-4f);   // c6, -c5
+  q = fmaf(y, q, 1.3333558146e-3f);
+  q = fmaf(y, q, -9.6181291076e-3f);
+  q = fmaf(y, q, 5.5504108665e-2f);
+  q = fmaf(y, q, -0.24022650696f);
+  q = fmaf(y, q, 0.69314718056f);
+  const float f = y * q;
+  const bool thick = y > 0.5f;
+  if (!__ballot(thick)) {
+    const double dP = P * (double)f;
+    P -= dP;
+    return dP;
+  }
+  const float m = thick ? __builtin_amdgcn_exp2f(-y) : f;
+  const double a = P * (double)m, rest = P - a;
+  P = thick ? a : rest;
+  return thick ? rest : a;
 }
+constexpr double kLog2e = 1.4426950408889634074;
+// what the cross-section is multiplied by for absorb's argument
+template <typename R> constexpr double kSigmaScale = sizeof(R) == 4 ? kLog2e : 1.0;
+
+constexpr int kZShift = 13;      // see line_index
 
 // Per-lane ray state. A ray carries NG energy groups of its source: they share
-// its geometry, and each has its own photon rate, cross-section and end. The
-// tree fields (source, cross-sections, accumulator, root grid) belong to the
-// lane's current tree and are reloaded only when the lane starts a ray of
-// another tree.
+// its geometry, and each has its own photon rate, cross-section and end. Only
+// what the step reads is held; the rest of the ray's tree and grid is read from
+// their tables by the rare paths (a ray start, a grid change).
 template <typename R, int NG>
 struct Ray {
   typename GeomOf<R>::type g;
-  uint64_t pix;
-  uint32_t tree;          // of the ray
-  int q;                  // grid index
-  int c0, c1, c2;         // local cell
-  int n0, n1, n2;         // grid dims
+  double rs, tbox;        // a step whose exit lies beyond rs may split, at tbox or beyond leaves the grid
+  int st[3];              // what crossing a plane of each axis adds to lin
   int lin;                // batch-wide cell index
+  uint32_t yz;            // the local cell's j + (k << kZShift)
+  int sy, sz;             // what crossing a y or z plane adds to it
+  int q;                  // grid index
+  bool root;              // it is the problem's root grid
+  uint64_t pix;
+  uint32_t tree;
   double P[NG], pmin[NG];
   bool alive[NG];         // groups the ray still carries (an ended group's P is 0)
   uint32_t slot0;         // the ray's accumulator of cell lin is acc[slot0 + astride * lin]
+  uint32_t astride;
   R sigma[NG];
   double eexc[NG];        // E - E_ion (moments only)
   R kap;                  // absorber column per root-cell length of the current cell
-  R split_t;              // float path: split when u^2 > split_t; float64 path: 12*4^l (inf: never)
-  double fpp;             // 4 pi phi_c (float64 path)
   unsigned segs;
-  // the lane's tree
-  uint32_t ltree;
+  uint32_t ltree;         // the tree whose constants the lane holds
   uint32_t stat0;
-  int n_grp;
-  int level;              // HEALPix level of the tree's rays in this launch
-  double sx, sy, sz;
-  int root, rn0, rn1, rn2, rcell;
-  bool cover;             // its deposits are scaled by the covering factor
-  uint32_t astride;       // deposit key of cell lin: slot0 + astride * lin (4: a radiation-pressure record)
   double mscale;          // E_ph / c, 0 when the problem does not ask for the momentum
+  double d[3];            // direction (the variants that need it at every step)
+  double ad[3];           // its magnitudes per local cell (covering factor, mixed mode)
+  double lpix;            // covering factor: width of the ray's pixel per unit radius, local cells; 0: not scaled
   double rhalt;           // time-dependent rays: radius where the tree's rays halt in this step
   // optically-thin approximation (section 2.4): while the ray is thin, the
   // absorber column it may still cross before its optical depth from the
   // source reaches tau_thin, rem = (tau_thin - tau) / sigma (units of kap x
-  // radius), and the tree's constants for it
+  // radius), and the split radius of thin rays
   bool thin;
   double rem;
   double kap64;           // the current cell's column in float64 (the thin decision's optical depth)
-  R split_t_thin;         // split thresholds of thin rays, as split_t and fpp
-  double fpp_thin;
+  double rs_thin;
   long long mark_base;
   unsigned tsegs;         // the ray's thin segments
 
@@ -407,103 +439,132 @@ struct Ray {
   }
 };
 
-template <typename R, int NG>
+// Why an idle lane's ray goes on: with a new frame after it crossed into or out
+// of a child grid along axis 0..2 (kCross + axis), or in the cell it is in
+// (kResyncFrame). The step loop has no frame code of its own: it holds the
+// whole state of every lane, and with the frame's temporaries on top overflows
+// the register budget (spills in the loop took the 128^3 workload from 8 to
+// 10.5 ms). Such a ray waits, idle, for the wave's next refill, where little else is live.
+constexpr int kFresh = 0, kResyncFrame = 1, kCross = 2;
+
+template <typename R, int NG, int PHYS>
 struct Tracer {
+  static constexpr bool COVER = (PHYS & kPhysCover) != 0, RADP = (PHYS & kPhysRadp) != 0, THIN = (PHYS & kPhysThin) != 0;
+  using L_t = Ray<R, NG>;
   const TraceArgs<R>& a;
   __device__ explicit Tracer(const TraceArgs<R>& args) : a(args) {}
 
-  __device__ void root_frame(Ray<R, NG>& L) const {
-    L.q = L.root;
-    L.n0 = L.rn0; L.n1 = L.rn1; L.n2 = L.rn2;
-    const double sl[3] = {L.sx, L.sy, L.sz};
-    L.g.set_frame(sl, L.c0, L.c1, L.c2, false);
-    L.lin = L.rcell + L.c0 + L.n0 * (L.c1 + L.n1 * L.c2);
+  // Radius (root cells) beyond which an exit splits a ray of `level`: the
+  // canonical test 12 * 4^l < (4 pi phi) u^2, u the exit distance in local cells,
+  // solved for it. The float64 mode takes it a little short, and decides exits
+  // within 2^-37 of it by the test itself (splits()).
+  static __device__ double split_radius(double split_r, int level, int level_max, double hinv) {
+    if (level >= level_max) return __builtin_huge_val();
+    const double rs = ldexp(split_r, level) * hinv;
+    return sizeof(R) == 4 ? rs : rs * (1.0 - 0x1p-38);
   }
+  __device__ int level_of(const TreeDev& S) const { return S.level_init + (a.gen - S.gen0); }
 
-  __device__ void child_frame(Ray<R, NG>& L, int q) const {
-    const GridDev& G = a.grids[q];
+  // The ray's frame in grid q at local cell c: source in its cells, planes,
+  // strides, split radius and cell index.
+  __device__ void frame(L_t& L, const TreeDev& S, int q, const int c[3]) const {
+    const bool child = q != S.root_grid;
+    int n[3] = {S.rnx, S.rny, S.rnz};
+    double sl[3] = {S.sx, S.sy, S.sz};
+    long long off = S.rcell_off;
+    if (child) {
+      const GridDev& G = a.grids[q];
+      n[0] = G.nx; n[1] = G.ny; n[2] = G.nz;
+      sl[0] = 2.0 * (S.sx - (double)G.ox); sl[1] = 2.0 * (S.sy - (double)G.oy); sl[2] = 2.0 * (S.sz - (double)G.oz);
+      off = G.cell_off;
+    }
     L.q = q;
-    L.n0 = G.nx; L.n1 = G.ny; L.n2 = G.nz;
-    const double sl[3] = {2.0 * (L.sx - (double)G.ox), 2.0 * (L.sy - (double)G.oy), 2.0 * (L.sz - (double)G.oz)};
-    L.g.set_frame(sl, L.c0, L.c1, L.c2, true);
-    L.lin = (int)G.cell_off + L.c0 + G.nx * (L.c1 + G.ny * L.c2);
+    L.root = !child;
+    L.g.frame(sl, c, n, child, L.tbox);
+    const int level = level_of(S);
+    const double hinv = child ? 0.5 : 1.0;
+    L.rs = split_radius(S.split_r, level, S.level_max, hinv);
+    if constexpr (THIN) L.rs_thin = split_radius(S.split_r_thin, level, S.level_max, hinv);
+    if constexpr (COVER) {
+      // sqrt(pi/3) 2^-l, the pixel's width at unit distance
+      L.lpix = S.covering ? ldexp(1.0233267079464885, -level) / hinv : 0.0;
+      if constexpr (sizeof(R) == 4) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) L.ad[k] = fabs(L.d[k]) / hinv;
+      }
+    }
+    const int sx = n[0], sxy = n[0] * n[1];
+    L.st[0] = L.g.up(0) ? 1 : -1;
+    L.st[1] = L.g.up(1) ? sx : -sx;
+    L.st[2] = L.g.up(2) ? sxy : -sxy;
+    L.lin = (int)off + c[0] + sx * (c[1] + n[1] * c[2]);
+    L.yz = (uint32_t)c[1] + ((uint32_t)c[2] << kZShift);
+    L.sy = L.g.up(1) ? 1 : -1;
+    L.sz = L.g.up(2) ? 1 << kZShift : -(1 << kZShift);
   }
 
-  // Enter child grid `ch` from root cell (rc0, rc1, rc2) across axis `ax`
-  // moving in direction `dir`, at the current radius: along the crossing axis
-  // the fine cell follows from the face, along the others from the position,
-  // kept among the two fine cells under the root cell.
-  __device__ void enter_child(Ray<R, NG>& L, int ch, int rc0, int rc1, int rc2, int ax, int dir) const {
+  // Local cell of batch-wide index lin in grid q.
+  __device__ void cell(const TreeDev& S, int q, int lin, int c[3]) const {
+    int nx = S.rnx, ny = S.rny;
+    long long off = S.rcell_off;
+    if (q != S.root_grid) {
+      const GridDev& G = a.grids[q];
+      nx = G.nx; ny = G.ny;
+      off = G.cell_off;
+    }
+    const unsigned local = (unsigned)(lin - (int)off);
+    const unsigned row = local / (unsigned)nx;
+    c[0] = (int)(local - row * (unsigned)nx);
+    c[2] = (int)(row / (unsigned)ny);
+    c[1] = (int)(row - (unsigned)c[2] * (unsigned)ny);
+  }
+
+  // From root cell c, covered by child grid `ch`, into the child's cell: along
+  // the crossing axis it follows from the face, along the others from the
+  // position x on the ray (direction v), kept among the two fine cells under the
+  // root cell. ax = 3: from the position along every axis (a ray that starts).
+  __device__ void into_child(int ch, int c[3], const double x[3], const double v[3], int ax) const {
     const GridDev& G = a.grids[ch];
-    const int rc[3] = {rc0, rc1, rc2};
     const int o[3] = {G.ox, G.oy, G.oz};
-    const double sr[3] = {L.sx, L.sy, L.sz};
-    const double r = L.g.radius64();
-    int c[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const int lo = 2 * (rc[k] - o[k]);
-      if (k == ax) {
-        c[k] = lo + (dir < 0 ? 1 : 0);
-      } else {
-        const double dk = L.g.dir64(k);
-        const double x = __dadd_rn(sr[k], __dmul_rn(r, dk));
-        const int cl = cell_rule(2.0 * (x - (double)o[k]), dk);
-        c[k] = cl < lo ? lo : (cl > lo + 1 ? lo + 1 : cl);
-      }
+      const int lo = 2 * (c[k] - o[k]);
+      const int at = min(max(cell_rule(2.0 * (x[k] - (double)o[k]), v[k]), lo), lo + 1);
+      c[k] = k == ax ? lo + (v[k] < 0.0 ? 1 : 0) : at;
     }
-    L.c0 = c[0]; L.c1 = c[1]; L.c2 = c[2];
-    child_frame(L, ch);
   }
 
-  // After a step along `ax` by `dir` out of the current grid, or into a root
-  // cell covered by a child: find the new leaf cell. Returns false when the
-  // ray left the root grid.
-  __device__ bool settle(Ray<R, NG>& L, int ax, int dir) const {
-    const bool inside = find_cell(L, ax, dir);
-    finish_vector_loads();
-    return inside;
-  }
-  __device__ bool find_cell(Ray<R, NG>& L, int ax, int dir) const {
-    if (L.q == L.root) {
-      if ((unsigned)L.c0 >= (unsigned)L.n0 || (unsigned)L.c1 >= (unsigned)L.n1 || (unsigned)L.c2 >= (unsigned)L.n2)
-        return false;
-      const R k = a.kappa[L.lin];
-      if (k < (R)0) {
-        enter_child(L, (int)(-k) - 1, L.c0, L.c1, L.c2, ax, dir);
-        L.kap = a.kappa[L.lin];
-      } else {
-        L.kap = k;
-      }
-      return true;
+  // The leaf cell (grid q, local cell c) a ray goes on in after it crossed a
+  // face of cell `from` of grid q along `ax`, out of a child grid or into a root
+  // cell under one. Returns false when it left the root grid.
+  __device__ bool cross(const TreeDev& S, int& q, int from, int ax, int c[3], const double x[3], const double v[3]) const {
+    cell(S, q, from, c);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] += k == ax ? (v[k] < 0.0 ? -1 : 1) : 0;
+    if (q != S.root_grid) {
+      const GridDev& G = a.grids[q];
+      if ((unsigned)c[0] < (unsigned)G.nx && (unsigned)c[1] < (unsigned)G.ny && (unsigned)c[2] < (unsigned)G.nz)
+        return true;                               // crossed within a plane tie of the child's face
+      c[0] = G.ox + floor_half(c[0]); c[1] = G.oy + floor_half(c[1]); c[2] = G.oz + floor_half(c[2]);
+      q = S.root_grid;
     }
-    if ((unsigned)L.c0 < (unsigned)L.n0 && (unsigned)L.c1 < (unsigned)L.n1 && (unsigned)L.c2 < (unsigned)L.n2) {
-      L.kap = a.kappa[L.lin];
-      return true;
-    }
-    const GridDev& G = a.grids[L.q];
-    const int rc0 = G.ox + floor_half(L.c0), rc1 = G.oy + floor_half(L.c1), rc2 = G.oz + floor_half(L.c2);
-    if ((unsigned)rc0 >= (unsigned)L.rn0 || (unsigned)rc1 >= (unsigned)L.rn1 || (unsigned)rc2 >= (unsigned)L.rn2)
+    if ((unsigned)c[0] >= (unsigned)S.rnx || (unsigned)c[1] >= (unsigned)S.rny || (unsigned)c[2] >= (unsigned)S.rnz)
       return false;
-    const int rlin = L.rcell + rc0 + L.rn0 * (rc1 + L.rn1 * rc2);
-    const R k = a.kappa[rlin];
+    const R k = a.kappa[(int)S.rcell_off + c[0] + S.rnx * (c[1] + S.rny * c[2])];
     if (k < (R)0) {
-      enter_child(L, (int)(-k) - 1, rc0, rc1, rc2, ax, dir);
-      L.kap = a.kappa[L.lin];
-    } else {
-      L.c0 = rc0; L.c1 = rc1; L.c2 = rc2;
-      root_frame(L);
-      L.kap = k;
+      q = (int)(-k) - 1;
+      into_child(q, c, x, v, ax);
     }
     return true;
   }
 
   // A ray starts in three steps:
   //   fetch  - its queue record (a child of a split ray), its halted record,
-  //            or its tree and pixel (a seed, whose rates load_tree gives);
-  //   tree   - the tree's constants, unless the lane already holds them;
+  //            or its tree and pixel (a seed); a ray that changes frames (see
+  //            Again) has its state;
+  //   tree   - the tree's constants;
   //   locate - direction, start cell and frame, and that cell's absorber column.
-  __device__ void fetch_child(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+  __device__ void fetch_child(L_t& L, unsigned long long i, double& r64) const {
     const unsigned long long slot = i >> 2;
     L.tree = a.in.tree[slot];
     L.pix = 4ull * a.in.pix[slot] + (i & 3ull);
@@ -511,7 +572,7 @@ struct Tracer {
 #pragma unroll
     for (int g = 0; g < NG; ++g) L.P[g] = 0.25 * a.in.P[g * a.in.pstride + slot];
   }
-  __device__ void fetch_held(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+  __device__ void fetch_held(L_t& L, unsigned long long i, double& r64) const {
     const unsigned long long slot = a.held_order[a.held_first + i];
     L.tree = a.held.tree[slot];
     L.pix = a.held.pix[slot];
@@ -519,7 +580,7 @@ struct Tracer {
 #pragma unroll
     for (int g = 0; g < NG; ++g) L.P[g] = a.held.P[g * a.held.pstride + slot];
   }
-  __device__ void fetch_seed(Ray<R, NG>& L, unsigned long long i, double& r64) const {
+  __device__ void fetch_seed(L_t& L, unsigned long long i, double& r64) const {
     const unsigned long long npix = 12ull << (2 * a.seed_level);
     L.tree = (uint32_t)(a.seed_begin + i / npix);
     L.pix = i % npix;
@@ -528,49 +589,20 @@ struct Tracer {
     for (int g = 0; g < NG; ++g) L.P[g] = a.trees[L.tree].P0[g];
   }
 
-  __device__ void load_tree(Ray<R, NG>& L) const {
-    const TreeDev& S = a.trees[L.tree];
-    const int level = S.level_init + (a.gen - S.gen0);
+  __device__ void load_tree(L_t& L, const TreeDev& S) const {
     L.ltree = L.tree;
-    L.level = level;
-    L.sx = S.sx; L.sy = S.sy; L.sz = S.sz;
     L.slot0 = (uint32_t)S.acc_slot;
     L.stat0 = S.stat0;
-    L.n_grp = S.n_grp;
-    L.root = S.root_grid;
-    L.rn0 = S.rnx; L.rn1 = S.rny; L.rn2 = S.rnz;
-    L.rcell = (int)S.rcell_off;
-    L.cover = S.covering != 0;
     L.astride = S.acc_stride;
-    L.mscale = S.mom_scale;
-    L.rhalt = S.r_halt;
+    if constexpr (RADP) L.mscale = S.mom_scale;
+    if constexpr ((PHYS & kPhysHalt) != 0) L.rhalt = S.r_halt;
+    if constexpr (THIN) L.mark_base = S.mark_base;
+    const int level = level_of(S);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       L.pmin[g] = ldexp(S.pmin0[g], -2 * (level - S.level_init));
-      L.sigma[g] = sizeof(R) == 4 ? (R)S.sigma32[g] : (R)S.sigma64[g];
+      L.sigma[g] = (R)(S.sigma64[g] * kSigmaScale<R>);
       L.eexc[g] = S.eexc[g];
-    }
-    const bool can_split = level < S.level_max;
-    if constexpr (sizeof(R) == 4) {
-      L.split_t = can_split ? ldexpf(S.split_t2_base, 2 * level) : FLT_MAX;
-      L.fpp = 0.0;
-    } else {
-      L.split_t = can_split ? ldexp(12.0, 2 * level) : __builtin_huge_val();
-      L.fpp = S.four_pi_phi_c;
-    }
-  }
-
-  // The optically-thin constants of the lane's tree (after load_tree).
-  __device__ void load_thin(Ray<R, NG>& L) const {
-    const TreeDev& S = a.trees[L.tree];
-    L.mark_base = S.mark_base;
-    const bool can_split = L.level < S.level_max;
-    if constexpr (sizeof(R) == 4) {
-      L.split_t_thin = can_split ? ldexpf(S.split_t2_thin, 2 * L.level) : FLT_MAX;
-      L.fpp_thin = 0.0;
-    } else {
-      L.split_t_thin = L.split_t;
-      L.fpp_thin = S.four_pi_phi_thin;
     }
   }
 
@@ -581,9 +613,8 @@ struct Tracer {
   // approximation. rem is capped at kRemMax (a zero cross-section), which
   // keeps every record finite.
   static constexpr double kRemMax = 1e300;
-  __device__ void thin_start(Ray<R, NG>& L, bool seed) const {
+  __device__ void thin_start(L_t& L, const TreeDev& S, bool seed) const {
     L.tsegs = 0;
-    const TreeDev& S = a.trees[L.tree];
     if (seed) {
       L.thin = S.tau_thin > 0.0;
       const double r = S.tau_thin / S.sigma64[0];
@@ -591,7 +622,7 @@ struct Tracer {
     } else if (L.P[0] < 0.0) {
       L.thin = true;
       L.rem = -L.P[0] - 1.0;
-      L.P[0] = ldexp(S.P0[0], -2 * (L.level - S.level_init));
+      L.P[0] = ldexp(S.P0[0], -2 * (level_of(S) - S.level_init));
     } else {
       L.thin = false;
     }
@@ -600,118 +631,73 @@ struct Tracer {
   // Does the ray's current cell hold its source (inside or on its boundary)?
   // Only a cell within sqrt(3) local cells of the source can: nearer than 2
   // the test is taken exactly, on the source's float64 local coordinates.
-  __device__ bool holds_source(const Ray<R, NG>& L) const {
-    const bool child = L.q != L.root;
-    if (L.g.radius64() * (child ? 2.0 : 1.0) >= 2.0) return false;
-    double sl[3] = {L.sx, L.sy, L.sz};
-    if (child) {
+  __device__ bool holds_source(const L_t& L) const {
+    if (L.g.r >= 2.0 * L.g.hinv) return false;
+    const TreeDev& S = a.trees[L.tree];
+    double sl[3] = {S.sx, S.sy, S.sz};
+    if (L.q != S.root_grid) {
       const GridDev& G = a.grids[L.q];
-      sl[0] = 2.0 * (L.sx - (double)G.ox);
-      sl[1] = 2.0 * (L.sy - (double)G.oy);
-      sl[2] = 2.0 * (L.sz - (double)G.oz);
+      sl[0] = 2.0 * (S.sx - (double)G.ox);
+      sl[1] = 2.0 * (S.sy - (double)G.oy);
+      sl[2] = 2.0 * (S.sz - (double)G.oz);
     }
-    const int c[3] = {L.c0, L.c1, L.c2};
+    int c[3];
+    cell(S, L.q, L.lin, c);
     bool in = true;
 #pragma unroll
     for (int k = 0; k < 3; ++k) in = in && (double)c[k] <= sl[k] && sl[k] <= (double)c[k] + 1.0;
     return in;
   }
 
-  // Start cell of a fetched ray whose tree constants are loaded. Returns false
-  // when the ray starts outside the root grid; otherwise the ray is framed in
-  // the root cell holding s + r d and `k` receives that cell's column.
-  __device__ bool locate(Ray<R, NG>& L, double r64, R& k) const {
-    L.segs = 0;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      L.alive[g] = NG == 1 || (g < L.n_grp && L.P[g] >= 0.0);   // a record may hold fewer rates than NG
-      if (NG > 1) L.P[g] = L.alive[g] ? L.P[g] : 0.0;
-    }
+  // Start of a fetched ray (again = kFresh: in its leaf cell, the root cell
+  // holding s + r d or where a child grid covers that the fine cell under it,
+  // exact in floating point and kept in range regardless), or a new frame of one
+  // in flight. Returns false when it is outside the root grid.
+  __device__ bool locate(L_t& L, const TreeDev& S, double r64, int again, int from, int q) const {
     double v[3];
-    healpix_dir(L.level, L.pix, v[0], v[1], v[2]);
+    healpix_dir(level_of(S), L.pix, v[0], v[1], v[2]);
     L.g.set_dir(v);
-    L.g.set_radius(r64);
-    const double x0 = __dadd_rn(L.sx, __dmul_rn(r64, v[0]));
-    const double x1 = __dadd_rn(L.sy, __dmul_rn(r64, v[1]));
-    const double x2 = __dadd_rn(L.sz, __dmul_rn(r64, v[2]));
-    L.c0 = cell_rule(x0, v[0]); L.c1 = cell_rule(x1, v[1]); L.c2 = cell_rule(x2, v[2]);
-    if ((unsigned)L.c0 >= (unsigned)L.rn0 || (unsigned)L.c1 >= (unsigned)L.rn1 || (unsigned)L.c2 >= (unsigned)L.rn2)
+    L.g.r = r64;
+    if constexpr (RADP || (COVER && sizeof(R) == 4)) {
+      L.d[0] = v[0]; L.d[1] = v[1]; L.d[2] = v[2];
+    }
+    const double x[3] = {__dadd_rn(S.sx, __dmul_rn(r64, v[0])), __dadd_rn(S.sy, __dmul_rn(r64, v[1])),
+                         __dadd_rn(S.sz, __dmul_rn(r64, v[2]))};
+    int c[3];
+    if (again == kFresh) {
+      L.segs = 0;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        L.alive[g] = NG == 1 || (g < S.n_grp && L.P[g] >= 0.0);   // a record may hold fewer rates than NG
+        if (NG > 1) L.P[g] = L.alive[g] ? L.P[g] : 0.0;
+      }
+      q = S.root_grid;
+      c[0] = cell_rule(x[0], v[0]); c[1] = cell_rule(x[1], v[1]); c[2] = cell_rule(x[2], v[2]);
+      if ((unsigned)c[0] >= (unsigned)S.rnx || (unsigned)c[1] >= (unsigned)S.rny || (unsigned)c[2] >= (unsigned)S.rnz)
+        return false;
+      const R k = a.kappa[(int)S.rcell_off + c[0] + S.rnx * (c[1] + S.rny * c[2])];
+      if (k < (R)0) {
+        q = (int)(-k) - 1;
+        into_child(q, c, x, v, 3);
+      }
+    } else if (again == kResyncFrame) {
+      cell(S, q, from, c);
+    } else if (!cross(S, q, from, again - kCross, c, x, v)) {
       return false;
-    root_frame(L);
-    k = a.kappa[L.lin];
+    }
+    frame(L, S, q, c);
+    L.kap = a.kappa[L.lin];
     return true;
   }
 
-  // The located ray becomes active: in the root cell, or when that cell is
-  // covered by a child grid, in the fine cell under it that holds s + r d
-  // (exact in floating point; kept in range regardless).
-  __device__ void begin(Ray<R, NG>& L, R k) const {
-    if (k >= (R)0) {
-      L.kap = k;
-      return;
-    }
-    const int ch = (int)(-k) - 1;
-    const GridDev& G = a.grids[ch];
-    const double r64 = L.g.radius64();
-    const double v[3] = {L.g.dir64(0), L.g.dir64(1), L.g.dir64(2)};
-    const double x0 = __dadd_rn(L.sx, __dmul_rn(r64, v[0]));
-    const double x1 = __dadd_rn(L.sy, __dmul_rn(r64, v[1]));
-    const double x2 = __dadd_rn(L.sz, __dmul_rn(r64, v[2]));
-    const int f0 = 2 * (L.c0 - G.ox), f1 = 2 * (L.c1 - G.oy), f2 = 2 * (L.c2 - G.oz);
-    L.c0 = min(max(cell_rule(2.0 * (x0 - (double)G.ox), v[0]), f0), f0 + 1);
-    L.c1 = min(max(cell_rule(2.0 * (x1 - (double)G.oy), v[1]), f1), f1 + 1);
-    L.c2 = min(max(cell_rule(2.0 * (x2 - (double)G.oz), v[2]), f2), f2 + 1);
-    child_frame(L, ch);
-    L.kap = a.kappa[L.lin];
-  }
-
-  // Float64 re-evaluation of the split test for the current cell, in the
-  // canonical form 12 * 4^l < (4 pi phi_c) * u^2, u = t_exit in local cells.
-  __device__ bool split_exact(const Ray<R, NG>& L, bool thin) const {
-    const bool sp = split_exact64(L, thin);
+  // An exit beyond the split radius: does the ray split? (Mixed mode: yes.)
+  __device__ bool splits(const L_t& L, double te, bool thin) const {
+    if (sizeof(R) == 4 || te > (thin ? L.rs_thin : L.rs) * (1.0 + 0x1p-37)) return true;
+    const TreeDev& S = a.trees[L.tree];
+    const double u = L.q != S.root_grid ? 2.0 * te : te;
+    const bool sp = ldexp(12.0, 2 * level_of(S)) < (thin ? S.four_pi_phi_thin : S.four_pi_phi_c) * (u * u);
     finish_vector_loads();
     return sp;
-  }
-  __device__ bool split_exact64(const Ray<R, NG>& L, bool thin) const {
-    const TreeDev& S = a.trees[L.tree];
-    const bool child = L.q != L.root;
-    int o[3] = {0, 0, 0};
-    if (child) {
-      const GridDev& G = a.grids[L.q];
-      o[0] = G.ox; o[1] = G.oy; o[2] = G.oz;
-    }
-    const double v[3] = {L.g.dir64(0), L.g.dir64(1), L.g.dir64(2)};
-    const double h = child ? 2.0 : 1.0;
-    const double s[3] = {L.sx, L.sy, L.sz};
-    const int c[3] = {L.c0, L.c1, L.c2};
-    double te = __builtin_huge_val();
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (v[k] == 0.0) continue;
-      const double sl = child ? h * (s[k] - (double)o[k]) : s[k];
-      const double b = (double)(c[k] + (v[k] > 0.0 ? 1 : 0));
-      const double t = ((b - sl) / v[k]) / h;
-      te = t < te ? t : te;
-    }
-    const double u = te * h;
-    return ldexp(12.0, 2 * L.level) < (thin ? S.four_pi_phi_thin : S.four_pi_phi_c) * (u * u);
-  }
-
-  // thin: the ray is optically thin in this cell and is split against
-  // min(1, phi_c) rays per cell face (section 2.4)
-  __device__ bool split_test(const Ray<R, NG>& L, int ax, bool thin = false) const {
-    if constexpr (sizeof(R) == 4) {
-      const float u = L.g.local_u(ax);
-      const float t = thin ? L.split_t_thin : L.split_t;
-      const float gap = u * u - t;
-      const float tol = t * 9.6e-7f;           // 16 float ulp: beyond every rounding of u^2
-      if (gap > tol) return true;
-      if (gap < -tol) return false;
-      return split_exact(L, thin);
-    } else {
-      const double u = L.g.local_u(ax);
-      return L.split_t < (thin ? L.fpp_thin : L.fpp) * (u * u);
-    }
   }
 
   // Covering factor of the segment that starts at the current radius R_0 and
@@ -719,38 +705,59 @@ struct Tracer {
   // the distance from the segment's midpoint to the nearest face of its cell,
   // L_pix = R_0 theta_pix the pixel's width at entry (theta_pix =
   // sqrt(4 pi / N_pix) = sqrt(pi/3) 2^-l), both in local cells, and
-  // f_c = (1/2 + D_edge / L_pix)^2, at most 1 (1 also for R_0 = 0). Float64
-  // throughout, from the float64 direction and source.
-  __device__ double covering_factor(const Ray<R, NG>& L, double dr) const {
-    const double h = (double)L.g.hloc;
-    const double r0 = L.g.radius64();
-    const double rmid = (r0 + 0.5 * dr) * h;
-    const int c[3] = {L.c0, L.c1, L.c2};
+  // f_c = (1/2 + D_edge / L_pix)^2, at most 1 (1 also for R_0 = 0). The mixed
+  // mode takes D_c,i from the distance left to the axis' next plane; along an
+  // axis without a direction component it comes from the source's coordinate.
+  __device__ double covering_factor(const L_t& L, double dr) const {
+    const double r0 = L.g.r;
     double dmax = 0.0;
+    if constexpr (sizeof(R) == 4) {
+      const double rmid = r0 + 0.5 * dr;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const double d = fabs(L.g.src64(k) + rmid * L.g.dir64(k) - ((double)c[k] + 0.5));
-      dmax = d > dmax ? d : dmax;
+      for (int k = 0; k < 3; ++k) {
+        double d;
+        if (L.ad[k] == 0.0) {
+          const TreeDev& S = a.trees[L.tree];
+          const GridDev& G = a.grids[L.q];
+          const double s = k == 0 ? S.sx : (k == 1 ? S.sy : S.sz);
+          const double sl = L.q != S.root_grid ? 2.0 * (s - (double)(k == 0 ? G.ox : (k == 1 ? G.oy : G.oz))) : s;
+          d = fabs(sl - floor(sl) - 0.5);
+          finish_vector_loads();
+        } else {
+          d = fabs((L.g.t[k] - rmid) * L.ad[k] - 0.5);
+        }
+        dmax = d > dmax ? d : dmax;
+      }
+    } else {
+      const double h = L.g.hloc();
+      const double rmid = (r0 + 0.5 * dr) * h;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double d = fabs(L.g.s[k] + rmid * L.g.d[k] - L.g.centre(k));
+        dmax = d > dmax ? d : dmax;
+      }
     }
-    const double lpix = r0 * h * ldexp(1.0233267079464885, -L.level);   // sqrt(pi/3) = 1.02332670794648848...
+    const double lpix = r0 * L.lpix;
     if (!(lpix > 0.0)) return 1.0;
     const double f = 0.5 + (0.5 - dmax) / lpix;
     return f * f >= 1.0 ? 1.0 : f * f;
   }
 };
 
-__device__ __forceinline__ unsigned long long bcast64(unsigned long long v, int src) {
-  const unsigned lo = __shfl((unsigned)v, src), hi = __shfl((unsigned)(v >> 32), src);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
+// Wave-uniform values in scalar registers: the first active lane's, lane 0's,
+// and the wave's number in its block (which the compiler cannot tell is uniform).
 __device__ __forceinline__ int uniform32(int v) { return __builtin_amdgcn_readfirstlane(v); }
-// A wave-uniform 64-bit value (the first active lane's) in scalar registers.
 __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
   return ((unsigned long long)hi << 32) | lo;
 }
+__device__ __forceinline__ unsigned long long lane0_64(unsigned long long v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 0);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 0);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ int wave_in_block() { return uniform32((int)(threadIdx.x / kWave)); }
 
 // Sums over the 64 lanes of a wave in which every lane is active (data-parallel
 // primitives: row shifts inside 16 lanes, then the two row broadcasts; the last
@@ -797,8 +804,8 @@ struct WaveTally {
   __device__ void init(int lane) {
     __shared__ unsigned long long scnt[kTraceBlock / kWave][kRows * NG];
     __shared__ double ssum[kTraceBlock / kWave][2 * NG];
-    cnt = scnt[threadIdx.x / kWave];
-    sum = ssum[threadIdx.x / kWave];
+    cnt = scnt[wave_in_block()];
+    sum = ssum[wave_in_block()];
     stat0 = kNoTree;
     clear(lane);
   }
@@ -893,218 +900,201 @@ struct WaveTally {
 
 // Every global store or atomic a wave issues stays outstanding in the same
 // in-order counter as its loads, so the next gather of an absorber column
-// may wait for it, and float64 atomics are performed at the memory side. The
-// trace therefore stages its writes in LDS and issues them in bulk: deposits
-// combine in a per-wave cache, evicted sums collect in a per-wave buffer
-// drained 64 atomics per instruction, and rays that split collect in a per-wave
-// stage written together.
+// may wait for it, and float64 atomics are performed at the memory side, one
+// 64-byte request at a time: 2.4e10 requests a second, whether a request holds
+// one sum or eight neighbouring ones. The trace therefore stages its writes in
+// LDS and issues them in bulk: deposits combine in a per-wave cache of
+// accumulator lines, evicted lines collect in a per-wave buffer drained eight
+// at a time, and rays that split are written when their wave refills.
 
-// Deposit combining: each wave keeps a direct-mapped table of (accumulator
-// record, NS float64 sums) in LDS. The rays of a wave come from one small patch
-// of HEALPix pixels, so each cell of their cone receives several of their
-// deposits a few steps apart; those add up in LDS and reach the float64
-// accumulators in HBM only when the entry is evicted or the launch ends.
-// Within an iteration every lane first compares its key, matching lanes add,
-// and only then may a lane claim the entry for a new key (one winner per
-// entry via compare-and-swap), so every deposit lands in its own cell's sums.
+// Deposit combining: each wave keeps a direct-mapped cache of accumulator lines,
+// eight consecutive float64 sums (64 bytes) each, in LDS. The rays of a wave
+// come from one small patch of HEALPix pixels, so each cell of their cone
+// receives several of their deposits a few steps apart, and the cells of a
+// line (eight of one sum, four of two) are crossed one after the other by rays
+// along x and side by side by the others. All of them add up in LDS; the line
+// leaves with one request when another takes its entry or the launch ends.
+// Against a table of single cells that is a third of the memory-side requests.
 //
-// NS: 1 for the absorbed rate alone; 2 for the moments of rays with several
-// groups (absorbed rate, energy); 4 for the radiation-pressure record. A
-// record's sums are neighbours in memory and leave with (entry, sum) spread over
-// consecutive lanes, so they go out in one instruction to one piece of a
-// cache line: the memory side takes one request for them. Which sums beyond the
-// first a record has: with NS = 2 those that are not zero (a one-group
-// problem's record in a batch of others is one sum, and its second sum stays 0);
-// with NS = 4 all four from rec_base on, one below it.
+// A deposit is NS consecutive sums of one cell's record, which never straddles a
+// line: the absorbed rate (1), the moments of rays with several groups (2:
+// absorbed rate, energy), or the radiation-pressure record (4). `sums` says how
+// many of them the lane's problem keeps (a batch may mix problems).
 //
-// Entries: what three blocks (two with NS = 4) leave of a CU's 160 KB of LDS.
-template <int NS> struct CacheShape;
-template <> struct CacheShape<1> { static constexpr int entries = 512, evict = 64; };
-template <> struct CacheShape<2> { static constexpr int entries = 416, evict = 64; };
-template <> struct CacheShape<4> { static constexpr int entries = 256, evict = 128; };
+// kLines and kOut: what three blocks leave of a CU's 160 KB of LDS.
+constexpr int kLineLog2 = 7, kLines = 1 << kLineLog2;
+constexpr int kOut = 24;                       // evicted lines waiting for their atomics
 
-template <int N>
-__device__ __forceinline__ uint32_t cache_index(uint32_t key) {
-  const uint32_t h = key * 0x9E3779B1u;
-  if constexpr ((N & (N - 1)) == 0) return h / (0x100000000ull / N);
-  return (uint32_t)(((uint64_t)(h >> 8) * (uint64_t)(N << 8)) >> 32);   // 24-bit factors
+// Entry of a line: 8 x 8 cells in y and z, two lines in x, so the lines a wave
+// uses at about the same time, those of a compact patch of cells, never share an
+// entry, and a line leaves when the wave has moved on by eight cells (a
+// multiplicative hash of the line number put about one conflict into every step
+// and as many requests on the memory side as a table of single cells). yz is the
+// local cell's j + (k << kZShift). Any value is correct: a line that is found
+// under two entries is summed in both.
+__device__ __forceinline__ uint32_t line_index(uint32_t line, uint32_t yz) {
+  return (yz & 7u) | ((yz >> (kZShift - 3)) & 0x38u) | ((line & 1u) << 6);
 }
 
 template <bool CACHE, int NS>
 struct DepositCache {
-  static constexpr int N = CacheShape<NS>::entries, E = CacheShape<NS>::evict;
-  uint32_t* key;
-  double* val;            // [NS][N]
-  uint32_t* ekey;         // evicted sums waiting for their global atomics
-  double* eval;           // [NS][E]
-  int ecount;             // wave-uniform
-  uint32_t rec_base;
+  uint32_t* key;          // line numbers; kNoSlot: empty
+  double* val;            // [kLines][8]
+  uint32_t* okey;
+  double* oval;           // [kOut][8]
+  uint2* moves;           // (entry, line) pairs of one call's evictions
+  int ocount;             // wave-uniform
 
-  static __device__ __forceinline__ void out(double* acc, uint32_t kk, int c, double v, uint32_t rec_base) {
-    if (c == 0 || (NS == 2 ? v != 0.0 : kk >= rec_base)) unsafeAtomicAdd(&acc[kk + c], v);
-  }
-
-  __device__ void init(int lane, uint32_t rb) {
-    rec_base = rb;
+  __device__ void init(int lane) {
     if constexpr (CACHE) {
-      __shared__ uint32_t skey[kTraceBlock / kWave][N];
-      __shared__ double sval[kTraceBlock / kWave][NS * N];
-      __shared__ uint32_t sekey[kTraceBlock / kWave][E];
-      __shared__ double seval[kTraceBlock / kWave][NS * E];
-      const int wv = threadIdx.x / kWave;
+      __shared__ uint32_t skey[kTraceBlock / kWave][kLines];
+      __shared__ double sval[kTraceBlock / kWave][8 * kLines];
+      __shared__ uint32_t sokey[kTraceBlock / kWave][kOut];
+      __shared__ double soval[kTraceBlock / kWave][8 * kOut];
+      __shared__ uint2 smoves[kTraceBlock / kWave][kWave];
+      const int wv = wave_in_block();
       key = skey[wv];
       val = sval[wv];
-      ekey = sekey[wv];
-      eval = seval[wv];
-      ecount = 0;
-      for (int e = lane; e < N; e += kWave) key[e] = kNoSlot;
+      okey = sokey[wv];
+      oval = soval[wv];
+      moves = smoves[wv];
+      ocount = 0;
+      for (int e = lane; e < kLines; e += kWave) key[e] = kNoSlot;
+      for (int e = lane; e < 8 * kLines; e += kWave) val[e] = 0.0;
       __builtin_amdgcn_wave_barrier();
     }
   }
-  // 64 buffered sums per global atomic instruction
+  static __device__ __forceinline__ void add_line(double* acc, uint32_t line, int j, double v) {
+    if (v != 0.0) unsafeAtomicAdd(&acc[((unsigned long long)line << 3) + j], v);
+  }
+  // eight lanes a line, eight lines an instruction
   __device__ void drain(double* acc, int lane) {
     if constexpr (CACHE) {
       __builtin_amdgcn_wave_barrier();
-      for (int j = lane; j < NS * ecount; j += kWave) {
-        const int i = j / NS, c = j % NS;
-        out(acc, ekey[i], c, eval[c * E + i], rec_base);
-      }
-      ecount = 0;
+      for (int j = lane; j < 8 * ocount; j += kWave) add_line(acc, okey[j >> 3], j & 7, oval[j]);
+      ocount = 0;
       __builtin_amdgcn_wave_barrier();
     }
   }
   // Every lane of the wave calls this (uniform control flow); one pass per
-  // call. Lanes whose key is in the table add to its sums; the others claim
-  // their entry by compare-and-swap. A winner swaps its deposit in and passes
-  // the entry's old sums to the eviction buffer. A lane that loses the claim
-  // sees the winner's key in the failed swap: if it is its own key (two rays
-  // of one tree entering the same cell) it adds to the new sums once the
-  // winner has swapped, otherwise it passes its deposit to the eviction
-  // buffer. The phases are separated by wave barriers: per thread the
-  // branches are exclusive, and without a convergent barrier between them
-  // the compiler may merge them into one if/else and reorder the LDS ops.
-  __device__ void add(double* acc, uint32_t k_new, const double (&v)[NS], bool has, int lane) {
+  // call. First every depositing lane reads its entry's line, exchanges its own
+  // in, and reads the entry again: the last read tells which line owns the
+  // entry from now on (lanes of different lines race for it; the last one wins).
+  // Where that differs from the first, the entry's sums belong to the old line:
+  // the lane whose exchange returned it (the first in the race; a lane that
+  // holds the old line itself can make it several) lists the entry, and eight
+  // lanes per listed entry exchange zeros in and move the old sums to the
+  // buffer (an entry listed twice moves zeros the second time). Then the lanes of
+  // the owning line add their deposits, and those of a losing line add theirs to
+  // memory. The LDS operations of a wave are performed in order, so no wait
+  // separates the exchanges from the adds. The phases are separated by wave
+  // barriers, which keep the compiler from merging them.
+  __device__ void add(double* acc, uint32_t slot, uint32_t yz, uint32_t sums, const double (&v)[NS], bool has, int lane) {
     if constexpr (!CACHE) {
       if (has) {
 #pragma unroll
-        for (int c = 0; c < NS; ++c) out(acc, k_new, c, v[c], rec_base);
+        for (int c = 0; c < NS; ++c)
+          if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
       }
       return;
     }
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (!__ballot(has)) return;
-    uint32_t h = 0, k = kNoSlot;
-    bool match = false;
+    const uint32_t line = slot >> 3;
+    uint32_t h = 0, was = kNoSlot, before = kNoSlot, owner = kNoSlot;
     if (has) {
-      h = cache_index<N>(k_new);
-      k = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      match = k == k_new;
+      h = line_index(line, yz);
+      was = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      before = __hip_atomic_exchange(&key[h], line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      owner = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
-    if (match) {
+    const bool displace = has && owner != was && before == was && was != kNoSlot;
+    const unsigned long long dmask = __ballot(displace);
+    if (dmask) {
+      const int n = __popcll(dmask);
+      if (displace) {
+        const int i = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(dmask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)dmask, 0u));
+        moves[i] = make_uint2(h, was);
+      }
+      __builtin_amdgcn_wave_barrier();
+      for (int i0 = 0; i0 < n; i0 += 8) {
+        const int m = n - i0 < 8 ? n - i0 : 8;
+        if (ocount + m > kOut) drain(acc, lane);
+        const int i = lane >> 3;
+        if (i < m) {
+          const uint2 mv = moves[i0 + i];
+          const double old = __hip_atomic_exchange(&val[8 * mv.x + (lane & 7)], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          oval[8 * ocount + lane] = old;
+          if ((lane & 7) == 0) okey[ocount + i] = mv.y;
+        }
+        ocount += m;
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    const bool mine = has && owner == line;
+    double* cell = &val[8 * h + (slot & 7u)];
+    if (mine) {
 #pragma unroll
       for (int c = 0; c < NS; ++c)
-        __hip_atomic_fetch_add(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (c == 0 || sums > (uint32_t)c)
+          __hip_atomic_fetch_add(cell + c, v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
-    const bool claim = has && !match;
-    bool won = false, join = false;
-    if (claim) {
-      uint32_t seen = k;
-      won = __hip_atomic_compare_exchange_strong(&key[h], &seen, k_new, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-      join = !won && seen == k_new;
-    }
-    __builtin_amdgcn_wave_barrier();
-    const bool leave = claim && !join && (!won || k != kNoSlot);
-    const unsigned long long omask = __ballot(leave);
-    const int n_out = __popcll(omask);
-    if (ecount + n_out > E) drain(acc, lane);             // room for this call's evictions (at most 64)
-    uint32_t ok = k_new;
-    double ov[NS];
-#pragma unroll
-    for (int c = 0; c < NS; ++c) ov[c] = v[c];
-    if (won) {
-      // the adds of this call precede the exchange, so the old sums are complete
+    if (has && !mine) {
 #pragma unroll
       for (int c = 0; c < NS; ++c)
-        ov[c] = __hip_atomic_exchange(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      ok = k;
+        if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
     }
-    __builtin_amdgcn_wave_barrier();
-    if (join) {
-#pragma unroll
-      for (int c = 0; c < NS; ++c)
-        __hip_atomic_fetch_add(&val[c * N + h], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    if (leave) {
-      const int e = ecount + __popcll(omask & below);
-      ekey[e] = ok;
-#pragma unroll
-      for (int c = 0; c < NS; ++c) eval[c * E + e] = ov[c];
-    }
-    ecount += n_out;
-    __builtin_amdgcn_wave_barrier();
   }
   __device__ void flush(double* acc, int lane) {
     if constexpr (CACHE) {
       drain(acc, lane);
-      for (int j = lane; j < NS * N; j += kWave) {
-        const int e = j / NS, c = j % NS;
-        const uint32_t kk = key[e];
-        if (kk != kNoSlot) out(acc, kk, c, val[c * N + e], rec_base);
+      for (int j = lane; j < 8 * kLines; j += kWave) {
+        const uint32_t line = key[j >> 3];
+        if (line != kNoSlot) add_line(acc, line, j & 7, val[j]);
       }
     }
   }
 };
 
-// Rays that split, waiting for their queue slots: a stage goes to the wave's
-// current segment of the next level's queue (its home segment at first)
-// through blocks of slots it reserves with one atomic, in coalesced stores. A
-// slot holds the split ray; its four children are formed when they are
-// claimed, so a split writes a quarter of the bytes its children would take
-// and the stage needs a quarter of the LDS. A segment that is full sends the
-// wave on to the next one, so the splits of a few neighbouring pixel ranges
-// (the rays towards a grid's corners, say) can fill one segment without losing
-// children while the queue has room elsewhere; only when every segment is full
-// are children lost (an overflow, which the host answers by tracing in smaller
-// chunks).
-constexpr int kStageCap = 32;
-
-template <int NG>
-struct SplitStage {
-  uint64_t* pix;
-  uint32_t* tree;
-  double* r;
-  double* P;                                    // [NG][kStageCap]
-  int count;                                    // wave-uniform
+// The rays of a wave that split go to the wave's current segment of the next
+// level's queue (its home segment at first) through blocks of slots it reserves
+// with one atomic, in coalesced stores. They wait in their idle lanes until the
+// wave refills and are written then, all at once and in lane order: 64 rays that
+// started as neighbouring pixels leave their children as neighbouring pixels,
+// whatever order they split in, so that a wave's rays stay a compact patch of the
+// sphere from level to level (written in the order of their splits, 16 or 32 at
+// a time, every level spread a wave's rays over several times the area, and the
+// deposit cache's lines with them). A slot holds the split ray; its four
+// children are formed when they are claimed, a quarter of the bytes. A segment
+// that is full sends the wave on to the next one, so the splits of a few
+// neighbouring pixel ranges (the rays towards a grid's corners, say) can fill one
+// segment without losing children while the queue has room elsewhere; only when
+// every segment is full are children lost (an overflow, which the host answers
+// by tracing in smaller chunks).
+template <typename R, int NG, bool THIN>
+struct SplitWriter {
   int wseg;                                     // segment of the wave's current reservation
   unsigned long long o_next, o_end;             // the wave's reserved slots of segment wseg
 
   __device__ void init(int home) {
-    __shared__ uint64_t spix[kTraceBlock / kWave][kStageCap];
-    __shared__ uint32_t stree[kTraceBlock / kWave][kStageCap];
-    __shared__ double sr[kTraceBlock / kWave][kStageCap];
-    __shared__ double sP[kTraceBlock / kWave][NG * kStageCap];
-    const int wv = threadIdx.x / kWave;
-    pix = spix[wv]; tree = stree[wv]; r = sr[wv]; P = sP[wv];
-    count = 0;
     wseg = home;
     o_next = o_end = 0;
   }
-  template <typename R>
-  __device__ void write(const TraceArgs<R>& a, int lane) {
-    __builtin_amdgcn_wave_barrier();
-    const unsigned long long need = (unsigned long long)count;
-    unsigned long long done = 0;
+  // the lanes with `split` (all lanes call)
+  __device__ void write(const TraceArgs<R>& a, const Ray<R, NG>& L, bool split, int lane) {
+    const unsigned long long mask = __ballot(split);
+    const int need = __popcll(mask);
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    int done = 0;
     int full = 0;                                           // segments found full in this call
     while (done < need) {
       if (o_next >= o_end) {
-        const unsigned long long want = need - done;
+        const unsigned long long want = (unsigned long long)(need - done);
         const unsigned long long grab = want > a.reserve ? want : a.reserve;
         unsigned long long fresh = 0;
         if (lane == 0) fresh = atomicAdd(&a.ctr->count[a.cout][wseg], grab);
-        fresh = bcast64(fresh, 0);
+        fresh = lane0_64(fresh);
         if (fresh >= a.seg_cap) {
           if (++full >= a.nseg) break;                      // every segment is full
           wseg = (wseg + 1) & (a.nseg - 1);
@@ -1113,56 +1103,39 @@ struct SplitStage {
         o_next = fresh;
         o_end = fresh + grab < a.seg_cap ? fresh + grab : a.seg_cap;
       }
-      const unsigned long long n = need - done < o_end - o_next ? need - done : o_end - o_next;
-      if ((unsigned long long)lane < n) {                   // n <= kStageCap <= 64
-        const unsigned long long slot = (unsigned long long)wseg * a.seg_cap + o_next + lane;
-        const int p = (int)done + lane;
-        a.out.pix[slot] = pix[p];
-        a.out.tree[slot] = tree[p];
-        a.out.r[slot] = r[p];
+      const unsigned long long room = o_end - o_next;
+      const int n = (unsigned long long)(need - done) < room ? need - done : (int)room;
+      if (split && rank >= done && rank < done + n) {
+        const unsigned long long slot = (unsigned long long)wseg * a.seg_cap + o_next + (unsigned)(rank - done);
+        a.out.pix[slot] = L.pix;
+        a.out.tree[slot] = L.tree;
+        a.out.r[slot] = L.g.r;
+        // a thin ray's record carries its remaining column as -4 (1 + rem), an ended group a negative rate
+        if constexpr (THIN) {
+          a.out.P[slot] = L.thin ? -4.0 * (1.0 + L.rem) : L.P[0];
+        } else {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) a.out.P[g * a.out.pstride + slot] = P[g * kStageCap + p];
+          for (int g = 0; g < NG; ++g) a.out.P[g * a.out.pstride + slot] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
+        }
       }
-      o_next += n;
+      o_next += (unsigned long long)n;
       done += n;
     }
-    if (done < need && done + lane < need) {
-      if (lane == 0) atomicOr(&a.ctr->err, kErrOverflow);
-      atomicAdd(&a.ctr->lost_rays, 4ull);
+    if (done < need && lane == 0) {
+      atomicOr(&a.ctr->err, kErrOverflow);
+      atomicAdd(&a.ctr->lost_rays, 4ull * (unsigned long long)(need - done));
     }
-    count = 0;
-    __builtin_amdgcn_wave_barrier();
   }
   // all lanes of the wave, at its end: the unused slots of its last
   // reservation become empty slots
-  template <typename R>
   __device__ void close(const TraceArgs<R>& a, int lane) const {
     for (unsigned long long i = o_next + lane; i < o_end; i += kWave)
       a.out.tree[(unsigned long long)wseg * a.seg_cap + i] = kNoTree;
   }
 };
 
-// PHYS selects the optional physics some tree of the launch asks for:
-// kPhysCover scales deposits by the covering factor (section 2.3), kPhysRadp
-// adds the absorbed momentum E_ph dP / c n to three more sums per cell
-// (radiation pressure, section 2.5.4), kPhysHalt halts every ray at its
-// tree's radius r_halt (time-dependent rays, section 2.1 and section 3.1
-// step 3j): the segment in that cell ends there and the ray, with the
-// photons it still carries, goes to the halt list for the next step.
-// kPhysThin applies the optically-thin approximation (section 2.4, Eq.
-// optthin): a ray whose optical depth from its source stays below tau_thin
-// through a cell removes no photons there, is split against min(1, phi_c)
-// rays per cell face, and sets its tree's mark on the cell (a byte; the rate
-// sigma P / (Omega_ray r_cell^2) is the same for every thin ray of a tree,
-// so finalize adds it once per marked tree); in a cell that holds the source
-// it adds its general deposit to the cell's second sum instead.
-// PHYS = 0 is the plain trace.
-constexpr int kPhysCover = 1, kPhysRadp = 2, kPhysHalt = 4, kPhysThin = 8;
-
 // Waves per SIMD the register budget is set for: three (at most 168 VGPRs),
-// which the LDS of a block (four waves) also allows; two for the
-// radiation-pressure variant with its four-sum deposit table, whose LDS
-// leaves room for two blocks per CU.
+// which the LDS of a block (four waves) also allows.
 //
 // NG: energy groups a ray carries (its tree's pack is at most that; the
 // radiation-pressure and optically-thin variants carry one). With NG > 1 a
@@ -1173,8 +1146,8 @@ constexpr int kPhysCover = 1, kPhysRadp = 2, kPhysHalt = 4, kPhysThin = 8;
 // Traced one group per ray, the 128^3 workload (16 sources, 4 groups) made 895
 // million steps in neutral gas and 2.3 billion in ionised gas; carrying the
 // four groups together makes 580 million of either.
-template <typename R, bool CACHE, int PHYS, int NG>
-__global__ __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(CACHE && (PHYS & kPhysRadp) ? 2 : 3)))
+template <typename R, bool CACHE, int PHYS, int NG, bool PART>
+__global__ __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && NG > 2 ? 2 : 3)))
 void trace_level_kernel(TraceArgs<R> a) {
   constexpr bool COVER = (PHYS & kPhysCover) != 0, RADP = (PHYS & kPhysRadp) != 0, HALT = (PHYS & kPhysHalt) != 0;
   constexpr bool THIN = (PHYS & kPhysThin) != 0;
@@ -1212,19 +1185,22 @@ void trace_level_kernel(TraceArgs<R> a) {
     const unsigned long long waves = (unsigned long long)gridDim.x * (kTraceBlock / kWave);
     unsigned chunk = (unsigned)a.chunk;
     while (chunk >= 2u * kWave && (unsigned long long)chunk * waves > n) chunk >>= 1;
-    s_chunk[threadIdx.x / kWave] = chunk;   // every lane holds the same sum and stores the same value
+    s_chunk[wave_in_block()] = chunk;   // every lane holds the same sum and stores the same value
   }
   // the wave's home segment: it claims there first and writes its splits there
-  const int home = (int)((blockIdx.x * (kTraceBlock / kWave) + threadIdx.x / kWave) % (unsigned)K);
-  const Tracer<R, NG> T(a);
+  const int home = (int)((blockIdx.x * (kTraceBlock / kWave) + wave_in_block()) % (unsigned)K);
+  const Tracer<R, NG, PHYS> T(a);
   Ray<R, NG> L;
   int ended = -1;          // kind of the lane's ray that ended and is not yet tallied
   DepositCache<CACHE, NS> cache;
-  cache.init(lane, a.rec_base);
-  SplitStage<NG> stage;
-  stage.init(home);
+  cache.init(lane);
+  SplitWriter<R, NG, THIN> splits;
+  splits.init(home);
   bool active = false;
-  unsigned steps = 0;
+  int again = kFresh;      // an idle lane whose ray goes on in a new frame
+  int from = 0;            // the cell it comes from
+  unsigned steps = 0;      // of the wave since rays last started in it
+  unsigned framed = 0;     // of the wave since all of its rays last had new frames
   L.ltree = kNoTree;
   L.stat0 = kNoTree;
   L.segs = 0;
@@ -1241,13 +1217,12 @@ void trace_level_kernel(TraceArgs<R> a) {
   // time-dependent rays: the wave's reserved block [h_next, h_end) of the
   // halt list, and the rays it halted in this launch
   unsigned long long h_next = 0, h_end = 0, h_count = 0;
-  // the step's two uniform operands, held in vector registers in the float
-  // kernels: their scalar registers are full, and from there the operands
-  // were reloaded (a kernel-argument load and lane reads of spilled scalars)
-  // at every step; the float64 kernels have no vector registers to spare
+  // the step's column pointer, held in vector registers in the float kernels:
+  // their scalar registers are full, and from there it was reloaded (a
+  // kernel-argument load and lane reads of spilled scalars) at every step; the
+  // float64 kernels have no vector registers to spare
   uint64_t kappa_v = (uint64_t)a.kappa;
-  unsigned max_steps_v = a.max_steps;
-  if constexpr (sizeof(R) == 4) asm volatile("" : "+v"(kappa_v), "+v"(max_steps_v));
+  if constexpr (sizeof(R) == 4) asm volatile("" : "+v"(kappa_v));
   const __attribute__((address_space(1))) R* const kappa_step = (const __attribute__((address_space(1))) R*)kappa_v;
   // the float kernel with the optically-thin approximation gathers the
   // float64 columns instead (the same values before rounding to float), so
@@ -1264,12 +1239,28 @@ void trace_level_kernel(TraceArgs<R> a) {
     // many chunks as that takes), then all of them start in one pass; lanes
     // whose slot turns out empty wait for the next refill.
     const unsigned long long idle = __ballot(!active);
-    if (!drained && idle && (__popcll(idle) >= a.refill || idle == ~0ull)) {
+    const unsigned long long going = __ballot(again != kFresh);
+    if (__builtin_expect((!drained || going) && (idle == ~0ull || (PART && idle && __popcll(idle) >= a.refill)), 0)) {
       if (__ballot(ended >= 0)) {
+        splits.write(a, L, ended == 2, lane);
         tally.ended(a.stats, L, ended, lane);
         ended = -1;
       }
-      unsigned long long left = idle;
+      if constexpr (!PART) {
+        // no lane holds a ray but those going on, of which this is all that is live
+        Ray<R, NG> keep;
+        keep.pix = L.pix; keep.tree = L.tree; keep.q = L.q; keep.segs = L.segs; keep.g.r = L.g.r;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          keep.P[g] = L.P[g];
+          keep.alive[g] = L.alive[g];
+        }
+        if constexpr (THIN) {
+          keep.thin = L.thin; keep.rem = L.rem; keep.tsegs = L.tsegs;
+        }
+        L = keep;
+      }
+      unsigned long long left = drained ? 0ull : idle & ~going;
       bool take = false, child = false;
       unsigned long long q = 0;
       while (left) {
@@ -1291,9 +1282,9 @@ void trace_level_kernel(TraceArgs<R> a) {
                   uniform64(__hip_atomic_load(&head_in[w_seg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
               if (seen < c_size) {
                 unsigned long long b = 0;
-                const unsigned long long chunk = uniform32((int)s_chunk[threadIdx.x / kWave]);
+                const unsigned long long chunk = uniform32((int)s_chunk[wave_in_block()]);
                 if (lane == 0) b = atomicAdd(&head_in[w_seg], chunk);
-                b = bcast64(b, 0);
+                b = lane0_64(b);
                 if (b < c_size) {
                   w_nch = c_nch;
                   w_slo = c_slo;
@@ -1320,9 +1311,9 @@ void trace_level_kernel(TraceArgs<R> a) {
             const unsigned long long s_slo = ((unsigned long long)sg * n_extra) >> kshift;
             const unsigned long long s_size = s_nch + ((((unsigned long long)sg + 1) * n_extra) >> kshift) - s_slo;
             unsigned long long b = 0;
-            const unsigned long long chunk = uniform32((int)s_chunk[threadIdx.x / kWave]);
+            const unsigned long long chunk = uniform32((int)s_chunk[wave_in_block()]);
             if (lane == 0) b = atomicAdd(&head_in[sg], chunk);
-            b = bcast64(b, 0);
+            b = lane0_64(b);
             w_seg = sg;
             if (b < s_size) {
               w_nch = s_nch;
@@ -1346,143 +1337,138 @@ void trace_level_kernel(TraceArgs<R> a) {
         w_next += __popcll(got_mask);
         left &= ~got_mask;
       }
-      if (take) {
-        double r64;
-        if (child) T.fetch_child(L, q, r64);
-        else if (HALT && q < n_held) T.fetch_held(L, q, r64);
-        else T.fetch_seed(L, q - n_held, r64);
-        if (L.tree != kNoTree) {
-          if (L.tree != L.ltree) {
-            T.load_tree(L);
-            if constexpr (THIN) T.load_thin(L);
-          }
-          if constexpr (THIN) T.thin_start(L, !child);
-          R k;
-          if (T.locate(L, r64, k)) {
-            T.begin(L, k);
-            if constexpr (K64) L.kap64 = a.kappa64[L.lin];
-            else if constexpr (THIN) L.kap64 = (double)L.kap;
-            active = true;
-            steps = 0;
-          } else {
-            ended = 0;                     // starts outside the root grid: escaped at once
-          }
+      if (take || again != kFresh) {
+        double r64 = L.g.r;
+        if (take) {
+          if (child) T.fetch_child(L, q, r64);
+          else if (HALT && q < n_held) T.fetch_held(L, q, r64);
+          else T.fetch_seed(L, q - n_held, r64);
         }
+        if (L.tree != kNoTree) {
+          const TreeDev& S = a.trees[L.tree];
+          if (!PART || L.tree != L.ltree) T.load_tree(L, S);
+          if constexpr (THIN) {
+            if (take) T.thin_start(L, S, !child);
+          }
+          active = T.locate(L, S, r64, again, from, L.q);
+          if (!active) ended = 0;            // outside the root grid: escaped
+          else if constexpr (K64) L.kap64 = a.kappa64[L.lin];
+          else if constexpr (THIN) L.kap64 = (double)L.kap;
+        }
+        again = kFresh;
       }
+      if (idle == ~0ull) framed = 0;
+      if (__ballot(take)) steps = 0;
       // the tree of the first ray started is the one the wave's tally follows
-      const unsigned long long started = __ballot(take && L.tree != kNoTree);
+      const unsigned long long started = __ballot(active);
       if (started) tally.follow(a.stats, (uint32_t)__builtin_amdgcn_readlane((int)L.stat0, __ffsll((long long)started) - 1), lane);
       finish_vector_loads();
     }
-    if (!__ballot(active)) {
-      if (drained) break;
+    if (__builtin_expect(!__ballot(active), 0)) {
+      if (drained && !__ballot(again != kFresh)) break;
       continue;
     }
     // ---- one cell: exit plane, split test, deposit, step ----
-    int ax = 0;
-    bool split = false;
-    int e_dir = 0, e_cnew = 0, e_lin = 0;
-    bool e_in = false;
+    // The steps since rays last started bound every active ray's own. The
+    // bound is never reached by a correct trace (cell indices move monotonically).
+    if (__builtin_expect(++steps > a.max_steps, 0)) {
+      if (lane == 0) atomicOr(&a.ctr->err, kErrInternal);
+      break;
+    }
+    if constexpr (sizeof(R) == 4) {
+      if (__builtin_expect(++framed > kResync, 0)) {
+        // every ray in flight goes on in the same cell, its plane distances formed afresh
+        if (active) {
+          again = kResyncFrame;
+          from = L.lin;
+          active = false;
+        }
+        continue;
+      }
+    }
+    Exit x{0.0, false, false};
+    bool split = false, leave = false;
+    int nlin = 0;
     R kpre = (R)0;
     double kpre64 = 0.0;
     bool thin_here = false;
     double tc64 = 0.0;
     if (active) {
-      ax = L.g.exit_axis();
+      x = L.g.exit();
       // the next cell is known from the exit axis alone: its column is
       // gathered now, under the split test, the deposit and its combining
-      // (an index outside the grid reads cell 0 of the batch, unused)
-      e_dir = L.g.dirf(ax) > 0.0f ? 1 : -1;
-      e_cnew = sel3(ax, L.c0, L.c1, L.c2) + e_dir;
-      e_in = (unsigned)e_cnew < (unsigned)sel3(ax, L.n0, L.n1, L.n2);
-      e_lin = L.lin + e_dir * sel3(ax, 1, L.n0, L.n0 * L.n1);
+      // (a step out of the grid reads cell 0 of the batch, unused)
+      leave = x.t >= L.tbox;
+      nlin = L.lin + x.pick(L.st[0], L.st[1], L.st[2]);
       if constexpr (K64) {
-        kpre64 = kappa64_step[e_in ? e_lin : 0];
+        kpre64 = kappa64_step[leave ? 0 : nlin];
       } else {
-        kpre = kappa_step[e_in ? e_lin : 0];
+        kpre = kappa_step[leave ? 0 : nlin];
       }
+      double rs = L.rs;
       if constexpr (THIN) {
         // optically thin in this cell: the optical depth on leaving it, in
         // float64, below tau_thin
         if (L.thin) {
-          const double dr64 = L.g.exit64(ax) - L.g.radius64();
+          const double dr64 = x.t - L.g.r;
           tc64 = dr64 > 0.0 ? L.kap64 * dr64 : 0.0;
           thin_here = tc64 < L.rem;
         }
-        split = T.split_test(L, ax, thin_here);
-      } else {
-        split = T.split_test(L, ax);
+        rs = thin_here ? L.rs_thin : rs;
       }
+      if (x.t > rs) split = T.splits(L, x.t, thin_here);
     }
-    for (unsigned long long smask = __ballot(split); smask;) {
-      // as many of the splitting lanes as the stage has room for; a full stage is written out
-      if (stage.count == kStageCap) stage.write(a, lane);
-      const int e = stage.count + __popcll(smask & below);
-      const bool put = ((smask >> lane) & 1ull) && e < kStageCap;
-      if (put) {
-        stage.pix[e] = L.pix;
-        stage.tree[e] = L.tree;
-        stage.r[e] = L.g.radius64();
-        // a thin ray's record carries its remaining column as -4 (1 + rem), an ended group a negative rate
-        if constexpr (THIN) {
-          stage.P[e] = L.thin ? -4.0 * (1.0 + L.rem) : L.P[0];
-        } else {
-#pragma unroll
-          for (int g = 0; g < NG; ++g) stage.P[g * kStageCap + e] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
-        }
-        ended = 2;
-        active = false;
-      }
-      const unsigned long long done = __ballot(put);
-      stage.count += __popcll(done);
-      smask &= ~done;
+    if (split) {
+      ended = 2;
+      active = false;
     }
     bool dep = false, moved = false;
     uint32_t dkey = 0;
     double dval = 0.0, hval = 0.0, mval = 0.0;   // absorbed rate, its energy moment, momentum rate
-    int s_ax = 0, s_dir = 0;
+    const int here = L.lin;
+    const uint32_t yz = L.yz;
     bool halt = false;
     if (active) {
-      R dr = L.g.chord(ax);
-      bool pos = L.g.positive(dr, ax);
+      double dr = x.t - L.g.r;
+      bool pos = L.g.positive(dr, x.t);
       if constexpr (HALT) {
         // the ray reaches its halting radius inside this cell: the segment ends there
-        if (L.g.exit64(ax) > L.rhalt) {
+        if (x.t > L.rhalt) {
           halt = true;
-          dr = (R)(L.rhalt - L.g.radius64());
-          pos = dr > (R)0;
+          dr = L.rhalt - L.g.r;
+          pos = dr > 0.0;
         }
       }
       if (THIN && pos && thin_here) {
         // thin: no photons removed
         if (T.holds_source(L)) {
           double Pc = L.P[0];
-          dval = absorb(Pc, L.kap * L.sigma[0] * dr);
+          dval = absorb(Pc, L.kap * L.sigma[0] * (R)dr);
           if constexpr (COVER) {
-            if (L.cover) dval *= T.covering_factor(L, (double)dr);
+            if (L.lpix > 0.0) dval *= T.covering_factor(L, dr);
           }
           dkey = L.slot0 + L.astride * (uint32_t)L.lin + 1u;
           dep = true;
-        } else if (sizeof(R) == 4 || (double)dr > L.g.exit64(ax) * 0x1p-40) {
+        } else if (dr > x.t * 0x1p-40) {
           // the tree's mark on the cell: a plain byte store (every thin ray
           // of the tree that crosses the cell stores the same 1); a segment
           // shorter than 2^-40 of its exit radius (a ray through an edge or
-          // a corner) does not cross the cell, which the float path's
-          // plane-tie test already decides
+          // a corner) does not cross the cell
           a.mark[L.mark_base + (long long)L.lin] = 1;
         }
         L.rem -= tc64;
         L.segs++;
         L.tsegs++;
-        L.g.advance(ax);
+        L.g.r = x.t;
       } else if (pos) {
+        const R col = L.kap * (R)dr;
         if constexpr (NG == 1) {
-          dval = absorb(L.P[0], L.kap * L.sigma[0] * dr);
+          dval = absorb(L.P[0], col * L.sigma[0]);
         } else {
 #pragma unroll
           for (int g = 0; g < NG; ++g) {
             if (!__ballot(L.alive[g])) continue;
-            const double d = absorb(L.P[g], L.kap * L.sigma[g] * dr);   // 0 for an ended group's P = 0
+            const double d = absorb(L.P[g], col * L.sigma[g]);   // 0 for an ended group's P = 0
             dval += d;
             hval = fma(d, L.eexc[g], hval);
           }
@@ -1493,8 +1479,8 @@ void trace_level_kernel(TraceArgs<R> a) {
           mval = dval * L.mscale;
         }
         if constexpr (COVER) {
-          if (L.cover) {
-            const double fc = T.covering_factor(L, (double)dr);
+          if (L.lpix > 0.0) {
+            const double fc = T.covering_factor(L, dr);
             dval *= fc;
             hval *= fc;
           }
@@ -1502,19 +1488,14 @@ void trace_level_kernel(TraceArgs<R> a) {
         dkey = NS > 1 || THIN ? L.slot0 + L.astride * (uint32_t)L.lin : L.slot0 + (uint32_t)L.lin;
         dep = true;
         L.segs++;
-        if (HALT && halt) L.g.set_radius(L.rhalt);
-        else L.g.advance(ax);
+        L.g.r = HALT && halt ? L.rhalt : x.t;
       }
     }
     if (active && !(HALT && halt)) {
       // step across the exit face
-      const int dir = e_dir;
-      const int cnew = e_cnew;
-      L.c0 = ax == 0 ? cnew : L.c0;
-      L.c1 = ax == 1 ? cnew : L.c1;
-      L.c2 = ax == 2 ? cnew : L.c2;
-      L.lin = e_lin;
-      L.g.step(ax, cnew);
+      L.lin = nlin;
+      L.yz += (uint32_t)x.pick(0, L.sy, L.sz);
+      L.g.step(x);
       if constexpr (NG == 1) {
         if (L.P[0] < L.pmin[0]) {
           ended = 1;
@@ -1523,7 +1504,7 @@ void trace_level_kernel(TraceArgs<R> a) {
       } else {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-          if (L.alive[g] && L.P[g] < L.pmin[g]) {
+          if (__builtin_expect(L.alive[g] && L.P[g] < L.pmin[g], 0)) {
             tally.truncated(a.stats, L, g);
             L.alive[g] = false;
             L.P[g] = 0.0;
@@ -1531,17 +1512,7 @@ void trace_level_kernel(TraceArgs<R> a) {
         }
         if (!L.any_alive()) active = false;
       }
-      if (!active) {
-      } else if (++steps > max_steps_v) {
-        // cell indices move monotonically, so this bound is never reached by a correct trace
-        atomicOr(&a.ctr->err, kErrInternal);
-        ended = 0;
-        active = false;
-      } else {
-        s_ax = ax;
-        s_dir = dir;
-        moved = true;
-      }
+      moved = active;
     }
     if constexpr (HALT) {
       // halted rays of the wave take consecutive records of its reserved
@@ -1555,7 +1526,7 @@ void trace_level_kernel(TraceArgs<R> a) {
         unsigned long long nb = 0;
         if (n > room) {
           if (lane == 0) nb = atomicAdd(&a.ctr->halt_count, (unsigned long long)kHaltBlock);
-          nb = bcast64(nb, 0);
+          nb = lane0_64(nb);
         }
         if (halt) {
           const unsigned long long rank = (unsigned long long)__popcll(hm & below);
@@ -1563,7 +1534,7 @@ void trace_level_kernel(TraceArgs<R> a) {
           if (i < a.halt_cap) {
             a.halt.pix[i] = L.pix;
             a.halt.tree[i] = L.tree;
-            a.halt.r[i] = dep ? L.rhalt : L.g.radius64();
+            a.halt.r[i] = L.g.r;
 #pragma unroll
             for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
             a.halt_lev[i] = a.gen;
@@ -1587,17 +1558,17 @@ void trace_level_kernel(TraceArgs<R> a) {
       // for a problem that does not ask for it: its key is a one-sum slot)
       double v[NS] = {dval, 0.0, 0.0, 0.0};
       if (dep && mval != 0.0) {
-        v[1] = mval * L.g.dir64(0);
-        v[2] = mval * L.g.dir64(1);
-        v[3] = mval * L.g.dir64(2);
+        v[1] = mval * L.d[0];
+        v[2] = mval * L.d[1];
+        v[3] = mval * L.d[2];
       }
-      cache.add(a.acc, dkey, v, dep, lane);
+      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
     } else if constexpr (NS == 2) {
       const double v[NS] = {dval, hval};
-      cache.add(a.acc, dkey, v, dep, lane);
+      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
     } else {
       const double v[NS] = {dval};
-      cache.add(a.acc, dkey, v, dep, lane);
+      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
     }
     // the gathered column is taken on every path, so that no load is in
     // flight across the loop's back edge
@@ -1609,25 +1580,25 @@ void trace_level_kernel(TraceArgs<R> a) {
     } else {
       asm volatile("" ::"v"(kpre));
     }
-    const bool kneg = moved && (!e_in || kpre < (R)0);
+    const bool kneg = moved && (leave || kpre < (R)0);
     L.kap = (moved && !kneg) ? kpre : L.kap;
     if constexpr (THIN) L.kap64 = (moved && !kneg) ? (K64 ? kpre64 : (double)kpre) : L.kap64;
-    if (kneg && !T.settle(L, s_ax, s_dir)) {
-      ended = 0;
+    if (kneg) {
+      // out of the root grid, or into another frame
       active = false;
-    }
-    if constexpr (K64) {
-      if (kneg && active) {
-        L.kap64 = a.kappa64[L.lin];
-        finish_vector_loads();
+      if (leave && L.root) {
+        ended = 0;
+      } else {
+        again = kCross + x.axis();
+        from = here;
       }
-    } else if constexpr (THIN) {
-      if (kneg) L.kap64 = (double)L.kap;
     }
   }
-  if (stage.count) stage.write(a, lane);
   cache.flush(a.acc, lane);
-  if (__ballot(ended >= 0)) tally.ended(a.stats, L, ended, lane);
+  if (__ballot(ended >= 0)) {
+    splits.write(a, L, ended == 2, lane);
+    tally.ended(a.stats, L, ended, lane);
+  }
   tally.flush(a.stats, lane);
   if constexpr (HALT) {
     // the unfilled rest of the wave's last block: empty records (no photons,
@@ -1644,7 +1615,7 @@ void trace_level_kernel(TraceArgs<R> a) {
     if (lane == 0 && h_count) atomicAdd(&a.ctr->halt_levels[a.gen], h_count);
   }
   // unused slots of the wave's last reserved block become empty slots
-  stage.close(a, lane);
+  splits.close(a, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1872,12 +1843,12 @@ template <typename R, int PHYS, int NG>
 static void launch_one(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
   if (cache) {
     static int plain = 0, mine = 0;
-    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1>, plain);
-    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG>, mine);
+    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1, false>, plain);
+    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG, false>, mine);
     if (m < p) blocks = (blocks * m + p - 1) / p;
-    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG, false>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   } else {
-    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG, false>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   }
 }
 
@@ -1998,8 +1969,8 @@ hipError_t trace_occupancy(int precision, bool cache, int* blocks_per_cu) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, kernel, kTraceBlock, 0);
   };
   if (precision == 0)
-    return cache ? ask(trace_level_kernel<double, true, 0, 1>) : ask(trace_level_kernel<double, false, 0, 1>);
-  return cache ? ask(trace_level_kernel<float, true, 0, 1>) : ask(trace_level_kernel<float, false, 0, 1>);
+    return cache ? ask(trace_level_kernel<double, true, 0, 1, false>) : ask(trace_level_kernel<double, false, 0, 1, false>);
+  return cache ? ask(trace_level_kernel<float, true, 0, 1, false>) : ask(trace_level_kernel<float, false, 0, 1, false>);
 }
 
 }  // namespace moray

@@ -322,12 +322,11 @@ void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const
     d.P0[k] = Sp.photon_frac[g] * S.ndot / npix0;
     d.pmin0[k] = P.params.p_min_frac * d.P0[k];
     d.sigma64[k] = Sp.sigma_cm2[g];
-    d.sigma32[k] = (float)Sp.sigma_cm2[g];
     if (pd.acc_mode == kAccMoments) d.eexc[k] = (Sp.energy_ev[g] - Sp.e_ion_ev) * kEvErgConst;
   }
   d.n_grp = n;
   d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
-  d.split_t2_base = P.params.phi_c > 0.0 ? (float)(12.0 / (4.0 * kPiConst * P.params.phi_c)) : FLT_MAX;
+  d.split_r = P.params.phi_c > 0.0 ? std::sqrt(12.0 / d.four_pi_phi_c) : HUGE_VAL;
   d.acc_stride = (uint32_t)pd.acc_stride;
   const long long plane = pd.acc_planes > 1 ? g0 : 0;
   d.acc_slot = pd.acc_off + (long long)pd.acc_stride * (plane * pd.n_cells - pd.cell_off);
@@ -563,6 +562,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     pd.acc_mode = own ? kAccThin : (packed && pd.n_groups > 1 ? kAccMoments : kAccSums);
     pd.acc_stride = pd.acc_mode == kAccSums ? 1 : 2;
     pd.acc_planes = pd.acc_mode == kAccMoments ? 1 : pd.n_groups;
+    n_plain = (n_plain + 7) & ~7LL;          // a 64-byte line holds sums of one problem
     pd.acc_off = n_plain;
     n_plain += pd.acc_stride * pd.acc_planes * pd.n_cells;
   }
@@ -644,7 +644,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
       const double dx_root = P.grids[0].dx_cm;
       d.tau_thin = P.params.tau_thin;
       d.four_pi_phi_thin = 4.0 * kPiConst * phi_thin;
-      d.split_t2_thin = phi_thin > 0.0 ? (float)(12.0 / (4.0 * kPiConst * phi_thin)) : FLT_MAX;
+      d.split_r_thin = phi_thin > 0.0 ? std::sqrt(12.0 / d.four_pi_phi_thin) : HUGE_VAL;
       d.mark_base = pd.mark_off + (long long)t * pd.n_cells - pd.cell_off;
       d.thin_coef = d.sigma64[0] * (d.P0[0] * std::ldexp(12.0, 2 * P.params.level_init)) /
                     (4.0 * kPiConst * dx_root * dx_root);
@@ -875,7 +875,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
           using R = decltype(zero);
           TraceArgs<R> A{};
           A.grids = (GridDev*)c->grids.p; A.trees = (TreeDev*)c->trees.p; A.kappa = (R*)c->kappa.p;
-          A.acc = (double*)c->acc.p; A.rec_base = (uint32_t)rec_base; A.in = queue(l & 1); A.out = queue((l + 1) & 1);
+          A.acc = (double*)c->acc.p; A.in = queue(l & 1); A.out = queue((l + 1) & 1);
           A.seg_cap = seg_cap; A.nseg = nseg; A.ctr = ctr; A.stats = stats; A.gen = l; A.cin = l; A.cout = l + 1;
           A.seed_level = l;
           A.seed_begin = lo < hi ? lo : 0; A.seed_end = lo < hi ? hi : 0;
