@@ -30,6 +30,10 @@
 
 namespace moray {
 
+// The active lanes where p holds, from its lane mask itself (an int predicate
+// costs a select and a compare).
+__device__ __forceinline__ unsigned long long wave_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
 // ---------------------------------------------------------------------------
 // HEALPix nested pixel centre (Gorski et al. 2005), float64.
 // Face f, in-face coordinates (ix, iy) from the even/odd bits of the in-face
@@ -184,20 +188,24 @@ constexpr int kPhysCover = 1, kPhysRadp = 2, kPhysHalt = 4, kPhysThin = 8;
 // ---------------------------------------------------------------------------
 constexpr double kFar = 1e300;
 
-// v_min_f64 alone (fmin would first quiet its operands, which are never NaN here)
+// v_min_f64 and v_max_f64 alone (fmin and fmax would first quiet their operands,
+// which are never NaN here)
 __device__ __forceinline__ double min_f64(double x, double y) {
   double r;
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
   return r;
 }
-// x where m, else 0, for an x whose low word is 0 (one select)
-__device__ __forceinline__ double masked_hi(bool m, int hi) { return __hiloint2double(m ? hi : 0, 0); }
+__device__ __forceinline__ double max_f64(double x, double y) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
 
 // The current cell's exit: distance, and which axis (neither flag: x). Ties go
 // to the lowest axis.
 struct Exit {
   double t;
-  bool y, z;
+  bool y, z;               // z overrides y
   __device__ int axis() const { return z ? 2 : (y ? 1 : 0); }
   template <typename T> __device__ T pick(T a, T b, T c) const { return z ? c : (y ? b : a); }
 };
@@ -251,12 +259,15 @@ struct Geom64 {
     e.z = t[2] < m;
     return e;
   }
-  __device__ void step(const Exit& e) {
+  __device__ void step(const Exit& e, const int (&st)[3], int sy, int sz, int& lin, uint32_t& yz) {
+    const bool ax[3] = {!e.y && !e.z, e.y && !e.z, e.z};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      b[k] += masked_hi(k == 2 ? e.z : (k == 1 ? e.y && !e.z : !e.y && !e.z), sgn[k]);
+      b[k] += __hiloint2double(ax[k] ? sgn[k] : 0, 0);
       t[k] = quotient(k, b[k]);                    // (b - s) kFar and more without a component: far
     }
+    lin += e.pick(st[0], st[1], st[2]);
+    yz += (uint32_t)e.pick(0, sy, sz);
   }
   // a segment counts when it is longer than 0
   static __device__ bool positive(double dr, double) { return dr > 0.0; }
@@ -266,14 +277,13 @@ struct Geom64 {
 };
 
 // Mixed mode: the planes of an axis are equally spaced, so a step adds the
-// spacing e = 1/|d| to that axis' t: one select and one fma per axis, against the
-// plane coordinate, its difference from the source, the product and its error
-// terms. A t that has been stepped N times is off by at most N/2 of its ulps;
+// spacing e = 1/|d| to that axis' t, against the plane coordinate, its
+// difference from the source, the product and its error terms. A t that has been stepped N times is off by at most N/2 of its ulps;
 // kResync steps, after which t is formed afresh, keep that below 2^-42 of t.
 // Segments shorter than 2^-40 of their exit radius are plane ties (dr = 0 in
 // exact arithmetic, or a length no float64 coordinate resolves) and are not
 // counted.
-constexpr int kResync = 2048;
+constexpr unsigned kResync = 2048;
 struct Geom32 {
   double t[3], e[3];       // distance to the next plane, spacing (0: no component along the axis)
   double r;
@@ -314,10 +324,32 @@ struct Geom32 {
     x.z = t[2] < m;
     return x;
   }
-  __device__ void step(const Exit& x) {
-    t[0] = fma(masked_hi(!x.y && !x.z, 0x3ff00000), e[0], t[0]);
-    t[1] = fma(masked_hi(x.y && !x.z, 0x3ff00000), e[1], t[1]);
-    t[2] = fma(masked_hi(x.z, 0x3ff00000), e[2], t[2]);
+  // Across the exit face, in every lane of the wave (a lane without a ray steps
+  // over values nothing reads): t, the cell index and its yz, axis by axis under
+  // the axis' lane mask, which takes 8 vector instructions where selects take 18.
+  __device__ void step(const Exit& x, const int (&st)[3], int sy, int sz, int& lin, uint32_t& yz) {
+    const unsigned long long mz = wave_mask(x.z), my = wave_mask(x.y);
+    unsigned long long all, m;
+    asm volatile(
+        "s_mov_b64 %[all], exec\n\t"
+        "s_or_b64 %[m], %[my], %[mz]\n\t"
+        "s_andn2_b64 exec, %[all], %[m]\n\t"
+        "v_add_f64 %[t0], %[t0], %[e0]\n\t"
+        "v_add_u32 %[lin], %[lin], %[s0]\n\t"
+        "s_andn2_b64 exec, %[my], %[mz]\n\t"
+        "v_add_f64 %[t1], %[t1], %[e1]\n\t"
+        "v_add_u32 %[lin], %[lin], %[s1]\n\t"
+        "v_add_u32 %[yz], %[yz], %[sy]\n\t"
+        "s_mov_b64 exec, %[mz]\n\t"
+        "v_add_f64 %[t2], %[t2], %[e2]\n\t"
+        "v_add_u32 %[lin], %[lin], %[s2]\n\t"
+        "v_add_u32 %[yz], %[yz], %[sz]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [t0] "+v"(t[0]), [t1] "+v"(t[1]), [t2] "+v"(t[2]), [lin] "+v"(lin), [yz] "+v"(yz), [all] "=&s"(all),
+          [m] "=&s"(m)
+        : [e0] "v"(e[0]), [e1] "v"(e[1]), [e2] "v"(e[2]), [s0] "v"(st[0]), [s1] "v"(st[1]), [s2] "v"(st[2]),
+          [sy] "v"(sy), [sz] "v"(sz), [my] "s"(my), [mz] "s"(mz)
+        : "scc");
   }
   static __device__ bool positive(double dr, double t) { return fma(t, -0x1p-40, dr) > 0.0; }
   __device__ double hloc() const { return 1.0 / hinv; }
@@ -373,7 +405,7 @@ __device__ __forceinline__ double absorb(double& P, float y) {
   q = fmaf(y, q, 0.69314718056f);
   const float f = y * q;
   const bool thick = y > 0.5f;
-  if (!__ballot(thick)) {
+  if (!wave_mask(thick)) {
     const double dP = P * (double)f;
     P -= dP;
     return dP;
@@ -388,6 +420,7 @@ constexpr double kLog2e = 1.4426950408889634074;
 template <typename R> constexpr double kSigmaScale = sizeof(R) == 4 ? kLog2e : 1.0;
 
 constexpr int kZShift = 13;      // see line_index
+constexpr unsigned kNoCut = 0xffffffffu;
 
 // Per-lane ray state. A ray carries NG energy groups of its source: they share
 // its geometry, and each has its own photon rate, cross-section and end. Only
@@ -396,7 +429,7 @@ constexpr int kZShift = 13;      // see line_index
 template <typename R, int NG>
 struct Ray {
   typename GeomOf<R>::type g;
-  double rs, tbox;        // a step whose exit lies beyond rs may split, at tbox or beyond leaves the grid
+  double rs, tbox;        // a step whose exit lies beyond rs splits the ray, at tbox or beyond leaves the grid
   int st[3];              // what crossing a plane of each axis adds to lin
   int lin;                // batch-wide cell index
   uint32_t yz;            // the local cell's j + (k << kZShift)
@@ -406,7 +439,8 @@ struct Ray {
   uint64_t pix;
   uint32_t tree;
   double P[NG], pmin[NG];
-  bool alive[NG];         // groups the ray still carries (an ended group's P is 0)
+  bool alive[NG];         // groups the ray still carries
+  unsigned cut[NG];       // of a group truncated in this flight, its segments (its P is what it had left); kNoCut: not
   uint32_t slot0;         // the ray's accumulator of cell lin is acc[slot0 + astride * lin]
   uint32_t astride;
   R sigma[NG];
@@ -430,13 +464,6 @@ struct Ray {
   double rs_thin;
   long long mark_base;
   unsigned tsegs;         // the ray's thin segments
-
-  __device__ bool any_alive() const {
-    bool m = alive[0];
-#pragma unroll
-    for (int g = 1; g < NG; ++g) m = m || alive[g];
-    return m;
-  }
 };
 
 // Why an idle lane's ray goes on: with a new frame after it crossed into or out
@@ -455,13 +482,25 @@ struct Tracer {
   __device__ explicit Tracer(const TraceArgs<R>& args) : a(args) {}
 
   // Radius (root cells) beyond which an exit splits a ray of `level`: the
-  // canonical test 12 * 4^l < (4 pi phi) u^2, u the exit distance in local cells,
-  // solved for it. The float64 mode takes it a little short, and decides exits
-  // within 2^-37 of it by the test itself (splits()).
-  static __device__ double split_radius(double split_r, int level, int level_max, double hinv) {
+  // canonical test 12 * 4^l < (4 pi phi) u^2, u = t h the exit distance in local
+  // cells, solved for t. The float64 mode moves it to the largest t that fails
+  // the test as float64 evaluates it (which is monotonic in t), so that
+  // comparing with it is the test.
+  static __device__ double split_radius(double split_r, double four_pi_phi, int level, int level_max, bool child) {
     if (level >= level_max) return __builtin_huge_val();
-    const double rs = ldexp(split_r, level) * hinv;
-    return sizeof(R) == 4 ? rs : rs * (1.0 - 0x1p-38);
+    const double h = child ? 2.0 : 1.0;
+    double rs = ldexp(split_r, level) / h;
+    if constexpr (sizeof(R) == 8) {
+      const double need = ldexp(12.0, 2 * level);
+      auto test = [&](double t) { return need < four_pi_phi * ((t * h) * (t * h)); };
+      for (int i = 0; i < 8 && test(rs); ++i) rs = __longlong_as_double(__double_as_longlong(rs) - 1);
+      for (int i = 0; i < 8; ++i) {
+        const double up = __longlong_as_double(__double_as_longlong(rs) + 1);
+        if (test(up)) break;
+        rs = up;
+      }
+    }
+    return rs;
   }
   __device__ int level_of(const TreeDev& S) const { return S.level_init + (a.gen - S.gen0); }
 
@@ -483,8 +522,8 @@ struct Tracer {
     L.g.frame(sl, c, n, child, L.tbox);
     const int level = level_of(S);
     const double hinv = child ? 0.5 : 1.0;
-    L.rs = split_radius(S.split_r, level, S.level_max, hinv);
-    if constexpr (THIN) L.rs_thin = split_radius(S.split_r_thin, level, S.level_max, hinv);
+    L.rs = split_radius(S.split_r, S.four_pi_phi_c, level, S.level_max, child);
+    if constexpr (THIN) L.rs_thin = split_radius(S.split_r_thin, S.four_pi_phi_thin, level, S.level_max, child);
     if constexpr (COVER) {
       // sqrt(pi/3) 2^-l, the pixel's width at unit distance
       L.lpix = S.covering ? ldexp(1.0233267079464885, -level) / hinv : 0.0;
@@ -669,7 +708,7 @@ struct Tracer {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         L.alive[g] = NG == 1 || (g < S.n_grp && L.P[g] >= 0.0);   // a record may hold fewer rates than NG
-        if (NG > 1) L.P[g] = L.alive[g] ? L.P[g] : 0.0;
+        L.cut[g] = kNoCut;
       }
       q = S.root_grid;
       c[0] = cell_rule(x[0], v[0]); c[1] = cell_rule(x[1], v[1]); c[2] = cell_rule(x[2], v[2]);
@@ -688,16 +727,6 @@ struct Tracer {
     frame(L, S, q, c);
     L.kap = a.kappa[L.lin];
     return true;
-  }
-
-  // An exit beyond the split radius: does the ray split? (Mixed mode: yes.)
-  __device__ bool splits(const L_t& L, double te, bool thin) const {
-    if (sizeof(R) == 4 || te > (thin ? L.rs_thin : L.rs) * (1.0 + 0x1p-37)) return true;
-    const TreeDev& S = a.trees[L.tree];
-    const double u = L.q != S.root_grid ? 2.0 * te : te;
-    const bool sp = ldexp(12.0, 2 * level_of(S)) < (thin ? S.four_pi_phi_thin : S.four_pi_phi_c) * (u * u);
-    finish_vector_loads();
-    return sp;
   }
 
   // Covering factor of the segment that starts at the current radius R_0 and
@@ -757,6 +786,10 @@ __device__ __forceinline__ unsigned long long lane0_64(unsigned long long v) {
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 0);
   return ((unsigned long long)hi << 32) | lo;
 }
+// the lane's place among the lanes of a mask
+__device__ __forceinline__ int lane_rank(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
 __device__ __forceinline__ int wave_in_block() { return uniform32((int)(threadIdx.x / kWave)); }
 
 // Sums over the 64 lanes of a wave in which every lane is active (data-parallel
@@ -792,8 +825,8 @@ __device__ __forceinline__ T wave_total(T x) {     // valid in the last lane
 // rates from one reduction, so a ray end puts no atomic into the memory
 // counter the next column gather waits on (a global atomic per ray end took
 // the 128^3 workload, 16 sources and 4 groups, from 11.7 to 21 ms).
-// kind: 0 escaped, 1 truncated, 2 split, 3 halted (its segments only: the
-// photons it holds are summed from the halt list).
+// kind: 0 escaped, 1 every group truncated, 2 split, 3 halted (its segments only:
+// the photons it holds are summed from the halt list).
 template <int NG, bool THIN>
 struct WaveTally {
   static constexpr int kRows = 5;                  // segs, splits, n_esc, n_trunc, thin_segs
@@ -852,34 +885,24 @@ struct WaveTally {
       unsafeAtomicAdd(&st.trunc_P, P);
     }
   }
-  // group g of the calling lane's ray is truncated (any subset of lanes)
-  template <typename RAY>
-  __device__ void truncated(SgStats* stats, const RAY& L, int g) {
-    if (L.stat0 == stat0) {
-      __hip_atomic_fetch_add(&cnt[g], (unsigned long long)L.segs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&cnt[3 * NG + g], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&sum[NG + g], L.P[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-      direct(stats[L.stat0 + g], L.segs, 0u, 1, L.P[g]);
-    }
-  }
-  // the groups still alive of every lane whose ray ended with `kind` >= 0 (all lanes)
+  // every lane whose ray ended with `kind` >= 0 (all lanes): its groups, those
+  // truncated in this flight and those that ended with the ray
   template <typename RAY>
   __device__ void ended(SgStats* stats, const RAY& L, int kind, int lane) {
-    const bool here = kind >= 0 && L.stat0 == stat0;
+    const bool over = kind >= 0;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      const bool mine = kind >= 0 && L.alive[g];
-      const bool in = here && L.alive[g];
-      if (!__ballot(mine)) continue;
-      const unsigned segs = wave_total(in ? L.segs : 0u);
-      const unsigned tsegs = THIN ? wave_total(in ? L.tsegs : 0u) : 0u;
-      const int n_esc = __popcll(__ballot(in && kind == 0)), n_trunc = __popcll(__ballot(in && kind == 1));
-      const int n_split = __popcll(__ballot(in && kind == 2));
-      const double esc = n_esc ? wave_total(in && kind == 0 ? L.P[g] : 0.0) : 0.0;
-      const double trunc = n_trunc ? wave_total(in && kind == 1 ? L.P[g] : 0.0) : 0.0;
+      const bool cut = over && !L.alive[g] && L.cut[g] != kNoCut, live = over && L.alive[g];
+      if (!wave_mask(cut || live)) continue;
+      const bool here = L.stat0 == stat0;
+      const unsigned mine = live ? L.segs : L.cut[g];
+      const unsigned segs = wave_total(here && (cut || live) ? mine : 0u);
+      const unsigned tsegs = THIN ? wave_total(here && (cut || live) ? L.tsegs : 0u) : 0u;
+      const int n_esc = __popcll(wave_mask(here && live && kind == 0)), n_trunc = __popcll(wave_mask(here && cut));
+      const int n_split = __popcll(wave_mask(here && live && kind == 2));
+      const double esc = n_esc ? wave_total(here && live && kind == 0 ? L.P[g] : 0.0) : 0.0;
+      const double trunc = n_trunc ? wave_total(here && cut ? L.P[g] : 0.0) : 0.0;
       if (lane == kWave - 1) {
-        // the wave's only writer here; truncated() adds atomically, at other times
         cnt[g] += segs;
         if (n_split) cnt[NG + g] += (unsigned)n_split;
         if (n_esc) {
@@ -892,7 +915,8 @@ struct WaveTally {
         }
         if (THIN) cnt[4 * NG + g] += tsegs;
       }
-      if (mine && !in) direct(stats[L.stat0 + g], L.segs, THIN ? L.tsegs : 0u, kind, L.P[g]);
+      if ((cut || live) && !here)
+        direct(stats[L.stat0 + g], mine, THIN ? L.tsegs : 0u, cut ? 1 : kind, L.P[g]);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -976,20 +1000,39 @@ struct DepositCache {
       __builtin_amdgcn_wave_barrier();
     }
   }
-  // Every lane of the wave calls this (uniform control flow); one pass per
-  // call. First every depositing lane reads its entry's line, exchanges its own
-  // in, and reads the entry again: the last read tells which line owns the
+  // A deposit takes two calls, made by every lane of the wave (uniform control
+  // flow), so that the arithmetic of the deposit runs under the first's round
+  // trip. probe: every depositing lane reads its entry's line, exchanges its own
+  // in, and reads the entry again; the last read tells which line owns the
   // entry from now on (lanes of different lines race for it; the last one wins).
-  // Where that differs from the first, the entry's sums belong to the old line:
-  // the lane whose exchange returned it (the first in the race; a lane that
-  // holds the old line itself can make it several) lists the entry, and eight
-  // lanes per listed entry exchange zeros in and move the old sums to the
-  // buffer (an entry listed twice moves zeros the second time). Then the lanes of
-  // the owning line add their deposits, and those of a losing line add theirs to
-  // memory. The LDS operations of a wave are performed in order, so no wait
+  // add: where the owner differs from the line before, the entry's sums belong to
+  // that: the lane whose exchange returned it (the first in the race; a
+  // lane that holds the old line itself can make it several) lists the entry,
+  // and eight lanes per listed entry exchange zeros in and move the old sums to
+  // the buffer (an entry listed twice moves zeros the second time). Then the lanes
+  // of the owning line add their deposits, and those of a losing line add theirs
+  // to memory. The LDS operations of a wave are performed in order, so no wait
   // separates the exchanges from the adds. The phases are separated by wave
   // barriers, which keep the compiler from merging them.
-  __device__ void add(double* acc, uint32_t slot, uint32_t yz, uint32_t sums, const double (&v)[NS], bool has, int lane) {
+  struct Probe {
+    uint32_t h, was, before, owner;
+  };
+  __device__ __forceinline__ Probe probe(uint32_t slot, uint32_t yz, bool has) {
+    Probe p{0u, kNoSlot, kNoSlot, kNoSlot};
+    if constexpr (CACHE) {
+      if (has) {
+        const uint32_t line = slot >> 3;
+        p.h = line_index(line, yz);
+        p.was = __hip_atomic_load(&key[p.h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        p.before = __hip_atomic_exchange(&key[p.h], line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        p.owner = __hip_atomic_load(&key[p.h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    return p;
+  }
+  __device__ __forceinline__ void add(double* acc, const Probe& p, uint32_t slot, uint32_t sums, const double (&v)[NS],
+                                      bool has, int lane) {
     if constexpr (!CACHE) {
       if (has) {
 #pragma unroll
@@ -998,24 +1041,11 @@ struct DepositCache {
       }
       return;
     }
-    if (!__ballot(has)) return;
-    const uint32_t line = slot >> 3;
-    uint32_t h = 0, was = kNoSlot, before = kNoSlot, owner = kNoSlot;
-    if (has) {
-      h = line_index(line, yz);
-      was = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      before = __hip_atomic_exchange(&key[h], line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      owner = __hip_atomic_load(&key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __builtin_amdgcn_wave_barrier();
-    const bool displace = has && owner != was && before == was && was != kNoSlot;
-    const unsigned long long dmask = __ballot(displace);
+    const bool displace = has && p.owner != p.was && p.before == p.was && p.was != kNoSlot;
+    const unsigned long long dmask = wave_mask(displace);
     if (dmask) {
       const int n = __popcll(dmask);
-      if (displace) {
-        const int i = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(dmask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)dmask, 0u));
-        moves[i] = make_uint2(h, was);
-      }
+      if (displace) moves[lane_rank(dmask)] = make_uint2(p.h, p.was);
       __builtin_amdgcn_wave_barrier();
       for (int i0 = 0; i0 < n; i0 += 8) {
         const int m = n - i0 < 8 ? n - i0 : 8;
@@ -1031,8 +1061,8 @@ struct DepositCache {
         __builtin_amdgcn_wave_barrier();
       }
     }
-    const bool mine = has && owner == line;
-    double* cell = &val[8 * h + (slot & 7u)];
+    const bool mine = has && p.owner == slot >> 3;
+    double* cell = &val[8 * p.h + (slot & 7u)];
     if (mine) {
 #pragma unroll
       for (int c = 0; c < NS; ++c)
@@ -1040,10 +1070,12 @@ struct DepositCache {
           __hip_atomic_fetch_add(cell + c, v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
-    if (has && !mine) {
+    if (wave_mask(has && !mine)) {
+      if (has && !mine) {
 #pragma unroll
-      for (int c = 0; c < NS; ++c)
-        if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
+        for (int c = 0; c < NS; ++c)
+          if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
+      }
     }
   }
   __device__ void flush(double* acc, int lane) {
@@ -1083,9 +1115,9 @@ struct SplitWriter {
   }
   // the lanes with `split` (all lanes call)
   __device__ void write(const TraceArgs<R>& a, const Ray<R, NG>& L, bool split, int lane) {
-    const unsigned long long mask = __ballot(split);
+    const unsigned long long mask = wave_mask(split);
     const int need = __popcll(mask);
-    const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+    const int rank = lane_rank(mask);
     int done = 0;
     int full = 0;                                           // segments found full in this call
     while (done < need) {
@@ -1131,6 +1163,64 @@ struct SplitWriter {
   __device__ void close(const TraceArgs<R>& a, int lane) const {
     for (unsigned long long i = o_next + lane; i < o_end; i += kWave)
       a.out.tree[(unsigned long long)wseg * a.seg_cap + i] = kNoTree;
+  }
+};
+
+// Time-dependent rays: the halted rays of a wave take consecutive records of its
+// reserved block of the halt list, and of new blocks (one atomic per kHaltBlock
+// records) once that is full: a counter every wave of the device shares is not
+// touched at every halt. Written when the wave refills, like the split rays.
+template <typename R, int NG>
+struct HaltWriter {
+  unsigned long long h_next, h_end, h_count;   // reserved records, rays halted in this launch
+
+  __device__ void init() { h_next = h_end = h_count = 0; }
+  // the lanes with `halt` (all lanes call)
+  __device__ void write(const TraceArgs<R>& a, const Ray<R, NG>& L, bool halt, int lane) {
+    const unsigned long long hm = wave_mask(halt);
+    if (!hm) return;
+    const unsigned long long n = (unsigned long long)__popcll(hm);
+    const unsigned long long room = h_end - h_next;
+    unsigned long long nb = 0;
+    if (n > room) {
+      if (lane == 0) nb = atomicAdd(&a.ctr->halt_count, (unsigned long long)kHaltBlock);
+      nb = lane0_64(nb);
+    }
+    if (halt) {
+      const unsigned long long rank = (unsigned long long)lane_rank(hm);
+      const unsigned long long i = rank < room ? h_next + rank : nb + (rank - room);
+      if (i < a.halt_cap) {
+        a.halt.pix[i] = L.pix;
+        a.halt.tree[i] = L.tree;
+        a.halt.r[i] = L.g.r;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
+        a.halt_lev[i] = a.gen;
+      } else {
+        atomicOr(&a.ctr->err, kErrOverflow);
+      }
+    }
+    if (n > room) {
+      h_next = nb + (n - room);
+      h_end = nb + (unsigned long long)kHaltBlock;
+    } else {
+      h_next += n;
+    }
+    h_count += n;
+  }
+  // the unfilled rest of the wave's last block: empty records (no photons,
+  // a level above every real one); the level's count once per wave
+  __device__ void close(const TraceArgs<R>& a, int lane) const {
+    for (unsigned long long i = h_next + lane; i < h_end; i += kWave)
+      if (i < a.halt_cap) {
+        a.halt.pix[i] = 0;
+        a.halt.tree[i] = 0;
+        a.halt.r[i] = 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = 0.0;
+        a.halt_lev[i] = kHaltHole;
+      }
+    if (lane == 0 && h_count) atomicAdd(&a.ctr->halt_levels[a.gen], h_count);
   }
 };
 
@@ -1199,7 +1289,7 @@ void trace_level_kernel(TraceArgs<R> a) {
   bool active = false;
   int again = kFresh;      // an idle lane whose ray goes on in a new frame
   int from = 0;            // the cell it comes from
-  unsigned steps = 0;      // of the wave since rays last started in it
+  unsigned steps = 0;      // of the wave since rays last started or changed grids in it
   unsigned framed = 0;     // of the wave since all of its rays last had new frames
   L.ltree = kNoTree;
   L.stat0 = kNoTree;
@@ -1214,9 +1304,8 @@ void trace_level_kernel(TraceArgs<R> a) {
   unsigned long long w_next = 0, w_end = 0, w_nch = 0, w_slo = 0;
   int w_seg = home;
   bool drained = false;
-  // time-dependent rays: the wave's reserved block [h_next, h_end) of the
-  // halt list, and the rays it halted in this launch
-  unsigned long long h_next = 0, h_end = 0, h_count = 0;
+  HaltWriter<R, NG> halts;
+  if constexpr (HALT) halts.init();
   // the step's column pointer, held in vector registers in the float kernels:
   // their scalar registers are full, and from there it was reloaded (a
   // kernel-argument load and lane reads of spilled scalars) at every step; the
@@ -1238,14 +1327,16 @@ void trace_level_kernel(TraceArgs<R> a) {
     // Every idle lane first gets its queue slot or seed number (claiming as
     // many chunks as that takes), then all of them start in one pass; lanes
     // whose slot turns out empty wait for the next refill.
-    const unsigned long long idle = __ballot(!active);
-    const unsigned long long going = __ballot(again != kFresh);
-    if (__builtin_expect((!drained || going) && (idle == ~0ull || (PART && idle && __popcll(idle) >= a.refill)), 0)) {
-      if (__ballot(ended >= 0)) {
+    const unsigned long long idle = wave_mask(!active);
+    const unsigned long long going = wave_mask(again != kFresh);
+    if (!PART || idle == ~0ull || __popcll(idle) >= a.refill) {
+      if (wave_mask(ended >= 0)) {
         splits.write(a, L, ended == 2, lane);
+        if constexpr (HALT) halts.write(a, L, ended == 3, lane);
         tally.ended(a.stats, L, ended, lane);
         ended = -1;
       }
+      if (drained && !going && idle == ~0ull) break;
       if constexpr (!PART) {
         // no lane holds a ray but those going on, of which this is all that is live
         Ray<R, NG> keep;
@@ -1254,12 +1345,14 @@ void trace_level_kernel(TraceArgs<R> a) {
         for (int g = 0; g < NG; ++g) {
           keep.P[g] = L.P[g];
           keep.alive[g] = L.alive[g];
+          keep.cut[g] = L.cut[g];
         }
         if constexpr (THIN) {
           keep.thin = L.thin; keep.rem = L.rem; keep.tsegs = L.tsegs;
         }
         L = keep;
       }
+      const unsigned long long crossed = wave_mask(again >= kCross);
       unsigned long long left = drained ? 0ull : idle & ~going;
       bool take = false, child = false;
       unsigned long long q = 0;
@@ -1302,7 +1395,7 @@ void trace_level_kernel(TraceArgs<R> a) {
                                               (((unsigned long long)lane * n_extra) >> kshift);
               has = __hip_atomic_load(&head_in[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < size;
             }
-            const unsigned long long live = __ballot(has);
+            const unsigned long long live = wave_mask(has);
             if (!live) break;
             const unsigned long long ahead = live & (~0ull << w_seg);
             const int sg = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
@@ -1333,7 +1426,7 @@ void trace_level_kernel(TraceArgs<R> a) {
           child = idx < w_nch;
           q = child ? 4ull * (unsigned long long)w_seg * a.seg_cap + idx : w_slo + (idx - w_nch);
         }
-        const unsigned long long got_mask = __ballot(mine);
+        const unsigned long long got_mask = wave_mask(mine);
         w_next += __popcll(got_mask);
         left &= ~got_mask;
       }
@@ -1358,263 +1451,180 @@ void trace_level_kernel(TraceArgs<R> a) {
         again = kFresh;
       }
       if (idle == ~0ull) framed = 0;
-      if (__ballot(take)) steps = 0;
+      if (wave_mask(take) || crossed) steps = 0;
       // the tree of the first ray started is the one the wave's tally follows
-      const unsigned long long started = __ballot(active);
+      const unsigned long long started = wave_mask(active);
       if (started) tally.follow(a.stats, (uint32_t)__builtin_amdgcn_readlane((int)L.stat0, __ffsll((long long)started) - 1), lane);
       finish_vector_loads();
     }
-    if (__builtin_expect(!__ballot(active), 0)) {
-      if (drained && !__ballot(again != kFresh)) break;
-      continue;
+    // ---- step until the wave refills ----
+    // Nothing but the step itself is in this loop: rays that split, end, halt or
+    // change frames are marked and dealt with at the refill.
+    unsigned long long running = wave_mask(active);
+    while (running) {
+      // ---- one cell: exit plane, split test, deposit, step ----
+      // In every lane; those without a ray compute on values nothing reads.
+      const Exit x = L.g.exit();
+      const int here = L.lin;
+      const uint32_t yz = L.yz;
+      const bool leave = x.t >= L.tbox;
+      bool thin_here = false;
+      double tc64 = 0.0, rs = L.rs;
+      if constexpr (THIN) {
+        // optically thin in this cell: the optical depth on leaving it, in
+        // float64, below tau_thin
+        const double dr64 = x.t - L.g.r;
+        tc64 = dr64 > 0.0 ? L.kap64 * dr64 : 0.0;
+        thin_here = L.thin && tc64 < L.rem;
+        rs = thin_here ? L.rs_thin : rs;
+      }
+      const bool split = active && x.t > rs;
+      ended = split ? 2 : ended;
+      const bool go = active && !split;
+      // the segment in this cell, before the step moves the planes
+      double dr = x.t - L.g.r;
+      bool pos = go && L.g.positive(dr, x.t), halt = false;
+      double r_end = x.t;
+      if constexpr (HALT) {
+        // the ray reaches its halting radius inside this cell: the segment ends there
+        halt = go && x.t > L.rhalt;
+        r_end = halt ? L.rhalt : r_end;
+        dr = halt ? L.rhalt - L.g.r : dr;
+        pos = halt ? dr > 0.0 : pos;
+      }
+      double fc = 1.0;
+      if constexpr (COVER) {
+        if (pos && L.lpix > 0.0) fc = T.covering_factor(L, dr);
+      }
+      bool own = false;                        // thin: the cell holds the source
+      if constexpr (THIN) {
+        if (pos && thin_here) own = T.holds_source(L);
+      }
+      // across the exit face; the next cell's column is gathered now, under the
+      // deposit and its combining (a ray that leaves its grid reads cell 0 of the
+      // batch, unused)
+      L.g.step(x, L.st, L.sy, L.sz, L.lin, L.yz);
+      R kpre = (R)0;
+      double kpre64 = 0.0;
+      const int next = go && !leave ? L.lin : 0;
+      if constexpr (K64) {
+        kpre64 = kappa64_step[next];
+      } else {
+        kpre = kappa_step[next];
+      }
+      const bool thinly = THIN && pos && thin_here;
+      const bool dep = pos && (!thinly || own);
+      const uint32_t slot = (NS > 1 || THIN ? L.slot0 + L.astride * (uint32_t)here : L.slot0 + (uint32_t)here) +
+                            (thinly ? 1u : 0u);
+      const typename DepositCache<CACHE, NS>::Probe probe = cache.probe(slot, yz, dep);
+      double v[NS];                            // absorbed rate, then its energy moment or the momentum rate
+#pragma unroll
+      for (int c = 0; c < NS; ++c) v[c] = 0.0;
+      if (go) {
+        const R col = L.kap * (R)(pos ? dr : 0.0);
+        L.segs += pos ? 1u : 0u;
+        if constexpr (THIN) {
+          if (thinly) {
+            // no photons removed
+            double Pc = L.P[0];
+            v[0] = absorb(Pc, col * L.sigma[0]);
+            // the tree's mark on the cell: a plain byte store (every thin ray
+            // of the tree that crosses the cell stores the same 1); a segment
+            // shorter than 2^-40 of its exit radius (a ray through an edge or
+            // a corner) does not cross the cell
+            if (!own && dr > x.t * 0x1p-40) a.mark[L.mark_base + (long long)here] = 1;
+            L.rem -= tc64;
+            L.tsegs++;
+          } else if (pos) {
+            v[0] = absorb(L.P[0], col * L.sigma[0]);
+            L.thin = false;
+          }
+        } else {
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            if (NG == 1 || L.alive[g]) {
+              const double d = absorb(L.P[g], col * L.sigma[g]);
+              v[0] += d;
+              if constexpr (NG > 1) v[1] = fma(d, L.eexc[g], v[1]);
+            }
+          }
+        }
+        if constexpr (RADP) {
+          // the momentum rate along the ray, of the absorbed radiation itself, before
+          // any covering-factor scaling (zero for a problem that does not ask for it)
+          const double m = v[0] * L.mscale;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) v[1 + k] = m * L.d[k];
+        }
+        if constexpr (COVER) {
+          v[0] *= fc;
+          if constexpr (NG > 1) v[1] *= fc;
+        }
+        L.g.r = max_f64(L.g.r, r_end);
+        if (!(HALT && halt)) {
+          bool any = false;
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            if (L.alive[g] && L.P[g] < L.pmin[g]) {
+              L.alive[g] = false;
+              L.cut[g] = L.segs;
+            }
+            any = any || L.alive[g];
+          }
+          ended = any ? ended : 1;
+        } else {
+          ended = 3;
+        }
+      }
+      cache.add(a.acc, probe, slot, THIN ? 1u : L.astride, v, dep, lane);
+      active = go && ended < 0;
+      // the gather completes here, on every path: left in flight across the
+      // loop's back edge it would make the compiler drain the whole counter
+      if constexpr (K64) {
+        asm volatile("" ::"v"(kpre64));
+        kpre = (R)kpre64;
+      } else {
+        asm volatile("" ::"v"(kpre));
+      }
+      L.kap = kpre;
+      if constexpr (THIN) L.kap64 = K64 ? kpre64 : (double)kpre;
+      if (active && (leave || kpre < (R)0)) {
+        // out of the root grid, or into another frame
+        active = false;
+        if (leave && L.root) {
+          ended = 0;
+        } else {
+          again = kCross + x.axis();
+          from = here;
+        }
+      }
+      running = wave_mask(active);
+      // the steps since rays last started or changed grids bound every active ray's own; the
+      // bound is never reached by a correct trace (cell indices move monotonically)
+      if (++steps >= a.max_steps) break;
+      if constexpr (PART) {
+        if (__popcll(~running) >= a.refill && !drained) break;
+      }
+      if constexpr (sizeof(R) == 4) {
+        if (++framed >= kResync) break;
+      }
     }
-    // ---- one cell: exit plane, split test, deposit, step ----
-    // The steps since rays last started bound every active ray's own. The
-    // bound is never reached by a correct trace (cell indices move monotonically).
-    if (__builtin_expect(++steps > a.max_steps, 0)) {
+    if (steps >= a.max_steps && running) {
       if (lane == 0) atomicOr(&a.ctr->err, kErrInternal);
       break;
     }
     if constexpr (sizeof(R) == 4) {
-      if (__builtin_expect(++framed > kResync, 0)) {
+      if (framed >= kResync && active) {
         // every ray in flight goes on in the same cell, its plane distances formed afresh
-        if (active) {
-          again = kResyncFrame;
-          from = L.lin;
-          active = false;
-        }
-        continue;
-      }
-    }
-    Exit x{0.0, false, false};
-    bool split = false, leave = false;
-    int nlin = 0;
-    R kpre = (R)0;
-    double kpre64 = 0.0;
-    bool thin_here = false;
-    double tc64 = 0.0;
-    if (active) {
-      x = L.g.exit();
-      // the next cell is known from the exit axis alone: its column is
-      // gathered now, under the split test, the deposit and its combining
-      // (a step out of the grid reads cell 0 of the batch, unused)
-      leave = x.t >= L.tbox;
-      nlin = L.lin + x.pick(L.st[0], L.st[1], L.st[2]);
-      if constexpr (K64) {
-        kpre64 = kappa64_step[leave ? 0 : nlin];
-      } else {
-        kpre = kappa_step[leave ? 0 : nlin];
-      }
-      double rs = L.rs;
-      if constexpr (THIN) {
-        // optically thin in this cell: the optical depth on leaving it, in
-        // float64, below tau_thin
-        if (L.thin) {
-          const double dr64 = x.t - L.g.r;
-          tc64 = dr64 > 0.0 ? L.kap64 * dr64 : 0.0;
-          thin_here = tc64 < L.rem;
-        }
-        rs = thin_here ? L.rs_thin : rs;
-      }
-      if (x.t > rs) split = T.splits(L, x.t, thin_here);
-    }
-    if (split) {
-      ended = 2;
-      active = false;
-    }
-    bool dep = false, moved = false;
-    uint32_t dkey = 0;
-    double dval = 0.0, hval = 0.0, mval = 0.0;   // absorbed rate, its energy moment, momentum rate
-    const int here = L.lin;
-    const uint32_t yz = L.yz;
-    bool halt = false;
-    if (active) {
-      double dr = x.t - L.g.r;
-      bool pos = L.g.positive(dr, x.t);
-      if constexpr (HALT) {
-        // the ray reaches its halting radius inside this cell: the segment ends there
-        if (x.t > L.rhalt) {
-          halt = true;
-          dr = L.rhalt - L.g.r;
-          pos = dr > 0.0;
-        }
-      }
-      if (THIN && pos && thin_here) {
-        // thin: no photons removed
-        if (T.holds_source(L)) {
-          double Pc = L.P[0];
-          dval = absorb(Pc, L.kap * L.sigma[0] * (R)dr);
-          if constexpr (COVER) {
-            if (L.lpix > 0.0) dval *= T.covering_factor(L, dr);
-          }
-          dkey = L.slot0 + L.astride * (uint32_t)L.lin + 1u;
-          dep = true;
-        } else if (dr > x.t * 0x1p-40) {
-          // the tree's mark on the cell: a plain byte store (every thin ray
-          // of the tree that crosses the cell stores the same 1); a segment
-          // shorter than 2^-40 of its exit radius (a ray through an edge or
-          // a corner) does not cross the cell
-          a.mark[L.mark_base + (long long)L.lin] = 1;
-        }
-        L.rem -= tc64;
-        L.segs++;
-        L.tsegs++;
-        L.g.r = x.t;
-      } else if (pos) {
-        const R col = L.kap * (R)dr;
-        if constexpr (NG == 1) {
-          dval = absorb(L.P[0], col * L.sigma[0]);
-        } else {
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            if (!__ballot(L.alive[g])) continue;
-            const double d = absorb(L.P[g], col * L.sigma[g]);   // 0 for an ended group's P = 0
-            dval += d;
-            hval = fma(d, L.eexc[g], hval);
-          }
-        }
-        if constexpr (THIN) L.thin = false;
-        if constexpr (RADP) {
-          // the absorbed radiation itself, before any covering-factor scaling
-          mval = dval * L.mscale;
-        }
-        if constexpr (COVER) {
-          if (L.lpix > 0.0) {
-            const double fc = T.covering_factor(L, dr);
-            dval *= fc;
-            hval *= fc;
-          }
-        }
-        dkey = NS > 1 || THIN ? L.slot0 + L.astride * (uint32_t)L.lin : L.slot0 + (uint32_t)L.lin;
-        dep = true;
-        L.segs++;
-        L.g.r = HALT && halt ? L.rhalt : x.t;
-      }
-    }
-    if (active && !(HALT && halt)) {
-      // step across the exit face
-      L.lin = nlin;
-      L.yz += (uint32_t)x.pick(0, L.sy, L.sz);
-      L.g.step(x);
-      if constexpr (NG == 1) {
-        if (L.P[0] < L.pmin[0]) {
-          ended = 1;
-          active = false;
-        }
-      } else {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          if (__builtin_expect(L.alive[g] && L.P[g] < L.pmin[g], 0)) {
-            tally.truncated(a.stats, L, g);
-            L.alive[g] = false;
-            L.P[g] = 0.0;
-          }
-        }
-        if (!L.any_alive()) active = false;
-      }
-      moved = active;
-    }
-    if constexpr (HALT) {
-      // halted rays of the wave take consecutive records of its reserved
-      // block of the halt list, and of a new block (one atomic per
-      // kHaltBlock records) once that is full: a counter every wave of the
-      // device shares is not touched at every halt
-      const unsigned long long hm = __ballot(halt);
-      if (hm) {
-        const unsigned long long n = (unsigned long long)__popcll(hm);
-        const unsigned long long room = h_end - h_next;
-        unsigned long long nb = 0;
-        if (n > room) {
-          if (lane == 0) nb = atomicAdd(&a.ctr->halt_count, (unsigned long long)kHaltBlock);
-          nb = lane0_64(nb);
-        }
-        if (halt) {
-          const unsigned long long rank = (unsigned long long)__popcll(hm & below);
-          const unsigned long long i = rank < room ? h_next + rank : nb + (rank - room);
-          if (i < a.halt_cap) {
-            a.halt.pix[i] = L.pix;
-            a.halt.tree[i] = L.tree;
-            a.halt.r[i] = L.g.r;
-#pragma unroll
-            for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
-            a.halt_lev[i] = a.gen;
-          } else {
-            atomicOr(&a.ctr->err, kErrOverflow);
-          }
-          ended = 3;
-          active = false;
-        }
-        if (n > room) {
-          h_next = nb + (n - room);
-          h_end = nb + (unsigned long long)kHaltBlock;
-        } else {
-          h_next += n;
-        }
-        h_count += n;
-      }
-    }
-    if constexpr (RADP) {
-      // the momentum rate along the ray, from the float64 direction (zero
-      // for a problem that does not ask for it: its key is a one-sum slot)
-      double v[NS] = {dval, 0.0, 0.0, 0.0};
-      if (dep && mval != 0.0) {
-        v[1] = mval * L.d[0];
-        v[2] = mval * L.d[1];
-        v[3] = mval * L.d[2];
-      }
-      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
-    } else if constexpr (NS == 2) {
-      const double v[NS] = {dval, hval};
-      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
-    } else {
-      const double v[NS] = {dval};
-      cache.add(a.acc, dkey, yz, THIN ? 1u : L.astride, v, dep, lane);
-    }
-    // the gathered column is taken on every path, so that no load is in
-    // flight across the loop's back edge
-    // the gather completes here, on every path: left in flight across the
-    // loop's back edge it would make the compiler drain the whole counter
-    if constexpr (K64) {
-      asm volatile("" ::"v"(kpre64));
-      kpre = (R)kpre64;
-    } else {
-      asm volatile("" ::"v"(kpre));
-    }
-    const bool kneg = moved && (leave || kpre < (R)0);
-    L.kap = (moved && !kneg) ? kpre : L.kap;
-    if constexpr (THIN) L.kap64 = (moved && !kneg) ? (K64 ? kpre64 : (double)kpre) : L.kap64;
-    if (kneg) {
-      // out of the root grid, or into another frame
-      active = false;
-      if (leave && L.root) {
-        ended = 0;
-      } else {
-        again = kCross + x.axis();
-        from = here;
+        again = kResyncFrame;
+        from = L.lin;
+        active = false;
       }
     }
   }
   cache.flush(a.acc, lane);
-  if (__ballot(ended >= 0)) {
-    splits.write(a, L, ended == 2, lane);
-    tally.ended(a.stats, L, ended, lane);
-  }
   tally.flush(a.stats, lane);
-  if constexpr (HALT) {
-    // the unfilled rest of the wave's last block: empty records (no photons,
-    // a level above every real one); the level's count once per wave
-    for (unsigned long long i = h_next + lane; i < h_end; i += kWave)
-      if (i < a.halt_cap) {
-        a.halt.pix[i] = 0;
-        a.halt.tree[i] = 0;
-        a.halt.r[i] = 0.0;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = 0.0;
-        a.halt_lev[i] = kHaltHole;
-      }
-    if (lane == 0 && h_count) atomicAdd(&a.ctr->halt_levels[a.gen], h_count);
-  }
-  // unused slots of the wave's last reserved block become empty slots
+  if constexpr (HALT) halts.close(a, lane);
   splits.close(a, lane);
 }
 
