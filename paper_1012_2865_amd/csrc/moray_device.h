@@ -85,7 +85,7 @@ struct TreeDev {
   double pmin0[kPack];     // p_min_frac * P0 (quartered per level below the seeds)
   double sigma64[kPack];   // cross-section, cm^2
   double eexc[kPack];      // E - E_ion, erg (0 where the problem's records have no second moment)
-  long long acc_slot;      // accumulator of cell c (batch numbering) is acc[acc_slot + acc_stride * c]
+  long long acc_slot;      // accumulator of cell c (batch numbering) is acc[acc_slot + (c << acc_shift)]
   double split_r;          // sqrt(12 / (4 pi phi_c)): a ray of level l splits beyond 2^l times this many
                            // local cells; infinite when the problem never splits
   int level_init;
@@ -100,7 +100,7 @@ struct TreeDev {
   int covering;            // scale deposits into the accumulators by the covering factor
   int n_grp;               // groups of the pack
   uint32_t stat0;          // statistics of its first group (those of the others follow)
-  uint32_t acc_stride = 1; // its problem's acc_stride
+  uint32_t acc_shift = 0;  // log2 of its problem's acc_stride
   double mom_scale;        // E_ph / c of the (one) group (erg s/cm), 0 without radiation pressure
   double r_halt = __builtin_huge_val();   // time-dependent rays: radius (root cells) where the
                                           // tree's rays halt in this step

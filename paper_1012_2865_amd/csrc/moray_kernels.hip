@@ -33,6 +33,8 @@ namespace moray {
 // The active lanes where p holds, from its lane mask itself (an int predicate
 // costs a select and a compare).
 __device__ __forceinline__ unsigned long long wave_mask(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// The lane's bit of a wave-uniform mask, the mask itself serving as the predicate.
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // ---------------------------------------------------------------------------
 // HEALPix nested pixel centre (Gorski et al. 2005), float64.
@@ -441,8 +443,8 @@ struct Ray {
   double P[NG], pmin[NG];
   bool alive[NG];         // groups the ray still carries
   unsigned cut[NG];       // of a group truncated in this flight, its segments (its P is what it had left); kNoCut: not
-  uint32_t slot0;         // the ray's accumulator of cell lin is acc[slot0 + astride * lin]
-  uint32_t astride;
+  uint32_t slot0;         // the ray's accumulator of cell lin is acc[slot0 + (lin << ashift)]
+  uint32_t ashift;
   R sigma[NG];
   double eexc[NG];        // E - E_ion (moments only)
   R kap;                  // absorber column per root-cell length of the current cell
@@ -632,7 +634,7 @@ struct Tracer {
     L.ltree = L.tree;
     L.slot0 = (uint32_t)S.acc_slot;
     L.stat0 = S.stat0;
-    L.astride = S.acc_stride;
+    L.ashift = S.acc_shift;
     if constexpr (RADP) L.mscale = S.mom_scale;
     if constexpr ((PHYS & kPhysHalt) != 0) L.rhalt = S.r_halt;
     if constexpr (THIN) L.mark_base = S.mark_base;
@@ -942,8 +944,8 @@ struct WaveTally {
 //
 // A deposit is NS consecutive sums of one cell's record, which never straddles a
 // line: the absorbed rate (1), the moments of rays with several groups (2:
-// absorbed rate, energy), or the radiation-pressure record (4). `sums` says how
-// many of them the lane's problem keeps (a batch may mix problems).
+// absorbed rate, energy), or the radiation-pressure record (4). `shift` says how
+// many of them (2^shift) the lane's problem keeps (a batch may mix problems).
 //
 // kLines and kOut: what three blocks leave of a CU's 160 KB of LDS.
 constexpr int kLineLog2 = 7, kLines = 1 << kLineLog2;
@@ -1017,12 +1019,12 @@ struct DepositCache {
   struct Probe {
     uint32_t h, was, before, owner;
   };
-  __device__ __forceinline__ Probe probe(uint32_t slot, uint32_t yz, bool has) {
+  __device__ __forceinline__ Probe probe(uint32_t slot, uint32_t yz, unsigned long long has) {
     Probe p{0u, kNoSlot, kNoSlot, kNoSlot};
     if constexpr (CACHE) {
-      if (has) {
-        const uint32_t line = slot >> 3;
-        p.h = line_index(line, yz);
+      const uint32_t line = slot >> 3;
+      p.h = line_index(line, yz);
+      if (in_mask(has)) {
         p.was = __hip_atomic_load(&key[p.h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         p.before = __hip_atomic_exchange(&key[p.h], line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         p.owner = __hip_atomic_load(&key[p.h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1031,21 +1033,23 @@ struct DepositCache {
     }
     return p;
   }
-  __device__ __forceinline__ void add(double* acc, const Probe& p, uint32_t slot, uint32_t sums, const double (&v)[NS],
-                                      bool has, int lane) {
-    if constexpr (!CACHE) {
-      if (has) {
+  // v[c] belongs to the lane's problem where c < 2^shift
+  __device__ __forceinline__ void add(double* acc, const Probe& p, uint32_t slot, uint32_t shift, const double (&v)[NS],
+                                      unsigned long long has, int lane) {
+    auto to_memory = [&]() {
 #pragma unroll
-        for (int c = 0; c < NS; ++c)
-          if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
-      }
+      for (int c = 0; c < NS; ++c)
+        if (c == 0 || (c >> shift) == 0) unsafeAtomicAdd(&acc[slot + c], v[c]);
+    };
+    if constexpr (!CACHE) {
+      if (in_mask(has)) to_memory();
       return;
     }
-    const bool displace = has && p.owner != p.was && p.before == p.was && p.was != kNoSlot;
-    const unsigned long long dmask = wave_mask(displace);
-    if (dmask) {
-      const int n = __popcll(dmask);
-      if (displace) moves[lane_rank(dmask)] = make_uint2(p.h, p.was);
+    const unsigned long long displace =
+        has & wave_mask(p.owner != p.was) & wave_mask(p.before == p.was) & wave_mask(p.was != kNoSlot);
+    if (displace) {
+      const int n = __popcll(displace);
+      if (in_mask(displace)) moves[lane_rank(displace)] = make_uint2(p.h, p.was);
       __builtin_amdgcn_wave_barrier();
       for (int i0 = 0; i0 < n; i0 += 8) {
         const int m = n - i0 < 8 ? n - i0 : 8;
@@ -1061,21 +1065,18 @@ struct DepositCache {
         __builtin_amdgcn_wave_barrier();
       }
     }
-    const bool mine = has && p.owner == slot >> 3;
+    const unsigned long long mine = has & wave_mask(p.owner == slot >> 3);
     double* cell = &val[8 * p.h + (slot & 7u)];
-    if (mine) {
+    if (in_mask(mine)) {
 #pragma unroll
       for (int c = 0; c < NS; ++c)
-        if (c == 0 || sums > (uint32_t)c)
+        if (c == 0 || (c >> shift) == 0)
           __hip_atomic_fetch_add(cell + c, v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
-    if (wave_mask(has && !mine)) {
-      if (has && !mine) {
-#pragma unroll
-        for (int c = 0; c < NS; ++c)
-          if (c == 0 || sums > (uint32_t)c) unsafeAtomicAdd(&acc[slot + c], v[c]);
-      }
+    const unsigned long long lost = has & ~mine;
+    if (lost) {
+      if (in_mask(lost)) to_memory();
     }
   }
   __device__ void flush(double* acc, int lane) {
@@ -1459,46 +1460,57 @@ void trace_level_kernel(TraceArgs<R> a) {
     }
     // ---- step until the wave refills ----
     // Nothing but the step itself is in this loop: rays that split, end, halt or
-    // change frames are marked and dealt with at the refill.
-    unsigned long long running = wave_mask(active);
-    while (running) {
+    // change frames are marked and dealt with at the refill. What is known of the
+    // lanes is kept as wave-uniform masks: a flag carried through the loop per
+    // lane is merged with its old value under the execution mask, three scalar
+    // instructions a flag and branch.
+    unsigned long long run = wave_mask(active);               // lanes with a ray in flight
+    unsigned long long at_split = 0, at_end = 0, at_out = 0, at_halt = 0, at_cross = 0;
+    unsigned long long carries[NG];                           // lanes whose ray carries group g
+#pragma unroll
+    for (int g = 0; g < NG; ++g) carries[g] = wave_mask(active && L.alive[g]);
+    const unsigned long long root = wave_mask(L.root);
+    while (run) {
       // ---- one cell: exit plane, split test, deposit, step ----
       // In every lane; those without a ray compute on values nothing reads.
       const Exit x = L.g.exit();
       const int here = L.lin;
       const uint32_t yz = L.yz;
-      const bool leave = x.t >= L.tbox;
-      bool thin_here = false;
+      const unsigned long long leave = wave_mask(x.t >= L.tbox);
+      unsigned long long thin = 0;
       double tc64 = 0.0, rs = L.rs;
       if constexpr (THIN) {
         // optically thin in this cell: the optical depth on leaving it, in
         // float64, below tau_thin
         const double dr64 = x.t - L.g.r;
         tc64 = dr64 > 0.0 ? L.kap64 * dr64 : 0.0;
-        thin_here = L.thin && tc64 < L.rem;
+        const bool thin_here = L.thin && tc64 < L.rem;
+        thin = wave_mask(thin_here);
         rs = thin_here ? L.rs_thin : rs;
       }
-      const bool split = active && x.t > rs;
-      ended = split ? 2 : ended;
-      const bool go = active && !split;
+      const unsigned long long split = run & wave_mask(x.t > rs);
+      at_split |= split;
+      const unsigned long long go = run & ~split;
       // the segment in this cell, before the step moves the planes
-      double dr = x.t - L.g.r;
-      bool pos = go && L.g.positive(dr, x.t), halt = false;
-      double r_end = x.t;
+      double dr = x.t - L.g.r, r_end = x.t;
+      unsigned long long pos = go & wave_mask(L.g.positive(dr, x.t)), halt = 0;
       if constexpr (HALT) {
         // the ray reaches its halting radius inside this cell: the segment ends there
-        halt = go && x.t > L.rhalt;
-        r_end = halt ? L.rhalt : r_end;
-        dr = halt ? L.rhalt - L.g.r : dr;
-        pos = halt ? dr > 0.0 : pos;
+        const bool halts_here = x.t > L.rhalt;
+        halt = go & wave_mask(halts_here);
+        r_end = halts_here ? L.rhalt : r_end;
+        dr = halts_here ? L.rhalt - L.g.r : dr;
+        pos = (pos & ~halt) | (halt & wave_mask(dr > 0.0));
       }
       double fc = 1.0;
       if constexpr (COVER) {
-        if (pos && L.lpix > 0.0) fc = T.covering_factor(L, dr);
+        if (in_mask(pos) && L.lpix > 0.0) fc = T.covering_factor(L, dr);
       }
-      bool own = false;                        // thin: the cell holds the source
+      unsigned long long own = 0;              // thin: the cell holds the source
       if constexpr (THIN) {
-        if (pos && thin_here) own = T.holds_source(L);
+        bool o = false;
+        if (in_mask(pos & thin)) o = T.holds_source(L);
+        own = wave_mask(o);
       }
       // across the exit face; the next cell's column is gathered now, under the
       // deposit and its combining (a ray that leaves its grid reads cell 0 of the
@@ -1506,78 +1518,73 @@ void trace_level_kernel(TraceArgs<R> a) {
       L.g.step(x, L.st, L.sy, L.sz, L.lin, L.yz);
       R kpre = (R)0;
       double kpre64 = 0.0;
-      const int next = go && !leave ? L.lin : 0;
+      const unsigned next = in_mask(go & ~leave) ? (unsigned)L.lin : 0u;
       if constexpr (K64) {
         kpre64 = kappa64_step[next];
       } else {
         kpre = kappa_step[next];
       }
-      const bool thinly = THIN && pos && thin_here;
-      const bool dep = pos && (!thinly || own);
-      const uint32_t slot = (NS > 1 || THIN ? L.slot0 + L.astride * (uint32_t)here : L.slot0 + (uint32_t)here) +
-                            (thinly ? 1u : 0u);
+      const unsigned long long thinly = pos & thin, dep = (pos & ~thinly) | (thinly & own);
+      uint32_t slot = NS > 1 || THIN ? L.slot0 + ((uint32_t)here << L.ashift) : L.slot0 + (uint32_t)here;
+      if constexpr (THIN) slot += in_mask(thinly) ? 1u : 0u;
       const typename DepositCache<CACHE, NS>::Probe probe = cache.probe(slot, yz, dep);
       double v[NS];                            // absorbed rate, then its energy moment or the momentum rate
 #pragma unroll
       for (int c = 0; c < NS; ++c) v[c] = 0.0;
-      if (go) {
-        const R col = L.kap * (R)(pos ? dr : 0.0);
-        L.segs += pos ? 1u : 0u;
-        if constexpr (THIN) {
-          if (thinly) {
-            // no photons removed
-            double Pc = L.P[0];
-            v[0] = absorb(Pc, col * L.sigma[0]);
-            // the tree's mark on the cell: a plain byte store (every thin ray
-            // of the tree that crosses the cell stores the same 1); a segment
-            // shorter than 2^-40 of its exit radius (a ray through an edge or
-            // a corner) does not cross the cell
-            if (!own && dr > x.t * 0x1p-40) a.mark[L.mark_base + (long long)here] = 1;
-            L.rem -= tc64;
-            L.tsegs++;
-          } else if (pos) {
-            v[0] = absorb(L.P[0], col * L.sigma[0]);
-            L.thin = false;
-          }
-        } else {
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            if (NG == 1 || L.alive[g]) {
-              const double d = absorb(L.P[g], col * L.sigma[g]);
-              v[0] += d;
-              if constexpr (NG > 1) v[1] = fma(d, L.eexc[g], v[1]);
-            }
-          }
+      const R col = L.kap * (in_mask(pos) ? (R)dr : (R)0);
+      L.segs += in_mask(pos) ? 1u : 0u;
+      if constexpr (THIN) {
+        if (in_mask(thinly)) {
+          // no photons removed
+          double Pc = L.P[0];
+          v[0] = absorb(Pc, col * L.sigma[0]);
+          // the tree's mark on the cell: a plain byte store (every thin ray
+          // of the tree that crosses the cell stores the same 1); a segment
+          // shorter than 2^-40 of its exit radius (a ray through an edge or
+          // a corner) does not cross the cell
+          if (!in_mask(own) && dr > x.t * 0x1p-40) a.mark[L.mark_base + (long long)here] = 1;
+          L.rem -= tc64;
+          L.tsegs++;
+        } else if (in_mask(pos)) {
+          v[0] = absorb(L.P[0], col * L.sigma[0]);
+          L.thin = false;
         }
-        if constexpr (RADP) {
-          // the momentum rate along the ray, of the absorbed radiation itself, before
-          // any covering-factor scaling (zero for a problem that does not ask for it)
-          const double m = v[0] * L.mscale;
+      } else {
 #pragma unroll
-          for (int k = 0; k < 3; ++k) v[1 + k] = m * L.d[k];
-        }
-        if constexpr (COVER) {
-          v[0] *= fc;
-          if constexpr (NG > 1) v[1] *= fc;
-        }
-        L.g.r = max_f64(L.g.r, r_end);
-        if (!(HALT && halt)) {
-          bool any = false;
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            if (L.alive[g] && L.P[g] < L.pmin[g]) {
-              L.alive[g] = false;
-              L.cut[g] = L.segs;
-            }
-            any = any || L.alive[g];
+        for (int g = 0; g < NG; ++g) {
+          if (in_mask(go & carries[g])) {
+            const double d = absorb(L.P[g], col * L.sigma[g]);
+            v[0] += d;
+            if constexpr (NG > 1) v[1] = fma(d, L.eexc[g], v[1]);
           }
-          ended = any ? ended : 1;
-        } else {
-          ended = 3;
         }
       }
-      cache.add(a.acc, probe, slot, THIN ? 1u : L.astride, v, dep, lane);
-      active = go && ended < 0;
+      if constexpr (RADP) {
+        // the momentum rate along the ray, of the absorbed radiation itself, before
+        // any covering-factor scaling (zero for a problem that does not ask for it)
+        const double m = v[0] * L.mscale;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[1 + k] = m * L.d[k];
+      }
+      if constexpr (COVER) {
+        v[0] *= fc;
+        if constexpr (NG > 1) v[1] *= fc;
+      }
+      if (in_mask(go)) L.g.r = max_f64(L.g.r, r_end);
+      // truncated groups (not in a ray that halts here), and rays without a group left
+      const unsigned long long on = go & ~halt;
+      unsigned long long any = 0;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const unsigned long long low = on & carries[g] & wave_mask(L.P[g] < L.pmin[g]);
+        if (in_mask(low)) L.cut[g] = L.segs;
+        carries[g] &= ~low;
+        any |= carries[g];
+      }
+      at_halt |= halt;
+      at_end |= on & ~any;
+      run = on & any;
+      cache.add(a.acc, probe, slot, THIN ? 0u : L.ashift, v, dep, lane);
       // the gather completes here, on every path: left in flight across the
       // loop's back edge it would make the compiler drain the whole counter
       if constexpr (K64) {
@@ -1588,28 +1595,37 @@ void trace_level_kernel(TraceArgs<R> a) {
       }
       L.kap = kpre;
       if constexpr (THIN) L.kap64 = K64 ? kpre64 : (double)kpre;
-      if (active && (leave || kpre < (R)0)) {
-        // out of the root grid, or into another frame
-        active = false;
-        if (leave && L.root) {
-          ended = 0;
-        } else {
+      // out of the root grid, or into another frame
+      const unsigned long long out = run & leave & root;
+      at_out |= out;
+      const unsigned long long cross = run & ~out & (leave | wave_mask(kpre < (R)0));
+      run &= ~(out | cross);
+      if (cross) {
+        at_cross |= cross;
+        if (in_mask(cross)) {
           again = kCross + x.axis();
           from = here;
         }
       }
-      running = wave_mask(active);
       // the steps since rays last started or changed grids bound every active ray's own; the
       // bound is never reached by a correct trace (cell indices move monotonically)
       if (++steps >= a.max_steps) break;
       if constexpr (PART) {
-        if (__popcll(~running) >= a.refill && !drained) break;
+        if (__popcll(~run) >= a.refill && !drained) break;
       }
       if constexpr (sizeof(R) == 4) {
         if (++framed >= kResync) break;
       }
     }
-    if (steps >= a.max_steps && running) {
+    active = in_mask(run);
+    if (in_mask(at_split)) ended = 2;
+    if (in_mask(at_end)) ended = 1;
+    if (in_mask(at_out)) ended = 0;
+    if (in_mask(at_halt)) ended = 3;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      if (in_mask(run | at_split | at_end | at_out | at_halt | at_cross)) L.alive[g] = in_mask(carries[g]);
+    if (steps >= a.max_steps && run) {
       if (lane == 0) atomicOr(&a.ctr->err, kErrInternal);
       break;
     }

@@ -327,7 +327,7 @@ void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const
   d.n_grp = n;
   d.four_pi_phi_c = 4.0 * kPiConst * P.params.phi_c;
   d.split_r = P.params.phi_c > 0.0 ? std::sqrt(12.0 / d.four_pi_phi_c) : HUGE_VAL;
-  d.acc_stride = (uint32_t)pd.acc_stride;
+  d.acc_shift = pd.acc_stride == 4 ? 2u : (pd.acc_stride == 2 ? 1u : 0u);
   const long long plane = pd.acc_planes > 1 ? g0 : 0;
   d.acc_slot = pd.acc_off + (long long)pd.acc_stride * (plane * pd.n_cells - pd.cell_off);
   d.problem = root.problem;
