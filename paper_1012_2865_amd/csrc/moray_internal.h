@@ -138,6 +138,20 @@ inline size_t slot_bytes(int planes) { return sizeof(uint64_t) + sizeof(uint32_t
 // that keep a plane of accumulators per group).
 void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const ProblemDev& pd, const GridDev& root);
 
+// Level at which the seeds of `trees` trees enter (see the trace kernel): the
+// finest, not beyond `top` (the finest any of them reaches), that still has no
+// more pixels than kDescendLanes and than the level queue has room for (`cap`:
+// a queue too small for a level is reported as such). The repeated part of the work is
+// about that of the last level, on lanes that would otherwise idle; one more level
+// would queue several pixels behind each lane.
+constexpr long long kDescendLanes = 200000;
+inline int descend_level(long long trees, int l0, int top, size_t cap) {
+  const long long most = cap < (size_t)kDescendLanes ? (long long)cap : kDescendLanes;
+  int l = l0;
+  while (l < top && trees * (12ll << (2 * (l + 1))) <= most) ++l;
+  return l;
+}
+
 // Segments of a level queue for `cap` rays: a power of two up to kSegMax, so
 // the trace kernel splits a launch's seeds among them with shifts.
 inline int queue_segments(size_t cap) {

@@ -438,7 +438,8 @@ struct Ray {
   int sy, sz;             // what crossing a y or z plane adds to it
   int q;                  // grid index
   bool root;              // it is the problem's root grid
-  uint64_t pix;
+  uint64_t pix;           // its pixel, or the one it descends to (see descend)
+  int more;               // levels it has still to descend
   uint32_t tree;
   double P[NG], pmin[NG];
   bool alive[NG];         // groups the ray still carries
@@ -449,7 +450,6 @@ struct Ray {
   double eexc[NG];        // E - E_ion (moments only)
   R kap;                  // absorber column per root-cell length of the current cell
   unsigned segs;
-  uint32_t ltree;         // the tree whose constants the lane holds
   uint32_t stat0;
   double mscale;          // E_ph / c, 0 when the problem does not ask for the momentum
   double d[3];            // direction (the variants that need it at every step)
@@ -470,11 +470,11 @@ struct Ray {
 
 // Why an idle lane's ray goes on: with a new frame after it crossed into or out
 // of a child grid along axis 0..2 (kCross + axis), or in the cell it is in
-// (kResyncFrame). The step loop has no frame code of its own: it holds the
+// (kResyncFrame), or as its own child (kChild, see descend). The step loop has no frame code of its own: it holds the
 // whole state of every lane, and with the frame's temporaries on top overflows
 // the register budget (spills in the loop took the 128^3 workload from 8 to
 // 10.5 ms). Such a ray waits, idle, for the wave's next refill, where little else is live.
-constexpr int kFresh = 0, kResyncFrame = 1, kCross = 2;
+constexpr int kFresh = 0, kResyncFrame = 1, kChild = 2, kCross = 3;
 
 template <typename R, int NG, int PHYS>
 struct Tracer {
@@ -504,7 +504,18 @@ struct Tracer {
     }
     return rs;
   }
-  __device__ int level_of(const TreeDev& S) const { return S.level_init + (a.gen - S.gen0); }
+  // Descend. The coarse levels hold few rays, each of which crosses few cells: a
+  // launch per level for them is a chain of dependent loads on an idle device
+  // (30 to 80 us a level, most of a small problem's solve). The seeds therefore
+  // enter at a finer level, that of the launch: one lane per pixel of it, each of
+  // which traces its pixel's ancestors from the seed level on, going on in place
+  // as its own child where a ray splits. All descendants of a pixel trace it alike;
+  // the first of them (low bits 0) owns it and alone deposits and counts. What the
+  // others repeat costs lanes that would idle otherwise.
+  __device__ int level_of(const TreeDev& S) const { return S.level_init + (a.gen - S.gen0); }   // of the launch
+  __device__ int level_of(const TreeDev& S, const L_t& L) const { return level_of(S) - L.more; }
+  static __device__ uint64_t pixel(const L_t& L) { return L.pix >> (2 * L.more); }
+  static __device__ bool owner(const L_t& L) { return (L.pix & ((1ull << (2 * L.more)) - 1ull)) == 0ull; }
 
   // The ray's frame in grid q at local cell c: source in its cells, planes,
   // strides, split radius and cell index.
@@ -522,7 +533,7 @@ struct Tracer {
     L.q = q;
     L.root = !child;
     L.g.frame(sl, c, n, child, L.tbox);
-    const int level = level_of(S);
+    const int level = level_of(S, L);
     const double hinv = child ? 0.5 : 1.0;
     L.rs = split_radius(S.split_r, S.four_pi_phi_c, level, S.level_max, child);
     if constexpr (THIN) L.rs_thin = split_radius(S.split_r_thin, S.four_pi_phi_thin, level, S.level_max, child);
@@ -609,6 +620,7 @@ struct Tracer {
     const unsigned long long slot = i >> 2;
     L.tree = a.in.tree[slot];
     L.pix = 4ull * a.in.pix[slot] + (i & 3ull);
+    L.more = 0;
     r64 = a.in.r[slot];
 #pragma unroll
     for (int g = 0; g < NG; ++g) L.P[g] = 0.25 * a.in.P[g * a.in.pstride + slot];
@@ -617,6 +629,7 @@ struct Tracer {
     const unsigned long long slot = a.held_order[a.held_first + i];
     L.tree = a.held.tree[slot];
     L.pix = a.held.pix[slot];
+    L.more = 0;
     r64 = a.held.r[slot];
 #pragma unroll
     for (int g = 0; g < NG; ++g) L.P[g] = a.held.P[g * a.held.pstride + slot];
@@ -625,20 +638,21 @@ struct Tracer {
     const unsigned long long npix = 12ull << (2 * a.seed_level);
     L.tree = (uint32_t)(a.seed_begin + i / npix);
     L.pix = i % npix;
+    const TreeDev& S = a.trees[L.tree];
+    L.more = a.gen - S.gen0;
     r64 = 0.0;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) L.P[g] = a.trees[L.tree].P0[g];
+    for (int g = 0; g < NG; ++g) L.P[g] = S.P0[g];
   }
 
   __device__ void load_tree(L_t& L, const TreeDev& S) const {
-    L.ltree = L.tree;
     L.slot0 = (uint32_t)S.acc_slot;
     L.stat0 = S.stat0;
     L.ashift = S.acc_shift;
     if constexpr (RADP) L.mscale = S.mom_scale;
     if constexpr ((PHYS & kPhysHalt) != 0) L.rhalt = S.r_halt;
     if constexpr (THIN) L.mark_base = S.mark_base;
-    const int level = level_of(S);
+    const int level = level_of(S, L);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       L.pmin[g] = ldexp(S.pmin0[g], -2 * (level - S.level_init));
@@ -663,7 +677,7 @@ struct Tracer {
     } else if (L.P[0] < 0.0) {
       L.thin = true;
       L.rem = -L.P[0] - 1.0;
-      L.P[0] = ldexp(S.P0[0], -2 * (level_of(S) - S.level_init));
+      L.P[0] = ldexp(S.P0[0], -2 * (level_of(S) - S.level_init));   // a queue record: of the launch's level
     } else {
       L.thin = false;
     }
@@ -696,7 +710,7 @@ struct Tracer {
   // in flight. Returns false when it is outside the root grid.
   __device__ bool locate(L_t& L, const TreeDev& S, double r64, int again, int from, int q) const {
     double v[3];
-    healpix_dir(level_of(S), L.pix, v[0], v[1], v[2]);
+    healpix_dir(level_of(S, L), pixel(L), v[0], v[1], v[2]);
     L.g.set_dir(v);
     L.g.r = r64;
     if constexpr (RADP || (COVER && sizeof(R) == 4)) {
@@ -705,7 +719,7 @@ struct Tracer {
     const double x[3] = {__dadd_rn(S.sx, __dmul_rn(r64, v[0])), __dadd_rn(S.sy, __dmul_rn(r64, v[1])),
                          __dadd_rn(S.sz, __dmul_rn(r64, v[2]))};
     int c[3];
-    if (again == kFresh) {
+    if (again == kFresh || again == kChild) {
       L.segs = 0;
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
@@ -1191,12 +1205,13 @@ struct HaltWriter {
       const unsigned long long rank = (unsigned long long)lane_rank(hm);
       const unsigned long long i = rank < room ? h_next + rank : nb + (rank - room);
       if (i < a.halt_cap) {
-        a.halt.pix[i] = L.pix;
+        a.halt.pix[i] = L.pix >> (2 * L.more);
         a.halt.tree[i] = L.tree;
         a.halt.r[i] = L.g.r;
 #pragma unroll
         for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
-        a.halt_lev[i] = a.gen;
+        a.halt_lev[i] = a.gen - L.more;
+        if (L.more) atomicAdd(&a.ctr->halt_levels[a.gen - L.more], 1ull);
       } else {
         atomicOr(&a.ctr->err, kErrOverflow);
       }
@@ -1207,7 +1222,7 @@ struct HaltWriter {
     } else {
       h_next += n;
     }
-    h_count += n;
+    h_count += (unsigned long long)__popcll(wave_mask(halt && L.more == 0));
   }
   // the unfilled rest of the wave's last block: empty records (no photons,
   // a level above every real one); the level's count once per wave
@@ -1292,9 +1307,10 @@ void trace_level_kernel(TraceArgs<R> a) {
   int from = 0;            // the cell it comes from
   unsigned steps = 0;      // of the wave since rays last started or changed grids in it
   unsigned framed = 0;     // of the wave since all of its rays last had new frames
-  L.ltree = kNoTree;
   L.stat0 = kNoTree;
   L.segs = 0;
+  L.pix = 0;
+  L.more = 0;
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     L.alive[g] = false;
@@ -1329,19 +1345,22 @@ void trace_level_kernel(TraceArgs<R> a) {
     // many chunks as that takes), then all of them start in one pass; lanes
     // whose slot turns out empty wait for the next refill.
     const unsigned long long idle = wave_mask(!active);
-    const unsigned long long going = wave_mask(again != kFresh);
     if (!PART || idle == ~0ull || __popcll(idle) >= a.refill) {
       if (wave_mask(ended >= 0)) {
-        splits.write(a, L, ended == 2, lane);
-        if constexpr (HALT) halts.write(a, L, ended == 3, lane);
-        tally.ended(a.stats, L, ended, lane);
+        // (a lane that repeats another's ray reports nothing of it)
+        const bool owns = Tracer<R, NG, PHYS>::owner(L);
+        splits.write(a, L, ended == 2 && L.more == 0, lane);
+        if constexpr (HALT) halts.write(a, L, ended == 3 && owns, lane);
+        tally.ended(a.stats, L, owns ? ended : -1, lane);
+        if (ended == 2 && L.more > 0) again = kChild;
         ended = -1;
       }
+      const unsigned long long going = wave_mask(again != kFresh);
       if (drained && !going && idle == ~0ull) break;
       if constexpr (!PART) {
         // no lane holds a ray but those going on, of which this is all that is live
         Ray<R, NG> keep;
-        keep.pix = L.pix; keep.tree = L.tree; keep.q = L.q; keep.segs = L.segs; keep.g.r = L.g.r;
+        keep.pix = L.pix; keep.more = L.more; keep.tree = L.tree; keep.q = L.q; keep.segs = L.segs; keep.g.r = L.g.r;
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
           keep.P[g] = L.P[g];
@@ -1353,7 +1372,7 @@ void trace_level_kernel(TraceArgs<R> a) {
         }
         L = keep;
       }
-      const unsigned long long crossed = wave_mask(again >= kCross);
+      const unsigned long long crossed = wave_mask(again >= kChild);
       unsigned long long left = drained ? 0ull : idle & ~going;
       bool take = false, child = false;
       unsigned long long q = 0;
@@ -1438,9 +1457,15 @@ void trace_level_kernel(TraceArgs<R> a) {
           else if (HALT && q < n_held) T.fetch_held(L, q, r64);
           else T.fetch_seed(L, q - n_held, r64);
         }
+        if (again == kChild) {
+          L.more -= 1;
+          if constexpr (THIN) L.tsegs = 0;
+#pragma unroll
+          for (int g = 0; g < NG; ++g) L.P[g] = L.alive[g] ? 0.25 * L.P[g] : -1.0;
+        }
         if (L.tree != kNoTree) {
           const TreeDev& S = a.trees[L.tree];
-          if (!PART || L.tree != L.ltree) T.load_tree(L, S);
+          T.load_tree(L, S);
           if constexpr (THIN) {
             if (take) T.thin_start(L, S, !child);
           }
@@ -1469,7 +1494,7 @@ void trace_level_kernel(TraceArgs<R> a) {
     unsigned long long carries[NG];                           // lanes whose ray carries group g
 #pragma unroll
     for (int g = 0; g < NG; ++g) carries[g] = wave_mask(active && L.alive[g]);
-    const unsigned long long root = wave_mask(L.root);
+    const unsigned long long root = wave_mask(L.root), owners = wave_mask(active && Tracer<R, NG, PHYS>::owner(L));
     while (run) {
       // ---- one cell: exit plane, split test, deposit, step ----
       // In every lane; those without a ray compute on values nothing reads.
@@ -1524,7 +1549,7 @@ void trace_level_kernel(TraceArgs<R> a) {
       } else {
         kpre = kappa_step[next];
       }
-      const unsigned long long thinly = pos & thin, dep = (pos & ~thinly) | (thinly & own);
+      const unsigned long long thinly = pos & thin, dep = ((pos & ~thinly) | (thinly & own)) & owners;
       uint32_t slot = NS > 1 || THIN ? L.slot0 + ((uint32_t)here << L.ashift) : L.slot0 + (uint32_t)here;
       if constexpr (THIN) slot += in_mask(thinly) ? 1u : 0u;
       const typename DepositCache<CACHE, NS>::Probe probe = cache.probe(slot, yz, dep);

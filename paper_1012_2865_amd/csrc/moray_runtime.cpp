@@ -499,7 +499,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   std::vector<double> eexc;
   long long n_cells = 0;
   long long acc_legacy = 0;              // accumulators with one plane per group, the bound the interface states
-  int max_reach = 0, min_l0 = kMaxLevel;
+  int max_reach = 0, min_reach = kMaxLevel, min_l0 = kMaxLevel, max_l0 = 0;
   unsigned max_steps = 64;
   for (int i = 0; i < n_probs; ++i) {
     const moray_problem& P = probs[i];
@@ -529,7 +529,9 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     pd.n_cells = n_cells - pd.cell_off;
     max_steps = std::max<unsigned>(max_steps, (unsigned)std::min<long long>(steps * 2, 1u << 30));
     max_reach = std::max(max_reach, reach_level(P));
+    min_reach = std::min(min_reach, reach_level(P));
     min_l0 = std::min(min_l0, P.params.level_init);
+    max_l0 = std::max(max_l0, P.params.level_init);
   }
   if (n_cells >= (1LL << 31) - 1) return fail(c, MORAY_EINVAL, "batch exceeds 2^31 cells");
   // What the rays carry. A ray takes up to kPack energy groups of its source
@@ -865,8 +867,12 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
         launch_failed = true;
         break;
       }
-      for (int l = min_l0; l <= max_reach; ++l) {
-        const int lo = std::max(seed_lo[l], ch.begin), hi = std::min(seed_hi[l], ch.end);
+      // trees of one seed level enter at a finer one (trees of several at their own)
+      const int enter = min_l0 == max_l0 ? descend_level(ch.end - ch.begin, min_l0, min_reach, cap) : min_l0;
+      for (int l = enter; l <= max_reach; ++l) {
+        const int sl = min_l0 == max_l0 ? (l == enter ? min_l0 : kMaxLevel + 1) : l;    // seed level that enters here
+        const int lo = sl <= kMaxLevel ? std::max(seed_lo[sl], ch.begin) : 0;
+        const int hi = sl <= kMaxLevel ? std::min(seed_hi[sl], ch.end) : 0;
         auto queue = [&](int k) {
           return RayQueue{(uint64_t*)c->q_pix[k].p, (uint32_t*)c->q_tree[k].p, (double*)c->q_r[k].p,
                           (double*)c->q_P[k].p, qslots};

@@ -671,12 +671,19 @@ bool trip(Engine* E) {
     requeue(E, back);
   }
   const double t_admit = now_s();
+  // the level at which the admitted trees' seeds enter
+  int seed_level = 0;
+  if (!admitted.empty()) {
+    int top = kMaxLevel;
+    for (ServeProblem* p : admitted) top = std::min(top, reach_level(p->prob));
+    seed_level = descend_level(ttotal, admitted.front()->l0, top, E->qcap);
+  }
   {
     int t = tblock;
     for (ServeProblem* p : admitted) {
       p->tbase = t;
       t += p->ntrees;
-      p->gen0 = E->gen;
+      p->gen0 = E->gen - (seed_level - p->l0);
       p->t_admit = t_admit;
       const moray_status st = write_tables(E, p);
       if (st != MORAY_OK) {
@@ -755,7 +762,6 @@ bool trip(Engine* E) {
   const int seed_lo = admitted.empty() ? 0 : admitted.front()->tbase;
   int seed_hi = seed_lo;
   for (ServeProblem* p : admitted) seed_hi = std::max(seed_hi, p->tbase + p->ntrees);
-  const int seed_level = admitted.empty() ? 0 : admitted.front()->l0;
   const int blocks = std::max(1, c->num_cu * c->blocks_per_cu);
   auto queue = [&](int k) {
     return RayQueue{(uint64_t*)E->qpix[k].p, (uint32_t*)E->qtree[k].p, (double*)E->qr[k].p, (double*)E->qP[k].p,

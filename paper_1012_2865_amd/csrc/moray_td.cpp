@@ -427,7 +427,9 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   int l_hi = reach_level(P);
   for (int l = l_hi + 1; l < kLevels; ++l)
     if (t->lev_in[l]) l_hi = l;            // rays in flight from a step with a larger phi_c
-  int l_lo = emit ? P.params.level_init : kLevels;
+  // the level at which this step's seeds enter
+  const int enter = descend_level(trees_per, P.params.level_init, std::min(reach_level(P), l_hi), t->cap);
+  int l_lo = emit ? enter : kLevels;
   for (int l = 0; l < kLevels; ++l)
     if (t->lev_in[l]) { l_lo = std::min(l_lo, l); break; }
   unsigned max_steps = (unsigned)std::min<long long>(2 * steps_bound, 1LL << 30);
@@ -462,7 +464,7 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
       return MORAY_EDEVICE;
   }
   for (int l = l_lo; l <= l_hi; ++l) {
-    const bool seeds = emit && l == P.params.level_init;
+    const bool seeds = emit && l == enter;
     const int lo = seeds ? cur_slot * trees_per : 0, hi = seeds ? (cur_slot + 1) * trees_per : 0;
     e = fp32 ? launch_level<float>(c, t, l, lo, hi, first[l], t->lev_in[l], max_steps, reserve)
              : launch_level<double>(c, t, l, lo, hi, first[l], t->lev_in[l], max_steps, reserve);
