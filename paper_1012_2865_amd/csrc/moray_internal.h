@@ -141,10 +141,13 @@ void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const
 // Level at which the seeds of `trees` trees enter (see the trace kernel): the
 // finest, not beyond `top` (the finest any of them reaches), that still has no
 // more pixels than kDescendLanes and than the level queue has room for (`cap`:
-// a queue too small for a level is reported as such). The repeated part of the work is
-// about that of the last level, on lanes that would otherwise idle; one more level
-// would queue several pixels behind each lane.
-constexpr long long kDescendLanes = 200000;
+// a queue too small for a level is reported as such). kDescendLanes: half the
+// lanes the device holds at once, on which the repeated part of the work runs
+// beside the rest. One 32^3 source, and 20 steps of a 64^3 front: 203 us and
+// 5.3 ms at 13 thousand, 174 us and 4.3 ms at 50 to 100 thousand, 218 us and
+// 5.4 ms at 200 to 400 thousand, 267 us and 6.8 ms beyond; larger problems
+// differ by less than 2%.
+constexpr long long kDescendLanes = 100000;
 inline int descend_level(long long trees, int l0, int top, size_t cap) {
   const long long most = cap < (size_t)kDescendLanes ? (long long)cap : kDescendLanes;
   int l = l0;
