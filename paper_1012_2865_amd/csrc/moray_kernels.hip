@@ -203,6 +203,18 @@ __device__ __forceinline__ double max_f64(double x, double y) {
   return r;
 }
 
+// x = max(x, y) in the lanes of a mask (as a branch: two instructions more, and its wait)
+__device__ __forceinline__ void max_where(double& x, double y, unsigned long long lanes) {
+  unsigned long long all;
+  asm volatile(
+      "s_mov_b64 %[all], exec\n\t"
+      "s_mov_b64 exec, %[lanes]\n\t"
+      "v_max_f64 %[x], %[x], %[y]\n\t"
+      "s_mov_b64 exec, %[all]"
+      : [x] "+v"(x), [all] "=&s"(all)
+      : [y] "v"(y), [lanes] "s"(lanes));
+}
+
 // The current cell's exit: distance, and which axis (neither flag: x). Ties go
 // to the lowest axis.
 struct Exit {
@@ -803,8 +815,8 @@ __device__ __forceinline__ unsigned long long lane0_64(unsigned long long v) {
   return ((unsigned long long)hi << 32) | lo;
 }
 // the lane's place among the lanes of a mask
-__device__ __forceinline__ int lane_rank(unsigned long long m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+__device__ __forceinline__ unsigned lane_rank(unsigned long long m, unsigned base) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, base));
 }
 __device__ __forceinline__ int wave_in_block() { return uniform32((int)(threadIdx.x / kWave)); }
 
@@ -998,29 +1010,34 @@ __device__ __forceinline__ uint32_t line_place(uint32_t h, uint32_t j) { return 
 
 template <bool CACHE, int NS>
 struct DepositCache {
-  uint32_t* key;          // line numbers; kNoSlot: empty
-  double* val;            // [kLines][8]
+  static constexpr int kWaves = kTraceBlock / kWave;
+  uint32_t* key;          // line numbers of all waves' entries; kNoSlot: empty
+  double* val;            // [8] each
   uint32_t* okey;
-  double* oval;           // [kOut][8]
+  double* oval;           // [kOut][8] each
   uint2* moves;           // (entry, line) pairs of one call's evictions
+  uint32_t first;         // the wave's first entry
   int ocount;             // wave-uniform
 
   __device__ void init(int lane) {
     if constexpr (CACHE) {
-      __shared__ uint32_t skey[kTraceBlock / kWave][kLines];
-      __shared__ double sval[kTraceBlock / kWave][8 * kLines];
-      __shared__ uint32_t sokey[kTraceBlock / kWave][kOut];
-      __shared__ double soval[kTraceBlock / kWave][8 * kOut];
-      __shared__ uint2 smoves[kTraceBlock / kWave][kWave];
+      __shared__ uint32_t skey[kWaves * kLines];
+      __shared__ double sval[8 * kWaves * kLines];
+      __shared__ uint32_t sokey[kWaves][kOut];
+      __shared__ double soval[kWaves][8 * kOut];
+      __shared__ uint2 smoves[kWaves * kWave];
       const int wv = wave_in_block();
-      key = skey[wv];
-      val = sval[wv];
+      key = skey;
+      val = sval;
       okey = sokey[wv];
       oval = soval[wv];
-      moves = smoves[wv];
+      moves = smoves;
       ocount = 0;
-      for (int e = lane; e < kLines; e += kWave) key[e] = kNoSlot;
-      for (int e = lane; e < 8 * kLines; e += kWave) val[e] = 0.0;
+      // in a vector register: the step loop has scalar ones to spare for nothing
+      first = (uint32_t)(threadIdx.x / kWave) * kLines;
+      asm volatile("" : "+v"(first));
+      for (int e = lane; e < kLines; e += kWave) key[first + e] = kNoSlot;
+      for (int e = lane; e < 8 * kLines; e += kWave) val[8 * first + e] = 0.0;
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -1031,33 +1048,55 @@ struct DepositCache {
   __device__ void drain(double* acc, int lane) {
     if constexpr (CACHE) {
       __builtin_amdgcn_wave_barrier();
-      for (int j = lane; j < 8 * ocount; j += kWave) add_line(acc, okey[j >> 3], j & 7, oval[j]);
+      static_assert(8 * kOut % kWave == 0, "whole waves of sums");
+      double v[8 * kOut / kWave];
+      uint32_t line[8 * kOut / kWave];
+#pragma unroll
+      for (int k = 0; k < 8 * kOut / kWave; ++k) {
+        v[k] = oval[lane + k * kWave];
+        line[k] = okey[(lane + k * kWave) >> 3];
+      }
+#pragma unroll
+      for (int k = 0; k < 8 * kOut / kWave; ++k)
+        if (lane + k * kWave < 8 * ocount) add_line(acc, line[k], lane & 7, v[k]);
       ocount = 0;
       __builtin_amdgcn_wave_barrier();
     }
   }
-  // A deposit takes two calls, made by every lane of the wave (uniform control
-  // flow), so that the arithmetic of the deposit runs under the first's round
-  // trip. probe: every depositing lane reads its entry's line, exchanges its own
+  // A deposit takes four calls, made by every lane of the wave (uniform control
+  // flow), with the step's other work between them, so that no LDS round trip is
+  // waited for where it is asked (issued and awaited in one place, three of them
+  // took a fifth of the step).
+  // probe: every lane that may deposit reads its entry's line, exchanges its own
   // in, and reads the entry again; the last read tells which line owns the
   // entry from now on (lanes of different lines race for it; the last one wins).
-  // add: where the owner differs from the line before, the entry's sums belong to
+  // list: where the owner differs from the line before, the entry's sums belong to
   // that: the lane whose exchange returned it (the first in the race; a
-  // lane that holds the old line itself can make it several) lists the entry,
-  // and eight lanes per listed entry exchange zeros in and move the old sums to
-  // the buffer (an entry listed twice moves zeros the second time). Then the lanes
+  // lane that holds the old line itself can make it several) lists the entry.
+  // add: eight lanes per listed entry exchange zeros in and get the old sums
+  // (an entry listed twice gives zeros the second time); then the lanes
   // of the owning line add their deposits, and those of a losing line add theirs
   // to memory. The LDS operations of a wave are performed in order, so no wait
-  // separates the exchanges from the adds. The phases are separated by wave
-  // barriers, which keep the compiler from merging them.
+  // separates the exchanges from the adds.
+  // keep: the old sums go to the buffer.
+  // The phases are separated by wave barriers, which keep the compiler from merging them.
   struct Probe {
     uint32_t h, was, before, owner;
+    unsigned long long moved;            // lanes that listed an entry
+    int count;                           // entries whose sums are still to be kept
+    uint2 listed;                        // the entry (x) and line the lane's eight move
+    double old;                          // its sum
   };
-  __device__ __forceinline__ Probe probe(uint32_t slot, uint32_t yz, unsigned long long has) {
-    Probe p{0u, kNoSlot, kNoSlot, kNoSlot};
+  __device__ __forceinline__ Probe probe(uint32_t slot, uint32_t yz, unsigned long long has) const {
+    Probe p;
+    p.moved = 0;
     if constexpr (CACHE) {
       const uint32_t line = slot >> 3;
-      p.h = line_index(line, yz);
+      p.h = first | line_index(line, yz);
+      // undefined in the other lanes, and not known to be: a constant there lets the
+      // compiler compare at once, which waits for the reads
+      asm("" : "=v"(p.was), "=v"(p.before), "=v"(p.owner));
+      asm("" : "=v"(p.listed), "=v"(p.old));
       if (in_mask(has)) {
         p.was = __hip_atomic_load(&key[p.h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         p.before = __hip_atomic_exchange(&key[p.h], line, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1067,8 +1106,40 @@ struct DepositCache {
     }
     return p;
   }
+  __device__ __forceinline__ void list(Probe& p, unsigned long long has, int lane) const {
+    if constexpr (CACHE) {
+      p.moved = has & wave_mask(p.owner != p.was) & wave_mask(p.before == p.was) & wave_mask(p.was != kNoSlot);
+      if (p.moved) {
+        if (in_mask(p.moved)) moves[lane_rank(p.moved, first / (kLines / kWave))] = make_uint2(p.h, p.was);
+        __builtin_amdgcn_wave_barrier();
+        p.listed = moves[first / (kLines / kWave) + (lane >> 3)];   // past the listed ones: unused
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  // the sums of `count` listed entries (at most eight)
+  __device__ __forceinline__ void take(double* acc, Probe& p, int count, int lane) {
+    if (ocount + count > kOut) drain(acc, lane);
+    p.count = count;
+    if ((lane >> 3) < count)
+      p.old = __hip_atomic_exchange(&val[line_place(p.listed.x, lane)], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ __forceinline__ void keep(const Probe& p, int lane) {
+    if constexpr (CACHE) {
+      if (p.moved) {
+        const int i = lane >> 3;
+        if (i < p.count) {
+          oval[8 * ocount + lane] = p.old;
+          if ((lane & 7) == 0) okey[ocount + i] = p.listed.y;
+        }
+        ocount += p.count;
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
   // v[c] belongs to the lane's problem where c < 2^shift
-  __device__ __forceinline__ void add(double* acc, const Probe& p, uint32_t slot, uint32_t shift, const double (&v)[NS],
+  __device__ __forceinline__ void add(double* acc, Probe& p, uint32_t slot, uint32_t shift, const double (&v)[NS],
                                       unsigned long long has, int lane) {
     auto to_memory = [&]() {
 #pragma unroll
@@ -1079,25 +1150,15 @@ struct DepositCache {
       if (in_mask(has)) to_memory();
       return;
     }
-    const unsigned long long displace =
-        has & wave_mask(p.owner != p.was) & wave_mask(p.before == p.was) & wave_mask(p.was != kNoSlot);
-    if (displace) {
-      const int n = __popcll(displace);
-      if (in_mask(displace)) moves[lane_rank(displace)] = make_uint2(p.h, p.was);
-      __builtin_amdgcn_wave_barrier();
-      for (int i0 = 0; i0 < n; i0 += 8) {
-        const int m = n - i0 < 8 ? n - i0 : 8;
-        if (ocount + m > kOut) drain(acc, lane);
-        const int i = lane >> 3;
-        if (i < m) {
-          const uint2 mv = moves[i0 + i];
-          const double old = __hip_atomic_exchange(&val[line_place(mv.x, lane)], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          oval[8 * ocount + lane] = old;
-          if ((lane & 7) == 0) okey[ocount + i] = mv.y;
-        }
-        ocount += m;
-        __builtin_amdgcn_wave_barrier();
+    if (p.moved) {
+      const int n = __popcll(p.moved);
+      int i0 = 0;
+      for (; i0 + 8 < n; i0 += 8) {
+        take(acc, p, 8, lane);
+        keep(p, lane);
+        p.listed = moves[first / (kLines / kWave) + i0 + 8 + (lane >> 3)];
       }
+      take(acc, p, n - i0, lane);
     }
     const unsigned long long mine = has & wave_mask(p.owner == slot >> 3);
     // (a record is aligned to its length, so its sums are places apart by XOR)
@@ -1118,8 +1179,8 @@ struct DepositCache {
     if constexpr (CACHE) {
       drain(acc, lane);
       for (int j = lane; j < 8 * kLines; j += kWave) {
-        const uint32_t line = key[j >> 3];
-        if (line != kNoSlot) add_line(acc, line, j & 7, val[line_place(j >> 3, j)]);
+        const uint32_t h = first + (uint32_t)(j >> 3), line = key[h];
+        if (line != kNoSlot) add_line(acc, line, j & 7, val[line_place(h, j)]);
       }
     }
   }
@@ -1284,8 +1345,6 @@ void trace_level_kernel(TraceArgs<R> a) {
   const int lane = threadIdx.x & (kWave - 1);
   const int pos = lane_pos(lane);
   if (__hip_atomic_load(&a.ctr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrBadInput) return;   // set before this launch: the whole grid
-  WaveTally<NG, THIN> tally;
-  tally.init(lane);
   const int K = a.nseg;                      // a power of two
   const int kshift = __ffs(K) - 1;
   const unsigned long long npix = 12ull << (2 * a.seed_level);
@@ -1309,6 +1368,7 @@ void trace_level_kernel(TraceArgs<R> a) {
       n += ((unsigned long long)hi << 32) | lo;
     }
     n += n_extra;
+    if (n == 0) return;                      // a level no ray reached (the host launches all it may need)
     const unsigned long long waves = (unsigned long long)gridDim.x * (kTraceBlock / kWave);
     unsigned chunk = (unsigned)a.chunk;
     while (chunk >= 2u * kWave && (unsigned long long)chunk * waves > n) chunk >>= 1;
@@ -1319,6 +1379,8 @@ void trace_level_kernel(TraceArgs<R> a) {
   const Tracer<R, NG, PHYS> T(a);
   Ray<R, NG> L;
   int ended = -1;          // kind of the lane's ray that ended and is not yet tallied
+  WaveTally<NG, THIN> tally;
+  tally.init(lane);
   DepositCache<CACHE, NS> cache;
   cache.init(lane);
   SplitWriter<R, NG, THIN> splits;
@@ -1495,6 +1557,10 @@ void trace_level_kernel(TraceArgs<R> a) {
           if (!active) ended = 0;            // outside the root grid: escaped
           else if constexpr (K64) L.kap64 = a.kappa64[L.lin];
           else if constexpr (THIN) L.kap64 = (double)L.kap;
+          if constexpr (NG > 1) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) L.sigma[g] = L.alive[g] ? L.sigma[g] : (R)0;
+          }
         }
         again = kFresh;
       }
@@ -1517,9 +1583,21 @@ void trace_level_kernel(TraceArgs<R> a) {
 #pragma unroll
     for (int g = 0; g < NG; ++g) carries[g] = wave_mask(active && L.alive[g]);
     const unsigned long long root = wave_mask(L.root), owners = wave_mask(active && Tracer<R, NG, PHYS>::owner(L));
+    // Steps until the wave must look up: the steps since rays last started or
+    // changed grids bound every active ray's own (a bound never reached by a correct trace:
+    // cell indices move monotonically), and the mixed mode forms its distances afresh.
+    unsigned todo = a.max_steps - steps;
+    if constexpr (sizeof(R) == 4) todo = todo < kResync - framed ? todo : kResync - framed;
+    const unsigned allowed = todo;
     while (run) {
       // ---- one cell: exit plane, split test, deposit, step ----
       // In every lane; those without a ray compute on values nothing reads.
+      typename DepositCache<CACHE, NS>::Probe probe;
+      uint32_t slot = NS > 1 || THIN ? L.slot0 + ((uint32_t)L.lin << L.ashift) : L.slot0 + (uint32_t)L.lin;
+      // (with the optically-thin approximation only once it is known which rays
+      // are thin here: those deposit nothing and would displace lines for it)
+      const unsigned long long probed = run & owners;
+      if constexpr (!THIN) probe = cache.probe(slot, L.yz, probed);
       const Exit x = L.g.exit();
       const int here = L.lin;
       const uint32_t yz = L.yz;
@@ -1572,13 +1650,16 @@ void trace_level_kernel(TraceArgs<R> a) {
         kpre = kappa_step[next];
       }
       const unsigned long long thinly = pos & thin, dep = ((pos & ~thinly) | (thinly & own)) & owners;
-      uint32_t slot = NS > 1 || THIN ? L.slot0 + ((uint32_t)here << L.ashift) : L.slot0 + (uint32_t)here;
-      if constexpr (THIN) slot += in_mask(thinly) ? 1u : 0u;
-      const typename DepositCache<CACHE, NS>::Probe probe = cache.probe(slot, yz, dep);
+      if constexpr (THIN) {
+        slot += in_mask(thinly) ? 1u : 0u;
+        probe = cache.probe(slot, yz, dep);
+      }
+      cache.list(probe, THIN ? dep : probed, lane);
       double v[NS];                            // absorbed rate, then its energy moment or the momentum rate
 #pragma unroll
       for (int c = 0; c < NS; ++c) v[c] = 0.0;
-      const R col = L.kap * (in_mask(pos) ? (R)dr : (R)0);
+      R col = L.kap * (R)dr;
+      col = in_mask(pos) ? col : (R)0;
       L.segs += in_mask(pos) ? 1u : 0u;
       if constexpr (THIN) {
         if (in_mask(thinly)) {
@@ -1599,10 +1680,12 @@ void trace_level_kernel(TraceArgs<R> a) {
       } else {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-          if (in_mask(go & carries[g])) {
+          // a lane that does not go on has no column, one without the group no
+          // cross-section: both absorb nothing
+          if (NG == 1 || (go & carries[g])) {
             const double d = absorb(L.P[g], col * L.sigma[g]);
-            v[0] += d;
-            if constexpr (NG > 1) v[1] = fma(d, L.eexc[g], v[1]);
+            v[0] = g == 0 ? d : v[0] + d;
+            if constexpr (NG > 1) v[1] = g == 0 ? d * L.eexc[g] : fma(d, L.eexc[g], v[1]);
           }
         }
       }
@@ -1617,15 +1700,20 @@ void trace_level_kernel(TraceArgs<R> a) {
         v[0] *= fc;
         if constexpr (NG > 1) v[1] *= fc;
       }
-      if (in_mask(go)) L.g.r = max_f64(L.g.r, r_end);
+      max_where(L.g.r, r_end, go);
       // truncated groups (not in a ray that halts here), and rays without a group left
       const unsigned long long on = go & ~halt;
       unsigned long long any = 0;
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const unsigned long long low = on & carries[g] & wave_mask(L.P[g] < L.pmin[g]);
-        if (in_mask(low)) L.cut[g] = L.segs;
-        carries[g] &= ~low;
+        if (low) {
+          if (in_mask(low)) {
+            L.cut[g] = L.segs;
+            L.sigma[g] = (R)0;
+          }
+          carries[g] &= ~low;
+        }
         any |= carries[g];
       }
       at_halt |= halt;
@@ -1640,6 +1728,7 @@ void trace_level_kernel(TraceArgs<R> a) {
       } else {
         asm volatile("" ::"v"(kpre));
       }
+      cache.keep(probe, lane);
       L.kap = kpre;
       if constexpr (THIN) L.kap64 = K64 ? kpre64 : (double)kpre;
       // out of the root grid, or into another frame
@@ -1654,16 +1743,13 @@ void trace_level_kernel(TraceArgs<R> a) {
           from = here;
         }
       }
-      // the steps since rays last started or changed grids bound every active ray's own; the
-      // bound is never reached by a correct trace (cell indices move monotonically)
-      if (++steps >= a.max_steps) break;
+      if (--todo == 0) break;
       if constexpr (PART) {
         if (__popcll(~run) >= a.refill && !drained) break;
       }
-      if constexpr (sizeof(R) == 4) {
-        if (++framed >= kResync) break;
-      }
     }
+    steps += allowed - todo;
+    framed += allowed - todo;
     active = in_mask(run);
     if (in_mask(at_split)) ended = 2;
     if (in_mask(at_end)) ended = 1;
