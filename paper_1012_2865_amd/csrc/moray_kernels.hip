@@ -215,6 +215,11 @@ __device__ __forceinline__ void max_where(double& x, double y, unsigned long lon
       : [y] "v"(y), [lanes] "s"(lanes));
 }
 
+// n += 1 there
+__device__ __forceinline__ void count_where(unsigned& n, unsigned long long lanes) {
+  asm("v_addc_co_u32_e64 %0, vcc, 0, %0, %1" : "+v"(n) : "s"(lanes) : "vcc");
+}
+
 // The current cell's exit: distance, and which axis (neither flag: x). Ties go
 // to the lowest axis.
 struct Exit {
@@ -433,7 +438,6 @@ constexpr double kLog2e = 1.4426950408889634074;
 // what the cross-section is multiplied by for absorb's argument
 template <typename R> constexpr double kSigmaScale = sizeof(R) == 4 ? kLog2e : 1.0;
 
-constexpr int kZShift = 13;      // see line_index
 constexpr unsigned kNoCut = 0xffffffffu;
 
 // Per-lane ray state. A ray carries NG energy groups of its source: they share
@@ -446,7 +450,7 @@ struct Ray {
   double rs, tbox;        // a step whose exit lies beyond rs splits the ray, at tbox or beyond leaves the grid
   int st[3];              // what crossing a plane of each axis adds to lin
   int lin;                // batch-wide cell index
-  uint32_t yz;            // the local cell's j + (k << kZShift)
+  uint32_t yz;            // the local cell's j + 8 k
   int sy, sz;             // what crossing a y or z plane adds to it
   int q;                  // grid index
   bool root;              // it is the problem's root grid
@@ -562,9 +566,9 @@ struct Tracer {
     L.st[1] = L.g.up(1) ? sx : -sx;
     L.st[2] = L.g.up(2) ? sxy : -sxy;
     L.lin = (int)off + c[0] + sx * (c[1] + n[1] * c[2]);
-    L.yz = (uint32_t)c[1] + ((uint32_t)c[2] << kZShift);
+    L.yz = (uint32_t)c[1] + 8u * (uint32_t)c[2];
     L.sy = L.g.up(1) ? 1 : -1;
-    L.sz = L.g.up(2) ? 1 << kZShift : -(1 << kZShift);
+    L.sz = L.g.up(2) ? 8 : -8;
   }
 
   // Local cell of batch-wide index lin in grid q.
@@ -997,16 +1001,17 @@ constexpr int kOut = 24;                       // evicted lines waiting for thei
 // entry, and a line leaves when the wave has moved on by eight cells (a
 // multiplicative hash of the line number put about one conflict into every step
 // and as many requests on the memory side as a table of single cells). yz is the
-// local cell's j + (k << kZShift). Any value is correct: a line that is found
+// local cell's j + 8 k, whose low six bits differ between any two cells less than
+// eight apart in y and z. Any value is correct: a line that is found
 // under two entries is summed in both.
-__device__ __forceinline__ uint32_t line_index(uint32_t line, uint32_t yz) {
-  return (yz & 7u) | ((yz >> (kZShift - 3)) & 0x38u) | ((line & 1u) << 6);
+__device__ __forceinline__ uint32_t line_index(uint32_t slot, uint32_t yz) {
+  static_assert(kLines == 128, "two lines of 64 cells");
+  return ((slot << 3) & 64u) | (yz & 63u);
 }
-
-// Where sum j of entry h's line is kept: in 64 banks of 32 bits four entries side
+// Where sum j of entry h's line is kept (bytes): in 64 banks of 32 bits four entries side
 // by side have their own, so those of different z are rotated against each other
 // (radiation pressure 9.98 -> 8.67 ms).
-__device__ __forceinline__ uint32_t line_place(uint32_t h, uint32_t j) { return 8u * h + ((j ^ (h >> 3)) & 7u); }
+__device__ __forceinline__ uint32_t line_place(uint32_t h, uint32_t j) { return (h << 6) | (((j << 3) ^ h) & 56u); }
 
 template <bool CACHE, int NS>
 struct DepositCache {
@@ -1041,6 +1046,7 @@ struct DepositCache {
       __builtin_amdgcn_wave_barrier();
     }
   }
+  __device__ __forceinline__ double* at(uint32_t bytes) const { return (double*)((char*)val + bytes); }
   static __device__ __forceinline__ void add_line(double* acc, uint32_t line, int j, double v) {
     if (v != 0.0) unsafeAtomicAdd(&acc[((unsigned long long)line << 3) + j], v);
   }
@@ -1092,7 +1098,7 @@ struct DepositCache {
     p.moved = 0;
     if constexpr (CACHE) {
       const uint32_t line = slot >> 3;
-      p.h = first | line_index(line, yz);
+      p.h = first | line_index(slot, yz);
       // undefined in the other lanes, and not known to be: a constant there lets the
       // compiler compare at once, which waits for the reads
       asm("" : "=v"(p.was), "=v"(p.before), "=v"(p.owner));
@@ -1122,7 +1128,7 @@ struct DepositCache {
     if (ocount + count > kOut) drain(acc, lane);
     p.count = count;
     if ((lane >> 3) < count)
-      p.old = __hip_atomic_exchange(&val[line_place(p.listed.x, lane)], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      p.old = __hip_atomic_exchange(at(line_place(p.listed.x, lane)), 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __builtin_amdgcn_wave_barrier();
   }
   __device__ __forceinline__ void keep(const Probe& p, int lane) {
@@ -1167,7 +1173,7 @@ struct DepositCache {
 #pragma unroll
       for (int c = 0; c < NS; ++c)
         if (c == 0 || (c >> shift) == 0)
-          __hip_atomic_fetch_add(&val[place ^ (uint32_t)c], v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(at(place ^ (8u * c)), v[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __builtin_amdgcn_wave_barrier();
     const unsigned long long lost = has & ~mine;
@@ -1180,7 +1186,7 @@ struct DepositCache {
       drain(acc, lane);
       for (int j = lane; j < 8 * kLines; j += kWave) {
         const uint32_t h = first + (uint32_t)(j >> 3), line = key[h];
-        if (line != kNoSlot) add_line(acc, line, j & 7, val[line_place(h, j)]);
+        if (line != kNoSlot) add_line(acc, line, j & 7, *at(line_place(h, j)));
       }
     }
   }
@@ -1351,31 +1357,59 @@ void trace_level_kernel(TraceArgs<R> a) {
   // rays of the launch that are not children: resumed ones (time-dependent rays), then seeds
   const unsigned long long n_held = HALT ? a.n_held : 0ull;
   const unsigned long long n_extra = n_held + (unsigned long long)(a.seed_end - a.seed_begin) * npix;
-  const unsigned long long* cnt_in = a.ctr->count[a.cin];
   unsigned long long* head_in = a.ctr->head[a.cin];
-  // rays claimed per atomic: the launch's setting, halved while the level
-  // holds less than one claim for every wave of the launch, down to one ray
-  // per lane, so that a level of few rays spreads over the waves instead of
-  // queueing several rays behind each lane of a few of them
-  // (kept in LDS: the claim path alone reads it, and a scalar register held
-  // through the step loop would push the loop's own values out of theirs)
-  __shared__ unsigned s_chunk[kTraceBlock / kWave];
+  // The level's rays in units of `span`: those of each segment's children, then
+  // the others. A unit is the launch's setting, halved while the level holds less
+  // than one for every wave of the launch, down to one ray per lane. Wave `rank`
+  // of the launch starts with its share of the first `fixed` units (at most one),
+  // which takes no atomic; the others are claimed one by one from K equal parts of
+  // them. Claimed from the first ray on, the 3072 waves of a launch queued up at
+  // the counters of a small level: 5 to 50 us of the 35 to 90 a level took (a
+  // 32^3 source 173 -> 107 us, 20 steps of a 64^3 front 4.1 -> 3.1 ms).
+  __shared__ struct Level {
+    unsigned first[kSegMax], rays[kSegMax];  // of each segment: its first unit, its rays
+    unsigned children, fixed, open, span;    // units of children; units dealt at the start; the others; rays of one
+  } lev;                                     // (all waves store the same values)
+  const unsigned waves = gridDim.x * (kTraceBlock / kWave);
+  // the blocks of one XCD (every eighth) have consecutive ranks: their rays, and
+  // those that split from them, stay on it
+  const unsigned blk = (gridDim.x & 7u) ? blockIdx.x : (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const unsigned rank = blk * (kTraceBlock / kWave) + wave_in_block();
+  unsigned u_next, u_end;                    // the units the wave has claimed
   {
-    unsigned long long n = lane < K ? 4ull * min(cnt_in[lane], a.seg_cap) : 0ull;
+    const unsigned rays = lane < K ? (unsigned)(4ull * min(a.ctr->count[a.cin][lane], a.seg_cap)) : 0u;
+    unsigned long long all = rays;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
-      const unsigned lo = __shfl_xor((unsigned)n, o), hi = __shfl_xor((unsigned)(n >> 32), o);
-      n += ((unsigned long long)hi << 32) | lo;
+      const unsigned lo = __shfl_xor((unsigned)all, o), hi = __shfl_xor((unsigned)(all >> 32), o);
+      all += ((unsigned long long)hi << 32) | lo;
     }
-    n += n_extra;
-    if (n == 0) return;                      // a level no ray reached (the host launches all it may need)
-    const unsigned long long waves = (unsigned long long)gridDim.x * (kTraceBlock / kWave);
-    unsigned chunk = (unsigned)a.chunk;
-    while (chunk >= 2u * kWave && (unsigned long long)chunk * waves > n) chunk >>= 1;
-    s_chunk[wave_in_block()] = chunk;   // every lane holds the same sum and stores the same value
+    all = uniform64(all) + n_extra;
+    if (all == 0) return;                    // a level no ray reached (the host launches all it may need)
+    unsigned span = (unsigned)a.chunk;
+    while (span >= 2u * kWave && (unsigned long long)span * waves > all) span >>= 1;
+    unsigned upto = (rays + span - 1) / span;
+    const unsigned mine = upto;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const unsigned before = __shfl_up(upto, o);
+      upto += lane >= o ? before : 0u;
+    }
+    const unsigned children = __builtin_amdgcn_readlane(upto, kWave - 1);
+    const unsigned units = children + (unsigned)((n_extra + span - 1) / span);
+    const unsigned fixed = min(units, waves);
+    lev.first[lane] = upto - mine;
+    lev.rays[lane] = rays;
+    lev.children = children;
+    lev.fixed = fixed;
+    lev.open = units - fixed;
+    lev.span = span;
+    const double share = (double)fixed / (double)waves;
+    u_next = uniform32((int)(share * (double)rank));
+    u_end = rank + 1 == waves ? fixed : uniform32((int)(share * (double)(rank + 1)));
   }
-  // the wave's home segment: it claims there first and writes its splits there
-  const int home = (int)((blockIdx.x * (kTraceBlock / kWave) + wave_in_block()) % (unsigned)K);
+  // the segment the wave writes its splits to first, and the part it claims from first
+  const int home = (int)(((unsigned long long)rank * (unsigned)K) / waves);
   const Tracer<R, NG, PHYS> T(a);
   Ray<R, NG> L;
   int ended = -1;          // kind of the lane's ray that ended and is not yet tallied
@@ -1399,10 +1433,11 @@ void trace_level_kernel(TraceArgs<R> a) {
     L.alive[g] = false;
     L.P[g] = 0.0;
   }
-  // the wave's current claim: [w_next, w_end) of segment w_seg, whose first
-  // w_nch indices are children and the rest resumed rays and seeds from w_slo on
-  unsigned long long w_next = 0, w_end = 0, w_nch = 0, w_slo = 0;
-  int w_seg = home;
+  // the rays the wave takes next, [w_next, w_end): children, by their place in
+  // the queue, or resumed rays and seeds
+  unsigned long long w_next = 0, w_end = 0;
+  bool w_child = false;
+  int w_part = home;
   bool drained = false;
   HaltWriter<R, NG> halts;
   if constexpr (HALT) halts.init();
@@ -1462,73 +1497,63 @@ void trace_level_kernel(TraceArgs<R> a) {
       unsigned long long q = 0;
       while (left) {
         if (w_next >= w_end) {
-          // Claim a chunk: from the wave's current segment while it has rays
-          // left; once it is used up, every lane reads one segment's counters
-          // (one round trip for all of them), the wave picks the first segment
-          // with rays left after it, and claims there with one atomic; a claim
-          // that finds the segment used up in the meantime looks again. No
-          // segment with rays left: the level is drained.
-          bool got = false;
-          for (;;) {
-            // the current segment first: one load while it lasts
-            {
-              const unsigned long long c_nch = 4ull * min(cnt_in[w_seg], a.seg_cap);
-              const unsigned long long c_slo = ((unsigned long long)w_seg * n_extra) >> kshift;
-              const unsigned long long c_size = c_nch + ((((unsigned long long)w_seg + 1) * n_extra) >> kshift) - c_slo;
+          if (u_next >= u_end) {
+            // Claim a unit: from the wave's current part while it has units
+            // left; once it is used up, every lane reads one part's counter
+            // (one round trip for all of them), the wave picks the first part
+            // with units left after it, and claims there with one atomic; a claim
+            // that finds the part used up in the meantime looks again. No
+            // part with units left: the level is drained.
+            const unsigned open = (unsigned)uniform32((int)lev.open);
+            auto part = [&](unsigned p) { return (unsigned)(((unsigned long long)p * open) >> kshift); };
+            auto claim = [&](int p) {
+              const unsigned b0 = part((unsigned)p), size = part((unsigned)p + 1u) - b0;
+              unsigned long long b = 0;
+              if (lane == 0) b = atomicAdd(&head_in[p], 1ull);
+              b = lane0_64(b);
+              if (b >= size) return false;
+              u_next = (unsigned)uniform32((int)lev.fixed) + b0 + (unsigned)b;
+              u_end = u_next + 1u;
+              return true;
+            };
+            bool got = false;
+            while (open != 0) {
+              // the current part first: one load while it lasts
               const unsigned long long seen =
-                  uniform64(__hip_atomic_load(&head_in[w_seg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-              if (seen < c_size) {
-                unsigned long long b = 0;
-                const unsigned long long chunk = uniform32((int)s_chunk[wave_in_block()]);
-                if (lane == 0) b = atomicAdd(&head_in[w_seg], chunk);
-                b = lane0_64(b);
-                if (b < c_size) {
-                  w_nch = c_nch;
-                  w_slo = c_slo;
-                  w_next = b;
-                  w_end = min(b + chunk, c_size);
-                  got = true;
-                  break;
-                }
-              }
+                  uniform64(__hip_atomic_load(&head_in[w_part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+              if (seen < part((unsigned)w_part + 1u) - part((unsigned)w_part) && (got = claim(w_part))) break;
+              bool has = false;
+              if (lane < K)
+                has = __hip_atomic_load(&head_in[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                      part((unsigned)lane + 1u) - part((unsigned)lane);
+              const unsigned long long live = wave_mask(has);
+              if (!live) break;
+              const unsigned long long ahead = live & (~0ull << w_part);
+              w_part = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
+              if ((got = claim(w_part))) break;
             }
-            bool has = false;
-            if (lane < K) {
-              const unsigned long long size = 4ull * min(cnt_in[lane], a.seg_cap) +
-                                              ((((unsigned long long)lane + 1) * n_extra) >> kshift) -
-                                              (((unsigned long long)lane * n_extra) >> kshift);
-              has = __hip_atomic_load(&head_in[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < size;
-            }
-            const unsigned long long live = wave_mask(has);
-            if (!live) break;
-            const unsigned long long ahead = live & (~0ull << w_seg);
-            const int sg = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
-            // the chosen segment's rays, once more for the whole wave
-            const unsigned long long s_nch = 4ull * min(cnt_in[sg], a.seg_cap);
-            const unsigned long long s_slo = ((unsigned long long)sg * n_extra) >> kshift;
-            const unsigned long long s_size = s_nch + ((((unsigned long long)sg + 1) * n_extra) >> kshift) - s_slo;
-            unsigned long long b = 0;
-            const unsigned long long chunk = uniform32((int)s_chunk[wave_in_block()]);
-            if (lane == 0) b = atomicAdd(&head_in[sg], chunk);
-            b = lane0_64(b);
-            w_seg = sg;
-            if (b < s_size) {
-              w_nch = s_nch;
-              w_slo = s_slo;
-              w_next = b;
-              w_end = min(b + chunk, s_size);
-              got = true;
-              break;
-            }
+            if (!got) { drained = true; break; }
           }
-          if (!got) { drained = true; break; }
+          const unsigned children = (unsigned)uniform32((int)lev.children), span = (unsigned)uniform32((int)lev.span);
+          const unsigned u = u_next++;
+          w_child = u < children;
+          if (w_child) {
+            const int sg = __popcll(wave_mask(lane < K && lev.first[lane] <= u)) - 1;
+            const unsigned in = (u - (unsigned)uniform32((int)lev.first[sg])) * span;
+            const unsigned long long base = 4ull * (unsigned long long)sg * a.seg_cap;
+            w_next = base + in;
+            w_end = base + min(in + span, (unsigned)uniform32((int)lev.rays[sg]));
+          } else {
+            w_next = (unsigned long long)(u - children) * span;
+            w_end = min(w_next + span, n_extra);
+          }
         }
         const unsigned long long idx = w_next + __popcll(left & bits_below(pos));
         const bool mine = ((left >> pos) & 1ull) && idx < w_end;
         if (mine) {
           take = true;
-          child = idx < w_nch;
-          q = child ? 4ull * (unsigned long long)w_seg * a.seg_cap + idx : w_slo + (idx - w_nch);
+          child = w_child;
+          q = idx;
         }
         const unsigned long long got_mask = pos_mask(mine);
         w_next += __popcll(got_mask);
@@ -1599,8 +1624,8 @@ void trace_level_kernel(TraceArgs<R> a) {
       const unsigned long long probed = run & owners;
       if constexpr (!THIN) probe = cache.probe(slot, L.yz, probed);
       const Exit x = L.g.exit();
-      const int here = L.lin;
-      const uint32_t yz = L.yz;
+      const int here = L.lin;                  // (used with the optically-thin approximation alone,
+      const uint32_t yz = L.yz;                // whose step is not at its limit)
       const unsigned long long leave = wave_mask(x.t >= L.tbox);
       unsigned long long thin = 0;
       double tc64 = 0.0, rs = L.rs;
@@ -1643,6 +1668,8 @@ void trace_level_kernel(TraceArgs<R> a) {
       L.g.step(x, L.st, L.sy, L.sz, L.lin, L.yz);
       R kpre = (R)0;
       double kpre64 = 0.0;
+      R col = L.kap * (R)dr;
+      col = in_mask(pos) ? col : (R)0;
       const unsigned next = in_mask(go & ~leave) ? (unsigned)L.lin : 0u;
       if constexpr (K64) {
         kpre64 = kappa64_step[next];
@@ -1655,12 +1682,22 @@ void trace_level_kernel(TraceArgs<R> a) {
         probe = cache.probe(slot, yz, dep);
       }
       cache.list(probe, THIN ? dep : probed, lane);
+      // groups that fell below their cutoff here (not in a ray that halts here)
+      const unsigned long long on = go & ~halt;
+      auto cutoff = [&](int g) {
+        const unsigned long long low = on & carries[g] & wave_mask(L.P[g] < L.pmin[g]);
+        if (low) {
+          if (in_mask(low)) {
+            L.cut[g] = L.segs;
+            L.sigma[g] = (R)0;
+          }
+          carries[g] &= ~low;
+        }
+      };
       double v[NS];                            // absorbed rate, then its energy moment or the momentum rate
 #pragma unroll
       for (int c = 0; c < NS; ++c) v[c] = 0.0;
-      R col = L.kap * (R)dr;
-      col = in_mask(pos) ? col : (R)0;
-      L.segs += in_mask(pos) ? 1u : 0u;
+      count_where(L.segs, pos);
       if constexpr (THIN) {
         if (in_mask(thinly)) {
           // no photons removed
@@ -1677,6 +1714,7 @@ void trace_level_kernel(TraceArgs<R> a) {
           v[0] = absorb(L.P[0], col * L.sigma[0]);
           L.thin = false;
         }
+        cutoff(0);
       } else {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
@@ -1686,6 +1724,7 @@ void trace_level_kernel(TraceArgs<R> a) {
             const double d = absorb(L.P[g], col * L.sigma[g]);
             v[0] = g == 0 ? d : v[0] + d;
             if constexpr (NG > 1) v[1] = g == 0 ? d * L.eexc[g] : fma(d, L.eexc[g], v[1]);
+            cutoff(g);
           }
         }
       }
@@ -1701,21 +1740,9 @@ void trace_level_kernel(TraceArgs<R> a) {
         if constexpr (NG > 1) v[1] *= fc;
       }
       max_where(L.g.r, r_end, go);
-      // truncated groups (not in a ray that halts here), and rays without a group left
-      const unsigned long long on = go & ~halt;
-      unsigned long long any = 0;
+      unsigned long long any = 0;              // rays with a group left
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const unsigned long long low = on & carries[g] & wave_mask(L.P[g] < L.pmin[g]);
-        if (low) {
-          if (in_mask(low)) {
-            L.cut[g] = L.segs;
-            L.sigma[g] = (R)0;
-          }
-          carries[g] &= ~low;
-        }
-        any |= carries[g];
-      }
+      for (int g = 0; g < NG; ++g) any |= carries[g];
       at_halt |= halt;
       at_end |= on & ~any;
       run = on & any;
@@ -1740,7 +1767,7 @@ void trace_level_kernel(TraceArgs<R> a) {
         at_cross |= cross;
         if (in_mask(cross)) {
           again = kCross + x.axis();
-          from = here;
+          from = L.lin - x.pick(L.st[0], L.st[1], L.st[2]);
         }
       }
       if (--todo == 0) break;
