@@ -2,6 +2,7 @@
 // adaptive ray tracer. Not part of the public ABI.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <cstddef>
 #include <cstdint>
 
 namespace moray {
@@ -128,13 +129,19 @@ constexpr int kSegMax = 64;
 
 struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
-  unsigned long long head[kLevels][kSegMax];    // slots claimed from each segment
   unsigned long long lost_rays;                 // children dropped on overflow
   unsigned int err;                             // bit flags, see kErr*
   unsigned int pad;
   unsigned long long halt_count;                // time-dependent rays halted in this step
   unsigned long long halt_levels[kLevels];      // of them, per HEALPix level
+  // Units of each part of a level claimed beyond those dealt at its launch's start
+  // (see the trace kernel), 64 bytes apart: the memory side performs the atomics of
+  // one line one after the other, and waves that run out together claim together.
+  struct alignas(64) Head {
+    unsigned long long n;
+  } head[kLevels][kSegMax];
 };
+constexpr size_t kCountersRead = offsetof(Counters, head);   // the part the host reads
 
 constexpr unsigned kErrOverflow = 1u;
 constexpr unsigned kErrBadInput = 2u;

@@ -44,6 +44,14 @@ __device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin
 // z and sin(theta) come from exact integers; the azimuth is reduced to the
 // first octant before sin/cos so multiples of pi/4 are exact.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t compact_even_bits(uint32_t x) {
+  x &= 0x55555555u;
+  x = (x | (x >> 1)) & 0x33333333u;
+  x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+  x = (x | (x >> 4)) & 0x00FF00FFu;
+  x = (x | (x >> 8)) & 0x0000FFFFu;
+  return x;
+}
 __device__ __forceinline__ uint64_t compact_even_bits(uint64_t x) {
   x &= 0x5555555555555555ull;
   x = (x | (x >> 1)) & 0x3333333333333333ull;
@@ -85,61 +93,69 @@ __device__ __forceinline__ void sincos_octant(double beta, double& s, double& c)
   c = fma(x2, -pc, 1.0);
 }
 
+// 1/b, and a/b, of positive finite numbers far from the ends of the range: the
+// hardware's estimate and two Newton steps, without the scaling and special cases
+// of a general division (which take as many instructions again). The quotient's
+// last step is Markstein's: for integers below 2^20 it is the rounded quotient,
+// whose distance from a midpoint is then above 2^-75 of it.
+__device__ __forceinline__ double reciprocal(double b) {
+  double y = __builtin_amdgcn_rcp(b);
+  y = fma(fma(-b, y, 1.0), y, y);
+  return fma(fma(-b, y, 1.0), y, y);
+}
+__device__ __forceinline__ double ratio(double a, double b) {
+  const double y = reciprocal(b), q = a * y;
+  return fma(fma(-b, q, a), y, q);
+}
+// a/3 rounded (Markstein 1990)
+__device__ __forceinline__ double third(double a) {
+  const double q = a * (1.0 / 3.0);
+  return fma(fma(-3.0, q, a), 1.0 / 3.0, q);
+}
+
 // I is the integer type of the ring arithmetic: every intermediate is below
-// 16 Ns^2, so 32 bits hold it up to level 13.
+// 16 Ns^2, so 32 bits hold it up to level 13. The polar and equatorial rings, the
+// octants and the quarter turns differ by selects, not branches: the lanes of a
+// wave straddle them, and a ray start is a tenth of a large level.
 template <typename I>
 __device__ __forceinline__ void healpix_dir_t(int level, uint64_t pix, double& vx, double& vy, double& vz) {
+  using B = std::conditional_t<sizeof(I) == 4, uint32_t, uint64_t>;   // pixel numbers
   const I ns = (I)1 << level;
-  const int face = (int)(pix >> (2 * level));
-  const uint64_t ipf = pix & ((1ull << (2 * level)) - 1ull);
+  const int face = (int)((B)pix >> (2 * level));
+  const B ipf = (B)pix & (((B)1 << (2 * level)) - (B)1);
   const I ix = (I)compact_even_bits(ipf);
-  const I iy = (I)compact_even_bits(ipf >> 1);
+  const I iy = (I)compact_even_bits((B)(ipf >> 1));
   const int row = face >> 2;                              // 0 north, 1 equator, 2 south
   const I jr = (I)(row + 2) * ns - ix - iy - 1;
   const I jpf = 2 * (face & 3) + (row == 1 ? 0 : 1);
-  I nr;
-  int kshift;
-  double z, sth;
-  if (jr < ns || jr > 3 * ns) {
-    nr = (jr < ns) ? jr : 4 * ns - jr;
-    const double den = 3.0 * (double)ns * (double)ns;
-    z = (double)(3 * ns * ns - nr * nr) / den;
-    sth = (double)nr * sqrt((double)(6 * ns * ns - nr * nr)) / den;
-    if (jr > 3 * ns) z = -z;
-    kshift = 0;
-  } else {
-    nr = ns;
-    const I m = 2 * (2 * ns - jr);
-    z = (double)m / (3.0 * (double)ns);
-    sth = sqrt((double)(9 * ns * ns - m * m)) / (3.0 * (double)ns);
-    kshift = (int)((jr - ns) & 1);
-  }
+  const bool north = jr < ns, south = jr > 3 * ns, polar = north || south;
+  const I nr = north ? jr : (south ? 4 * ns - jr : ns);
+  const I m = 2 * (2 * ns - jr);
+  // z = (3 Ns^2 - nr^2) / (3 Ns^2) in the caps, m / (3 Ns) between them, and
+  // sin(theta) likewise
+  const int scale = polar ? -2 * level : -level;
+  double z = ldexp(third((double)(polar ? 3 * ns * ns - nr * nr : m)), scale);
+  const double root = sqrt((double)(polar ? 6 * ns * ns - nr * nr : 9 * ns * ns - m * m));
+  const double sth = ldexp(third(polar ? (double)nr * root : root), scale);
+  z = south ? -z : z;
+  const int kshift = polar ? 0 : (int)((jr - ns) & 1);
   I jp = (jpf * nr + ix - iy + 1 + kshift) >> 1;          // the numerator is always even
-  if (jp > 4 * nr) jp -= 4 * nr;
-  if (jp < 1) jp += 4 * nr;
-  const I num = 2 * jp - kshift - 1, den = 2 * nr;
-  const I q = num / den, rem = num - q * den;
-  double c, s;
-  if (2 * rem == den) {
-    c = s = sqrt(0.5);
-  } else {
-    const bool low = 2 * rem < den;
-    const I m = low ? rem : den - rem;
-    const double beta = ((double)m / (double)den) * (M_PI / 2.0);
-    double sb, cb;
-    sincos_octant(beta, sb, cb);
-    c = low ? cb : sb;
-    s = low ? sb : cb;
-  }
-  double cx, cy;
-  switch (q & 3) {
-    case 0: cx = c; cy = s; break;
-    case 1: cx = -s; cy = c; break;
-    case 2: cx = -c; cy = -s; break;
-    default: cx = s; cy = -c; break;
-  }
-  vx = sth * cx;
-  vy = sth * cy;
+  jp -= jp > 4 * nr ? 4 * nr : 0;
+  jp += jp < 1 ? 4 * nr : 0;
+  const I num = 2 * jp - kshift - 1, den = 2 * nr;        // quarter turns: num / den, below 4
+  const int q = (num >= den ? 1 : 0) + (num >= 2 * den ? 1 : 0) + (num >= 3 * den ? 1 : 0);
+  const I rem = num - (I)q * den;
+  const bool low = 2 * rem < den, diagonal = 2 * rem == den;
+  const I mo = low ? rem : den - rem;
+  double sb, cb;
+  if constexpr (sizeof(I) == 4) sincos_octant(ratio((double)mo, (double)den) * (M_PI / 2.0), sb, cb);
+  else sincos_octant(((double)mo / (double)den) * (M_PI / 2.0), sb, cb);
+  sb = diagonal ? M_SQRT1_2 : sb;
+  cb = diagonal ? M_SQRT1_2 : cb;
+  const bool odd = (q & 1) != 0;
+  const double cx = low != odd ? cb : sb, cy = low != odd ? sb : cb;
+  vx = sth * (q == 1 || q == 2 ? -cx : cx);
+  vy = sth * (q >= 2 ? -cy : cy);
   vz = z;
 }
 
@@ -314,7 +330,7 @@ struct Geom32 {
     hinv = 1.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      e[k] = v[k] == 0.0 ? 0.0 : 1.0 / fabs(v[k]);
+      e[k] = v[k] == 0.0 ? 0.0 : reciprocal(fabs(v[k]));
       if (v[k] < 0.0) neg |= 1u << k;
     }
   }
@@ -507,7 +523,7 @@ struct Tracer {
   static __device__ double split_radius(double split_r, double four_pi_phi, int level, int level_max, bool child) {
     if (level >= level_max) return __builtin_huge_val();
     const double h = child ? 2.0 : 1.0;
-    double rs = ldexp(split_r, level) / h;
+    double rs = ldexp(split_r, child ? level - 1 : level);
     if constexpr (sizeof(R) == 8) {
       const double need = ldexp(12.0, 2 * level);
       auto test = [&](double t) { return need < four_pi_phi * ((t * h) * (t * h)); };
@@ -550,15 +566,14 @@ struct Tracer {
     L.root = !child;
     L.g.frame(sl, c, n, child, L.tbox);
     const int level = level_of(S, L);
-    const double hinv = child ? 0.5 : 1.0;
     L.rs = split_radius(S.split_r, S.four_pi_phi_c, level, S.level_max, child);
     if constexpr (THIN) L.rs_thin = split_radius(S.split_r_thin, S.four_pi_phi_thin, level, S.level_max, child);
     if constexpr (COVER) {
       // sqrt(pi/3) 2^-l, the pixel's width at unit distance
-      L.lpix = S.covering ? ldexp(1.0233267079464885, -level) / hinv : 0.0;
+      L.lpix = S.covering ? ldexp(1.0233267079464885, child ? 1 - level : -level) : 0.0;
       if constexpr (sizeof(R) == 4) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) L.ad[k] = fabs(L.d[k]) / hinv;
+        for (int k = 0; k < 3; ++k) L.ad[k] = child ? 2.0 * fabs(L.d[k]) : fabs(L.d[k]);
       }
     }
     const int sx = n[0], sxy = n[0] * n[1];
@@ -751,13 +766,15 @@ struct Tracer {
         q = (int)(-k) - 1;
         into_child(q, c, x, v, 3);
       }
+      L.kap = k;
     } else if (again == kResyncFrame) {
       cell(S, q, from, c);
     } else if (!cross(S, q, from, again - kCross, c, x, v)) {
       return false;
     }
     frame(L, S, q, c);
-    L.kap = a.kappa[L.lin];
+    // (a ray that starts in a root cell has it already)
+    if ((again != kFresh && again != kChild) || q != S.root_grid) L.kap = a.kappa[L.lin];
     return true;
   }
 
@@ -800,7 +817,7 @@ struct Tracer {
     }
     const double lpix = r0 * L.lpix;
     if (!(lpix > 0.0)) return 1.0;
-    const double f = 0.5 + (0.5 - dmax) / lpix;
+    const double f = 0.5 + ratio(0.5 - dmax, lpix);
     return f * f >= 1.0 ? 1.0 : f * f;
   }
 };
@@ -936,34 +953,37 @@ struct WaveTally {
   // truncated in this flight and those that ended with the ray
   template <typename RAY>
   __device__ void ended(SgStats* stats, const RAY& L, int kind, int lane) {
-    const bool over = kind >= 0;
+    const bool over = kind >= 0, here = L.stat0 == stat0;
+    // the segments of the rays of which a group is live, summed once for all
+    // groups that are live in every one of them
+    const unsigned long long ends = wave_mask(over), ours = wave_mask(here);
+    const unsigned all = wave_total(over && here ? L.segs : 0u);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      const bool cut = over && !L.alive[g] && L.cut[g] != kNoCut, live = over && L.alive[g];
-      if (!wave_mask(cut || live)) continue;
-      const bool here = L.stat0 == stat0;
-      const unsigned mine = live ? L.segs : L.cut[g];
-      const unsigned segs = wave_total(here && (cut || live) ? mine : 0u);
-      const unsigned tsegs = THIN ? wave_total(here && (cut || live) ? L.tsegs : 0u) : 0u;
-      const int n_esc = __popcll(wave_mask(here && live && kind == 0)), n_trunc = __popcll(wave_mask(here && cut));
-      const int n_split = __popcll(wave_mask(here && live && kind == 2));
-      const double esc = n_esc ? wave_total(here && live && kind == 0 ? L.P[g] : 0.0) : 0.0;
-      const double trunc = n_trunc ? wave_total(here && cut ? L.P[g] : 0.0) : 0.0;
+      const unsigned long long live = ends & wave_mask(L.alive[g]), cut = ends & ~live & wave_mask(L.cut[g] != kNoCut);
+      if (!(cut | live)) continue;
+      const unsigned mine = in_mask(live) ? L.segs : L.cut[g];
+      const unsigned segs = live == ends ? all : wave_total(in_mask((cut | live) & ours) ? mine : 0u);
+      const unsigned tsegs = THIN ? wave_total(in_mask((cut | live) & ours) ? L.tsegs : 0u) : 0u;
+      const unsigned long long split = wave_mask(kind == 2) & live & ours, out = wave_mask(kind == 0) & live & ours;
+      const unsigned long long trunc = cut & ours;
+      const double esc_P = out ? wave_total(in_mask(out) ? L.P[g] : 0.0) : 0.0;
+      const double trunc_P = trunc ? wave_total(in_mask(trunc) ? L.P[g] : 0.0) : 0.0;
       if (lane == kWave - 1) {
         cnt[g] += segs;
-        if (n_split) cnt[NG + g] += (unsigned)n_split;
-        if (n_esc) {
-          cnt[2 * NG + g] += (unsigned)n_esc;
-          sum[g] += esc;
+        if (split) cnt[NG + g] += (unsigned)__popcll(split);
+        if (out) {
+          cnt[2 * NG + g] += (unsigned)__popcll(out);
+          sum[g] += esc_P;
         }
-        if (n_trunc) {
-          cnt[3 * NG + g] += (unsigned)n_trunc;
-          sum[NG + g] += trunc;
+        if (trunc) {
+          cnt[3 * NG + g] += (unsigned)__popcll(trunc);
+          sum[NG + g] += trunc_P;
         }
         if (THIN) cnt[4 * NG + g] += tsegs;
       }
-      if ((cut || live) && !here)
-        direct(stats[L.stat0 + g], mine, THIN ? L.tsegs : 0u, cut ? 1 : kind, L.P[g]);
+      if (in_mask((cut | live) & ~ours))
+        direct(stats[L.stat0 + g], mine, THIN ? L.tsegs : 0u, in_mask(cut) ? 1 : kind, L.P[g]);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -1357,10 +1377,12 @@ void trace_level_kernel(TraceArgs<R> a) {
   // rays of the launch that are not children: resumed ones (time-dependent rays), then seeds
   const unsigned long long n_held = HALT ? a.n_held : 0ull;
   const unsigned long long n_extra = n_held + (unsigned long long)(a.seed_end - a.seed_begin) * npix;
-  unsigned long long* head_in = a.ctr->head[a.cin];
+  Counters::Head* head_in = a.ctr->head[a.cin];
   // The level's rays in units of `span`: those of each segment's children, then
-  // the others. A unit is the launch's setting, halved while the level holds less
-  // than one for every wave of the launch, down to one ray per lane. Wave `rank`
+  // the others. A unit is the launch's setting; of a level that holds no more than
+  // one for every wave of the launch each wave gets an equal share, in whole rays
+  // per lane (ragged float64 1.10 -> 0.91 ms against units halved until they were
+  // enough, of which some waves got two). Wave `rank`
   // of the launch starts with its share of the first `fixed` units (at most one),
   // which takes no atomic; the others are claimed one by one from K equal parts of
   // them. Claimed from the first ray on, the 3072 waves of a launch queued up at
@@ -1387,7 +1409,8 @@ void trace_level_kernel(TraceArgs<R> a) {
     all = uniform64(all) + n_extra;
     if (all == 0) return;                    // a level no ray reached (the host launches all it may need)
     unsigned span = (unsigned)a.chunk;
-    while (span >= 2u * kWave && (unsigned long long)span * waves > all) span >>= 1;
+    if (all <= (unsigned long long)span * waves)
+      span = (unsigned)((all + (unsigned long long)waves * kWave - 1) / ((unsigned long long)waves * kWave)) * kWave;
     unsigned upto = (rays + span - 1) / span;
     const unsigned mine = upto;
 #pragma unroll
@@ -1509,7 +1532,7 @@ void trace_level_kernel(TraceArgs<R> a) {
             auto claim = [&](int p) {
               const unsigned b0 = part((unsigned)p), size = part((unsigned)p + 1u) - b0;
               unsigned long long b = 0;
-              if (lane == 0) b = atomicAdd(&head_in[p], 1ull);
+              if (lane == 0) b = atomicAdd(&head_in[p].n, 1ull);
               b = lane0_64(b);
               if (b >= size) return false;
               u_next = (unsigned)uniform32((int)lev.fixed) + b0 + (unsigned)b;
@@ -1520,11 +1543,11 @@ void trace_level_kernel(TraceArgs<R> a) {
             while (open != 0) {
               // the current part first: one load while it lasts
               const unsigned long long seen =
-                  uniform64(__hip_atomic_load(&head_in[w_part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                  uniform64(__hip_atomic_load(&head_in[w_part].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
               if (seen < part((unsigned)w_part + 1u) - part((unsigned)w_part) && (got = claim(w_part))) break;
               bool has = false;
               if (lane < K)
-                has = __hip_atomic_load(&head_in[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                has = __hip_atomic_load(&head_in[lane].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
                       part((unsigned)lane + 1u) - part((unsigned)lane);
               const unsigned long long live = wave_mask(has);
               if (!live) break;
@@ -1820,7 +1843,7 @@ __global__ void reset_kernel(Counters* ctr, SgStats* stats, int n_sg) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < kLevels * kSegMax) {
     (&ctr->count[0][0])[i] = 0;
-    (&ctr->head[0][0])[i] = 0;
+    (&ctr->head[0][0])[i].n = 0;
   }
   if (i == 0) {
     ctr->lost_rays = 0; ctr->err = 0;
@@ -1833,7 +1856,7 @@ __global__ void reset_kernel(Counters* ctr, SgStats* stats, int n_sg) {
 __global__ void reset_levels_kernel(Counters* ctr) {
   for (int i = threadIdx.x; i < kLevels * kSegMax; i += blockDim.x) {
     (&ctr->count[0][0])[i] = 0;
-    (&ctr->head[0][0])[i] = 0;
+    (&ctr->head[0][0])[i].n = 0;
   }
 }
 
@@ -1842,7 +1865,7 @@ __global__ void reset_levels_kernel(Counters* ctr) {
 // cleared (the host has read them).
 __global__ void reset_generation_kernel(Counters* ctr, int cin, int cout) {
   for (int s = threadIdx.x; s < kSegMax; s += blockDim.x) {
-    ctr->head[cin][s] = 0;
+    ctr->head[cin][s].n = 0;
     ctr->count[cout][s] = 0;
   }
   if (threadIdx.x == 0) {

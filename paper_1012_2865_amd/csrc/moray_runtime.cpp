@@ -100,8 +100,8 @@ void collect(moray_ctx* c, const PlanHost& ph, const moray_problem* probs, int n
              double trace_ms) {
   char* hs = (char*)c->h_stage;
   const Counters* hctr = (const Counters*)hs;
-  const SgStats* hst = (const SgStats*)(hs + sizeof(Counters));
-  const double* hpart = (const double*)(hs + sizeof(Counters) + ph.n_sg * sizeof(SgStats));
+  const SgStats* hst = (const SgStats*)(hs + kCountersRead);
+  const double* hpart = (const double*)(hs + kCountersRead + ph.n_sg * sizeof(SgStats));
   unsigned long long peak = 0;
   for (int l = 0; l < kLevels; ++l) {
     unsigned long long n = 0;
@@ -775,7 +775,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   const int max_launches = (max_reach - min_l0 + 1);
 
   // pinned staging for the counters, the tree statistics and the partial sums
-  const size_t need_stage = sizeof(Counters) + n_sg * sizeof(SgStats) + fblocks.size() * 8;
+  const size_t need_stage = kCountersRead + n_sg * sizeof(SgStats) + fblocks.size() * 8;
   if (need_stage > c->h_stage_bytes && c->arena)
     return fail(c, MORAY_ENOMEM, "moray_trace_noalloc: the batch has more (source, group) trees and finalize blocks "
                                  "than the context's 1 MiB read-back staging holds");
@@ -790,8 +790,8 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   }
   char* hs = (char*)c->h_stage;
   Counters* hctr = (Counters*)hs;
-  SgStats* hst = (SgStats*)(hs + sizeof(Counters));
-  double* hpart = (double*)(hs + sizeof(Counters) + n_sg * sizeof(SgStats));
+  SgStats* hst = (SgStats*)(hs + kCountersRead);
+  double* hpart = (double*)(hs + kCountersRead + n_sg * sizeof(SgStats));
   if (capture) {
     if (!c->gstream && (!hip_ok(c, hipStreamCreateWithFlags(&c->gstream, hipStreamNonBlocking), "stream") ||
                         !hip_ok(c, hipEventCreateWithFlags(&c->gev, hipEventDisableTiming), "event")))
@@ -914,7 +914,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     }
 
     // ---- results ----
-    if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, sizeof(Counters), hipMemcpyDeviceToHost, strm), "copy") ||
+    if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, kCountersRead, hipMemcpyDeviceToHost, strm), "copy") ||
         (n_sg && !hip_ok(c, hipMemcpyAsync(hst, stats, n_sg * sizeof(SgStats), hipMemcpyDeviceToHost, strm), "copy")) ||
         (!fblocks.empty() &&
          !hip_ok(c, hipMemcpyAsync(hpart, c->partial.p, fblocks.size() * 8, hipMemcpyDeviceToHost, strm), "copy"))) {

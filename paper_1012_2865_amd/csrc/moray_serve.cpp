@@ -272,7 +272,7 @@ moray_status engine_setup(moray_ctx* c, Engine* E) {
       !pin((void**)&E->hprobs, (size_t)E->prob_cap * sizeof(ProblemDev)) ||
       !pin((void**)&E->htrees, (size_t)E->tree_cap * sizeof(TreeDev)) ||
       !pin((void**)&E->heexc, (size_t)E->prob_cap * kServeMaxGroups * 8) ||
-      !pin((void**)&E->hstats, (size_t)E->tree_cap * sizeof(SgStats)) || !pin((void**)&E->hctr, sizeof(Counters)))
+      !pin((void**)&E->hstats, (size_t)E->tree_cap * sizeof(SgStats)) || !pin((void**)&E->hctr, kCountersRead))
     return fail(c, MORAY_ENOMEM, "pinned host allocation failed");
   const double waves = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave);
   E->reserve = (unsigned long long)std::min<double>((double)kReserveMax, (double)E->qcap / (32.0 * waves));
@@ -699,7 +699,7 @@ bool trip(Engine* E) {
   }
   if (!admitted.empty()) {
     // field checks of the new problems: one bad request must not void the launch
-    if (!eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
+    if (!eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, kCountersRead, hipMemcpyDeviceToHost, s), "copy") ||
         !eok(E, hipStreamSynchronize(s), "synchronize")) {
       fail_all(E, MORAY_EDEVICE, E->err);
       return true;
@@ -711,7 +711,7 @@ bool trip(Engine* E) {
         // clear the flag, re-run this problem's checks alone
         if (!eok(E, hipMemcpyAsync(&((Counters*)E->ctr.p)->err, &zero, sizeof zero, hipMemcpyHostToDevice, s), "copy") ||
             !eok(E, hipStreamSynchronize(s), "synchronize") || write_tables(E, p) != MORAY_OK ||
-            !eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
+            !eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, kCountersRead, hipMemcpyDeviceToHost, s), "copy") ||
             !eok(E, hipStreamSynchronize(s), "synchronize")) {
           fail_all(E, MORAY_EDEVICE, E->err);
           return true;
@@ -781,7 +781,7 @@ bool trip(Engine* E) {
   hipError_t e = launch_reset_generation(s, (Counters*)E->ctr.p, cin, cout);
   if (e == hipSuccess) e = E->fp32 ? launch(0.0f) : launch(0.0);
   if (!eok(E, e, "trace") ||
-      !eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
+      !eok(E, hipMemcpyAsync(E->hctr, E->ctr.p, kCountersRead, hipMemcpyDeviceToHost, s), "copy") ||
       (shi > slo && !eok(E, hipMemcpyAsync(E->hstats + slo, (SgStats*)E->stats.p + slo,
                                               (size_t)(shi - slo) * sizeof(SgStats), hipMemcpyDeviceToHost, s),
                             "copy")) ||

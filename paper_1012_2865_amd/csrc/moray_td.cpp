@@ -135,7 +135,7 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
       for (long long f = 0; f < nc; f += per_fb) t->fb.push_back({q, (int)std::min(per_fb, nc - f), f});
     }
   }
-  const size_t stage = sizeof(Counters) + (size_t)per * sizeof(SgStats) + t->fb.size() * 8;
+  const size_t stage = kCountersRead + (size_t)per * sizeof(SgStats) + t->fb.size() * 8;
   for (int i = 0; i < 2 && st == MORAY_OK; ++i) {
     if ((st = ensure(c, t->pix[i], cap * 8, "ray pool")) || (st = ensure(c, t->tree[i], cap * 4, "ray pool")) ||
         (st = ensure(c, t->r[i], cap * 8, "ray pool")) || (st = ensure(c, t->P[i], cap * 8 * t->planes, "ray pool")) ||
@@ -477,9 +477,9 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
     return MORAY_EDEVICE;
   char* hs = (char*)t->h_stage;
   Counters* hctr = (Counters*)hs;
-  SgStats* hst = (SgStats*)(hs + sizeof(Counters));
-  double* hpart = (double*)(hs + sizeof(Counters) + (size_t)per * sizeof(SgStats));
-  if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, sizeof(Counters), hipMemcpyDeviceToHost, s), "copy") ||
+  SgStats* hst = (SgStats*)(hs + kCountersRead);
+  double* hpart = (double*)(hs + kCountersRead + (size_t)per * sizeof(SgStats));
+  if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, kCountersRead, hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipMemcpyAsync(hst, t->stats.p, (size_t)per * sizeof(SgStats), hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipMemcpyAsync(hpart, t->partial.p, t->fb.size() * 8, hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipStreamSynchronize(s), "synchronize"))
