@@ -16,11 +16,11 @@ hipError_t launch_reset(hipStream_t, Counters*, SgStats*, int);
 hipError_t launch_reset_levels(hipStream_t, Counters*);
 hipError_t launch_reset_generation(hipStream_t, Counters*, int cin, int cout);
 hipError_t launch_reset_stats(hipStream_t, SgStats*, int first, int count);
-// mark: the optically-thin marks the prep pass clears (NULL: none);
+// mark: the n_mark optically-thin marks the prep pass clears (NULL: none);
 // kappa64: where it also writes the columns in float64 (NULL: nowhere)
 template <typename R>
 hipError_t launch_prep(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long, long long, R*, double*,
-                       Counters*, uint8_t* mark = nullptr, double* kappa64 = nullptr);
+                       Counters*, uint8_t* mark = nullptr, long long n_mark = 0, double* kappa64 = nullptr);
 template <typename R>
 hipError_t launch_trace_level(hipStream_t, int, const TraceArgs<R>&, bool cache, int width, bool cover, bool radp,
                               bool thin = false);

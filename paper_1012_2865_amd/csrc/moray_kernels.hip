@@ -1883,12 +1883,20 @@ __global__ void reset_stats_kernel(SgStats* stats, int first, int count) {
 // `grids` holds the n_grids grids (grid-table indices grid_base...) whose
 // cells fill [cell_begin, cell_end) of the batch-wide numbering.
 template <typename R>
-__global__ void prep_kernel(const GridDev* grids, int n_grids, int grid_base, const ProblemDev* probs,
-                            long long cell_begin, long long cell_end, R* kappa, double* acc, Counters* ctr,
-                            uint8_t* mark, double* kappa64) {
-  for (long long c = cell_begin + blockIdx.x * (long long)blockDim.x + threadIdx.x; c < cell_end;
-       c += (long long)gridDim.x * blockDim.x) {
-    const int g = grid_of(grids, n_grids, c);
+__global__ void prep_kernel(const GridDev* __restrict__ grids, int n_grids, int grid_base,
+                            const ProblemDev* __restrict__ probs, long long cell_begin, long long cell_end,
+                            R* __restrict__ kappa, double* __restrict__ acc, Counters* ctr, uint8_t* __restrict__ mark,
+                            long long n_mark, double* __restrict__ kappa64) {
+  const long long thread = blockIdx.x * (long long)blockDim.x + threadIdx.x, threads = (long long)gridDim.x * blockDim.x;
+  // the marks, 16 bytes a store (a byte per tree of each cell took 170 of 188 us
+  // at 128^3 and 64 trees)
+  for (long long i = thread; i < n_mark / 16; i += threads) ((uint4*)mark)[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (long long i = n_mark / 16 * 16 + thread; i < n_mark; i += threads) mark[i] = 0;
+  for (long long c = cell_begin + thread; c < cell_end; c += threads) {
+    // the grid of the wave's first cell, which is nearly always every lane's
+    const long long c0 = (long long)uniform64((unsigned long long)c);
+    int g = grid_of(grids, n_grids, c0);
+    if (g + 1 < n_grids && grids[g + 1].cell_off <= c) g = grid_of(grids, n_grids, c);
     const GridDev& G = grids[g];
     const ProblemDev& P = probs[G.problem];
     const long long local = c - G.cell_off;
@@ -1909,9 +1917,12 @@ __global__ void prep_kernel(const GridDev* grids, int n_grids, int grid_base, co
     kappa[c] = (R)k64;
     if (kappa64) kappa64[c] = k64;
     const long long base = P.acc_off + P.acc_stride * (c - P.cell_off), gstride = P.acc_stride * P.n_cells;
-    for (int gr = 0; gr < P.acc_planes; ++gr)
-      for (int k = 0; k < P.acc_stride; ++k) acc[base + gr * gstride + k] = 0.0;
-    for (int t = 0; t < P.mark_trees; ++t) mark[P.mark_off + t * P.n_cells + (c - P.cell_off)] = 0;
+    if (P.acc_stride == 1) {
+      for (int gr = 0; gr < P.acc_planes; ++gr) acc[base + gr * gstride] = 0.0;
+    } else {                                       // 2 or 4, in records aligned to their length
+      for (int gr = 0; gr < P.acc_planes; ++gr)
+        for (int k = 0; k < P.acc_stride; k += 2) *(double2*)(acc + base + gr * gstride + k) = make_double2(0.0, 0.0);
+    }
   }
 }
 
@@ -1922,11 +1933,10 @@ __global__ void prep_kernel(const GridDev* grids, int n_grids, int grid_base, co
 // adds its rate thin_coef / r^2 (r from its source to the cell centre, root cells) to k_ph and
 // that times (E_g - E_ion) to the heating (section 2.4, Eq. optthin), whatever n_H x_HI is;
 // per-block sums of the absorbed rate (no atomics).
-__global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* grids, const ProblemDev* probs,
-                                                               const FinalBlock* blocks, const double* acc,
-                                                               const double* eexc, double* partial,
-                                                               const Counters* ctr, const TreeDev* trees,
-                                                               const uint8_t* mark) {
+__global__ __launch_bounds__(kFinalBlock) void finalize_kernel(
+    const GridDev* __restrict__ grids, const ProblemDev* __restrict__ probs, const FinalBlock* __restrict__ blocks,
+    const double* __restrict__ acc, const double* __restrict__ eexc, double* __restrict__ partial,
+    const Counters* __restrict__ ctr, const TreeDev* __restrict__ trees, const uint8_t* __restrict__ mark) {
   __shared__ double red[kFinalBlock / kWave];
   if (ctr->err & kErrBadInput) return;
   const FinalBlock B = blocks[blockIdx.x];
@@ -1964,13 +1974,35 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const GridDev* gr
       const double cx = G.is_child ? (double)G.ox + 0.5 * ((double)i + 0.5) : (double)i + 0.5;
       const double cy = G.is_child ? (double)G.oy + 0.5 * ((double)j + 0.5) : (double)j + 0.5;
       const double cz = G.is_child ? (double)G.oz + 0.5 * ((double)kk + 0.5) : (double)kk + 0.5;
-      for (int t = 0; t < P.mark_trees; ++t) {
-        if (!mark[P.mark_off + t * P.n_cells + (c - P.cell_off)]) continue;
-        const TreeDev& S = trees[P.tree_first + t];
-        const double dx0 = cx - S.sx, dx1 = cy - S.sy, dx2 = cz - S.sz;
-        const double kv = S.thin_coef / (dx0 * dx0 + dx1 * dx1 + dx2 * dx2);
-        kt += kv;
-        ht += kv * eexc[P.eexc_off + t % P.n_groups];
+      // Eight marks are read at a time, and the groups of a source share the
+      // reciprocal of its distance: read one by one under a branch, with a division
+      // each, 64 trees took 364 us at 128^3. The quotients are Markstein's (see ratio).
+      const uint8_t* at = mark + P.mark_off + (c - P.cell_off);
+      double d2 = 0.0, y = 0.0;
+      int group = 0;
+      bool known = false;                          // d2 and y are those of the current source
+      for (int t0 = 0; t0 < P.mark_trees; t0 += 8) {
+        uint8_t m[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = t0 + e < P.mark_trees ? at[(t0 + e) * P.n_cells] : (uint8_t)0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (t0 + e >= P.mark_trees) break;
+          if (group == 0) known = false;
+          if (wave_mask(m[e] != 0)) {
+            const TreeDev& S = trees[P.tree_first + t0 + e];
+            if (!known) {
+              const double dx0 = cx - S.sx, dx1 = cy - S.sy, dx2 = cz - S.sz;
+              d2 = dx0 * dx0 + dx1 * dx1 + dx2 * dx2;
+              y = reciprocal(d2);
+              known = true;
+            }
+            const double q = S.thin_coef * y, kv = m[e] ? fma(fma(-d2, q, S.thin_coef), y, q) : 0.0;
+            kt += kv;
+            ht += kv * eexc[P.eexc_off + group];
+          }
+          if (++group == P.n_groups) group = 0;
+        }
       }
     }
     const double nabs = (double)G.n_h[local] * (double)G.x_hi[local];
@@ -2026,12 +2058,12 @@ hipError_t launch_reset_levels(hipStream_t s, Counters* ctr) {
 template <typename R>
 hipError_t launch_prep(hipStream_t s, int num_cu, const GridDev* grids, int n_grids, int grid_base,
                        const ProblemDev* probs, long long cell_begin, long long cell_end, R* kappa, double* acc,
-                       Counters* ctr, uint8_t* mark, double* kappa64) {
+                       Counters* ctr, uint8_t* mark, long long n_mark, double* kappa64) {
   long long blocks = (cell_end - cell_begin + 255) / 256;
   if (blocks > 32LL * num_cu) blocks = 32LL * num_cu;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(prep_kernel<R>, dim3((unsigned)blocks), dim3(256), 0, s, grids, n_grids, grid_base, probs,
-                     cell_begin, cell_end, kappa, acc, ctr, mark, kappa64);
+                     cell_begin, cell_end, kappa, acc, ctr, mark, n_mark, kappa64);
   return hipGetLastError();
 }
 
@@ -2165,9 +2197,9 @@ hipError_t launch_finalize(hipStream_t s, int n_blocks, const GridDev* grids, co
 }
 
 template hipError_t launch_prep<float>(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long,
-                                       long long, float*, double*, Counters*, uint8_t*, double*);
+                                       long long, float*, double*, Counters*, uint8_t*, long long, double*);
 template hipError_t launch_prep<double>(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long,
-                                        long long, double*, double*, Counters*, uint8_t*, double*);
+                                        long long, double*, double*, Counters*, uint8_t*, long long, double*);
 template hipError_t launch_trace_level<float>(hipStream_t, int, const TraceArgs<float>&, bool, int, bool, bool, bool);
 template hipError_t launch_trace_level<double>(hipStream_t, int, const TraceArgs<double>&, bool, int, bool, bool, bool);
 template hipError_t launch_trace_level_halt<float>(hipStream_t, int, const TraceArgs<float>&, bool, int);

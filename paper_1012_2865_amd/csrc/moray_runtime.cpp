@@ -852,10 +852,10 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
     double* kappa64 = thin && fp32 ? (double*)c->kappa64.p : nullptr;
     hipError_t e = fp32 ? launch_prep<float>(strm, c->num_cu, (GridDev*)c->grids.p, n_grids_tot, 0,
                                              (ProblemDev*)c->probs.p, 0, n_cells, (float*)c->kappa.p, (double*)c->acc.p, ctr,
-                                             mark, kappa64)
+                                             mark, n_mark, kappa64)
                         : launch_prep<double>(strm, c->num_cu, (GridDev*)c->grids.p, n_grids_tot, 0,
                                               (ProblemDev*)c->probs.p, 0, n_cells, (double*)c->kappa.p,
-                                              (double*)c->acc.p, ctr, mark);
+                                              (double*)c->acc.p, ctr, mark, n_mark);
     if (!hip_ok(c, e, "prep")) {
       if (capturing) { abandon_capture(strm); continue; }
       return MORAY_EDEVICE;
