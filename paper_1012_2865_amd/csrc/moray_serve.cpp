@@ -883,7 +883,7 @@ ServeProblem* make_problem(const moray_problem& P, unsigned flags, moray_result*
     steps += 2LL * (G.nx + G.ny + G.nz);
   }
   p->max_steps = (unsigned)std::min<long long>(steps * 2, 1u << 30);
-  p->nacc = p->ncells * (p->ngroups > 1 ? 2 : 1);
+  p->nacc = (p->ncells * (p->ngroups > 1 ? 2 : 1) + 7) & ~7LL;   // a 64-byte line holds sums of one problem
   p->bound = serve_rays_estimate(p->prob);
   return p;
 }
