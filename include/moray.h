@@ -71,11 +71,11 @@ typedef struct {
   size_t hbm_budget_bytes;    /* cap on the context's device memory; 0 = half of the free memory */
   size_t queue_capacity;      /* rays per level buffer; 0 = sized from each problem's worst case */
   int waves_per_cu;           /* persistent trace waves per compute unit; 0 = default */
-  int refill_lanes;           /* a wave refetches rays once this many of its 64 lanes are idle; 0 = default (64:
-                                 once the whole wave is idle, so new rays start together) */
-  int chunk_rays;             /* rays a wave claims from the level queue per atomic; 0 = default (256);
-                                 the largest claim: on a level with fewer rays than one claim for
-                                 every wave of the launch, waves halve it, down to 64 */
+  int refill_lanes;           /* 0 to 64, reported back by moray_autotune; without effect: a wave refetches rays
+                                 once all of its 64 lanes are idle, so that they start and write together
+                                 (refetching at 24 idle lanes took 1.8 to 3 times as long) */
+  int chunk_rays;             /* rays of a level a wave takes at a time; 0 = default (256); a level of no
+                                 more than that for every wave of the launch is dealt in equal shares */
   void* hip_stream;           /* hipStream_t for every launch; NULL = the null stream */
   int profile;                /* nonzero: time every trace-kernel launch with HIP events */
   int deposit_cache;          /* >= 0: combine deposits in a per-wave LDS table (default);
@@ -220,8 +220,8 @@ moray_status moray_trace_noalloc(moray_ctx* ctx, const moray_problem* probs, int
 
 /* Launch settings chosen by moray_autotune. */
 typedef struct {
-  int chunk_rays;             /* rays a wave claims from a level queue per atomic */
-  int refill_lanes;           /* idle lanes of 64 that make a wave refetch rays */
+  int chunk_rays;             /* rays of a level a wave takes at a time */
+  int refill_lanes;           /* as the context was given it */
   int reserve_rays;           /* next-level queue slots a wave reserves per atomic (split-queue depth) */
   int waves_per_cu;           /* persistent trace waves per compute unit */
   double first_ms;            /* fastest solve of the batch with the settings the context had */
@@ -230,8 +230,8 @@ typedef struct {
 } moray_tune_result;
 
 /* Autotuner (not part of the paper's method): time the batch under candidate
- * launch settings, one coordinate-descent pass over chunk size, refill
- * threshold, reservation block and waves per compute unit (each setting the
+ * launch settings, one coordinate-descent pass over chunk size,
+ * reservation block and waves per compute unit (each setting the
  * fastest of three solves), and keep the fastest in the context for later
  * moray_trace calls. Fields as in moray_trace (flags); results go to scratch
  * device memory. max_trials bounds the settings timed (0 = all candidates).

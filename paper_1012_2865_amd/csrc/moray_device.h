@@ -179,7 +179,6 @@ struct TraceArgs {
   int seed_level;                      // HEALPix level of the seed rays of this launch
   int seed_begin, seed_end;            // trees seeded in this launch
   int chunk;                           // rays claimed per atomic
-  int refill;                          // idle lanes that trigger a refill
   unsigned max_steps;                  // hard cap on cells per ray (never reached)
   unsigned long long reserve;          // next-level slots a wave reserves at once
   // time-dependent rays: where rays halted in this step go (halt_cap records; level in halt_lev),

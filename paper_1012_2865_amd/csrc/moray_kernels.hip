@@ -168,7 +168,6 @@ __device__ void healpix_dir(int level, uint64_t pix, double& vx, double& vy, dou
 // component is >= 0, else to the lower one.
 __device__ __forceinline__ int cell_rule(double x, double d) { return d >= 0.0 ? (int)floor(x) : (int)ceil(x) - 1; }
 __device__ __forceinline__ int floor_half(int c) { return c >= 0 ? c / 2 : -((-c + 1) / 2); }
-template <typename T> __device__ __forceinline__ T sel3(int k, T a, T b, T c) { return k == 0 ? a : (k == 1 ? b : c); }
 
 // One in-order counter covers a wave's vector loads, stores and atomics. A
 // load still in flight where a rare path (a ray start, a grid change, a
@@ -387,7 +386,6 @@ struct Geom32 {
         : "scc");
   }
   static __device__ bool positive(double dr, double t) { return fma(t, -0x1p-40, dr) > 0.0; }
-  __device__ double hloc() const { return 1.0 / hinv; }
 };
 
 template <typename R> struct GeomOf;
@@ -1360,7 +1358,7 @@ struct HaltWriter {
 // Traced one group per ray, the 128^3 workload (16 sources, 4 groups) made 895
 // million steps in neutral gas and 2.3 billion in ionised gas; carrying the
 // four groups together makes 580 million of either.
-template <typename R, bool CACHE, int PHYS, int NG, bool PART>
+template <typename R, bool CACHE, int PHYS, int NG>
 __global__ __launch_bounds__(kTraceBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 && NG > 2 ? 2 : 3)))
 void trace_level_kernel(TraceArgs<R> a) {
   constexpr bool COVER = (PHYS & kPhysCover) != 0, RADP = (PHYS & kPhysRadp) != 0, HALT = (PHYS & kPhysHalt) != 0;
@@ -1446,7 +1444,6 @@ void trace_level_kernel(TraceArgs<R> a) {
   int again = kFresh;      // an idle lane whose ray goes on in a new frame
   int from = 0;            // the cell it comes from
   unsigned steps = 0;      // of the wave since rays last started or changed grids in it
-  unsigned framed = 0;     // of the wave since all of its rays last had new frames
   L.stat0 = kNoTree;
   L.segs = 0;
   L.pix = 0;
@@ -1481,144 +1478,142 @@ void trace_level_kernel(TraceArgs<R> a) {
       (const __attribute__((address_space(1))) double*)kappa64_v;
 
   for (;;) {
-    // ---- refill idle lanes from the wave's claim on the level queue ----
-    // Every idle lane first gets its queue slot or seed number (claiming as
-    // many chunks as that takes), then all of them start in one pass; lanes
-    // whose slot turns out empty wait for the next refill.
-    const unsigned long long idle = wave_mask(!active);
-    if (!PART || idle == ~0ull || __popcll(idle) >= a.refill) {
-      if (wave_mask(ended >= 0)) {
-        // (a lane that repeats another's ray reports nothing of it)
-        const bool owns = Tracer<R, NG, PHYS>::owner(L);
-        splits.write(a, L, ended == 2 && L.more == 0, lane);
-        if constexpr (HALT) halts.write(a, L, ended == 3 && owns, lane);
-        tally.ended(a.stats, L, owns ? ended : -1, lane);
-        if (ended == 2 && L.more > 0) again = kChild;
-        ended = -1;
-      }
-      const unsigned long long going = wave_mask(again != kFresh);
-      if (drained && !going && idle == ~0ull) break;
-      if constexpr (!PART) {
-        // no lane holds a ray but those going on, of which this is all that is live
-        Ray<R, NG> keep;
-        keep.pix = L.pix; keep.more = L.more; keep.tree = L.tree; keep.q = L.q; keep.segs = L.segs; keep.g.r = L.g.r;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          keep.P[g] = L.P[g];
-          keep.alive[g] = L.alive[g];
-          keep.cut[g] = L.cut[g];
-        }
-        if constexpr (THIN) {
-          keep.thin = L.thin; keep.rem = L.rem; keep.tsegs = L.tsegs;
-        }
-        L = keep;
-      }
-      const unsigned long long crossed = wave_mask(again >= kChild);
-      // the lanes that want a ray, in the order they get them (lane_pos)
-      unsigned long long left = drained ? 0ull : pos_mask(in_mask(idle & ~going));
-      bool take = false, child = false;
-      unsigned long long q = 0;
-      while (left) {
-        if (w_next >= w_end) {
-          if (u_next >= u_end) {
-            // Claim a unit: from the wave's current part while it has units
-            // left; once it is used up, every lane reads one part's counter
-            // (one round trip for all of them), the wave picks the first part
-            // with units left after it, and claims there with one atomic; a claim
-            // that finds the part used up in the meantime looks again. No
-            // part with units left: the level is drained.
-            const unsigned open = (unsigned)uniform32((int)lev.open);
-            auto part = [&](unsigned p) { return (unsigned)(((unsigned long long)p * open) >> kshift); };
-            auto claim = [&](int p) {
-              const unsigned b0 = part((unsigned)p), size = part((unsigned)p + 1u) - b0;
-              unsigned long long b = 0;
-              if (lane == 0) b = atomicAdd(&head_in[p].n, 1ull);
-              b = lane0_64(b);
-              if (b >= size) return false;
-              u_next = (unsigned)uniform32((int)lev.fixed) + b0 + (unsigned)b;
-              u_end = u_next + 1u;
-              return true;
-            };
-            bool got = false;
-            while (open != 0) {
-              // the current part first: one load while it lasts
-              const unsigned long long seen =
-                  uniform64(__hip_atomic_load(&head_in[w_part].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-              if (seen < part((unsigned)w_part + 1u) - part((unsigned)w_part) && (got = claim(w_part))) break;
-              bool has = false;
-              if (lane < K)
-                has = __hip_atomic_load(&head_in[lane].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                      part((unsigned)lane + 1u) - part((unsigned)lane);
-              const unsigned long long live = wave_mask(has);
-              if (!live) break;
-              const unsigned long long ahead = live & (~0ull << w_part);
-              w_part = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
-              if ((got = claim(w_part))) break;
-            }
-            if (!got) { drained = true; break; }
-          }
-          const unsigned children = (unsigned)uniform32((int)lev.children), span = (unsigned)uniform32((int)lev.span);
-          const unsigned u = u_next++;
-          w_child = u < children;
-          if (w_child) {
-            const int sg = __popcll(wave_mask(lane < K && lev.first[lane] <= u)) - 1;
-            const unsigned in = (u - (unsigned)uniform32((int)lev.first[sg])) * span;
-            const unsigned long long base = 4ull * (unsigned long long)sg * a.seg_cap;
-            w_next = base + in;
-            w_end = base + min(in + span, (unsigned)uniform32((int)lev.rays[sg]));
-          } else {
-            w_next = (unsigned long long)(u - children) * span;
-            w_end = min(w_next + span, n_extra);
-          }
-        }
-        const unsigned long long idx = w_next + __popcll(left & bits_below(pos));
-        const bool mine = ((left >> pos) & 1ull) && idx < w_end;
-        if (mine) {
-          take = true;
-          child = w_child;
-          q = idx;
-        }
-        const unsigned long long got_mask = pos_mask(mine);
-        w_next += __popcll(got_mask);
-        left &= ~got_mask;
-      }
-      if (take || again != kFresh) {
-        double r64 = L.g.r;
-        if (take) {
-          if (child) T.fetch_child(L, q, r64);
-          else if (HALT && q < n_held) T.fetch_held(L, q, r64);
-          else T.fetch_seed(L, q - n_held, r64);
-        }
-        if (again == kChild) {
-          L.more -= 1;
-          if constexpr (THIN) L.tsegs = 0;
-#pragma unroll
-          for (int g = 0; g < NG; ++g) L.P[g] = L.alive[g] ? 0.25 * L.P[g] : -1.0;
-        }
-        if (L.tree != kNoTree) {
-          const TreeDev& S = a.trees[L.tree];
-          T.load_tree(L, S);
-          if constexpr (THIN) {
-            if (take) T.thin_start(L, S, !child);
-          }
-          active = T.locate(L, S, r64, again, from, L.q);
-          if (!active) ended = 0;            // outside the root grid: escaped
-          else if constexpr (K64) L.kap64 = a.kappa64[L.lin];
-          else if constexpr (THIN) L.kap64 = (double)L.kap;
-          if constexpr (NG > 1) {
-#pragma unroll
-            for (int g = 0; g < NG; ++g) L.sigma[g] = L.alive[g] ? L.sigma[g] : (R)0;
-          }
-        }
-        again = kFresh;
-      }
-      if (idle == ~0ull) framed = 0;
-      if (wave_mask(take) || crossed) steps = 0;
-      // the tree of the first ray started is the one the wave's tally follows
-      const unsigned long long started = wave_mask(active);
-      if (started) tally.follow(a.stats, (uint32_t)__builtin_amdgcn_readlane((int)L.stat0, __ffsll((long long)started) - 1), lane);
-      finish_vector_loads();
+    // ---- refill: no lane has a ray in flight ----
+    // Every lane whose ray does not go on first gets its queue slot or seed number
+    // (from as many units as that takes), then all of them start in one pass; lanes
+    // whose slot turns out empty wait for the next refill. A wave that refilled at 24
+    // idle lanes kept the state of the others alive through this and wrote their
+    // splits out of order: 1.8 to 3 times as long.
+    if (wave_mask(ended >= 0)) {
+      // (a lane that repeats another's ray reports nothing of it)
+      const bool owns = Tracer<R, NG, PHYS>::owner(L);
+      splits.write(a, L, ended == 2 && L.more == 0, lane);
+      if constexpr (HALT) halts.write(a, L, ended == 3 && owns, lane);
+      tally.ended(a.stats, L, owns ? ended : -1, lane);
+      if (ended == 2 && L.more > 0) again = kChild;
+      ended = -1;
     }
+    const unsigned long long going = wave_mask(again != kFresh);
+    if (drained && !going) break;
+    {
+      // no lane holds a ray but those going on, of which this is all that is live
+      Ray<R, NG> keep;
+      keep.pix = L.pix; keep.more = L.more; keep.tree = L.tree; keep.q = L.q; keep.segs = L.segs; keep.g.r = L.g.r;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        keep.P[g] = L.P[g];
+        keep.alive[g] = L.alive[g];
+        keep.cut[g] = L.cut[g];
+      }
+      if constexpr (THIN) {
+        keep.thin = L.thin; keep.rem = L.rem; keep.tsegs = L.tsegs;
+      }
+      L = keep;
+    }
+    const unsigned long long crossed = wave_mask(again >= kChild);
+    // the lanes that want a ray, in the order they get them (lane_pos)
+    unsigned long long left = drained ? 0ull : pos_mask(again == kFresh);
+    bool take = false, child = false;
+    unsigned long long q = 0;
+    while (left) {
+      if (w_next >= w_end) {
+        if (u_next >= u_end) {
+          // Claim a unit: from the wave's current part while it has units
+          // left; once it is used up, every lane reads one part's counter
+          // (one round trip for all of them), the wave picks the first part
+          // with units left after it, and claims there with one atomic; a claim
+          // that finds the part used up in the meantime looks again. No
+          // part with units left: the level is drained.
+          const unsigned open = (unsigned)uniform32((int)lev.open);
+          auto part = [&](unsigned p) { return (unsigned)(((unsigned long long)p * open) >> kshift); };
+          auto claim = [&](int p) {
+            const unsigned b0 = part((unsigned)p), size = part((unsigned)p + 1u) - b0;
+            unsigned long long b = 0;
+            if (lane == 0) b = atomicAdd(&head_in[p].n, 1ull);
+            b = lane0_64(b);
+            if (b >= size) return false;
+            u_next = (unsigned)uniform32((int)lev.fixed) + b0 + (unsigned)b;
+            u_end = u_next + 1u;
+            return true;
+          };
+          bool got = false;
+          while (open != 0) {
+            // the current part first: one load while it lasts
+            const unsigned long long seen =
+                uniform64(__hip_atomic_load(&head_in[w_part].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            if (seen < part((unsigned)w_part + 1u) - part((unsigned)w_part) && (got = claim(w_part))) break;
+            bool has = false;
+            if (lane < K)
+              has = __hip_atomic_load(&head_in[lane].n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                    part((unsigned)lane + 1u) - part((unsigned)lane);
+            const unsigned long long live = wave_mask(has);
+            if (!live) break;
+            const unsigned long long ahead = live & (~0ull << w_part);
+            w_part = uniform32((int)__ffsll((long long)(ahead ? ahead : live)) - 1);
+            if ((got = claim(w_part))) break;
+          }
+          if (!got) { drained = true; break; }
+        }
+        const unsigned children = (unsigned)uniform32((int)lev.children), span = (unsigned)uniform32((int)lev.span);
+        const unsigned u = u_next++;
+        w_child = u < children;
+        if (w_child) {
+          const int sg = __popcll(wave_mask(lane < K && lev.first[lane] <= u)) - 1;
+          const unsigned in = (u - (unsigned)uniform32((int)lev.first[sg])) * span;
+          const unsigned long long base = 4ull * (unsigned long long)sg * a.seg_cap;
+          w_next = base + in;
+          w_end = base + min(in + span, (unsigned)uniform32((int)lev.rays[sg]));
+        } else {
+          w_next = (unsigned long long)(u - children) * span;
+          w_end = min(w_next + span, n_extra);
+        }
+      }
+      const unsigned long long idx = w_next + __popcll(left & bits_below(pos));
+      const bool mine = ((left >> pos) & 1ull) && idx < w_end;
+      if (mine) {
+        take = true;
+        child = w_child;
+        q = idx;
+      }
+      const unsigned long long got_mask = pos_mask(mine);
+      w_next += __popcll(got_mask);
+      left &= ~got_mask;
+    }
+    if (take || again != kFresh) {
+      double r64 = L.g.r;
+      if (take) {
+        if (child) T.fetch_child(L, q, r64);
+        else if (HALT && q < n_held) T.fetch_held(L, q, r64);
+        else T.fetch_seed(L, q - n_held, r64);
+      }
+      if (again == kChild) {
+        L.more -= 1;
+        if constexpr (THIN) L.tsegs = 0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) L.P[g] = L.alive[g] ? 0.25 * L.P[g] : -1.0;
+      }
+      if (L.tree != kNoTree) {
+        const TreeDev& S = a.trees[L.tree];
+        T.load_tree(L, S);
+        if constexpr (THIN) {
+          if (take) T.thin_start(L, S, !child);
+        }
+        active = T.locate(L, S, r64, again, from, L.q);
+        if (!active) ended = 0;            // outside the root grid: escaped
+        else if constexpr (K64) L.kap64 = a.kappa64[L.lin];
+        else if constexpr (THIN) L.kap64 = (double)L.kap;
+        if constexpr (NG > 1) {
+#pragma unroll
+          for (int g = 0; g < NG; ++g) L.sigma[g] = L.alive[g] ? L.sigma[g] : (R)0;
+        }
+      }
+      again = kFresh;
+    }
+    if (wave_mask(take) || crossed) steps = 0;
+    // the tree of the first ray started is the one the wave's tally follows
+    const unsigned long long started = wave_mask(active);
+    if (started) tally.follow(a.stats, (uint32_t)__builtin_amdgcn_readlane((int)L.stat0, __ffsll((long long)started) - 1), lane);
+    finish_vector_loads();
     // ---- step until the wave refills ----
     // Nothing but the step itself is in this loop: rays that split, end, halt or
     // change frames are marked and dealt with at the refill. What is known of the
@@ -1635,7 +1630,7 @@ void trace_level_kernel(TraceArgs<R> a) {
     // changed grids bound every active ray's own (a bound never reached by a correct trace:
     // cell indices move monotonically), and the mixed mode forms its distances afresh.
     unsigned todo = a.max_steps - steps;
-    if constexpr (sizeof(R) == 4) todo = todo < kResync - framed ? todo : kResync - framed;
+    if constexpr (sizeof(R) == 4) todo = todo < kResync ? todo : kResync;
     const unsigned allowed = todo;
     while (run) {
       // ---- one cell: exit plane, split test, deposit, step ----
@@ -1794,12 +1789,8 @@ void trace_level_kernel(TraceArgs<R> a) {
         }
       }
       if (--todo == 0) break;
-      if constexpr (PART) {
-        if (__popcll(~run) >= a.refill && !drained) break;
-      }
     }
     steps += allowed - todo;
-    framed += allowed - todo;
     active = in_mask(run);
     if (in_mask(at_split)) ended = 2;
     if (in_mask(at_end)) ended = 1;
@@ -1808,13 +1799,13 @@ void trace_level_kernel(TraceArgs<R> a) {
 #pragma unroll
     for (int g = 0; g < NG; ++g)
       if (in_mask(run | at_split | at_end | at_out | at_halt | at_cross)) L.alive[g] = in_mask(carries[g]);
-    if (steps >= a.max_steps && run) {
+    if (run && steps >= a.max_steps) {
       if (lane == 0) atomicOr(&a.ctr->err, kErrInternal);
       break;
     }
     if constexpr (sizeof(R) == 4) {
-      if (framed >= kResync && active) {
-        // every ray in flight goes on in the same cell, its plane distances formed afresh
+      if (active) {
+        // kResync steps: every ray in flight goes on in the same cell, its plane distances formed afresh
         again = kResyncFrame;
         from = L.lin;
         active = false;
@@ -2084,12 +2075,12 @@ template <typename R, int PHYS, int NG>
 static void launch_one(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
   if (cache) {
     static int plain = 0, mine = 0;
-    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1, false>, plain);
-    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG, false>, mine);
+    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1>, plain);
+    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG>, mine);
     if (m < p) blocks = (blocks * m + p - 1) / p;
-    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG, false>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   } else {
-    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG, false>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
   }
 }
 
@@ -2210,8 +2201,8 @@ hipError_t trace_occupancy(int precision, bool cache, int* blocks_per_cu) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, kernel, kTraceBlock, 0);
   };
   if (precision == 0)
-    return cache ? ask(trace_level_kernel<double, true, 0, 1, false>) : ask(trace_level_kernel<double, false, 0, 1, false>);
-  return cache ? ask(trace_level_kernel<float, true, 0, 1, false>) : ask(trace_level_kernel<float, false, 0, 1, false>);
+    return cache ? ask(trace_level_kernel<double, true, 0, 1>) : ask(trace_level_kernel<double, false, 0, 1>);
+  return cache ? ask(trace_level_kernel<float, true, 0, 1>) : ask(trace_level_kernel<float, false, 0, 1>);
 }
 
 }  // namespace moray

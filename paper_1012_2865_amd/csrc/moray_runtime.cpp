@@ -885,7 +885,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
           A.seg_cap = seg_cap; A.nseg = nseg; A.ctr = ctr; A.stats = stats; A.gen = l; A.cin = l; A.cout = l + 1;
           A.seed_level = l;
           A.seed_begin = lo < hi ? lo : 0; A.seed_end = lo < hi ? hi : 0;
-          A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = reserve;
+          A.chunk = c->chunk; A.max_steps = max_steps; A.reserve = reserve;
           A.mark = mark;
           A.kappa64 = kappa64;
           return launch_trace_level<R>(strm, blocks, A, c->cache, width, cover, radp, thin);
@@ -1253,7 +1253,6 @@ moray_status moray_autotune(moray_ctx* c, const moray_problem* probs, int n_prob
   std::vector<int> bpcs;
   for (int b = 1; b <= bpc_max; ++b) bpcs.push_back(b);
   std::vector<Knob> knobs = {{&c->chunk, {128, 256, 512, 1024}},
-                             {&c->refill, {8, 16, 24, 64}},
                              {&c->reserve_user, {64, 128, 256}},
                              {&c->blocks_per_cu, bpcs}};
   for (Knob& k : knobs) {

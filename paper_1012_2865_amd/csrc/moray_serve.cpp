@@ -775,7 +775,7 @@ bool trip(Engine* E) {
     A.seg_cap = E->seg_cap; A.nseg = E->nseg; A.ctr = (Counters*)E->ctr.p; A.stats = (SgStats*)E->stats.p;
     A.gen = g; A.cin = cin; A.cout = cout; A.seed_level = seed_level;
     A.seed_begin = seed_lo; A.seed_end = seed_hi;
-    A.chunk = c->chunk; A.refill = c->refill; A.max_steps = max_steps; A.reserve = E->reserve;
+    A.chunk = c->chunk; A.max_steps = max_steps; A.reserve = E->reserve;
     return launch_trace_level<R>(s, blocks, A, c->cache, width, cover, false);
   };
   hipError_t e = launch_reset_generation(s, (Counters*)E->ctr.p, cin, cout);

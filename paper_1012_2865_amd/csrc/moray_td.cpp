@@ -223,7 +223,6 @@ static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, in
   A.seed_begin = seed_lo;
   A.seed_end = seed_hi;
   A.chunk = c->chunk;
-  A.refill = c->refill;
   A.max_steps = max_steps;
   A.reserve = reserve;
   A.halt = pool_of(t, b);
