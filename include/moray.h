@@ -54,9 +54,8 @@ typedef enum {
 
 typedef enum {
   MORAY_FP64 = 0,        /* geometry, optical depth and accumulation in float64 */
-  MORAY_FP32_ACC64 = 1   /* geometry and optical depth in float32; photon counts,
-                            accumulators and split decisions near their threshold
-                            in float64 */
+  MORAY_FP32_ACC64 = 1   /* absorber columns and optical depth in float32; distances,
+                            split decisions, photon counts and accumulators in float64 */
 } moray_precision;
 
 /* flags of moray_trace */
@@ -347,12 +346,13 @@ moray_status moray_evolve(moray_ctx* ctx, const moray_problem* prob, unsigned fl
  * offsets, source and group counts and level_init; its fields may change from
  * step to step).
  * c_dt is c dt_P in root cells (c dt_P / dx_cm), > 0; pool_rays (1024 to
- * 2^34) bounds the rays in flight, with up to 63 empty records per wave of
- * each level launch (waves reserve the records of halted rays 64 at a time),
+ * 2^34) bounds the rays in flight (per energy group), with up to 255 empty records per wave of
+ * each level launch (waves reserve the records of halted rays 256 at a time),
  * and each level's queue (both grow when a step needs more, see moray_td_step); the state holds
- * about 144 bytes of device memory per pool ray (two pools of 32 B, two
- * level queues of 28 B and the 24 B of sort buffers that order the rays in
- * flight, the latter only below 2^32 rays). The covering factor is
+ * about 102 bytes of device memory per pool ray of one energy group, 41 with
+ * four (up to four groups of a source share a record: two pools, two level
+ * queues and the sort buffers that order the rays in
+ * flight, the latter only below 2^32 records). The covering factor is
  * not taken. Returns MORAY_EINVAL for bad arguments, MORAY_ENOMEM when the
  * buffers do not fit the context's HBM budget.
  *

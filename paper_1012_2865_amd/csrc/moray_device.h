@@ -126,6 +126,7 @@ struct SgStats {
 // reserve and claim rays spread over many addresses (a float64 or integer
 // atomic on one address serialises at the memory side).
 constexpr int kSegMax = 64;
+constexpr int kHaltSpread = 8;
 
 struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
@@ -133,7 +134,13 @@ struct Counters {
   unsigned int err;                             // bit flags, see kErr*
   unsigned int pad;
   unsigned long long halt_count;                // time-dependent rays halted in this step
-  unsigned long long halt_levels[kLevels];      // of them, per HEALPix level
+  // per HEALPix level, the rays that halted in this step and the photons they hold;
+  // a wave adds to one of kHaltSpread places (the memory side performs the atomics
+  // of one line one after the other)
+  struct alignas(64) Halted {
+    double P;
+    unsigned long long rays;
+  } halted[kLevels][kHaltSpread];
   // Units of each part of a level claimed beyond those dealt at its launch's start
   // (see the trace kernel), 64 bytes apart: the memory side performs the atomics of
   // one line one after the other, and waves that run out together claim together.
@@ -141,7 +148,8 @@ struct Counters {
     unsigned long long n;
   } head[kLevels][kSegMax];
 };
-constexpr size_t kCountersRead = offsetof(Counters, head);   // the part the host reads
+// the part the host reads, and that it reads after a time-dependent step
+constexpr size_t kCountersRead = offsetof(Counters, halted), kCountersReadTd = offsetof(Counters, head);
 
 constexpr unsigned kErrOverflow = 1u;
 constexpr unsigned kErrBadInput = 2u;

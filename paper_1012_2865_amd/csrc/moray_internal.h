@@ -30,12 +30,12 @@ hipError_t launch_trace_level_halt(hipStream_t, int, const TraceArgs<R>&, bool c
 // tree index lies in one of the n ranges [lo[i], hi[i]) (n <= kDropRanges).
 hipError_t launch_drop_trees(hipStream_t, uint32_t* tree, const Counters* ctr, int row, unsigned long long seg_cap,
                              int nseg, const int* lo, const int* hi, int n);
-hipError_t launch_sum_blocks(hipStream_t, int blocks, const double* v, unsigned long long n, int planes,
-                             unsigned long long pstride, double* part);
-// moray_td_kernels.hip: the halt list sorted by (level, tree, pixel)
+// moray_td_kernels.hip: the halt list sorted by (level, tree, pixel); levels are at most top_level but for
+// empty records
+int td_level_bits(int top_level);
 hipError_t td_sort_temp_bytes(unsigned long long cap, size_t* bytes);
 hipError_t launch_td_sort(hipStream_t, int num_cu, const RayQueue& pool, const int* lev, unsigned long long n,
-                          int tree_bits, int pix_bits, int pix_drop, unsigned long long* keys_in, unsigned long long* keys_out,
+                          int top_level, int tree_bits, int pix_bits, int pix_drop, void* keys_in, void* keys_out,
                           uint32_t* idx_in, uint32_t* idx_out, void* temp, size_t temp_bytes);
 // trees, mark: the tree table and the optically-thin marks (NULL when no problem uses them)
 hipError_t launch_finalize(hipStream_t, int, const GridDev*, const ProblemDev*, const FinalBlock*, const double*,

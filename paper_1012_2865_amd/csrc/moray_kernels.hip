@@ -17,9 +17,18 @@
 // kph): with one group the absorbed rate, with more the absorbed rate and its
 // energy moment, summed over the groups (Eq. gamma). Deposits combine in a
 // per-wave LDS table and reach the float64 accumulators in HBM as atomics only
-// when evicted; per-tree ray statistics combine per wave. Idle lanes refill
-// from a private chunk of the level queue claimed with one atomic. Splitting
-// lanes are compacted with a wave ballot into one queue slot each.
+// when evicted; per-tree ray statistics combine per wave. A wave whose rays have
+// all ended or split takes the next from its share of the level, or from units of
+// it claimed with one atomic each, after it has written the rays that split, one
+// queue slot each, in the order of their pixels.
+//
+// What bounds it, on the 128^3 workload (16 sources, 4 groups; 4.1 ms): 580
+// million steps in 9.95 million wave steps (58 of 64 lanes with a ray), each about
+// 115 vector and 100 scalar instructions and ten of LDS: the vector units are busy
+// 70% of the step loop, which is three quarters of the time; a tenth goes to ray
+// starts (a chain of memory round trips of 17 thousand cycles each), the rest to
+// the ends of the levels. Without its memory-side atomics a build was 2 to 4%
+// faster, with its gathers all in cache 0 to 3%, without deposits 20%.
 #include "moray_device.h"
 
 #include <hip/hip_runtime.h>
@@ -1213,7 +1222,7 @@ struct DepositCache {
 // The rays of a wave that split go to the wave's current segment of the next
 // level's queue (its home segment at first) through blocks of slots it reserves
 // with one atomic, in coalesced stores. They wait in their idle lanes until the
-// wave refills and are written then, all at once and in lane order: 64 rays that
+// wave refills and are written then, all at once and in the order they started (lane_pos): 64 rays that
 // started as neighbouring pixels leave their children as neighbouring pixels,
 // whatever order they split in, so that a wave's rays stay a compact patch of the
 // sphere from level to level (written in the order of their splits, 16 or 32 at
@@ -1294,8 +1303,14 @@ struct SplitWriter {
 template <typename R, int NG>
 struct HaltWriter {
   unsigned long long h_next, h_end, h_count;   // reserved records, rays halted in this launch
+  double held;                                 // the lane's: photons they hold
+  int place;                                   // of Counters::halted
 
-  __device__ void init() { h_next = h_end = h_count = 0; }
+  __device__ void init(int home) {
+    h_next = h_end = h_count = 0;
+    held = 0.0;
+    place = home % kHaltSpread;
+  }
   // the lanes with `halt` (all lanes call)
   __device__ void write(const TraceArgs<R>& a, const Ray<R, NG>& L, bool halt, int lane) {
     const unsigned long long hm = pos_mask(halt);
@@ -1315,9 +1330,13 @@ struct HaltWriter {
         a.halt.tree[i] = L.tree;
         a.halt.r[i] = L.g.r;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = NG == 1 || L.alive[g] ? L.P[g] : -1.0;
+        for (int g = 0; g < NG; ++g) {
+          const bool live = NG == 1 || L.alive[g];
+          a.halt.P[g * a.halt.pstride + i] = live ? L.P[g] : -1.0;
+          held += live ? L.P[g] : 0.0;
+        }
         a.halt_lev[i] = a.gen - L.more;
-        if (L.more) atomicAdd(&a.ctr->halt_levels[a.gen - L.more], 1ull);
+        if (L.more) atomicAdd(&a.ctr->halted[a.gen - L.more][place].rays, 1ull);
       } else {
         atomicOr(&a.ctr->err, kErrOverflow);
       }
@@ -1342,7 +1361,9 @@ struct HaltWriter {
         for (int g = 0; g < NG; ++g) a.halt.P[g * a.halt.pstride + i] = 0.0;
         a.halt_lev[i] = kHaltHole;
       }
-    if (lane == 0 && h_count) atomicAdd(&a.ctr->halt_levels[a.gen], h_count);
+    const double sum = wave_total(held);
+    if (lane == kWave - 1 && sum > 0.0) unsafeAtomicAdd(&a.ctr->halted[a.gen][place].P, sum);
+    if (lane == 0 && h_count) atomicAdd(&a.ctr->halted[a.gen][place].rays, h_count);
   }
 };
 
@@ -1460,7 +1481,7 @@ void trace_level_kernel(TraceArgs<R> a) {
   int w_part = home;
   bool drained = false;
   HaltWriter<R, NG> halts;
-  if constexpr (HALT) halts.init();
+  if constexpr (HALT) halts.init(home);
   // the step's column pointer, held in vector registers in the float kernels:
   // their scalar registers are full, and from there it was reloaded (a
   // kernel-argument load and lane reads of spilled scalars) at every step; the
@@ -1839,7 +1860,7 @@ __global__ void reset_kernel(Counters* ctr, SgStats* stats, int n_sg) {
   if (i == 0) {
     ctr->lost_rays = 0; ctr->err = 0;
   }
-  if (i < kLevels) ctr->halt_levels[i] = 0;
+  if (i < kLevels * kHaltSpread) (&ctr->halted[0][0])[i] = Counters::Halted{0.0, 0ull};
   if (i == 0) ctr->halt_count = 0;
   if (i < n_sg) stats[i] = SgStats{0.0, 0.0, 0ull, 0ull, 0ull, 0ull};
 }
@@ -2134,34 +2155,6 @@ __global__ __launch_bounds__(256) void drop_trees_kernel(uint32_t* __restrict__ 
     for (int k = 0; k < r.n; ++k) drop = drop || ((int)t >= r.lo[k] && (int)t < r.hi[k]);
     if (t != kNoTree && drop) q[i] = kNoTree;
   }
-}
-
-// Per-block sums of the positive values of the first n of each plane of v (the photons the halted
-// rays hold; an ended group's rate is stored negative).
-__global__ __launch_bounds__(256) void sum_blocks_kernel(const double* __restrict__ v, unsigned long long n,
-                                                         int planes, unsigned long long pstride,
-                                                         double* __restrict__ part) {
-  __shared__ double red[256 / kWave];
-  double s = 0.0;
-  for (int g = 0; g < planes; ++g)
-    for (unsigned long long i = blockIdx.x * 256ull + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * 256ull) {
-      const double x = v[g * pstride + i];
-      s += x > 0.0 ? x : 0.0;
-    }
-  for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_down(s, off);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int w = 0; w < 256 / kWave; ++w) t += red[w];
-    part[blockIdx.x] = t;
-  }
-}
-
-hipError_t launch_sum_blocks(hipStream_t s, int blocks, const double* v, unsigned long long n, int planes,
-                             unsigned long long pstride, double* part) {
-  hipLaunchKernelGGL(sum_blocks_kernel, dim3(blocks), dim3(256), 0, s, v, n, planes, pstride, part);
-  return hipGetLastError();
 }
 
 hipError_t launch_drop_trees(hipStream_t s, uint32_t* tree, const Counters* ctr, int row, unsigned long long seg_cap,

@@ -1,7 +1,7 @@
 // Host runtime of the adaptive ray tracer: the C ABI declared in moray.h.
 //
 // A call validates the problems on the host, lays every problem of the batch
-// out in one cell numbering (grid, problem and (source, group) tables), sizes
+// out in one cell numbering (grid, problem and tree tables: a tree is a source and the groups its rays carry), sizes
 // the ping-pong ray queue from a geometric bound on the rays one HEALPix level
 // can hold, and enqueues reset -> prep -> trace_level(l0..l_reach) -> finalize
 // on the context's stream. Trees whose queue estimate exceeds the capacity

@@ -135,7 +135,7 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
       for (long long f = 0; f < nc; f += per_fb) t->fb.push_back({q, (int)std::min(per_fb, nc - f), f});
     }
   }
-  const size_t stage = kCountersRead + (size_t)per * sizeof(SgStats) + t->fb.size() * 8;
+  const size_t stage = kCountersReadTd + (size_t)per * sizeof(SgStats) + t->fb.size() * 8;
   for (int i = 0; i < 2 && st == MORAY_OK; ++i) {
     if ((st = ensure(c, t->pix[i], cap * 8, "ray pool")) || (st = ensure(c, t->tree[i], cap * 4, "ray pool")) ||
         (st = ensure(c, t->r[i], cap * 8, "ray pool")) || (st = ensure(c, t->P[i], cap * 8 * t->planes, "ray pool")) ||
@@ -451,13 +451,18 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   int tree_bits = 1;
   while (tree_bits < 31 && ((long long)1 << tree_bits) < n_trees) ++tree_bits;
   const int pix_all = 2 * l_hi + 4;
-  const int pix_bits = std::min(pix_all, 64 - 5 - tree_bits), pix_drop = pix_all - pix_bits;
+  // (or 32 by up to four bits: a pass of the sort less, on shorter keys, and sixteen
+  // neighbours in pool order are still neighbours)
+  const int above = td_level_bits(l_hi) + tree_bits;
+  int pix_bits = std::min(pix_all, 64 - above);
+  if (const int over = above + pix_bits - 32; over > 0 && over <= 4 && pix_bits > over) pix_bits -= over;
+  const int pix_drop = pix_all - pix_bits;
   unsigned long long first[kLevels] = {};
   if (t->n_in > 0) {
     unsigned long long o = 0;
     for (int l = 0; l < kLevels; ++l) { first[l] = o; o += t->lev_in[l]; }
-    if (!hip_ok(c, launch_td_sort(s, c->num_cu, pool_of(t, a), (const int*)t->lev[a].p, t->n_in, tree_bits, pix_bits,
-                                  pix_drop, (unsigned long long*)t->keys[0].p, (unsigned long long*)t->keys[1].p,
+    if (!hip_ok(c, launch_td_sort(s, c->num_cu, pool_of(t, a), (const int*)t->lev[a].p, t->n_in, l_hi, tree_bits, pix_bits,
+                                  pix_drop, t->keys[0].p, t->keys[1].p,
                                   (uint32_t*)t->order[0].p, (uint32_t*)t->order[1].p, t->sort_temp.p, t->sort_bytes),
                 "sort"))
       return MORAY_EDEVICE;
@@ -476,9 +481,9 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
     return MORAY_EDEVICE;
   char* hs = (char*)t->h_stage;
   Counters* hctr = (Counters*)hs;
-  SgStats* hst = (SgStats*)(hs + kCountersRead);
-  double* hpart = (double*)(hs + kCountersRead + (size_t)per * sizeof(SgStats));
-  if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, kCountersRead, hipMemcpyDeviceToHost, s), "copy") ||
+  SgStats* hst = (SgStats*)(hs + kCountersReadTd);
+  double* hpart = (double*)(hs + kCountersReadTd + (size_t)per * sizeof(SgStats));
+  if (!hip_ok(c, hipMemcpyAsync(hctr, ctr, kCountersReadTd, hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipMemcpyAsync(hst, t->stats.p, (size_t)per * sizeof(SgStats), hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipMemcpyAsync(hpart, t->partial.p, t->fb.size() * 8, hipMemcpyDeviceToHost, s), "copy") ||
       !hip_ok(c, hipStreamSynchronize(s), "synchronize"))
@@ -514,21 +519,13 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
     for (int si = 0; si < t->n_src; ++si)
       for (int g = 0; g < t->n_grp; ++g) Rr.emitted += Sp.photon_frac[g] * P.sources[si].ndot;
   for (size_t b = 0; b < t->fb.size(); ++b) Rr.absorbed += hpart[b];
-  // the photons the halted rays hold, summed over the halt list
+  // the photons the halted rays hold
   double h = 0.0;
+  for (const auto& level : hctr->halted)
+    for (const Counters::Halted& H : level) h += H.P;
   // the halt list's records (empty ones, which waves reserved and did not
-  // fill, hold no photons); records beyond the pool were never written
+  // fill, among them); records beyond the pool were never written
   const unsigned long long n_held = std::min<unsigned long long>(hctr->halt_count, t->cap);
-  if (n_held) {
-    const int nb = (int)std::min<size_t>(t->fb.size(), 1024);
-    if (!hip_ok(c, launch_sum_blocks(s, nb, (const double*)t->P[1 - t->cur].p, n_held, t->planes, t->cap,
-                                     (double*)t->partial.p),
-                "sum") ||
-        !hip_ok(c, hipMemcpyAsync(hpart, t->partial.p, (size_t)nb * 8, hipMemcpyDeviceToHost, s), "copy") ||
-        !hip_ok(c, hipStreamSynchronize(s), "synchronize"))
-      return MORAY_EDEVICE;
-    for (int b = 0; b < nb; ++b) h += hpart[b];
-  }
   for (int k = 0; k < per; ++k) {
     const SgStats& S = hst[k];
     if (Rr.escaped_sg) Rr.escaped_sg[k] = S.esc_P;
@@ -553,7 +550,10 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   Rr.from_graph = 0;
   // the halted rays are the next step's rays in flight
   t->n_in = n_held;
-  std::memcpy(t->lev_in, hctr->halt_levels, sizeof t->lev_in);
+  for (int l = 0; l < kLevels; ++l) {
+    t->lev_in[l] = 0;
+    for (const Counters::Halted& H : hctr->halted[l]) t->lev_in[l] += H.rays;
+  }
   t->cur = 1 - t->cur;
   t->step++;
   if (held) *held = h;
