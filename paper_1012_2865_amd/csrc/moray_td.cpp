@@ -123,8 +123,12 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
   t->n_pack = pack_count(t->n_grp);
   t->width = pack_width(t->n_grp);
   t->planes = rate_planes(t->width);
-  // pool_rays counts rays of one group; a record holds `width` of them
-  set_cap(t, std::max<size_t>(1024, pool_rays / (size_t)t->width));
+  // A record of several groups holds what as many rays of one group would, yet
+  // may have a single one left: as many records as pool_rays, unless they take
+  // more than 144 bytes per pool ray (divided by the groups, a pool that was large enough
+  // for its rays grew twice on its way to the steady state).
+  const double per_record = 82.0 + 20.0 * t->planes;   // two pools, the sort buffers, two queues of a quarter as many slots
+  set_cap(t, std::max<size_t>(1024, (size_t)((double)pool_rays * std::min(1.0, 144.0 / per_record))));
   const int n_trees = t->slots * t->n_src * t->n_pack;
   const size_t cap = t->cap, qslots = t->seg_cap * (size_t)t->nseg;
   const size_t rsz = c->precision == MORAY_FP32_ACC64 ? sizeof(float) : sizeof(double);
