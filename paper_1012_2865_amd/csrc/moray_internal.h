@@ -143,10 +143,10 @@ void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const
 // more pixels than kDescendLanes and than the level queue has room for (`cap`:
 // a queue too small for a level is reported as such). kDescendLanes: half the
 // lanes the device holds at once, on which the repeated part of the work runs
-// beside the rest. One 32^3 source, and 20 steps of a 64^3 front: 203 us and
-// 5.3 ms at 13 thousand, 174 us and 4.3 ms at 50 to 100 thousand, 218 us and
-// 5.4 ms at 200 to 400 thousand, 267 us and 6.8 ms beyond; larger problems
-// differ by less than 2%.
+// beside the rest. One 32^3 source, 20 steps of a 64^3 front, and the ragged
+// float64 case: 117 us, 3.50 and 1.00 ms at 3 thousand, 108 us, 3.19 and 0.97 ms at
+// 13 thousand, 112 us, 3.12 and 0.95 ms at 100 thousand, 132 us, 3.35 and
+// 0.94 ms at 200 thousand; larger problems differ by less than 2%.
 constexpr long long kDescendLanes = 100000;
 inline int descend_level(long long trees, int l0, int top, size_t cap) {
   const long long most = cap < (size_t)kDescendLanes ? (long long)cap : kDescendLanes;
