@@ -122,7 +122,8 @@ struct SgStats {
 };
 
 // A level queue is split into up to kSegMax segments of seg_cap slots, each
-// with its own write and claim counters, so the same-address atomics that
+// with its own write counter, and its rays into as many parts, each with its own
+// claim counter, so the same-address atomics that
 // reserve and claim rays spread over many addresses (a float64 or integer
 // atomic on one address serialises at the memory side).
 constexpr int kSegMax = 64;
@@ -186,7 +187,7 @@ struct TraceArgs {
   int cin, cout;                       // counter rows of the input and output queues
   int seed_level;                      // HEALPix level of the seed rays of this launch
   int seed_begin, seed_end;            // trees seeded in this launch
-  int chunk;                           // rays claimed per atomic
+  int chunk;                           // rays of a unit, at most
   unsigned max_steps;                  // hard cap on cells per ray (never reached)
   unsigned long long reserve;          // next-level slots a wave reserves at once
   // time-dependent rays: where rays halted in this step go (halt_cap records; level in halt_lev),
