@@ -93,6 +93,8 @@ struct moray_ctx {
                                    // of a launch sequence fails as if HIP had refused it
   bool overflow_serve_once = false;  // test hook (MORAY_INJECT_SERVE_OVERFLOW=1 at moray_init): the serving
                                      // engine's first launch with two or more problems reports a queue overflow
+  bool stale_serve_rates = false;    // test hook (MORAY_INJECT_SERVE_STALE_RATES=1 at moray_init): the serving
+                                     // engine's queue memory starts with NaN in every photon rate
   size_t allocated = 0;
   moray::DevBuf grids, probs, trees, stats, ctr, kappa, kappa64, acc, mark, eexc, fblocks, partial, fields, outs;
   moray::DevBuf q_pix[2], q_tree[2], q_r[2], q_P[2];

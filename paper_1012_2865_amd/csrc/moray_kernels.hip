@@ -761,7 +761,10 @@ struct Tracer {
       L.segs = 0;
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        L.alive[g] = NG == 1 || (g < S.n_grp && L.P[g] >= 0.0);   // a record may hold fewer rates than NG
+        // a record may hold fewer rates than NG: what it has in their place, which may be
+        // anything, must not reach the step (it computes every group some lane carries)
+        L.alive[g] = NG == 1 || (g < S.n_grp && L.P[g] >= 0.0);
+        if constexpr (NG > 1) L.P[g] = L.alive[g] ? L.P[g] : -1.0;
         L.cut[g] = kNoCut;
       }
       q = S.root_grid;

@@ -383,6 +383,7 @@ moray_status moray_init(moray_ctx** out, const moray_init_params* p) {
   c->profile = p->profile;
   if (const char* inj = std::getenv("MORAY_INJECT_CAPTURE_FAILURE")) c->fail_capture_once = inj[0] == '1';
   if (const char* inj = std::getenv("MORAY_INJECT_SERVE_OVERFLOW")) c->overflow_serve_once = inj[0] == '1';
+  if (const char* inj = std::getenv("MORAY_INJECT_SERVE_STALE_RATES")) c->stale_serve_rates = inj[0] == '1';
   c->refill = p->refill_lanes ? p->refill_lanes : 64;
   c->chunk = p->chunk_rays ? p->chunk_rays : 256;
   c->reserve_user = p->reserve_rays;

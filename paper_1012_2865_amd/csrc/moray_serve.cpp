@@ -266,6 +266,8 @@ moray_status engine_setup(moray_ctx* c, Engine* E) {
         (st = ensure(c, E->qr[i], qslots * 8, "serving ray queue")) ||
         (st = ensure(c, E->qP[i], qslots * 8 * kPack, "serving ray queue")))
       return st;
+    if (c->stale_serve_rates && !hip_ok(c, hipMemsetAsync(E->qP[i].p, 0xff, qslots * 8 * kPack, c->stream), "fill"))
+      return MORAY_EDEVICE;
   }
   auto pin = [&](void** p, size_t bytes) { return hipHostMalloc(p, bytes, hipHostMallocDefault) == hipSuccess; };
   if (!pin((void**)&E->hgrids, (size_t)E->grid_cap * sizeof(GridDev)) ||

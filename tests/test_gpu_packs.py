@@ -108,3 +108,32 @@ def test_thin_marks_of_odd_counts():
                 np.testing.assert_allclose(np.asarray(res[f][0].cpu()).ravel(), np.asarray(ref[f][0]).ravel(), rtol=1e-9)
     finally:
         M.moray_free(ctx)
+
+
+def _finite(res, name):
+    for f in ("k_ph", "heating"):
+        for q, v in enumerate(res[f]):
+            assert bool(np.isfinite(np.asarray(v.cpu())).all()), (name, f, q)
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+@pytest.mark.parametrize("narrow", [1, 2])
+def test_serving_rays_get_wider(monkeypatch, name, narrow):
+    # A request of one or two groups runs alone for a launch; then one of four joins (its own
+    # seed level keeps the two from entering together), and the launch reads four rates of rays
+    # that were queued with fewer. What the queue held there before must not matter: NaN here.
+    # Units of one ray put narrow and wide rays into the same waves.
+    first = _box(15, (48, 45, 47), narrow, sources=3, mean=1e-5, params=W.Params(level_init=1))
+    then = _box(16, (40, 44, 41), 4, sources=2, mean=1e-5, params=W.Params(level_init=2))
+    monkeypatch.setenv("MORAY_INJECT_SERVE_STALE_RATES", "1")
+    ctx = M.moray_init(precision=PRECISIONS[name], chunk_rays=1, waves_per_cu=4, queue_capacity=1 << 24)
+    monkeypatch.delenv("MORAY_INJECT_SERVE_STALE_RATES")
+    try:
+        tickets = [M.moray_trace_async(ctx, [M.problem_to_device(p)]) for p in (first, then)]
+        res = [M.moray_query(ctx, t)[0] for t in tickets]
+        assert res[0]["t_admit"] < res[1]["t_admit"] < res[0]["t_done"]       # it did join a running launch sequence
+        for r, p, k in zip(res, (first, then), ("narrow", "wide")):
+            _finite(r, k)
+            _check(r, O.trace(p), BAR[name], name=f"{name} {k}", fp64=name == "fp64")
+    finally:
+        M.moray_free(ctx)
