@@ -461,6 +461,14 @@ constexpr double kLog2e = 1.4426950408889634074;
 // what the cross-section is multiplied by for absorb's argument
 template <typename R> constexpr double kSigmaScale = sizeof(R) == 4 ? kLog2e : 1.0;
 
+// A column or cross-section as R: a float no larger than half the largest, so that a
+// column times a segment's length (below sqrt(3)) is finite and 0 times either is 0,
+// not NaN (a lane without the group or the segment multiplies by 0). 1.7e38 cm^-2 is
+// opaque to any cross-section above 1e-36 cm^2.
+template <typename R> __device__ __forceinline__ R in_range(double x) {
+  return sizeof(R) == 4 ? (R)fmin(x, 0.5 * (double)FLT_MAX) : (R)x;
+}
+
 constexpr unsigned kNoCut = 0xffffffffu;
 
 // Per-lane ray state. A ray carries NG energy groups of its source: they share
@@ -694,7 +702,7 @@ struct Tracer {
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       L.pmin[g] = ldexp(S.pmin0[g], -2 * (level - S.level_init));
-      L.sigma[g] = (R)(S.sigma64[g] * kSigmaScale<R>);
+      L.sigma[g] = in_range<R>(S.sigma64[g] * kSigmaScale<R>);
       L.eexc[g] = S.eexc[g];
     }
   }
@@ -1929,7 +1937,7 @@ __global__ void prep_kernel(const GridDev* __restrict__ grids, int n_grids, int 
           k64 = (double)(-(grid_base + q + 1));
       }
     }
-    kappa[c] = (R)k64;
+    kappa[c] = in_range<R>(k64);
     if (kappa64) kappa64[c] = k64;
     const long long base = P.acc_off + P.acc_stride * (c - P.cell_off), gstride = P.acc_stride * P.n_cells;
     if (P.acc_stride == 1) {

@@ -142,3 +142,26 @@ def test_batches_beyond_32_bit_accumulators_are_rejected(ctxs):
             M.moray_trace(ctx, [p], out_on_device=False)
         assert e.value.status == M.MORAY_EINVAL
         assert "2^32" in str(e.value)
+
+
+@pytest.mark.parametrize("precision", [M.MORAY_FP32_ACC64, M.MORAY_FP64])
+def test_columns_beyond_float_range(precision):
+    """Walls whose column exceeds the largest float: rays of several groups,
+    some of which have ended on the way, are absorbed there like any others."""
+    rng = W.rng_for(97, 40, 0)
+    n_h = (2e-3 * np.exp(rng.normal(0.0, 0.3, (9, 10, 32)))).astype(np.float32)
+    n_h[:, :, 26:] = 3e38                                  # times dx: 1e57 cm^-2 and more
+    p = W.Problem([W.Grid(n_h, np.full((9, 10, 32), 0.75, np.float32), 64.0 * W.DX_C1)],
+                  np.array([[1.3171, 4.6233, 5.2891, 1e49]]), W.hydrogen_spectrum((13.6, 20.0, 30.0, 60.0)), W.Params())
+    ref = O.trace(p)
+    assert ref["totals"]["rays_truncated"] > 0
+    ctx = M.moray_init(device=0, precision=precision)
+    try:
+        res = M.moray_trace(ctx, [M.problem_to_device(p)])[0]
+    finally:
+        M.moray_free(ctx)
+    fp64 = precision == M.MORAY_FP64
+    _check(res, ref, 1e-9 if fp64 else 1e-4, name="wall", fp64=fp64)
+    # the walls' own cells, whose rates are far below the box's largest
+    got, want = (np.asarray(a).reshape(n_h.shape)[:, :, 26] for a in (res["k_ph"][0].cpu(), ref["k_ph"][0]))
+    assert np.allclose(got, want, rtol=1e-9 if fp64 else 1e-4, atol=0.0)
