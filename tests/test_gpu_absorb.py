@@ -1,0 +1,50 @@
+"""Precision of the absorbed and of the transmitted photon rate of one segment.
+
+One ray along +x crosses a vacuum cell with the source at its centre, then a
+cell of unit width and unit column: its optical depth is the cross-section
+itself, and with a rate of 1 and n_H x_HI V = 1 the cell's k_ph is 1 - e^-tau
+as the kernel has it. What a second, opaque cell absorbs is e^-tau.
+
+Bars:
+* float64: 1 - e^-tau bit for bit as the platform's expm1 gives it (torch's
+  float64 expm1 on the device is the same library function).
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1012_2865_amd import moray as M
+from paper_1012_2865_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+LD = np.longdouble
+
+
+def _deposits(precision, taus):
+    """Rates absorbed of 1 in a cell of optical depth tau, and of the rest in an opaque one."""
+    par = W.Params(level_init=0, level_max=0, p_min_frac=0.0)
+    n_h = np.array([0.0, 1.0, 2.0 ** 20], np.float32).reshape(1, 1, 3)
+    # 12 rays of one photon a second each; the others leave through the sides of the first cell
+    probs = [M.problem_to_device(W.Problem([W.Grid(n_h, np.ones_like(n_h), 1.0)], np.array([[0.5, 0.5, 0.5, 12.0]]),
+                                           W.Spectrum(np.array([20.0]), np.array([t]), np.array([1.0])), par))
+             for t in taus]
+    ctx = M.moray_init(device=0, precision=precision)
+    try:
+        res = M.moray_trace(ctx, probs)
+    finally:
+        M.moray_free(ctx)
+    k = np.stack([r["k_ph"][0].cpu().numpy().ravel() for r in res])
+    return k[:, 1], k[:, 2] * 2.0 ** 20
+
+
+def _taus(lo, hi, n, seed):
+    return np.exp(W.rng_for(96, 77, seed).uniform(math.log(lo), math.log(hi), n))
+
+
+def test_absorbed_part_in_float64():
+    tau = np.concatenate([_taus(1e-9, 40.0, 3000, 2), [0.0, 36.7, 37.5, 700.0, 1e5]])
+    want = (-torch.expm1(-torch.from_numpy(tau).cuda())).cpu().numpy()
+    assert np.array_equal(_deposits(M.MORAY_FP64, tau)[0], want)
