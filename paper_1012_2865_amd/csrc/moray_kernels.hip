@@ -408,29 +408,29 @@ __device__ __forceinline__ double absorb(double& P, double tau) {
   P -= dP;
   return dP;
 }
-// Float32, of y = tau / ln 2 (the factor is folded into the cross-section):
-// 1 - 2^-y = y (c0 - c1 y + ...), c_n = ln2^(n+1) / (n+1)!, to y^7 for thin
-// segments (y <= 1/2; truncation below 2e-8), and for thick ones the transmitted
-// part P 2^-y from the hardware exp2 (1 ulp) and the absorbed part as the float64
-// difference, so that both are accurate to float rounding and dP + P_new = P to
-// float64 rounding. Where no lane is thick, as in ionised gas and for the
-// hardest photons everywhere, the wave takes the series alone.
+// Float32, of y = tau / ln 2 (the factor is folded into the cross-section). Thin
+// segments (y <= 1): 1 - 2^-y = y ln 2 - y^2 g(y), g of degree 4 fitted on [0, 1]
+// to the least relative error of the sum (1.1e-8). The small part, at most 0.31 of
+// the sum, is a float; the leading term and the sum are float64, so that little
+// more than the rounding of y is left: 2.3e-8 to 2.6e-8 rms for tau of 1e-4 to
+// 0.69 (with a float sum 3.4e-8 to 3.6e-8, with a float product y q(y) 4.3e-8 to 5.1e-8;
+// the 128^3 workload takes 4.09, 4.11 and 4.10 ms). Thick ones: the transmitted part P 2^-y from
+// the hardware exp2 (within 1.5 x 2^-24), and the absorbed part as the float64 difference. dP + P_new = P to
+// float64 rounding either way. Where no lane is thick, as in ionised gas and for
+// the hardest photons everywhere, the wave takes the series alone.
 __device__ __forceinline__ double absorb(double& P, float y) {
-  float q = fmaf(y, 1.5252733804e-5f, -1.5403530394e-4f);   // c6, -c5
-  q = fmaf(y, q, 1.3333558146e-3f);
-  q = fmaf(y, q, -9.6181291076e-3f);
-  q = fmaf(y, q, 5.5504108665e-2f);
-  q = fmaf(y, q, -0.24022650696f);
-  q = fmaf(y, q, 0.69314718056f);
-  const float f = y * q;
-  const bool thick = y > 0.5f;
+  float g = fmaf(y, -1.1519434e-4f, 1.2924776e-3f);
+  g = fmaf(y, g, -9.5979832e-3f);
+  g = fmaf(y, g, 5.5499703e-2f);
+  g = fmaf(y, g, -2.4022619e-1f);
+  const double f = fma((double)y, 0.69314718055994530942, (double)((y * y) * g));
+  const bool thick = y > 1.0f;
   if (!wave_mask(thick)) {
-    const double dP = P * (double)f;
+    const double dP = P * f;
     P -= dP;
     return dP;
   }
-  const float m = thick ? __builtin_amdgcn_exp2f(-y) : f;
-  const double a = P * (double)m, rest = P - a;
+  const double a = P * (thick ? (double)__builtin_amdgcn_exp2f(-y) : f), rest = P - a;
   P = thick ? a : rest;
   return thick ? rest : a;
 }

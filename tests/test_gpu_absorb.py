@@ -8,6 +8,11 @@ as the kernel has it. What a second, opaque cell absorbs is e^-tau.
 Bars:
 * float64: 1 - e^-tau bit for bit as the platform's expm1 gives it (torch's
   float64 expm1 on the device is the same library function).
+* mixed: the optical depth is rounded to a float (by up to 2^-24 of it, 2.4e-8
+  rms), and the small part of the sum, at most 0.31 of it, four times (2.4e-8 rms
+  each): sqrt(1 + 4 x 0.31^2) x 2.4e-8 = 2.9e-8 rms at most, 1e-7 in one value. A
+  float product y q(y) has 4.3e-8 to 5.1e-8 rms, a classical core with a final
+  rounding to float 3.4e-8 to 3.6e-8.
 """
 import math
 
@@ -42,6 +47,16 @@ def _deposits(precision, taus):
 
 def _taus(lo, hi, n, seed):
     return np.exp(W.rng_for(96, 77, seed).uniform(math.log(lo), math.log(hi), n))
+
+
+@pytest.mark.parametrize("lo,hi", [(1e-4, 1e-2), (1e-2, 0.1), (0.1, 0.35), (0.35, 0.693)])
+def test_absorbed_part_in_mixed_precision(lo, hi):
+    tau = _taus(lo, hi, 3000, 1)
+    want = -np.expm1(-tau.astype(LD))
+    e = ((_deposits(M.MORAY_FP32_ACC64, tau)[0] - want) / want).astype(np.float64)
+    rms, worst = float(np.sqrt(np.mean(e * e))), float(np.abs(e).max())
+    print(f"tau in [{lo}, {hi}]: rms {rms:.3e} max {worst:.3e}", flush=True)
+    assert rms < 2.9e-8 and worst < 1e-7
 
 
 def test_absorbed_part_in_float64():
