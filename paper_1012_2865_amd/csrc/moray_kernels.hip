@@ -415,7 +415,8 @@ __device__ __forceinline__ double absorb(double& P, double tau) {
 // more than the rounding of y is left: 2.3e-8 to 2.6e-8 rms for tau of 1e-4 to
 // 0.69 (with a float sum 3.4e-8 to 3.6e-8, with a float product y q(y) 4.3e-8 to 5.1e-8;
 // the 128^3 workload takes 4.09, 4.11 and 4.10 ms). Thick ones: the transmitted part P 2^-y from
-// the hardware exp2 (within 1.5 x 2^-24), and the absorbed part as the float64 difference. dP + P_new = P to
+// the hardware exp2 (within 1.5 x 2^-24, and below 2^-126, where it gives 0, from
+// 2^(64-y)), and the absorbed part as the float64 difference. dP + P_new = P to
 // float64 rounding either way. Where no lane is thick, as in ionised gas and for
 // the hardest photons everywhere, the wave takes the series alone.
 __device__ __forceinline__ double absorb(double& P, float y) {
@@ -430,7 +431,9 @@ __device__ __forceinline__ double absorb(double& P, float y) {
     P -= dP;
     return dP;
   }
-  const double a = P * (thick ? (double)__builtin_amdgcn_exp2f(-y) : f), rest = P - a;
+  float e = __builtin_amdgcn_exp2f(-y);
+  if (wave_mask(y > 126.0f)) e = y > 126.0f ? __builtin_amdgcn_exp2f(64.0f - y) * 0x1p-64f : e;
+  const double a = P * (thick ? (double)e : f), rest = P - a;
   P = thick ? a : rest;
   return thick ? rest : a;
 }

@@ -13,6 +13,9 @@ Bars:
   each): sqrt(1 + 4 x 0.31^2) x 2.4e-8 = 2.9e-8 rms at most, 1e-7 in one value. A
   float product y q(y) has 4.3e-8 to 5.1e-8 rms, a classical core with a final
   rounding to float 3.4e-8 to 3.6e-8.
+* transmitted: tau rounded to a float moves e^-tau by up to tau 2^-24 of it; the
+  hardware exponential is within 1.5 x 2^-24, and its float result below 2^-126
+  is a multiple of 2^-149.
 """
 import math
 
@@ -63,3 +66,11 @@ def test_absorbed_part_in_float64():
     tau = np.concatenate([_taus(1e-9, 40.0, 3000, 2), [0.0, 36.7, 37.5, 700.0, 1e5]])
     want = (-torch.expm1(-torch.from_numpy(tau).cuda())).cpu().numpy()
     assert np.array_equal(_deposits(M.MORAY_FP64, tau)[0], want)
+
+
+@pytest.mark.parametrize("lo,hi", [(0.7, 10.0), (10.0, 87.0), (87.0, 100.0)])
+def test_transmitted_part_in_mixed_precision(lo, hi):
+    tau = _taus(lo, hi, 500, 3)
+    want = np.exp(-tau.astype(LD))
+    got = _deposits(M.MORAY_FP32_ACC64, tau)[1]
+    assert np.all(np.abs(got - want) <= want * (tau + 1.5) * 2.0 ** -24 + 2.0 ** -149)
