@@ -129,6 +129,20 @@ struct SgStats {
 constexpr int kSegMax = 64;
 constexpr int kHaltSpread = 8;
 
+// Rays of a unit of a level of `all` rays (see the trace kernel), launched with
+// `waves` waves: `chunk`, or where the level holds no more than one such unit a wave
+// an equal share in whole rays per lane. Units are counted in 32 bits, and a level
+// may hold any number of seeds: `chunk` grows where there would be 2^30 units and
+// more (two trees whose seeds are of level 14, in units of one ray: 6.4e9).
+__host__ __device__ inline unsigned unit_rays(unsigned long long all, unsigned chunk, unsigned waves) {
+  if (all <= (unsigned long long)chunk * waves) {
+    const unsigned long long lanes = (unsigned long long)waves * kWave;
+    return (unsigned)((all + lanes - 1) / lanes) * kWave;
+  }
+  const unsigned least = (unsigned)(all >> 30) + 1u;
+  return chunk < least ? least : chunk;
+}
+
 struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
   unsigned long long lost_rays;                 // children dropped on overflow

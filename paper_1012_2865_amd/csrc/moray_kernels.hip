@@ -1409,6 +1409,7 @@ void trace_level_kernel(TraceArgs<R> a) {
   const unsigned rank = blk * (kTraceBlock / kWave) + wave_in_block();
   unsigned u_next, u_end;                    // the units the wave has claimed
   {
+    // (32 bits hold a segment: 64 of 2^30 slots would be terabytes)
     const unsigned rays = lane < K ? (unsigned)(4ull * min(a.ctr->count[a.cin][lane], a.seg_cap)) : 0u;
     unsigned long long all = rays;
 #pragma unroll
@@ -1418,9 +1419,7 @@ void trace_level_kernel(TraceArgs<R> a) {
     }
     all = uniform64(all) + n_extra;
     if (all == 0) return;                    // a level no ray reached (the host launches all it may need)
-    unsigned span = (unsigned)a.chunk;
-    if (all <= (unsigned long long)span * waves)
-      span = (unsigned)((all + (unsigned long long)waves * kWave - 1) / ((unsigned long long)waves * kWave)) * kWave;
+    const unsigned span = unit_rays(all, (unsigned)a.chunk, waves);
     unsigned upto = (rays + span - 1) / span;
     const unsigned mine = upto;
 #pragma unroll

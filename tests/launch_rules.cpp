@@ -1,0 +1,41 @@
+// Rules of the launches that hold on any device, checked on the host (test
+// infrastructure, built and run by tests/test_launch_rules.py). Exit status 0
+// when every check held.
+#include "moray_internal.h"
+
+#include <cstdio>
+
+using namespace moray;
+
+static int failures = 0;
+#define CHECK(cond)                                                   \
+  do {                                                                \
+    if (!(cond)) {                                                    \
+      std::printf("FAILED line %d: %s\n", __LINE__, #cond);          \
+      ++failures;                                                     \
+    }                                                                 \
+  } while (0)
+
+// Units of a level: all rays in them, counted in 32 bits.
+static void units() {
+  const unsigned chunks[] = {1, 63, 64, 100, 256, 4096, 1u << 20}, waves[] = {4, 1024, 3072};
+  const unsigned long long sizes[] = {1, 63, 64, 65, 1024, 196608, 262144, 262145, 786432, 786433,
+                                      1ull << 30, (1ull << 30) + 1, 1ull << 31, 1ull << 32, 6442450944ull, 3ull << 35};
+  for (unsigned w : waves)
+    for (unsigned c : chunks)
+      for (unsigned long long all : sizes) {
+        const unsigned span = unit_rays(all, c, w);
+        CHECK(span >= 1);
+        const unsigned long long n = (all + span - 1) / span;
+        CHECK(n + kSegMax < 1ull << 31);                       // each segment may end in a partial unit
+        CHECK((unsigned long long)(unsigned)n * span >= all);  // as the kernel counts them
+        if (all <= (unsigned long long)c * w) CHECK(n <= w && span % kWave == 0);
+        else if (all >> 30 < c) CHECK(span == c);
+      }
+}
+
+int main() {
+  units();
+  std::printf("%s\n", failures ? "SOME CHECK FAILED" : "ALL OK");
+  return failures ? 1 : 0;
+}
