@@ -143,6 +143,15 @@ __host__ __device__ inline unsigned unit_rays(unsigned long long all, unsigned c
   return chunk < least ? least : chunk;
 }
 
+// Blocks of a trace launch: those the context asks for, but no more than the
+// kernel keeps resident, `per_cu` on each of `num_cu` compute units. A wave
+// starts with its share of the level, so a block that waits for another's place
+// holds its share back.
+inline int launch_blocks(int asked, int per_cu, int num_cu) {
+  const long long resident = (long long)per_cu * num_cu;
+  return resident < asked ? (int)resident : asked;
+}
+
 struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
   unsigned long long lost_rays;                 // children dropped on overflow

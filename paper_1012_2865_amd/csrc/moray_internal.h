@@ -22,10 +22,10 @@ template <typename R>
 hipError_t launch_prep(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long, long long, R*, double*,
                        Counters*, uint8_t* mark = nullptr, long long n_mark = 0, double* kappa64 = nullptr);
 template <typename R>
-hipError_t launch_trace_level(hipStream_t, int, const TraceArgs<R>&, bool cache, int width, bool cover, bool radp,
-                              bool thin = false);
+hipError_t launch_trace_level(hipStream_t, int num_cu, int blocks, const TraceArgs<R>&, bool cache, int width, bool cover,
+                              bool radp, bool thin = false);
 template <typename R>
-hipError_t launch_trace_level_halt(hipStream_t, int, const TraceArgs<R>&, bool cache, int width);
+hipError_t launch_trace_level_halt(hipStream_t, int num_cu, int blocks, const TraceArgs<R>&, bool cache, int width);
 // Serving: empty the queued rays (counter row `row`, nseg segments) whose
 // tree index lies in one of the n ranges [lo[i], hi[i]) (n <= kDropRanges).
 hipError_t launch_drop_trees(hipStream_t, uint32_t* tree, const Counters* ctr, int row, unsigned long long seg_cap,

@@ -2069,58 +2069,54 @@ hipError_t launch_prep(hipStream_t s, int num_cu, const GridDev* grids, int n_gr
   return hipGetLastError();
 }
 
-// Blocks per CU a kernel can keep resident (looked up once per kernel).
+// Blocks per CU a kernel can keep resident.
 template <typename K>
-static int resident_blocks(K kernel, int& memo) {
-  if (memo <= 0) {
-    int n = 0;
-    memo = (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kTraceBlock, 0) == hipSuccess && n > 0) ? n : 1;
-  }
-  return memo;
+static int resident_blocks(K kernel) {
+  int n = 0;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kTraceBlock, 0) == hipSuccess && n > 0 ? n : 1;
 }
 
-// `blocks` is sized for the plain kernel's residency; a variant that keeps
-// fewer blocks per CU resident (the radiation-pressure table takes more LDS)
-// is launched with proportionally fewer, so its grid stays persistent.
+// `blocks` is what the context asks for, at most what the plain kernel keeps
+// resident. A variant may keep fewer: the float64 kernels for three or four groups
+// run at two waves a SIMD (200 to 220 VGPRs), the plain one at three.
+template <typename R, int PHYS, int NG, bool CACHE>
+static void launch_as(hipStream_t s, int num_cu, int blocks, const TraceArgs<R>& args) {
+  static const int per_cu = resident_blocks(trace_level_kernel<R, CACHE, PHYS, NG>);    // looked up once per kernel
+  blocks = launch_blocks(blocks, per_cu, num_cu);
+  hipLaunchKernelGGL((trace_level_kernel<R, CACHE, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
+}
 template <typename R, int PHYS, int NG>
-static void launch_one(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache) {
-  if (cache) {
-    static int plain = 0, mine = 0;
-    const int p = resident_blocks(trace_level_kernel<R, true, 0, 1>, plain);
-    const int m = resident_blocks(trace_level_kernel<R, true, PHYS, NG>, mine);
-    if (m < p) blocks = (blocks * m + p - 1) / p;
-    hipLaunchKernelGGL((trace_level_kernel<R, true, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
-  } else {
-    hipLaunchKernelGGL((trace_level_kernel<R, false, PHYS, NG>), dim3(blocks), dim3(kTraceBlock), 0, s, args);
-  }
+static void launch_one(hipStream_t s, int num_cu, int blocks, const TraceArgs<R>& args, bool cache) {
+  if (cache) launch_as<R, PHYS, NG, true>(s, num_cu, blocks, args);
+  else launch_as<R, PHYS, NG, false>(s, num_cu, blocks, args);
 }
 
 // `width`: the widest pack of the launch's trees; 3 takes the kernel for 4 (the
 // fourth group is never alive, which skips it)
 template <typename R, int PHYS>
-static void launch_phys(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width) {
-  if (width <= 1) launch_one<R, PHYS, 1>(s, blocks, args, cache);
-  else if (width == 2) launch_one<R, PHYS, 2>(s, blocks, args, cache);
-  else launch_one<R, PHYS, 4>(s, blocks, args, cache);
+static void launch_phys(hipStream_t s, int num_cu, int blocks, const TraceArgs<R>& args, bool cache, int width) {
+  if (width <= 1) launch_one<R, PHYS, 1>(s, num_cu, blocks, args, cache);
+  else if (width == 2) launch_one<R, PHYS, 2>(s, num_cu, blocks, args, cache);
+  else launch_one<R, PHYS, 4>(s, num_cu, blocks, args, cache);
 }
 
 template <typename R>
-hipError_t launch_trace_level(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width, bool cover,
-                              bool radp, bool thin) {
+hipError_t launch_trace_level(hipStream_t s, int num_cu, int blocks, const TraceArgs<R>& args, bool cache, int width,
+                              bool cover, bool radp, bool thin) {
   if ((thin && radp) || ((thin || radp) && width > 1) || width > kPack) return hipErrorInvalidValue;
-  if (thin && cover) launch_one<R, kPhysThin | kPhysCover, 1>(s, blocks, args, cache);
-  else if (thin) launch_one<R, kPhysThin, 1>(s, blocks, args, cache);
-  else if (cover && radp) launch_one<R, kPhysCover | kPhysRadp, 1>(s, blocks, args, cache);
-  else if (radp) launch_one<R, kPhysRadp, 1>(s, blocks, args, cache);
-  else if (cover) launch_phys<R, kPhysCover>(s, blocks, args, cache, width);
-  else launch_phys<R, 0>(s, blocks, args, cache, width);
+  if (thin && cover) launch_one<R, kPhysThin | kPhysCover, 1>(s, num_cu, blocks, args, cache);
+  else if (thin) launch_one<R, kPhysThin, 1>(s, num_cu, blocks, args, cache);
+  else if (cover && radp) launch_one<R, kPhysCover | kPhysRadp, 1>(s, num_cu, blocks, args, cache);
+  else if (radp) launch_one<R, kPhysRadp, 1>(s, num_cu, blocks, args, cache);
+  else if (cover) launch_phys<R, kPhysCover>(s, num_cu, blocks, args, cache, width);
+  else launch_phys<R, 0>(s, num_cu, blocks, args, cache, width);
   return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_trace_level_halt(hipStream_t s, int blocks, const TraceArgs<R>& args, bool cache, int width) {
+hipError_t launch_trace_level_halt(hipStream_t s, int num_cu, int blocks, const TraceArgs<R>& args, bool cache, int width) {
   if (width > kPack) return hipErrorInvalidValue;
-  launch_phys<R, kPhysHalt>(s, blocks, args, cache, width);
+  launch_phys<R, kPhysHalt>(s, num_cu, blocks, args, cache, width);
   return hipGetLastError();
 }
 
@@ -2174,10 +2170,10 @@ template hipError_t launch_prep<float>(hipStream_t, int, const GridDev*, int, in
                                        long long, float*, double*, Counters*, uint8_t*, long long, double*);
 template hipError_t launch_prep<double>(hipStream_t, int, const GridDev*, int, int, const ProblemDev*, long long,
                                         long long, double*, double*, Counters*, uint8_t*, long long, double*);
-template hipError_t launch_trace_level<float>(hipStream_t, int, const TraceArgs<float>&, bool, int, bool, bool, bool);
-template hipError_t launch_trace_level<double>(hipStream_t, int, const TraceArgs<double>&, bool, int, bool, bool, bool);
-template hipError_t launch_trace_level_halt<float>(hipStream_t, int, const TraceArgs<float>&, bool, int);
-template hipError_t launch_trace_level_halt<double>(hipStream_t, int, const TraceArgs<double>&, bool, int);
+template hipError_t launch_trace_level<float>(hipStream_t, int, int, const TraceArgs<float>&, bool, int, bool, bool, bool);
+template hipError_t launch_trace_level<double>(hipStream_t, int, int, const TraceArgs<double>&, bool, int, bool, bool, bool);
+template hipError_t launch_trace_level_halt<float>(hipStream_t, int, int, const TraceArgs<float>&, bool, int);
+template hipError_t launch_trace_level_halt<double>(hipStream_t, int, int, const TraceArgs<double>&, bool, int);
 
 hipError_t trace_occupancy(int precision, bool cache, int* blocks_per_cu) {
   auto ask = [&](auto kernel) {

@@ -889,7 +889,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
           A.chunk = c->chunk; A.max_steps = max_steps; A.reserve = reserve;
           A.mark = mark;
           A.kappa64 = kappa64;
-          return launch_trace_level<R>(strm, blocks, A, c->cache, width, cover, radp, thin);
+          return launch_trace_level<R>(strm, c->num_cu, blocks, A, c->cache, width, cover, radp, thin);
         };
         if (c->profile) (void)hipEventRecord(c->evs[2 * launches], strm);
         e = fp32 ? launch(0.0f) : launch(0.0);

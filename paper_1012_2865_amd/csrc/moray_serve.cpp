@@ -778,7 +778,7 @@ bool trip(Engine* E) {
     A.gen = g; A.cin = cin; A.cout = cout; A.seed_level = seed_level;
     A.seed_begin = seed_lo; A.seed_end = seed_hi;
     A.chunk = c->chunk; A.max_steps = max_steps; A.reserve = E->reserve;
-    return launch_trace_level<R>(s, blocks, A, c->cache, width, cover, false);
+    return launch_trace_level<R>(s, c->num_cu, blocks, A, c->cache, width, cover, false);
   };
   hipError_t e = launch_reset_generation(s, (Counters*)E->ctr.p, cin, cout);
   if (e == hipSuccess) e = E->fp32 ? launch(0.0f) : launch(0.0);

@@ -236,7 +236,7 @@ static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, in
   A.held_order = (const uint32_t*)t->order[1].p;
   A.held_first = held_first;
   A.n_held = n_held;
-  return launch_trace_level_halt<R>(c->stream, std::max(1, c->num_cu * c->blocks_per_cu), A, c->cache, t->width);
+  return launch_trace_level_halt<R>(c->stream, c->num_cu, std::max(1, c->num_cu * c->blocks_per_cu), A, c->cache, t->width);
 }
 
 // Doubles the pools, the level queues and the sort buffers of a state whose

@@ -34,8 +34,21 @@ static void units() {
       }
 }
 
+// Blocks of a launch: a context that asks for fewer blocks than a variant holds gets
+// them all (one a compute unit leaves none without), one that asks for more gets
+// as many as stay resident.
+static void blocks() {
+  CHECK(launch_blocks(256, 2, 256) == 256);
+  CHECK(launch_blocks(512, 2, 256) == 512);
+  CHECK(launch_blocks(768, 2, 256) == 512);
+  CHECK(launch_blocks(768, 3, 256) == 768);
+  CHECK(launch_blocks(1024, 3, 256) == 768);
+  CHECK(launch_blocks(1, 4, 256) == 1);
+}
+
 int main() {
   units();
+  blocks();
   std::printf("%s\n", failures ? "SOME CHECK FAILED" : "ALL OK");
   return failures ? 1 : 0;
 }
