@@ -402,9 +402,38 @@ template <> struct GeomOf<double> { using type = Geom64; };
 template <> struct GeomOf<float> { using type = Geom32; };
 
 // Photons removed in a segment of optical depth tau: dP = P (1 - e^-tau)
-// (Eq. flux), P -= dP. Float64 takes the definition literally.
+// (Eq. flux), P -= dP.
+//
+// Float64: 1 - e^-tau by Cody-Waite reduction x = -tau = k ln2 + r, |r| <= ln2/2,
+// and the Taylor series of expm1(r) to r^13 (the first omitted term is below
+// 1e-17 of r): e^x - 1 = 2^k expm1(r) + (2^k - 1). What r lost in rounding joins the
+// square: r^2/2 + its loss. Against the platform's expm1 (262144 points a range,
+// ulps rms and at most): tau 0.1 to 0.347 0.292 and 0.69 (0.292 and 0.97), 0.347 to
+// 0.5 0.376 and 0.92 (0.440 and 1.12), 0.5 to 3 0.302 and 0.66 (0.304 and 0.73),
+// elsewhere the same; without the loss 0.445 and 1.16. 64^3, 16 sources, 4 groups:
+// 1.41 ms with the platform's, 1.33 ms with this.
 __device__ __forceinline__ double absorb(double& P, double tau) {
-  const double dP = P * -expm1(-tau);
+  const double x = -fmin(tau, 745.0);                       // e^-745 is the smallest float64
+  const double k = __builtin_rint(x * 1.4426950408889634);
+  // ln 2 in two parts, the first with 32 bits so k times it is exact
+  const double x1 = fma(-k, 0.69314718036912381649, x);
+  const double r = fma(-k, 1.9082149292705877e-10, x1);
+  const double loss = fma(-k, 1.9082149292705877e-10, x1 - r);
+  double q = 1.0 / 6227020800.0;                            // 1/13!
+  q = fma(q, r, 1.0 / 479001600.0);
+  q = fma(q, r, 1.0 / 39916800.0);
+  q = fma(q, r, 1.0 / 3628800.0);
+  q = fma(q, r, 1.0 / 362880.0);
+  q = fma(q, r, 1.0 / 40320.0);
+  q = fma(q, r, 1.0 / 5040.0);
+  q = fma(q, r, 1.0 / 720.0);
+  q = fma(q, r, 1.0 / 120.0);
+  q = fma(q, r, 1.0 / 24.0);
+  q = fma(q, r, 1.0 / 6.0);
+  q = fma(q, r, 0.5);
+  q = fma(fma(r, r, loss + loss), q, r);
+  const double p2 = ldexp(1.0, (int)k);
+  const double dP = -P * fma(p2, q, p2 - 1.0);
   P -= dP;
   return dP;
 }
