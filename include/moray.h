@@ -346,15 +346,15 @@ moray_status moray_evolve(moray_ctx* ctx, const moray_problem* prob, unsigned fl
  * offsets, source and group counts and level_init; its fields may change from
  * step to step).
  * c_dt is c dt_P in root cells (c dt_P / dx_cm), > 0; pool_rays (1024 to
- * 2^34) bounds the rays in flight (those of up to four groups of a source share
- * a record; the pool has pool_rays records, or what 144 bytes per pool ray hold), with up to 255 empty records per wave of
- * each level launch (waves reserve the records of halted rays 256 at a time),
- * and each level's queue (both grow when a step needs more, see moray_td_step); the state holds
- * about 102 bytes of device memory per pool ray with one energy group, 144 with
- * four (two pools, two level queues and the sort buffers that order the rays in
- * flight, the latter only below 2^32 records). The covering factor is
- * not taken. Returns MORAY_EINVAL for bad arguments, MORAY_ENOMEM when the
- * buffers do not fit the context's HBM budget.
+ * 2^34, below 2^32 to be had: MORAY_ENOMEM above) is the number of records for the
+ * rays in flight. The rays of up to four groups of a source share a record, and
+ * each wave of a level's launch leaves up to 255 empty (waves reserve the records
+ * of halted rays 256 at a time). Each level's queue has room for as many rays.
+ * Both grow when a step needs more, see moray_td_step. The state holds 82 bytes of
+ * device memory per pool ray with one energy group, 102 with two and 142 with more
+ * (two pools, their sorted order and two level queues), and what the sort of the
+ * rays in flight needs. The covering factor is not taken. Returns MORAY_EINVAL for bad
+ * arguments, MORAY_ENOMEM when the buffers do not fit the context's HBM budget.
  *
  * moray_td_step: one step. The rays in flight continue; when emit is nonzero
  * the sources emit new seed rays with their current ndot (a source that emits

@@ -133,7 +133,14 @@ inline int pack_width(int n) { return (n + pack_count(n) - 1) / pack_count(n); }
 inline int rate_planes(int width) { return width <= 1 ? 1 : (width == 2 ? 2 : kPack); }
 
 // Bytes of one queue slot.
-inline size_t slot_bytes(int planes) { return sizeof(uint64_t) + sizeof(uint32_t) + sizeof(double) * (1 + planes); }
+constexpr size_t slot_bytes(int planes) { return sizeof(uint64_t) + sizeof(uint32_t) + sizeof(double) * (1 + planes); }
+
+// Bytes a time-dependent state holds per pool record, besides the sort's scratch: the
+// record and its level in both pools, its place in the sorted order, and its share
+// of two level queues.
+constexpr size_t td_record_bytes(int planes) {
+  return 2 * (slot_bytes(planes) + sizeof(int)) + sizeof(uint32_t) + 2 * slot_bytes(planes) / 4;
+}
 
 // The parts of a tree's record that follow from its problem: the rays of
 // source `src` carrying groups [g0, g0 + n) (one group per ray in the modes

@@ -42,7 +42,7 @@ struct moray_td {
   DevBuf pix[2], tree[2], r[2], P[2], lev[2];
   DevBuf qpix[2], qtree[2], qr[2], qP[2];
   DevBuf grids, probs, trees, stats, ctr, kappa, acc, eexc, fblocks, partial;
-  DevBuf keys[2], order[2], sort_temp;  // the halt list sorted by (level, tree, pixel)
+  DevBuf order, sort_temp;              // the halt list sorted by (level, tree, pixel)
   size_t sort_bytes = 0;
   std::vector<FinalBlock> fb;
   void* h_stage = nullptr;
@@ -75,9 +75,8 @@ static void td_release(moray_ctx* c, moray_td* t) {
                    &t->partial};
   for (DevBuf* b : all) release(c, *b);
   release(c, t->sort_temp);
+  release(c, t->order);
   for (int i = 0; i < 2; ++i) {
-    release(c, t->keys[i]);
-    release(c, t->order[i]);
     release(c, t->pix[i]); release(c, t->tree[i]); release(c, t->r[i]); release(c, t->P[i]); release(c, t->lev[i]);
     release(c, t->qpix[i]); release(c, t->qtree[i]); release(c, t->qr[i]); release(c, t->qP[i]);
   }
@@ -123,12 +122,11 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
   t->n_pack = pack_count(t->n_grp);
   t->width = pack_width(t->n_grp);
   t->planes = rate_planes(t->width);
-  // A record of several groups holds what as many rays of one group would, yet
-  // may have a single one left: as many records as pool_rays, unless they take
-  // more than 144 bytes per pool ray (divided by the groups, a pool that was large enough
-  // for its rays grew twice on its way to the steady state).
-  const double per_record = 82.0 + 20.0 * t->planes;   // two pools, the sort buffers, two queues of a quarter as many slots
-  set_cap(t, std::max<size_t>(1024, (size_t)((double)pool_rays * std::min(1.0, 144.0 / per_record))));
+  // A record of several groups may have a single one left, so the pool has as many
+  // records as it may hold rays (divided by the groups, a pool that was large enough for
+  // its rays grew twice on its way to the steady state).
+  static_assert(td_record_bytes(kPack) <= 144, "the device memory the interface states");
+  set_cap(t, pool_rays);
   const int n_trees = t->slots * t->n_src * t->n_pack;
   const size_t cap = t->cap, qslots = t->seg_cap * (size_t)t->nseg;
   const size_t rsz = c->precision == MORAY_FP32_ACC64 ? sizeof(float) : sizeof(double);
@@ -164,9 +162,7 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
     st = fail(c, MORAY_ENOMEM, "the ray pool exceeds the 2^32 records its sorting indexes");
   if (st == MORAY_OK) {
     if (!hip_ok(c, td_sort_temp_bytes(cap, &t->sort_bytes), "sort")) st = MORAY_EDEVICE;
-    for (int i = 0; i < 2 && st == MORAY_OK; ++i)
-      if ((st = ensure(c, t->keys[i], cap * 8, "sort keys")) || (st = ensure(c, t->order[i], cap * 4, "sort order")))
-        break;
+    if (st == MORAY_OK) st = ensure(c, t->order, cap * 4, "sort order");
     if (st == MORAY_OK) st = ensure(c, t->sort_temp, std::max<size_t>(t->sort_bytes, 256), "sort scratch");
   }
   if (st == MORAY_OK && hipHostMalloc(&t->h_stage, stage, hipHostMallocDefault) != hipSuccess) {
@@ -233,7 +229,7 @@ static hipError_t launch_level(moray_ctx* c, moray_td* t, int l, int seed_lo, in
   A.halt_lev = (int*)t->lev[b].p;
   A.halt_cap = t->cap;
   A.held = pool_of(t, t->cur);
-  A.held_order = (const uint32_t*)t->order[1].p;
+  A.held_order = (const uint32_t*)t->order.p;
   A.held_first = held_first;
   A.n_held = n_held;
   return launch_trace_level_halt<R>(c->stream, c->num_cu, std::max(1, c->num_cu * c->blocks_per_cu), A, c->cache, t->width);
@@ -248,23 +244,20 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
   size_t ncap = t->cap * 2;
   while ((double)ncap < 1.5 * (double)demand && ncap <= ((size_t)1 << 34)) ncap *= 2;
   if (ncap >= ((size_t)1 << 32)) return fail(c, MORAY_EQUEUE, "the ray pool cannot grow beyond 2^32 records");
-  const size_t pool_b = slot_bytes(t->planes) + 4, sort_b = 8 + 4;
   size_t sort_tmp = 0;
   if (!hip_ok(c, td_sort_temp_bytes(ncap, &sort_tmp), "sort")) return MORAY_EDEVICE;
-  const size_t nbytes = ncap * (2 * pool_b + 2 * sort_b) + ncap / 4 * 2 * slot_bytes(t->planes) +
-                        std::max<size_t>(sort_tmp, 256);
+  const size_t nbytes = ncap * td_record_bytes(t->planes) + std::max<size_t>(sort_tmp, 256);
   const int a = t->cur;
-  size_t old = t->sort_temp.bytes + t->pix[1 - a].bytes + t->tree[1 - a].bytes + t->r[1 - a].bytes +
+  size_t old = t->sort_temp.bytes + t->order.bytes + t->pix[1 - a].bytes + t->tree[1 - a].bytes + t->r[1 - a].bytes +
                t->P[1 - a].bytes + t->lev[1 - a].bytes;
   for (int i = 0; i < 2; ++i)
-    old += t->qpix[i].bytes + t->qtree[i].bytes + t->qr[i].bytes + t->qP[i].bytes + t->keys[i].bytes + t->order[i].bytes;
+    old += t->qpix[i].bytes + t->qtree[i].bytes + t->qr[i].bytes + t->qP[i].bytes;
   if (c->allocated - old + nbytes + 4096 > c->budget)
     return fail(c, MORAY_EQUEUE, "the ray pool or a level queue overflowed and cannot double within the HBM budget");
   // everything but the rays in flight can go first
   release(c, t->sort_temp);
+  release(c, t->order);
   for (int i = 0; i < 2; ++i) {
-    release(c, t->keys[i]);
-    release(c, t->order[i]);
     release(c, t->qpix[i]); release(c, t->qtree[i]); release(c, t->qr[i]); release(c, t->qP[i]);
   }
   release(c, t->pix[1 - a]); release(c, t->tree[1 - a]); release(c, t->r[1 - a]); release(c, t->P[1 - a]);
@@ -311,12 +304,8 @@ static moray_status td_grow(moray_ctx* c, moray_td* t, unsigned long long demand
     }
   }
   t->sort_bytes = sort_tmp;
-  for (int i = 0; i < 2; ++i)
-    if ((st = ensure(c, t->keys[i], ncap * 8, "sort keys")) || (st = ensure(c, t->order[i], ncap * 4, "sort order"))) {
-      t->broken = true;
-      return st;
-    }
-  if ((st = ensure(c, t->sort_temp, std::max<size_t>(sort_tmp, 256), "sort scratch"))) {
+  if ((st = ensure(c, t->order, ncap * 4, "sort order")) ||
+      (st = ensure(c, t->sort_temp, std::max<size_t>(sort_tmp, 256), "sort scratch"))) {
     t->broken = true;
     return st;
   }
@@ -465,9 +454,11 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   if (t->n_in > 0) {
     unsigned long long o = 0;
     for (int l = 0; l < kLevels; ++l) { first[l] = o; o += t->lev_in[l]; }
+    // The pool this step's halted rays will go to is not in use yet: the keys are sorted
+    // from the place of its pixels to that of its radii, and the indices from that of its trees.
+    const RayQueue b = pool_of(t, 1 - a);
     if (!hip_ok(c, launch_td_sort(s, c->num_cu, pool_of(t, a), (const int*)t->lev[a].p, t->n_in, l_hi, tree_bits, pix_bits,
-                                  pix_drop, t->keys[0].p, t->keys[1].p,
-                                  (uint32_t*)t->order[0].p, (uint32_t*)t->order[1].p, t->sort_temp.p, t->sort_bytes),
+                                  pix_drop, b.pix, b.r, b.tree, (uint32_t*)t->order.p, t->sort_temp.p, t->sort_bytes),
                 "sort"))
       return MORAY_EDEVICE;
   }

@@ -18,6 +18,7 @@ oracle's orc_trace_td on the same seeded inputs, through the C ABI:
 """
 import numpy as np
 import pytest
+import torch
 
 from oracle import oracle as O
 from paper_1012_2865_amd import moray as M
@@ -186,4 +187,45 @@ def test_small_pool_grows_and_matches_a_large_one(precision):
         for td in (big, small):
             if td:
                 M.moray_td_free(ctx, td)
+        M.moray_free(ctx)
+
+
+def _all_halt(groups, c_dt=4.0):
+    """196608 rays of level 7 (none splits) in a thin 16^3 box, all of which halt inside it in the first step."""
+    g = W.Grid(np.full((16, 16, 16), 1e-6, np.float32), np.full((16, 16, 16), 0.75, np.float32), W.DX_C1)
+    p = W.Problem([g], np.array([[8.1, 7.9, 8.2, 1e49]]), W.hydrogen_spectrum((13.6, 20.0, 30.0, 60.0)[:groups]),
+                  W.Params(level_init=7, level_max=7))
+    return p, M.problem_to_device(p), c_dt
+
+
+@pytest.mark.parametrize("precision", [M.MORAY_FP64, M.MORAY_FP32_ACC64])
+@pytest.mark.parametrize("groups", [1, 2, 3, 4])
+def test_a_pool_holds_as_many_records_as_asked_for(precision, groups):
+    """Whatever the groups a record carries. With four waves a compute unit
+    every wave of the launch gets an equal share of the 196608 rays, and
+    reserves one block of 256 records for them: 262144 in all on 256 compute
+    units, the last of which is used up to its 192nd. The context's budget has room
+    for 142 bytes a record and what the sort needs besides, but not to grow."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if cus != 256:
+        pytest.skip("the records a launch reserves are counted for 256 compute units")
+    p, dev, c_dt = _all_halt(groups)
+    ref, rays = O.trace_td(p, c_dt, None, emit=True)
+    assert len(rays) == 196608 * groups
+    pool = 4 * cus * 256
+    # 142 B and up to 24 B of sort scratch a record, and 2 MiB of tables
+    ctx = M.moray_init(device=0, precision=precision, waves_per_cu=4, hbm_budget_bytes=pool * 166 + (2 << 20))
+    td = None
+    try:
+        td = M.moray_td_create(ctx, dev, c_dt, pool)
+        for step in range(2):
+            if step:
+                ref, rays = O.trace_td(p, c_dt, rays, emit=False)
+            res, held = M.moray_td_step(ctx, td, dev, emit=step == 0)
+            assert held == pytest.approx(ref["held"], rel=1e-6)
+            rel, _ = _rel(res["k_ph"][0], ref["k_ph"][0])
+            assert rel <= (1e-9 if precision == M.MORAY_FP64 else 1e-4)
+    finally:
+        if td:
+            M.moray_td_free(ctx, td)
         M.moray_free(ctx)
