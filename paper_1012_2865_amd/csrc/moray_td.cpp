@@ -107,6 +107,8 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
     n_cells += (long long)prob->grids[q].nx * prob->grids[q].ny * prob->grids[q].nz;
   if ((double)n_cells * prob->spectrum->n_groups >= (double)kNoSlot)
     return fail(c, MORAY_EINVAL, "the grids need fewer than 2^32 - 1 accumulators (cells x groups)");
+  if (pool_rays >= ((size_t)1 << 32))
+    return fail(c, MORAY_ENOMEM, "the ray pool exceeds the 2^32 records its sorting indexes");
   if (!hip_ok(c, hipSetDevice(c->device), "hipSetDevice")) return MORAY_EDEVICE;
 
   moray_td* t = new moray_td();
@@ -158,8 +160,6 @@ moray_status moray_td_create(moray_ctx* c, const moray_problem* prob, double c_d
            (st = ensure(c, t->fblocks, t->fb.size() * sizeof(FinalBlock), "finalize blocks")) ||
            (st = ensure(c, t->partial, t->fb.size() * 8, "partial sums")));
   }
-  if (st == MORAY_OK && cap >= ((size_t)1 << 32))
-    st = fail(c, MORAY_ENOMEM, "the ray pool exceeds the 2^32 records its sorting indexes");
   if (st == MORAY_OK) {
     if (!hip_ok(c, td_sort_temp_bytes(cap, &t->sort_bytes), "sort")) st = MORAY_EDEVICE;
     if (st == MORAY_OK) st = ensure(c, t->order, cap * 4, "sort order");

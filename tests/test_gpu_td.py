@@ -229,3 +229,16 @@ def test_a_pool_holds_as_many_records_as_asked_for(precision, groups):
         if td:
             M.moray_td_free(ctx, td)
         M.moray_free(ctx)
+
+
+def test_a_pool_beyond_32_bit_records_is_refused_before_it_is_allocated():
+    _, dev, c_dt = _all_halt(1)
+    ctx = M.moray_init(device=0, hbm_budget_bytes=1 << 44)
+    try:
+        free = torch.cuda.mem_get_info()[0]
+        with pytest.raises(M.MorayError) as e:
+            M.moray_td_create(ctx, dev, c_dt, 1 << 32)
+        assert e.value.status == M.MORAY_ENOMEM and "2^32" in str(e.value)
+        assert torch.cuda.mem_get_info()[0] == free
+    finally:
+        M.moray_free(ctx)
