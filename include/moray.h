@@ -79,7 +79,8 @@ typedef struct {
   int profile;                /* nonzero: time every trace-kernel launch with HIP events */
   int deposit_cache;          /* >= 0: combine deposits in a per-wave LDS table (default);
                                  < 0: one float64 atomic per segment */
-  int reserve_rays;           /* next-level queue slots a wave reserves per atomic; 0 = from the queue size */
+  int reserve_rays;           /* rays of the next level a wave reserves room for per atomic, in queue slots of
+                                 four (at most 256); 0 = from the queue size */
 } moray_init_params;
 
 typedef struct {
@@ -220,8 +221,8 @@ moray_status moray_trace_noalloc(moray_ctx* ctx, const moray_problem* probs, int
 /* Launch settings chosen by moray_autotune. */
 typedef struct {
   int chunk_rays;             /* rays of a level a wave takes at a time */
-  int refill_lanes;           /* as the context was given it */
-  int reserve_rays;           /* next-level queue slots a wave reserves per atomic (split-queue depth) */
+  int refill_lanes;           /* as the context was given it (0: 64), or as the cache file has it; without effect */
+  int reserve_rays;           /* rays of the next level a wave reserves room for per atomic (split-queue depth) */
   int waves_per_cu;           /* persistent trace waves per compute unit */
   double first_ms;            /* fastest solve of the batch with the settings the context had */
   double best_ms;             /* fastest solve with the chosen settings */

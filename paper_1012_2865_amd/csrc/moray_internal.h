@@ -76,8 +76,9 @@ struct moray_ctx {
   hipStream_t stream = nullptr;
   size_t budget = 0;
   size_t queue_cap_user = 0;
-  int waves_per_cu = 0, refill = 0, chunk = 0, profile = 0;
-  int reserve_user = 0;          // next-level slots a wave reserves at once; 0 = from the queue size
+  int waves_per_cu = 0, chunk = 0, profile = 0;
+  int refill = 0;                // moray_init_params.refill_lanes, reported back and kept in tuning files; no launch reads it
+  int reserve_user = 0;          // next-level rays a wave reserves room for at once; 0 = from the queue size
   bool cache = true;
   int num_cu = 0;
   int blocks_per_cu = 1;

@@ -74,7 +74,7 @@ void put(std::string& k, const T& v) {
 // field and output pointers, flags and the context's launch settings.
 std::string plan_key(const moray_ctx* c, const moray_problem* probs, int n, unsigned flags, const moray_result* outs) {
   std::string k;
-  put(k, n); put(k, flags); put(k, c->precision); put(k, c->chunk); put(k, c->refill); put(k, c->blocks_per_cu);
+  put(k, n); put(k, flags); put(k, c->precision); put(k, c->chunk); put(k, c->blocks_per_cu);
   put(k, c->cache); put(k, c->reserve_user); put(k, c->queue_cap_user);
   for (int i = 0; i < n; ++i) {
     const moray_problem& P = probs[i];
@@ -1228,7 +1228,7 @@ moray_status moray_autotune(moray_ctx* c, const moray_problem* probs, int n_prob
     }
   }
   const unsigned fl = flags | MORAY_OUT_ON_DEVICE;
-  const int keep_chunk = c->chunk, keep_refill = c->refill, keep_reserve = c->reserve_user, keep_bpc = c->blocks_per_cu;
+  const int keep_chunk = c->chunk, keep_reserve = c->reserve_user, keep_bpc = c->blocks_per_cu;
   int trials = 0;
   // fastest of three solves (the second captures a graph, the third replays it)
   auto timed = [&](double& ms) -> moray_status {
@@ -1277,7 +1277,6 @@ moray_status moray_autotune(moray_ctx* c, const moray_problem* probs, int n_prob
   release(c, scratch);
   if (st != MORAY_OK) {
     c->chunk = keep_chunk;
-    c->refill = keep_refill;
     c->reserve_user = keep_reserve;
     c->blocks_per_cu = keep_bpc;
     return st;

@@ -178,3 +178,29 @@ def test_failed_capture_falls_back_to_eager(monkeypatch):
     finally:
         M.moray_free(ctx)
         M.moray_free(eager)
+
+
+def test_refill_lanes_is_echoed_and_changes_nothing(tmp_path):
+    """The setting is reported as it was given and as a tuning file has it, and
+    a captured launch sequence, in which it plays no part, outlives its change."""
+    p = M.problem_to_device(W.lognormal_problem(97, 4, 32, 2))
+    outs = [(torch.empty(32 ** 3, dtype=torch.float64, device="cuda"),
+             torch.empty(32 ** 3, dtype=torch.float64, device="cuda"))]
+    path = tmp_path / "tune.txt"
+    ctx = M.moray_init(device=0, precision=M.MORAY_FP32_ACC64, refill_lanes=20)
+    try:
+        # one trial: the settings the context has
+        r = M.moray_autotune(ctx, [p], max_trials=1, cache_path=str(path))
+        assert r["refill_lanes"] == 20 and r["from_cache"] is False
+        f = path.read_text().split(" ")
+        assert f[8] == "20"
+        path.write_text(" ".join(f[:8] + ["33"] + f[9:]))
+        before = [M.moray_trace(ctx, [p], outputs=outs)[0] for _ in range(3)]
+        assert before[-1]["from_graph"] == 1
+        r = M.moray_autotune(ctx, [p], max_trials=1, cache_path=str(path))
+        assert r["refill_lanes"] == 33 and r["from_cache"] is True
+        after = M.moray_trace(ctx, [p], outputs=outs)[0]
+        assert after["from_graph"] == 1
+        _cmp(after, before[0], "another refill setting")
+    finally:
+        M.moray_free(ctx)
