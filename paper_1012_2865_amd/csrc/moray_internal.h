@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -150,19 +151,25 @@ void fill_tree(TreeDev& d, const moray_problem& P, int src, int g0, int n, const
 
 // Level at which the seeds of `trees` trees enter (see the trace kernel): the
 // finest, not beyond `top` (the finest any of them reaches), that still has no
-// more pixels than kDescendLanes and than the level queue has room for (`cap`:
-// a queue too small for a level is reported as such). kDescendLanes: half the
-// lanes the device holds at once, on which the repeated part of the work runs
-// beside the rest. One 32^3 source, 20 steps of a 64^3 front, and the ragged
-// float64 case: 117 us, 3.50 and 1.00 ms at 3 thousand, 108 us, 3.19 and 0.97 ms at
-// 13 thousand, 112 us, 3.12 and 0.95 ms at 100 thousand, 132 us, 3.35 and
-// 0.94 ms at 200 thousand; larger problems differ by less than 2%.
-constexpr long long kDescendLanes = 100000;
-inline int descend_level(long long trees, int l0, int top, size_t cap) {
-  const long long most = cap < (size_t)kDescendLanes ? (long long)cap : kDescendLanes;
+// more pixels than half the lanes of the launch and than the level queue has room
+// for (`cap`: a queue too small for a level is reported as such). Half, so that the
+// repeated part of the work runs beside the rest: one 32^3 source, 20 steps of a 64^3
+// front, and the ragged float64 case: 117 us, 3.50 and 1.00 ms at 3 thousand, 108 us,
+// 3.19 and 0.97 ms at 13 thousand, 112 us, 3.12 and 0.95 ms at 98 thousand (half of
+// 256 CUs with three blocks each), 132 us, 3.35 and 0.94 ms at 200 thousand; larger
+// problems differ by less than 2%. Requests admitted to a running queue, whose rays
+// hold lanes already, enter alike: in Poisson streams of 20, 50, 100 and 150 requests a
+// second (edges 32 to 256) the mean latency was 9.9, 12.1, 117.2 and 62.3 ms, and 10.0,
+// 12.3, 116.9 and 60.4 ms with their seeds at their own level.
+inline int descend_level(long long trees, int l0, int top, size_t cap, long long lanes) {
+  const long long most = cap < (size_t)(lanes / 2) ? (long long)cap : lanes / 2;
   int l = l0;
   while (l < top && trees * (12ll << (2 * (l + 1))) <= most) ++l;
   return l;
+}
+// the lanes of a context's launches
+inline long long launch_lanes(const moray_ctx* c) {
+  return (long long)std::max(1, c->num_cu * c->blocks_per_cu) * kTraceBlock;
 }
 
 // Segments of a level queue for `cap` rays: a power of two up to kSegMax, so

@@ -869,7 +869,7 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
         break;
       }
       // trees of one seed level enter at a finer one (trees of several at their own)
-      const int enter = min_l0 == max_l0 ? descend_level(ch.end - ch.begin, min_l0, min_reach, cap) : min_l0;
+      const int enter = min_l0 == max_l0 ? descend_level(ch.end - ch.begin, min_l0, min_reach, cap, launch_lanes(c)) : min_l0;
       for (int l = enter; l <= max_reach; ++l) {
         const int sl = min_l0 == max_l0 ? (l == enter ? min_l0 : kMaxLevel + 1) : l;    // seed level that enters here
         const int lo = sl <= kMaxLevel ? std::max(seed_lo[sl], ch.begin) : 0;

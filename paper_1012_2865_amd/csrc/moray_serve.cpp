@@ -678,7 +678,7 @@ bool trip(Engine* E) {
   if (!admitted.empty()) {
     int top = kMaxLevel;
     for (ServeProblem* p : admitted) top = std::min(top, reach_level(p->prob));
-    seed_level = descend_level(ttotal, admitted.front()->l0, top, E->qcap);
+    seed_level = descend_level(ttotal, admitted.front()->l0, top, E->qcap, launch_lanes(c));
   }
   {
     int t = tblock;

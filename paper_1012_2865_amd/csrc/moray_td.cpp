@@ -420,7 +420,8 @@ moray_status moray_td_step(moray_ctx* c, moray_td* t, const moray_problem* prob,
   for (int l = l_hi + 1; l < kLevels; ++l)
     if (t->lev_in[l]) l_hi = l;            // rays in flight from a step with a larger phi_c
   // the level at which this step's seeds enter
-  const int enter = descend_level(trees_per, P.params.level_init, std::min(reach_level(P), l_hi), t->cap);
+  const int enter = descend_level(trees_per, P.params.level_init, std::min(reach_level(P), l_hi), t->cap,
+                                  launch_lanes(c));
   int l_lo = emit ? enter : kLevels;
   for (int l = 0; l < kLevels; ++l)
     if (t->lev_in[l]) { l_lo = std::min(l_lo, l); break; }

@@ -46,9 +46,32 @@ static void blocks() {
   CHECK(launch_blocks(1, 4, 256) == 1);
 }
 
+// The level the seeds enter at: never beyond the finest level, the queue or half the lanes
+// of the launch, and no coarser than these ask for.
+static void entries() {
+  moray_ctx c;
+  c.num_cu = 256;
+  c.blocks_per_cu = 3;
+  CHECK(launch_lanes(&c) == 196608);
+  c.blocks_per_cu = 1;
+  CHECK(launch_lanes(&c) == 65536);
+  const long long lanes[] = {1024, 65536, 196608}, trees[] = {1, 2, 7, 64, 5000};
+  const size_t caps[] = {256, 4096, 1u << 20};
+  for (long long n : lanes)
+    for (long long t : trees)
+      for (size_t cap : caps)
+        for (int l0 = 0; l0 <= 3; ++l0)
+          for (int top = l0; top <= 8; ++top) {
+            const int l = descend_level(t, l0, top, cap, n);
+            auto fits = [&](int k) { return t * (12ll << (2 * k)) <= n / 2 && (size_t)(t * (12ll << (2 * k))) <= cap; };
+            CHECK(l >= l0 && l <= top && (l == l0 || fits(l)) && (l == top || !fits(l + 1)));
+          }
+}
+
 int main() {
   units();
   blocks();
+  entries();
   std::printf("%s\n", failures ? "SOME CHECK FAILED" : "ALL OK");
   return failures ? 1 : 0;
 }
