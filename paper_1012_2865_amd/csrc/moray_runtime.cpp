@@ -662,14 +662,40 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
   size_t cap = c->queue_cap_user;
   const double per_ray = 2.0 * (double)slot_bytes(planes) / 4.0;
   const size_t out_stage = odev ? 0 : (size_t)n_cells * (radp ? 40 : 16);
-  const size_t fixed = (size_t)n_cells * rsz + (size_t)n_sums * 8 + (size_t)n_mark +
-                       (thin && fp32 ? (size_t)n_cells * 8 : 0) + (fdev ? 0 : (size_t)n_cells * 8) + out_stage +
-                       (size_t)n_trees * sizeof(TreeDev) + (size_t)n_sg * sizeof(SgStats) +
-                       grids.size() * sizeof(GridDev) + fblocks.size() * (sizeof(FinalBlock) + 8) +
-                       (c->arena ? (size_t)(1 << 20) : (size_t)(64 << 20));
+  struct Want {
+    DevBuf* buf;
+    size_t bytes;
+    const char* what;
+  };
+  const std::vector<Want> wants = {{&c->grids, grids.size() * sizeof(GridDev), "grid table"},
+                                   {&c->probs, pdev.size() * sizeof(ProblemDev), "problem table"},
+                                   {&c->trees, std::max<size_t>(1, n_trees) * sizeof(TreeDev), "source table"},
+                                   {&c->stats, std::max<size_t>(1, n_sg) * sizeof(SgStats), "statistics"},
+                                   {&c->ctr, sizeof(Counters), "counters"},
+                                   {&c->kappa, (size_t)n_cells * rsz, "absorber columns"},
+                                   {&c->acc, (size_t)std::max<long long>(1, n_sums) * 8, "accumulators"},
+                                   {&c->mark, (size_t)n_mark, "optically-thin marks"},
+                                   {&c->kappa64, thin && fp32 ? (size_t)n_cells * 8 : 0, "float64 absorber columns"},
+                                   {&c->eexc, eexc.size() * 8, "group energies"},
+                                   {&c->fblocks, fblocks.size() * sizeof(FinalBlock), "finalize blocks"},
+                                   {&c->partial, fblocks.size() * 8, "partial sums"},
+                                   {&c->fields, fdev ? 0 : (size_t)n_cells * 8, "field upload"},
+                                   {&c->outs, out_stage, "result staging"}};
+  // What the context holds for others (states of time-dependent rays, the
+  // iterations' fields), and what these buffers will take: they only grow.
+  auto taken = [](const DevBuf& b, size_t bytes) { return std::max(b.bytes, (bytes + 255) & ~size_t(255)); };
+  size_t others = c->allocated, fixed = 0;
+  for (const Want& w : wants) {
+    others -= w.buf->bytes;
+    fixed += taken(*w.buf, w.bytes);
+  }
+  DevBuf* const queue_bufs[] = {&c->q_pix[0], &c->q_tree[0], &c->q_r[0], &c->q_P[0],
+                                &c->q_pix[1], &c->q_tree[1], &c->q_r[1], &c->q_P[1]};
+  for (DevBuf* b : queue_bufs) others -= b->bytes;
   if (!cap) {
-    const size_t room = c->budget > c->allocated + fixed ? c->budget - fixed : 0;
-    const double fit = (double)room / per_ray;
+    // (and a margin, which the context's small buffers of later calls come out of)
+    const size_t used = others + fixed + (c->arena ? (size_t)(512 << 10) : (size_t)(63 << 20));
+    const double fit = (double)(c->budget > used ? c->budget - used : 0) / per_ray;
     const double slack = (double)std::max(1, c->num_cu * c->blocks_per_cu) * (kTraceBlock / kWave) * 4 * kReserveMax;
     cap = (size_t)std::max(4096.0, std::min({need + slack, fit, 2.0e9}));
   }
@@ -682,28 +708,17 @@ moray_status trace_impl(moray_ctx* c, const moray_problem* probs, int n_probs, u
 
   // ---- device memory ----
   moray_status st;
-  if ((st = ensure(c, c->grids, grids.size() * sizeof(GridDev), "grid table")) ||
-      (st = ensure(c, c->probs, pdev.size() * sizeof(ProblemDev), "problem table")) ||
-      (st = ensure(c, c->trees, std::max<size_t>(1, n_trees) * sizeof(TreeDev), "source table")) ||
-      (st = ensure(c, c->stats, std::max<size_t>(1, n_sg) * sizeof(SgStats), "statistics")) ||
-      (st = ensure(c, c->ctr, sizeof(Counters), "counters")) ||
-      (st = ensure(c, c->kappa, (size_t)n_cells * rsz, "absorber columns")) ||
-      (st = ensure(c, c->acc, (size_t)std::max<long long>(1, n_sums) * 8, "accumulators")) ||
-      (n_mark && (st = ensure(c, c->mark, (size_t)n_mark, "optically-thin marks"))) ||
-      (thin && fp32 && (st = ensure(c, c->kappa64, (size_t)n_cells * 8, "float64 absorber columns"))) ||
-      (st = ensure(c, c->eexc, eexc.size() * 8, "group energies")) ||
-      (st = ensure(c, c->fblocks, fblocks.size() * sizeof(FinalBlock), "finalize blocks")) ||
-      (st = ensure(c, c->partial, fblocks.size() * 8, "partial sums")))
-    return st;
-  if (!fdev && (st = ensure(c, c->fields, (size_t)n_cells * 8, "field upload"))) return st;
-  if (!odev && (st = ensure(c, c->outs, out_stage, "result staging"))) return st;
-  for (int i = 0; i < 2; ++i) {
-    if ((st = ensure(c, c->q_pix[i], qslots * 8, "ray queue")) ||
-        (st = ensure(c, c->q_tree[i], qslots * 4, "ray queue")) ||
-        (st = ensure(c, c->q_r[i], qslots * 8, "ray queue")) ||
-        (st = ensure(c, c->q_P[i], qslots * 8 * planes, "ray queue")))
-      return st;
-  }
+  const size_t queue_bytes[] = {qslots * 8, qslots * 4, qslots * 8, qslots * 8 * planes};    // of one of the two
+  // The queue holds nothing between calls: where rays of other widths left it with
+  // arrays that do not leave room for this call's, it starts afresh.
+  size_t queue_taken = 0;
+  for (int i = 0; i < 8; ++i) queue_taken += taken(*queue_bufs[i], queue_bytes[i & 3]);
+  if (!c->arena && others + fixed + queue_taken > c->budget)
+    for (DevBuf* b : queue_bufs) release(c, *b);
+  for (const Want& w : wants)
+    if (w.bytes && (st = ensure(c, *w.buf, w.bytes, w.what))) return st;
+  for (int i = 0; i < 8; ++i)
+    if ((st = ensure(c, *queue_bufs[i], queue_bytes[i & 3], "ray queue"))) return st;
   c->q_cap = cap;
 
   // field and output pointers
