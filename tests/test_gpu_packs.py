@@ -137,3 +137,74 @@ def test_serving_rays_get_wider(monkeypatch, name, narrow):
             _check(r, O.trace(p), BAR[name], name=f"{name} {k}", fp64=name == "fp64")
     finally:
         M.moray_free(ctx)
+
+
+def _nested_box(item, groups, **params):
+    """A box with a 2x-refined child that holds one of the sources; two packs from five groups on."""
+    p = _box(item, (20, 17, 18), groups, sources=3, mean=3e-3, params=W.Params(**params))
+    rng = W.rng_for(97, 100 + item, 0)
+    child = W.Grid((3e-3 * np.exp(rng.normal(0.0, 1.0, (8, 12, 10)))).astype(np.float32),
+                   rng.uniform(0.5, 1.0, (8, 12, 10)).astype(np.float32), p.grids[0].dx_cm / 2, parent=0, offset=(7, 4, 6))
+    p.grids.append(child)
+    p.sources[0, :3] = (9.3, 7.1, 8.2)
+    return p
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+@pytest.mark.parametrize("groups", [2, 5, 6])
+def test_packs_cross_nested_grids(name, groups):
+    _held(name, [_nested_box(17, groups)], groups)
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+@pytest.mark.parametrize("groups", [3, 5, 6])
+def test_packs_with_the_covering_factor(name, groups):
+    p = _nested_box(18, groups, covering=True)
+    ctx = M.moray_init(precision=PRECISIONS[name])
+    try:
+        res = M.moray_trace(ctx, [M.problem_to_device(p)])[0]
+    finally:
+        M.moray_free(ctx)
+    _check(res, O.trace(p), BAR[name], name=f"{name} covering {groups}", fp64=name == "fp64", conserving=False)
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+@pytest.mark.parametrize("groups", [5, 6])
+def test_packs_of_time_dependent_rays(name, groups):
+    # groups that end in different steps, rays that halt and are taken up again, splits on the way
+    p = _nested_box(19, groups)
+    dev, c_dt = M.problem_to_device(p), 5.0
+    ctx = M.moray_init(precision=PRECISIONS[name])
+    td = None
+    try:
+        td = M.moray_td_create(ctx, dev, c_dt, 1 << 20)
+        rays = None
+        for step, emit in enumerate([True, True, False, True]):
+            ref, rays = O.trace_td(p, c_dt, rays, emit=emit)
+            res, held = M.moray_td_step(ctx, td, dev, emit=emit)
+            for q in range(2):
+                want = np.asarray(ref["k_ph"][q]).ravel()
+                got = np.asarray(res["k_ph"][q].cpu()).ravel()
+                m = want > 1e-6 * want.max()
+                assert np.max(np.abs(got[m] / want[m] - 1.0)) <= BAR[name], (step, q)
+            assert held == pytest.approx(ref["held"], rel=BAR[name])
+            if name == "fp64":
+                for k in ("segments", "splits", "rays_escaped", "rays_truncated"):
+                    assert res[k] == ref["totals"][k], (step, k)
+    finally:
+        if td:
+            M.moray_td_free(ctx, td)
+        M.moray_free(ctx)
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+def test_one_option_in_a_batch_of_packs(name):
+    # an optically-thin problem puts every ray of its batch back to one group: same results
+    probs = [_box(20, (13, 9, 11), 4), _box(21, (11, 12, 9), 4, mean=1e-5, params=W.Params(tau_thin=0.05)), _nested_box(22, 5)]
+    ctx = M.moray_init(precision=PRECISIONS[name])
+    try:
+        res = M.moray_trace(ctx, [M.problem_to_device(p) for p in probs])
+    finally:
+        M.moray_free(ctx)
+    for k in (0, 2):
+        _check(res[k], O.trace(probs[k]), BAR[name], name=f"{name} beside a thin problem {k}", fp64=name == "fp64")
