@@ -154,7 +154,6 @@ inline int launch_blocks(int asked, int per_cu, int num_cu) {
 
 struct Counters {
   unsigned long long count[kLevels][kSegMax];   // slots written to each segment of each level queue
-  unsigned long long lost_rays;                 // children dropped on overflow
   unsigned int err;                             // bit flags, see kErr*
   unsigned int pad;
   unsigned long long halt_count;                // time-dependent rays halted in this step

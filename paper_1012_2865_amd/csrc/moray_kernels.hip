@@ -1303,10 +1303,7 @@ struct SplitWriter {
       o_next += (unsigned long long)n;
       done += n;
     }
-    if (done < need && lane == 0) {
-      atomicOr(&a.ctr->err, kErrOverflow);
-      atomicAdd(&a.ctr->lost_rays, 4ull * (unsigned long long)(need - done));
-    }
+    if (done < need && lane == 0) atomicOr(&a.ctr->err, kErrOverflow);
   }
   // all lanes of the wave, at its end: the unused slots of its last
   // reservation become empty slots
@@ -1876,9 +1873,7 @@ __global__ void reset_kernel(Counters* ctr, SgStats* stats, int n_sg) {
     (&ctr->count[0][0])[i] = 0;
     (&ctr->head[0][0])[i].n = 0;
   }
-  if (i == 0) {
-    ctr->lost_rays = 0; ctr->err = 0;
-  }
+  if (i == 0) ctr->err = 0;
   if (i < kLevels * kHaltSpread) (&ctr->halted[0][0])[i] = Counters::Halted{0.0, 0ull};
   if (i == 0) ctr->halt_count = 0;
   if (i < n_sg) stats[i] = SgStats{0.0, 0.0, 0ull, 0ull, 0ull, 0ull};
@@ -1899,10 +1894,7 @@ __global__ void reset_generation_kernel(Counters* ctr, int cin, int cout) {
     ctr->head[cin][s].n = 0;
     ctr->count[cout][s] = 0;
   }
-  if (threadIdx.x == 0) {
-    ctr->err &= ~kErrOverflow;
-    ctr->lost_rays = 0;
-  }
+  if (threadIdx.x == 0) ctr->err &= ~kErrOverflow;
 }
 
 __global__ void reset_stats_kernel(SgStats* stats, int first, int count) {
