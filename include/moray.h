@@ -68,7 +68,8 @@ typedef struct {
   int device;                 /* HIP device ordinal */
   int precision;              /* moray_precision */
   size_t hbm_budget_bytes;    /* cap on the context's device memory; 0 = half of the free memory */
-  size_t queue_capacity;      /* rays per level buffer; 0 = sized from each problem's worst case */
+  size_t queue_capacity;      /* rays (of up to four groups) per level buffer; 0 = sized from each problem's
+                                 worst case */
   int waves_per_cu;           /* persistent trace waves per compute unit; 0 = default */
   int refill_lanes;           /* 0 to 64, reported back by moray_autotune; without effect: a wave refetches rays
                                  once all of its 64 lanes are idle, so that they start and write together
@@ -163,7 +164,10 @@ typedef struct {
   double truncated;           /* photon rate left in rays ended by p_min_frac */
   unsigned long long segments;        /* (ray, cell) crossings with dr > 0 that deposited */
   unsigned long long rays_seeded, splits, rays_escaped, rays_truncated;
-  unsigned long long peak_level_rays; /* largest level population of this solve's ray queue */
+  unsigned long long peak_level_rays; /* largest level population of this solve's ray queue: rays of up to four
+                                         groups each (as queue_capacity counts them), with the places waves
+                                         reserved and left; levels that the launch the seeds enter at traces
+                                         in place are never queued */
   double trace_ms;            /* summed trace-kernel device time of the call (profile only) */
   int trace_launches;         /* trace-kernel launches the problem took part in */
   double t_admit, t_done;     /* asynchronous solves: CLOCK_MONOTONIC seconds when the problem

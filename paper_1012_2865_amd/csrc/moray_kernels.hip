@@ -179,8 +179,8 @@ __device__ __forceinline__ int cell_rule(double x, double d) { return d >= 0.0 ?
 __device__ __forceinline__ int floor_half(int c) { return c >= 0 ? c / 2 : -((-c + 1) / 2); }
 
 // One in-order counter covers a wave's vector loads, stores and atomics. A
-// load still in flight where a rare path (a ray start, a grid change, a
-// float64 split re-check) rejoins the hot loop makes the compiler wait at the
+// load still in flight where a rare path (a ray start, a grid change, the source's
+// coordinate for the covering factor) rejoins the hot loop makes the compiler wait at the
 // join for that counter to reach zero, which includes every deposit atomic
 // issued since; those paths therefore finish their own loads before rejoining.
 __device__ __forceinline__ void finish_vector_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0) alone
@@ -917,7 +917,7 @@ __device__ __forceinline__ T wave_total(T x) {     // valid in the last lane
 // counter the next column gather waits on (a global atomic per ray end took
 // the 128^3 workload, 16 sources and 4 groups, from 11.7 to 21 ms).
 // kind: 0 escaped, 1 every group truncated, 2 split, 3 halted (its segments only:
-// the photons it holds are summed from the halt list).
+// the photons it holds are summed where its record is written).
 template <int NG, bool THIN>
 struct WaveTally {
   static constexpr int kRows = 5;                  // segs, splits, n_esc, n_trunc, thin_segs

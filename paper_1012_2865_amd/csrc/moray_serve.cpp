@@ -103,7 +103,7 @@ struct ServeProblem {
   std::vector<double> energy, sigma, frac;
   moray_spectrum spec{};
   moray_problem prob{};
-  double bound = 0.0;            // ray-queue share: rays one level of all its trees can hold
+  double bound = 0.0;            // ray-queue share, see serve_rays_estimate
   long long ncells = 0, nacc = 0;
   int ngroups = 0, width = 1, ntrees = 0, l0 = 0;   // width: groups a ray carries
   unsigned max_steps = 64;
@@ -119,10 +119,12 @@ struct ServeProblem {
   int nstats() const { return (int)sources.size() * ngroups; }
 };
 
-// Ray-queue share of a problem for admission: the largest level population
-// of one tree measured on lognormal grids of 64^3..256^3 is 6-14 rays per
-// unit of face area (N^2); 4 phi_c per unit, capped by the pixel count,
-// covers it. An underestimate only costs a restart.
+// Ray-queue share of a problem for admission, as if each of its groups traced its
+// rays alone: the largest level population of one source and group measured on
+// lognormal grids of 64^3..256^3 is 6-14 rays per unit of face area (N^2); 4 phi_c
+// per unit, capped by the pixel count, covers it. The groups of a pack share their
+// rays, so a problem of several groups is charged for up to four times the rays it
+// queues. An underestimate only costs a restart.
 double serve_rays_estimate(const moray_problem& P) {
   const int lr = reach_level(P);
   double face = 0.0;
