@@ -1191,6 +1191,43 @@ struct DepositCache {
       }
     }
   }
+  // Without the cache: NS neighbouring lanes add the NS sums of one of their records at
+  // a time, so that a record leaves with one request, not with one a sum (64^3 with a
+  // nested grid, 6 sources, 4 groups 2.98 -> 1.69 ms; with radiation pressure 9.82 -> 2.52 ms).
+  static __device__ __forceinline__ void add_records(double* acc, uint32_t slot, uint32_t shift, const double (&v)[NS],
+                                                     unsigned long long has, int lane) {
+    if constexpr (NS == 1) {
+      if (in_mask(has)) unsafeAtomicAdd(&acc[slot], v[0]);
+    } else {
+      add_record_of<0>(acc, slot, shift, v, has, lane);
+      add_record_of<1>(acc, slot, shift, v, has, lane);
+      if constexpr (NS == 4) {
+        add_record_of<2>(acc, slot, shift, v, has, lane);
+        add_record_of<3>(acc, slot, shift, v, has, lane);
+      }
+    }
+  }
+  // the records of the lanes whose number is Q modulo NS (every lane calls)
+  template <int Q>
+  static __device__ __forceinline__ void add_record_of(double* acc, uint32_t slot, uint32_t shift, const double (&v)[NS],
+                                                       unsigned long long has, int lane) {
+    // quad permutation: each lane reads the Q-th of its NS lanes
+    static constexpr int kFrom = NS == 4 ? Q * 0x55 : (Q | Q << 2 | (2 + Q) << 4 | (2 + Q) << 6);
+    auto from = [](unsigned x) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, kFrom, 0xf, 0xf, false); };
+    const unsigned c = (unsigned)lane & (NS - 1u);
+    double w = 0.0;
+#pragma unroll
+    for (unsigned k = 0; k < NS; ++k) {
+      const unsigned long long u = __double_as_longlong(v[k]);
+      const double x = __longlong_as_double(((unsigned long long)from((unsigned)(u >> 32)) << 32) | from((unsigned)u));
+      w = k == c ? x : w;
+    }
+    // (All of them are read before any branch: a lane reads nothing from one that is not
+    // active. And it reads how many sums there are, not the shift: folded into
+    // v_lshrrev_b32_dpp, the permutation reached the number that is shifted.)
+    const unsigned at = from(slot) + c, sums = from(1u << shift), owner = from(in_mask(has) ? 1u : 0u);
+    if (owner != 0u && c < sums) unsafeAtomicAdd(&acc[at], w);
+  }
   // v[c] belongs to the lane's problem where c < 2^shift
   __device__ __forceinline__ void add(double* acc, Probe& p, uint32_t slot, uint32_t shift, const double (&v)[NS],
                                       unsigned long long has, int lane) {
@@ -1200,7 +1237,7 @@ struct DepositCache {
         if (c == 0 || (c >> shift) == 0) unsafeAtomicAdd(&acc[slot + c], v[c]);
     };
     if constexpr (!CACHE) {
-      if (in_mask(has)) to_memory();
+      add_records(acc, slot, shift, v, has, lane);
       return;
     }
     if (p.moved) {

@@ -208,3 +208,27 @@ def test_one_option_in_a_batch_of_packs(name):
         M.moray_free(ctx)
     for k in (0, 2):
         _check(res[k], O.trace(probs[k]), BAR[name], name=f"{name} beside a thin problem {k}", fp64=name == "fp64")
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+@pytest.mark.parametrize("groups", [1, 2, 4, 6])
+def test_packs_without_the_deposit_cache(name, groups):
+    _held(name, [_nested_box(23, groups), _box(24, (9, 7, 5), 1), _box(25, (13, 11, 3), groups)], groups, deposit_cache=-1)
+
+
+@pytest.mark.parametrize("name", list(PRECISIONS))
+def test_radiation_pressure_without_the_deposit_cache(name):
+    p = _nested_box(26, 3)
+    dev = M.problem_to_device(p)
+    res = []
+    for cache in (0, -1):
+        ctx = M.moray_init(precision=PRECISIONS[name], deposit_cache=cache)
+        try:
+            res.append(M.moray_trace(ctx, [dev], want_accel=True)[0])
+        finally:
+            M.moray_free(ctx)
+        _check(res[-1], O.trace(p), BAR[name], name=f"{name} cache {cache}", fp64=name == "fp64")
+    # the same segments, added in another order
+    for q in range(2):
+        a, b = (np.asarray(r["accel"][q].cpu()) for r in res)
+        assert np.max(np.abs(a - b)) <= 1e-12 * np.max(np.abs(b))
