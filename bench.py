@@ -40,6 +40,11 @@ sys.path.insert(0, ROOT)
 METRIC = "ray-cell segments/s on 1 MI355X (batched FP32 vs plain FP64); p50/p99 solve latency"
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_SEGMENT = {"fp32": 36, "fp64": 40}     # absorber read + two float64 read-modify-writes
+# What `achieved` prices; said beside it in every roofline object
+BYTES_MODEL = ("algorithmic: every group's crossing of a cell as if it gathered and deposited by itself (36 B; "
+               "40 B in float64, 5 B where optically thin). A ray of four groups gathers once and deposits two "
+               "sums, combined in LDS, so it moves less and the fraction may exceed 1; what moves is `traffic`, "
+               "and what binds is vector issue and the float64 atomics (see `atomics` where given)")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_trace_level.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_1012_2865_amd", "csrc", "moray_kernels.hip")
 COPY_BYTES = 1 << 30                              # calibration copy of the counter pass
@@ -650,7 +655,7 @@ def _thin_workloads(M, steps, peaks=None, oracle_threads=0):
                "speedup_over_plain": sp / st, "absorbed_over_emitted": res[0]["absorbed"] / res[0]["emitted"],
                "dtype": "f32+f64acc",
                "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
+                            "frac": achieved / HBM_PEAK_GBS, "bytes_model": BYTES_MODEL, "traffic": traffic,
                             "traffic_source": "FETCH_SIZE + WRITE_SIZE counter passes of this kernel source "
                                               "(--counter-variant thin), per launch, read from "
                                               "profiles/traffic_trace_level.json (null: none for this workload "
@@ -744,7 +749,7 @@ def _roofline(M, workload, dev, tune, peaks):
     achieved = algo_bytes / (kms * 1e-3) / 1e9
     traffic = _traffic(workload, "fp32")
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
+            "frac": achieved / HBM_PEAK_GBS, "bytes_model": BYTES_MODEL, "traffic": traffic,
             "traffic_source": "FETCH_SIZE + WRITE_SIZE counter passes of this kernel source, per launch, read from "
                               "profiles/traffic_trace_level.json (null: kernel changed since)",
             "kernel": "trace_level_kernel<float>", "launches_per_step": launches,
